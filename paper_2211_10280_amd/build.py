@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtensair.so")
 SOURCES = ["api.hip", "sample.hip", "sort.hip", "grad.hip", "apply.hip", "dense.hip", "probe.hip", "noalloc.hip"]
-HEADERS = ["dev_common.h", "kernels.h", os.path.join("..", "..", "include", "tensair.h")]
+HEADERS = ["dev_common.h", "kernels.h", "aux_dev.h", "prep_dev.h", os.path.join("..", "..", "include", "tensair.h")]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off",                       # fused multiply-adds only where the source says fmaf

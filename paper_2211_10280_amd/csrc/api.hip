@@ -40,8 +40,7 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 struct Sizes {
     i64 Bmax, Pmax, Omax;
     int key_bits, passes, bits, nd;
-    int nblk_out, nblk_in;     // radix blocks
-    int sblk_out, sblk_in;     // scan blocks
+    size_t pub_words;          // what the preparation's workgroups publish, and their tickets (prep_layout)
     int tiles_out, tiles_in;   // segmented-reduction tiles
     i64 words;
 };
@@ -65,6 +64,38 @@ bool config_ok(const tensair_config *c, const char **why)
     return true;
 }
 
+// What the preparation of a mini-batch of O occurrences and n centers publishes between its workgroups, in 32-bit
+// words from the start of the set's area: a ticket per phase, the segment scan's words (64 bits; in-side for row counts
+// and weights, then out-side), then per pass of the sort the groups' counts (counted passes) of the in-side and the
+// out-side list and the two lists' tiles' digit words.
+#define PREP_TICKETS 8
+struct PrepLayout {
+    bool chained;
+    size_t seg_in, seg_out, pass0;
+    size_t groups, group_out;                // words of a pass's groups, the out-side ones among them
+    size_t tile0, per_pass, tile_out;        // words of the tiles of pass i: from tile0 + i * per_pass
+    size_t clear, words;                     // what the keys clear, from the start; all
+};
+PrepLayout prep_layout(const Sizes &s, int O, int n)
+{
+    PrepLayout l;
+    const size_t ti = (size_t)tn_prep_tiles(n), to = (size_t)tn_prep_tiles(O);
+    l.seg_in = PREP_TICKETS;
+    l.seg_out = l.seg_in + 2 * (2 * (size_t)tn_prep_seg_tiles(n));
+    l.pass0 = l.seg_out + 2 * (size_t)tn_prep_seg_tiles(O);
+    l.chained = ti + to <= TN_PREP_CHAIN_MAX;
+    const size_t gi = l.chained ? 0 : (ti + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
+    const size_t go = l.chained ? 0 : (to + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
+    l.groups = (gi + go) * s.nd;
+    l.group_out = gi * s.nd;
+    l.tile0 = l.pass0 + s.passes * l.groups;
+    l.tile_out = ti * s.nd;
+    l.per_pass = l.chained ? (ti + to) * s.nd : 0;      // counted: written and read within a pass, one set is enough
+    l.words = l.tile0 + (l.chained ? s.passes : 1) * (ti + to) * s.nd;
+    l.clear = l.chained ? l.words : l.tile0;
+    return l;
+}
+
 Sizes sizes_of(const tensair_config &c)
 {
     Sizes s;
@@ -76,10 +107,12 @@ Sizes sizes_of(const tensair_config &c)
     s.key_bits = kb;
     tn_radix_shape(kb, &s.passes, &s.bits);
     s.nd = 1 << s.bits;
-    s.nblk_out = (int)((s.Omax + TN_RADIX_TILE - 1) / TN_RADIX_TILE);
-    s.nblk_in = (int)((s.Bmax + TN_RADIX_TILE - 1) / TN_RADIX_TILE);
-    s.sblk_out = (int)((s.Omax + TN_SCAN_TILE - 1) / TN_SCAN_TILE);
-    s.sblk_in = (int)((s.Bmax + TN_SCAN_TILE - 1) / TN_SCAN_TILE);
+    const PrepLayout l = prep_layout(s, (int)s.Omax, (int)s.Bmax);
+    s.pub_words = l.words;
+    if (!l.chained) {   // a smaller mini-batch may be chained, which takes more per tile
+        const size_t most = l.pass0 + (size_t)s.passes * TN_PREP_CHAIN_MAX * s.nd;
+        if (s.pub_words < most) s.pub_words = most;
+    }
     s.tiles_out = (int)((s.Omax + tn_seg_tile(s.Omax) - 1) / tn_seg_tile(s.Omax));   // worst case over n <= Omax
     if (s.Omax > 65536 && s.tiles_out < 65536 / 8) s.tiles_out = 65536 / 8;
     s.tiles_in = (int)((s.Bmax + tn_seg_tile(s.Bmax) - 1) / tn_seg_tile(s.Bmax));
@@ -104,10 +137,11 @@ int tn_fail(int code, const char *fmt, ...)
 // coming mini-batch can be filled (tensair_prefetch) while the kernels of the current one still read theirs.
 struct BatchSet {
     u32 *keys[3], *vals[2];
-    u32 *counts_out, *totals_out, *counts_in, *totals_in;
+    u32 *hist;             // digit counts of both key lists, all passes; zero between mini-batches ...
+    bool hist_clean = false;   // ... once everything enqueued so far has run
+    u32 *pub;              // see prep_layout
     int *seg_of, *seg_start;
     int *long_cnt;
-    int *blk_heads, *blk_weight;
     int *pair_center;
     // row index of a prefetched mini-batch, copied to the caller's buffers when it is consumed
     int *ids_in, *ids_out, *n_rows, *off_in, *off_out;
@@ -134,8 +168,7 @@ struct tensair_model {
     Sizes sz;
     void *w_in, *w_out;
     // carved from the caller's workspace
-    u32 *thr;
-    int *alias;
+    uint2 *draw;               // alias table: threshold, alias
     int *status;
     BatchSet set[2];
     int *long_list;
@@ -198,8 +231,7 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
     const size_t NE = (size_t)(s.Omax + s.Bmax);
     const size_t K1 = (size_t)(c.max_peers + 1 > 2 ? c.max_peers + 1 : 2);   // the gradient sum indexes two sources
     char *p;
-    p = take(V * 4); if (m) m->thr = (u32 *)p;
-    p = take(V * 4); if (m) m->alias = (int *)p;
+    p = take(V * 8); if (m) m->draw = (uint2 *)p;
     p = take(256); if (m) m->status = (int *)p;
     const size_t cap_in = (size_t)(s.Bmax < (i64)V ? s.Bmax : (i64)V);
     const size_t cap_out = (size_t)(s.Omax < (i64)V ? s.Omax : (i64)V);
@@ -207,15 +239,11 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
         BatchSet *b = m ? &m->set[u] : nullptr;
         for (int i = 0; i < 3; ++i) { p = take(NE * 4); if (b) b->keys[i] = (u32 *)p; }
         for (int i = 0; i < 2; ++i) { p = take(NE * 4); if (b) b->vals[i] = (u32 *)p; }
-        p = take((size_t)s.nd * s.nblk_out * 4); if (b) b->counts_out = (u32 *)p;
-        p = take((size_t)s.nd * 4); if (b) b->totals_out = (u32 *)p;
-        p = take((size_t)s.nd * s.nblk_in * 4); if (b) b->counts_in = (u32 *)p;
-        p = take((size_t)s.nd * 4); if (b) b->totals_in = (u32 *)p;
+        p = take((size_t)2 * s.passes * s.nd * 4); if (b) b->hist = (u32 *)p;
+        p = take(s.pub_words * 4); if (b) b->pub = (u32 *)p;
         p = take(NE * 4); if (b) b->seg_of = (int *)p;
         p = take((NE + 2) * 4); if (b) b->seg_start = (int *)p;   // out-side rows at 0, in-side at Omax+1
         p = take(256); if (b) b->long_cnt = (int *)p;
-        p = take((size_t)(s.sblk_out + s.sblk_in) * 4); if (b) b->blk_heads = (int *)p;
-        p = take((size_t)(s.sblk_out + s.sblk_in) * 4); if (b) b->blk_weight = (int *)p;
         p = take((size_t)s.Pmax * 4); if (b) b->pair_center = (int *)p;
         p = take(cap_in * 4); if (b) b->ids_in = (int *)p;
         p = take(cap_out * 4); if (b) b->ids_out = (int *)p;
@@ -407,9 +435,13 @@ int tensair_model_init(tensair_model **out, const tensair_config *cfg, void *w_i
         return fail(TENSAIR_EINVAL, "unigram_counts has no positive entry");
     }
     hipStream_t st = (hipStream_t)stream;
-    hipError_t e = hipMemcpyAsync(m->thr, m->h_thr.data(), (size_t)cfg->vocab * 4, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(m->alias, m->h_alias.data(), (size_t)cfg->vocab * 4, hipMemcpyHostToDevice, st);
+    // threshold and alias of a bucket side by side: a draw reads both with one access
+    std::vector<uint32_t> draw(2 * (size_t)cfg->vocab);
+    for (i64 i = 0; i < cfg->vocab; ++i) {
+        draw[2 * (size_t)i] = m->h_thr[(size_t)i];
+        draw[2 * (size_t)i + 1] = (uint32_t)m->h_alias[(size_t)i];
+    }
+    hipError_t e = hipMemcpyAsync(m->draw, draw.data(), (size_t)cfg->vocab * 8, hipMemcpyHostToDevice, st);
     int zero[4] = {0, 0, 0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(m->status, zero, sizeof(zero), hipMemcpyHostToDevice, st);
     if (e == hipSuccess && fill_tables) {
@@ -488,87 +520,141 @@ static BatchWork batch_work(const tensair_config &c, const int32_t *tokens, i64 
     return w;
 }
 
-// keys: out-side occurrences at [0, O), in-side centers at [Omax, Omax + n_centers)
-static void enqueue_keys(tensair_model *m, BatchSet &S, const BatchWork &w, int32_t *negatives_dbg, hipStream_t st)
-{
-    const tensair_config &c = m->cfg;
-    tn_launch_build_keys(w.b, c.vocab, m->thr, m->alias, c.seed, c.worker_id, w.epoch,
-                         (c.flags & TENSAIR_RESAMPLE_NEGATIVES) != 0, S.keys[0], S.keys[0] + m->sz.Omax,
-                         S.pair_center, negatives_dbg, m->status, st);
-}
+// Whether the preparation of a mini-batch is a chained one, and its phases: the keys, the sort (per pass one, or a
+// count and a pass), the segments (one, or the heads and the segments).
+static bool prep_chained(const BatchWork &w) { return tn_prep_tiles((int)w.O) + tn_prep_tiles(w.b.n_centers) <= TN_PREP_CHAIN_MAX; }
+static int prep_phases(const Sizes &s, bool chained) { return chained ? s.passes + 2 : 2 * s.passes + 3; }
+static int prep_sort_end(const Sizes &s, bool chained) { return prep_phases(s, chained) - (chained ? 1 : 2); }
 
 struct RowIndexDst {
     int *ids, *n_rows, *offsets;
     i64 capacity;
 };
 
-static SegProb seg_prob(const tensair_model *m, const BatchSet &S, int side, int n)
+// A key list in sorted order and its segments (side 0: W_out, 1: W_in)
+struct SortedSide {
+    const u32 *keys, *vals;
+    int *seg_of, *seg_start, *long_cnt;
+};
+
+static SortedSide sorted_side(const tensair_model *m, const BatchSet &S, int side)
 {
-    const Sizes &s = m->sz;
-    SegProb p;
-    memset(&p, 0, sizeof(p));
-    const size_t at = side ? (size_t)s.Omax : 0;
-    p.keys = S.keys[S.kb] + at;
-    p.vals = S.vals[S.cur] + at;
-    p.n = n;
-    p.nblk = (n + TN_SCAN_TILE - 1) / TN_SCAN_TILE;
-    p.blk_heads = S.blk_heads + (side ? s.sblk_out : 0);
-    p.blk_weight = S.blk_weight + (side ? s.sblk_out : 0);
-    p.seg_of = S.seg_of + at;
-    p.seg_start = S.seg_start + (side ? (size_t)s.Omax + 1 : 0);
-    p.long_cnt = S.long_cnt + side;
-    p.weighted = side;
-    return p;
+    const size_t at = side ? (size_t)m->sz.Omax : 0;
+    return {S.keys[S.kb] + at, S.vals[S.cur] + at, S.seg_of + at, S.seg_start + (side ? (size_t)m->sz.Omax + 1 : 0),
+            S.long_cnt + side};
 }
 
-// stable sort of both key lists by row id, then unique row ids and the segment of every sorted entry
-// LDS that the sort asks for beyond its counters where it runs next to the forward pass or the reductions of a
-// step (a preparation that was not tucked under a table update): 40 KB per workgroup, four workgroups per compute
-// unit, is the occupancy at which it was measured not to crowd them (hot-row configuration: 0.66 against 0.69 ms
-// per step with the sort at full occupancy); under a table update, or alone, it takes what it needs.
-#ifndef TN_SORT_LDS_BESIDE
-#define TN_SORT_LDS_BESIDE 40960
-#endif
-#ifndef TN_SORT_LDS_INLINE
-#define TN_SORT_LDS_INLINE 0
-#endif
-
-static void enqueue_sort_segments(tensair_model *m, BatchSet &S, const BatchWork &w, const RowIndexDst &in,
-                                  const RowIndexDst &out, size_t min_lds, hipStream_t st, hipStream_t st_mark)
+// One phase as it is launched.  Key lists: out-side occurrences at [0, O), in-side centers at [Omax, Omax + n_centers);
+// the unsorted keys in keys[0] are never written again (the forward pass reads them); the passes go 0 -> 1 -> 2 -> 1.
+static void make_prep_phase(tensair_model *m, BatchSet &S, const BatchWork &w, int phase, const RowIndexDst &in,
+                            const RowIndexDst &out, int32_t *negatives_dbg, PrepPhase &x)
 {
     const tensair_config &c = m->cfg;
     const Sizes &s = m->sz;
-    RadixProb ro, ri;
-    for (int i = 0; i < 3; ++i) {
-        ro.keys[i] = S.keys[i];
-        ri.keys[i] = S.keys[i] + s.Omax;
+    const PrepLayout l = prep_layout(s, (int)w.O, w.b.n_centers);
+    memset(&x, 0, sizeof(x));
+    const int n[2] = {(int)w.O, w.b.n_centers};
+    const size_t at[2] = {0, (size_t)s.Omax};
+    if (phase == 0) {
+        PrepKeys &k = x.keys;
+        x.kind = PREP_KEYS;
+        const i64 slots = (i64)w.b.n_centers * 2 * c.window * (c.negatives + 1);
+        x.blocks = (int)((slots + 256 * PREP_KEYS_ITEMS - 1) / (256 * PREP_KEYS_ITEMS));
+        k.b = w.b;
+        k.V = c.vocab;
+        k.draw = m->draw;
+        k.k0 = (u32)(c.seed & 0xFFFFFFFFu);
+        k.k1 = (u32)(c.seed >> 32);
+        k.ctr3 = c.worker_id + 65536u * w.epoch;
+        k.resample = (c.flags & TENSAIR_RESAMPLE_NEGATIVES) != 0;
+        k.out_keys = S.keys[0];
+        k.in_keys = S.keys[0] + s.Omax;
+        k.pair_center = S.pair_center;
+        k.neg_dbg = negatives_dbg;
+        k.status = m->status;
+        k.hist = l.chained ? S.hist : nullptr;
+        k.passes = s.passes;
+        k.bits = s.bits;
+        k.clear = S.pub;
+        k.n_clear = l.clear;
+    } else if (phase < prep_sort_end(s, l.chained)) {
+        PrepPass &p = x.pass;
+        const int i = l.chained ? phase - 1 : (phase - 1) / 2;
+        x.kind = l.chained ? PREP_PASS : (phase & 1) ? PREP_COUNT : PREP_PASS_COUNTED;
+        const int kin = i == 0 ? 0 : (i & 1) ? 1 : 2, kout = (i & 1) ? 2 : 1;
+        for (int t = 0; t < 2; ++t) {
+            PrepPassList &q = p.p[t];
+            q.kin = S.keys[kin] + at[t];
+            q.kout = S.keys[kout] + at[t];
+            q.vin = S.vals[i & 1] + at[t];
+            q.vout = S.vals[(i & 1) ^ 1] + at[t];
+            q.n = n[t];
+            q.tiles = tn_prep_tiles(n[t]);
+            q.state = S.pub + l.tile0 + (size_t)i * l.per_pass + (t == 0 ? l.tile_out : 0);
+            q.hist = l.chained ? S.hist + (size_t)(t * s.passes + i) * s.nd
+                               : S.pub + l.pass0 + (size_t)i * l.groups + (t == 0 ? l.group_out : 0);
+            x.blocks += q.tiles;
+        }
+        p.ticket = S.pub + i;
+        p.shift = i * s.bits;
+        p.bits = s.bits;
+        p.first = i == 0;
+        S.kb = kout;
+        S.cur = (i & 1) ^ 1;
+    } else {
+        PrepSegments &g = x.seg;
+        x.kind = l.chained ? PREP_SEGMENTS : phase == prep_phases(s, false) - 1 ? PREP_SEGMENTS_COUNTED : PREP_HEADS;
+        for (int t = 0; t < 2; ++t) {
+            PrepSegmentsList &q = g.p[t];
+            const RowIndexDst &d = t ? in : out;
+            const SortedSide v = sorted_side(m, S, t);
+            q.keys = v.keys;
+            q.vals = v.vals;
+            q.n = n[t];
+            q.tiles = tn_prep_seg_tiles(n[t]);
+            q.state = (u64 *)(S.pub + (t ? l.seg_in : l.seg_out));
+            q.seg_of = v.seg_of;
+            q.seg_start = v.seg_start;
+            q.long_cnt = v.long_cnt;
+            q.row_ids = d.ids;
+            q.n_rows = d.n_rows;
+            q.seg_offsets = d.offsets;
+            q.capacity = d.capacity;
+            x.blocks += q.tiles;
+        }
+        g.begin = w.b.begin;
+        g.T = w.b.T;
+        g.w = c.window;
+        g.hist = S.hist;
+        g.n_hist = 2 * s.passes * s.nd;
+        g.ticket = S.pub + s.passes;
+        g.status = m->status;
     }
-    for (int i = 0; i < 2; ++i) {
-        ro.vals[i] = S.vals[i];
-        ri.vals[i] = S.vals[i] + s.Omax;
-    }
-    ro.n = (int)w.O;
-    ro.nblk = (int)((w.O + TN_RADIX_TILE - 1) / TN_RADIX_TILE);
-    ro.counts = S.counts_out;
-    ro.totals = S.totals_out;
-    ri.n = w.b.n_centers;
-    ri.nblk = (w.b.n_centers + TN_RADIX_TILE - 1) / TN_RADIX_TILE;
-    ri.counts = S.counts_in;
-    ri.totals = S.totals_in;
-    S.cur = tn_launch_radix_sort(ro, ri, s.key_bits, min_lds, st, &S.kb);
-    if (st_mark) mark(m, PF_SORT, st_mark);
+}
 
-    SegProb so = seg_prob(m, S, 0, (int)w.O), si = seg_prob(m, S, 1, w.b.n_centers);
-    so.row_ids = out.ids;
-    so.n_rows = out.n_rows;
-    so.seg_offsets = out.offsets;
-    so.capacity = out.capacity;
-    si.row_ids = in.ids;
-    si.n_rows = in.n_rows;
-    si.seg_offsets = in.offsets;
-    si.capacity = in.capacity;
-    tn_launch_segments(so, si, w.b.begin, w.b.T, c.window, m->status, st);
-    if (st_mark) mark(m, PF_SEGMENTS, st_mark);
+// Notes that a phase is enqueued; the keys of a chained preparation add to digit counts that must be zero, which its
+// segments leave behind -- unless it was left unfinished (an announcement dropped, a failed call): then they are
+// cleared here.
+static void before_prep_phase(tensair_model *m, BatchSet &S, int kind, hipStream_t st)
+{
+    if (kind == PREP_KEYS) {
+        if (!S.hist_clean) tn_launch_prep_clear(S.hist, 2 * m->sz.passes * m->sz.nd, st);
+        S.hist_clean = false;
+    } else if (kind == PREP_SEGMENTS || kind == PREP_SEGMENTS_COUNTED) {
+        S.hist_clean = true;
+    }
+}
+
+// the phases [from, to) as launches of their own
+static void enqueue_prep(tensair_model *m, BatchSet &S, const BatchWork &w, int from, int to, const RowIndexDst &in,
+                         const RowIndexDst &out, int32_t *negatives_dbg, hipStream_t st)
+{
+    for (int phase = from; phase < to; ++phase) {
+        PrepPhase x;
+        make_prep_phase(m, S, w, phase, in, out, negatives_dbg, x);
+        before_prep_phase(m, S, x.kind, st);
+        tn_launch_prep(x, st);
+    }
 }
 
 static int check_batch(const tensair_model *m, const int32_t *tokens, i64 n_tokens, i64 center_begin, int n_centers,
@@ -605,15 +691,15 @@ static int enqueue_prepare(tensair_model *m, const Prefetched &d, bool late)
     const tensair_config &c = m->cfg;
     BatchSet &S = m->set[1 - m->busy];
     const BatchWork w = batch_work(c, d.tokens, d.n_tokens, d.begin, d.n_centers, d.epoch, d.P);
-    enqueue_keys(m, S, w, nullptr, m->side);
+    const RowIndexDst in = {S.ids_in, S.n_rows, S.off_in, tensair_capacity_in(&c, c.max_centers)};
+    const RowIndexDst out = {S.ids_out, S.n_rows + 1, S.off_out, tensair_capacity_out(&c, c.max_centers)};
+    enqueue_prep(m, S, w, 0, 1, in, out, nullptr, m->side);
     if (late) {
         HIP_TRY(hipEventRecord(m->ev_keys, m->side));
         m->keys_ticket = ++m->side_ticket;
     }
     m->pend_late = late;
-    const RowIndexDst in = {S.ids_in, S.n_rows, S.off_in, tensair_capacity_in(&c, c.max_centers)};
-    const RowIndexDst out = {S.ids_out, S.n_rows + 1, S.off_out, tensair_capacity_out(&c, c.max_centers)};
-    enqueue_sort_segments(m, S, w, in, out, late ? TN_SORT_LDS_BESIDE : 0, m->side, nullptr);
+    enqueue_prep(m, S, w, 1, prep_phases(m->sz, prep_chained(w)), in, out, nullptr, m->side);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(m->ev_prep, m->side));
     m->prep_ticket = ++m->side_ticket;
@@ -636,6 +722,7 @@ static void abandon_side_work(tensair_model *m)
     m->fused_apply = nullptr;
     m->fused_index_done = false;
     m->mask_clean[0] = m->mask_clean[1] = false;
+    m->set[0].hist_clean = m->set[1].hist_clean = false;
 }
 
 int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, int64_t center_begin,
@@ -833,7 +920,10 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         }
     } else {
         // 1. keys
-        enqueue_keys(m, S, w, negatives_dbg, st);
+        const RowIndexDst in = {grad_out->in.row_ids, grad_out->in.n_rows, seg_offsets_in, grad_out->in.capacity};
+        const RowIndexDst out = {grad_out->out.row_ids, grad_out->out.n_rows, seg_offsets_out,
+                                 grad_out->out.capacity};
+        enqueue_prep(m, S, w, 0, 1, in, out, negatives_dbg, st);
         mark(m, PF_KEYS, st);
         hipStream_t s_fwd = st;
         if (overlap) {
@@ -863,10 +953,11 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
             }
         }
         // 3./4. sort and segments, row index straight into the caller's buffers
-        const RowIndexDst in = {grad_out->in.row_ids, grad_out->in.n_rows, seg_offsets_in, grad_out->in.capacity};
-        const RowIndexDst out = {grad_out->out.row_ids, grad_out->out.n_rows, seg_offsets_out,
-                                 grad_out->out.capacity};
-        enqueue_sort_segments(m, S, w, in, out, TN_SORT_LDS_INLINE, st, st);
+        const int sorted = prep_sort_end(s, prep_chained(w));
+        enqueue_prep(m, S, w, 1, sorted, in, out, nullptr, st);
+        mark(m, PF_SORT, st);
+        enqueue_prep(m, S, w, sorted, prep_phases(s, prep_chained(w)), in, out, nullptr, st);
+        mark(m, PF_SEGMENTS, st);
         if (overlap) {   // behind the forward pass (not behind a preparation enqueued after it)
             HIP_TRY(hipStreamWaitEvent(st, m->ev_fwd, 0));
             if (fwd_ticket > m->main_ticket) m->main_ticket = fwd_ticket;
@@ -874,7 +965,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     }
 
     // 5. segmented reductions: duplicates of a row summed in sorted (= occurrence) order
-    const SegProb so = seg_prob(m, S, 0, (int)w.O), si = seg_prob(m, S, 1, n_centers);
+    const SortedSide so = sorted_side(m, S, 0), si = sorted_side(m, S, 1);
     SegReduceArgs r_in, r_out;
     memset(&r_in, 0, sizeof(r_in));
     r_in.D = c.dim;

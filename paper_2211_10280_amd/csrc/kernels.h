@@ -13,27 +13,21 @@ typedef int64_t i64;
 // sorted entries per wave in the segmented reduction: small problems get small tiles so that
 // enough waves exist to hide the latency of the row loads
 static inline int tn_seg_tile(i64 n) { return n <= 65536 ? 8 : 32; }
-#define TN_RADIX_TILE 2048  // keys per block in a radix pass (256 threads x 8)
-#define TN_RADIX_MAX_BITS 11  // widest digit of a radix pass
-#ifndef TN_RADIX_WIDE_KEYS
-#define TN_RADIX_WIDE_KEYS 16 // keys with more bits than this are sorted in digits of at most TN_RADIX_NARROW bits
-#endif
-#ifndef TN_RADIX_NARROW
-#define TN_RADIX_NARROW 8
-#endif
-// Number of passes and digit width for keys of `key_bits` bits.  A pass scatters every key to the place of its
-// digit; with d-bit digits a block of TN_RADIX_TILE keys writes runs of about TN_RADIX_TILE / 2^d neighbouring
-// keys, and runs of two (11-bit digits) cost the memory system far more than their bytes when the sort shares the
-// chip with a bandwidth-bound kernel.  Large vocabularies therefore take one pass more with narrower digits
-// (measured at 20 and 21 key bits: the step 0.6 % and 2 % faster); small ones keep the fewest passes.
+#define TN_RADIX_TILE 2048    // keys per workgroup in a pass of the sort
+#define TN_RADIX_MAX_BITS 9   // widest digit of a pass
+#define TN_RADIX_MAX_ND (1 << TN_RADIX_MAX_BITS)
+#define TN_RADIX_MAX_PASSES 4
+#define TN_RADIX_MAX_PASSES_ND (3 * TN_RADIX_MAX_ND)   // digits of all passes together, at most (28 key bits: 4 x 128)
+// Number of passes and digit width for keys of `key_bits` bits: the fewest passes.  A pass is bound by round trips to
+// memory, and a digit's keys leave a tile as one run, so wider digits cost little; 9 bits are what a tile's counters
+// and their chained scan take without slowing the pass down.
 static inline void tn_radix_shape(int key_bits, int *passes, int *bits)
 {
     if (key_bits < 1) key_bits = 1;
-    const int widest = key_bits > TN_RADIX_WIDE_KEYS ? TN_RADIX_NARROW : TN_RADIX_MAX_BITS;
-    *passes = (key_bits + widest - 1) / widest;
+    *passes = (key_bits + TN_RADIX_MAX_BITS - 1) / TN_RADIX_MAX_BITS;
     *bits = (key_bits + *passes - 1) / *passes;
 }
-#define TN_SCAN_TILE 2048   // entries per block in the head scan
+#define TN_SCAN_TILE 2048   // entries per workgroup in the segment scan
 #define TN_SEG_XBLOCK 256    // tiles of the segmented reduction per block of partials
 #define TN_SEG_CROSS_MIN 16384  // problems with more tiles than this get partials per block of tiles
 
@@ -51,44 +45,75 @@ struct BatchDesc {
     i64 pair_base;    // pairs_before(begin)
     i64 P;            // pairs in the batch
 };
-// resample: a negative equal to the pair's center or context word is drawn once more (words 2, 3)
-void tn_launch_build_keys(const BatchDesc &b, i64 V, const u32 *thr, const int *alias, u64 seed,
-                          u32 worker, u32 epoch, bool resample, u32 *out_keys, u32 *in_keys,
-                          int *pair_center, int *neg_dbg, int *status, hipStream_t st);
 
-// ---- stage 2: stable LSD radix sort of (key, value) for two independent problems at once
-struct RadixProb {
-    u32 *keys[3];   // input in keys[0], which is never written (other work may still read it);
-                    // the passes go 0 -> 1 -> 2 -> 1 -> ...
-    u32 *vals[2];   // values, ping-pong; the first pass writes the entry index (input order) itself
-    int n;
-    int nblk;       // ceil(n / TN_RADIX_TILE)
-    u32 *counts;    // [2^bits][nblk] scratch
-    u32 *totals;    // [2^bits] scratch
+// ---- preparation of a mini-batch (prep_dev.h): one launch per phase -- keys, the passes of the sort, segments
+#define PREP_KEYS_ITEMS 4   // slots per thread
+struct PrepKeys {
+    BatchDesc b;
+    i64 V;
+    const uint2 *draw;     // [V] alias table: threshold, alias
+    u32 k0, k1, ctr3;
+    int resample;          // a negative equal to the pair's center or context word is drawn once more
+    u32 *out_keys, *in_keys;
+    int *pair_center, *neg_dbg, *status;
+    u32 *hist;             // [2 lists][passes][2^bits] digit counts, added to: zero before (NULL: not wanted)
+    int passes, bits;
+    u32 *clear;            // what the later phases publish into and their tickets: zeroed
+    size_t n_clear;
 };
-// returns which vals buffer (0/1) holds the sorted values; *key_buf = which keys buffer (1/2)
-// min_lds_bytes: LDS to request per workgroup beyond what the counters need (0 = none): holds the occupancy of
-// the sort down where it runs next to a kernel that it should not crowd
-int tn_launch_radix_sort(RadixProb p0, RadixProb p1, int key_bits, size_t min_lds_bytes, hipStream_t st, int *key_buf);
-
-// ---- stage 3: unique ids, segment index of every sorted entry, weighted segment offsets
-struct SegProb {
-    const u32 *keys;      // sorted keys
-    const u32 *vals;      // sorted values
-    int n;
-    int nblk;             // ceil(n / TN_SCAN_TILE)
-    int *blk_heads;       // [nblk] scratch
-    int *blk_weight;      // [nblk] scratch
-    int *seg_of;          // [n] out: row index (0..U-1) of every sorted entry
-    int *seg_start;       // [U+1] out: index of the first sorted entry of every row, then n
-    int *long_cnt;        // [1] zeroed here: the segmented reduction counts its long rows in it
-    int *row_ids;         // [capacity] out
-    int *n_rows;          // [1] out
-    int *seg_offsets;     // [U+1] out or NULL
+struct PrepPassList {
+    const u32 *kin, *vin;  // vin: not read by the first pass, whose values are the entries' places
+    u32 *kout, *vout;
+    u32 *state;            // [tiles][2^bits] published words (chained), digit counts (counted)
+    u32 *hist;             // [2^bits] keys per digit (chained); [groups][2^bits] per group of tiles (counted)
+    int n, tiles;
+};
+struct PrepPass {
+    PrepPassList p[2];     // out-side, in-side
+    u32 *ticket;
+    int shift, bits, first;
+};
+struct PrepSegmentsList {
+    const u32 *keys;       // sorted keys
+    const u32 *vals;       // sorted values
+    int n, tiles;
+    u64 *state;            // [tiles] published words; in-side: [2][tiles], the second for the weights
+    int *seg_of;           // [n] out: row index (0..U-1) of every sorted entry
+    int *seg_start;        // [U+1] out: index of the first sorted entry of every row, then n
+    int *long_cnt;         // [1] zeroed here: the segmented reduction counts its long rows in it
+    int *row_ids;          // [capacity] out
+    int *n_rows;           // [1] out
+    int *seg_offsets;      // [U+1] out or NULL
     i64 capacity;
-    int weighted;         // 0: every entry weighs 1; 1: entry = center index, weighs its pair count
 };
-void tn_launch_segments(SegProb p0, SegProb p1, i64 begin, i64 T, int w, int *status, hipStream_t st);
+struct PrepSegments {
+    PrepSegmentsList p[2];
+    i64 begin, T;
+    int w;
+    u32 *hist;             // zeroed for the next mini-batch
+    int n_hist;
+    u32 *ticket;
+    int *status;
+};
+// chained preparations: keys, passes, segments; counted ones: keys, (count, counted pass)..., heads, counted segments
+enum { PREP_KEYS, PREP_PASS, PREP_SEGMENTS, PREP_COUNT, PREP_PASS_COUNTED, PREP_HEADS, PREP_SEGMENTS_COUNTED };
+struct PrepPhase {
+    int kind;
+    int blocks;            // workgroups
+    union {
+        PrepKeys keys;
+        PrepPass pass;
+        PrepSegments seg;
+    };
+};
+#define TN_PREP_GROUP 64       // tiles per group of a counted pass
+#ifndef TN_PREP_CHAIN_MAX
+#define TN_PREP_CHAIN_MAX 128  // most tiles of a chained pass
+#endif
+static inline int tn_prep_tiles(int n) { return (n + TN_RADIX_TILE - 1) / TN_RADIX_TILE; }
+static inline int tn_prep_seg_tiles(int n) { return (n + TN_SCAN_TILE - 1) / TN_SCAN_TILE; }
+void tn_launch_prep(const PrepPhase &x, hipStream_t st);   // the phase as a launch of its own
+void tn_launch_prep_clear(u32 *hist, int n, hipStream_t st);
 
 // row ids / row count / segment offsets of a prepared mini-batch -> the consuming call's buffers
 struct RowIndexCopy {
@@ -97,7 +122,6 @@ struct RowIndexCopy {
         int *dst_ids, *dst_n, *dst_off;         // dst_off may be NULL
     } side[2];
 };
-void tn_launch_copy_row_index(const RowIndexCopy &c, i64 max_rows, hipStream_t st);
 
 // ---- stage 4: forward pass and per-center partial of the W_in gradient
 struct FwdArgs {

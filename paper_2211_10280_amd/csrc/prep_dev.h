@@ -1,0 +1,547 @@
+// Preparation of a mini-batch -- everything about it that does not depend on the tables -- as device functions, so
+// that each phase can run as a kernel of its own or ride in another launch (see aux_dev.h):
+//   keys      pair enumeration, Philox/alias negative sampling; the key lists (row ids of all occurrences), their
+//             digit histograms for every pass of the sort
+//   pass      one pass of a stable LSD radix sort of (row id, entry), both lists at once
+//   segments  unique row ids and the segment of every sorted entry
+//
+// TensAIR (arXiv 2211.10280) trains "a default skip-gram model" (Section 4.4); the mini-batch is an encoded message
+// (Section 3, "Stream Processing").  Here the message is a run of center positions of a token stream; the (center,
+// context) pairs and their negatives are derived on the GPU as pure functions of position, so no pair list crosses
+// the ABI.  The sparse gradient of a mini-batch touches only a small part of the model (Section 4, "Sparse vs. Dense
+// Models"); rows touched more than once (frequent words) must be summed.  Sorting the occurrences by row id turns
+// every row into one contiguous segment, so the later reduction and the table update are free of write conflicts and
+// need no floating-point atomics; stability fixes the order of the additions inside a segment.  All of this is
+// integer work and bit-exact.
+//
+// A tile of keys is ranked inside its workgroup; what the lower tiles hold of every digit comes in one of two ways.
+//   chained (few tiles): a pass is one launch.  Every tile publishes its digit counts, then the sums up to it, and adds
+//     up what it needs from the nearest tiles below it.  Tiles are dealt by a ticket, so a workgroup only ever waits
+//     for workgroups that have started before it and that themselves wait for none above them: every wait ends,
+//     whatever the order of dispatch.  A published word carries its value and its state together, so no fence is
+//     needed.  At 10^4..10^5 keys a pass is bound by the latency of launches and of round trips to memory, not by
+//     bytes, and launches fewer are what counts: count, scan and scatter as launches of their own took 19 us per
+//     pass of 61 000 keys, this takes 14 and rides in another launch.
+//   counted (many tiles): a launch before the pass counts the digits of every tile and sums them over groups of
+//     tiles; a tile adds up the groups below its own and the tiles of its group below itself.  Tickets cost 55 ns
+//     each, one after the other (a single word that all XCDs add to): 110 us at 2 000 tiles.
+#pragma once
+#include "dev_common.h"
+#include "kernels.h"
+
+// A tile's published word, for counts (32 bits): 0 nothing yet; 1 + count of the tile; PREP_INCL + count of all
+// tiles up to and including it.  Counts of a tile are at most TN_RADIX_TILE < PREP_INCL - 1.
+#define PREP_INCL 4096u
+#define PREP_LOOK 8       // words of lower tiles that a thread has in flight
+// ... and for the segment scan (64 bits): state in the top two bits (0 nothing, 1 the tile's own, 2 up to it)
+#define PREP_SEG_OWN (1ull << 62)
+#define PREP_SEG_INCL (2ull << 62)
+#define PREP_SEG_VALUE ((1ull << 62) - 1ull)
+
+__device__ __forceinline__ u32 peek(const u32 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ u64 peek(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void post(u32 *p, u32 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void post(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// the ticket of this workgroup (same in every thread); `word`: a shared word
+__device__ __forceinline__ int take_ticket(u32 *counter, u32 *word)
+{
+    if (threadIdx.x == 0) *word = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int t = uniform((int)*word);
+    __syncthreads();
+    return t;
+}
+
+// ---------------------------------------------------------------- keys
+// Slot s of the mini-batch is (center i, offset index q, k): k = 0 is the context, k = 1..N are the negatives.
+// Writes the out-side key list [pair][N+1] (pair-major, the order of the occurrence list), the in-side key of every
+// center, the center token of every pair and (for chained passes) the digit counts of both lists; clears the words that the sort's and
+// the segment scan's workgroups will publish, and their tickets.  A thread takes PREP_KEYS_ITEMS slots, one of every
+// THREADS, so that their table lookups are in flight together.
+template <int THREADS>
+__device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblocks, u32 *lds)
+{
+    constexpr int ITEMS = PREP_KEYS_ITEMS;
+    const BatchDesc &b = a.b;
+    const int nd = 1 << a.bits, nhist = a.passes * nd;   // counters of one list
+    const u32 dmask = (u32)nd - 1u;
+    if (a.hist)
+        for (int i = threadIdx.x; i < 2 * nhist; i += THREADS) lds[i] = 0;
+    for (size_t i = (size_t)block * THREADS + threadIdx.x; i < a.n_clear; i += (size_t)nblocks * THREADS) a.clear[i] = 0;
+    __syncthreads();
+    const u32 Np1 = (u32)b.N + 1u, w = (u32)b.w, per_center = 2u * w * Np1;
+    const u32 total = (u32)b.n_centers * per_center;     // fits 31 bits (checked with the configuration)
+    const u32 s0 = (u32)block * (u32)(THREADS * ITEMS) + threadIdx.x;
+    u32 key[ITEMS];
+    int in_key[ITEMS];      // >= 0: the slot is its center's first, and this is the center's word
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        key[j] = 0xFFFFFFFFu;
+        in_key[j] = -1;
+        const u32 t = s0 + (u32)j * THREADS;
+        if (t >= total) continue;
+        const u32 i = t / per_center, rem = t - i * per_center, q = rem / Np1, k = rem - q * Np1;
+        const i64 p = b.begin + (i64)i;
+        int c = b.tok[p];
+        if ((u32)c >= (u32)a.V) {  // invalid token: keep every later access in range, flag it
+            c = 0;
+            atomicOr(a.status, ST_BAD_ID);
+        }
+        if (rem == 0) {
+            a.in_keys[i] = (u32)c;
+            in_key[j] = c;
+        }
+        const i64 left = p < b.w ? p : b.w, right = (b.T - 1 - p) < b.w ? (b.T - 1 - p) : b.w;
+        i64 rank, o;
+        if (q < w) {
+            if ((i64)q < (i64)w - left) continue;
+            rank = (i64)q - ((i64)w - left);
+            o = (i64)q - (i64)w;
+        } else {
+            if ((i64)(q - w) >= right) continue;
+            rank = left + (i64)(q - w);
+            o = (i64)(q - w) + 1;
+        }
+        const i64 pair = pairs_before(p, b.T, b.w) - b.pair_base + rank;
+        int ctx = b.tok[p + o];
+        if ((u32)ctx >= (u32)a.V) {
+            ctx = 0;
+            atomicOr(a.status, ST_BAD_ID);
+        }
+        int id;
+        if (k == 0) {
+            id = ctx;
+            a.pair_center[pair] = c;
+        } else {
+            const philox_out r = philox4x32_10((u32)((u64)p & 0xFFFFFFFFu), (u32)((u64)p >> 32), q * 65536u + (k - 1u),
+                                               a.ctr3, a.k0, a.k1);
+            u32 bkt = (u32)(((u64)r.r0 * (u64)a.V) >> 32);
+            uint2 e = a.draw[bkt];           // threshold, alias
+            id = (r.r1 < e.x) ? (int)bkt : (int)e.y;
+            if (a.resample && (id == c || id == ctx)) {   // the variant: one more draw from the block's other two words
+                bkt = (u32)(((u64)r.r2 * (u64)a.V) >> 32);
+                e = a.draw[bkt];
+                id = (r.r3 < e.x) ? (int)bkt : (int)e.y;
+            }
+            if (a.neg_dbg) a.neg_dbg[pair * b.N + (k - 1u)] = id;
+        }
+        a.out_keys[pair * Np1 + k] = (u32)id;
+        key[j] = (u32)id;
+    }
+    if (!a.hist) return;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        if (key[j] != 0xFFFFFFFFu)
+            for (int p = 0; p < a.passes; ++p) atomicAdd(&lds[p * nd + ((key[j] >> (p * a.bits)) & dmask)], 1u);
+        if (in_key[j] >= 0)
+            for (int p = 0; p < a.passes; ++p) atomicAdd(&lds[nhist + p * nd + (((u32)in_key[j] >> (p * a.bits)) & dmask)], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * nhist; i += THREADS)
+        if (lds[i]) atomicAdd(&a.hist[i], lds[i]);
+}
+
+// ---------------------------------------------------------------- one pass of the sort
+// block-wide exclusive scan of two numbers per thread
+template <int THREADS>
+__device__ __forceinline__ void prep_scan2(u32 a, u32 b, u32 &ea, u32 &eb, u32 *sm)
+{
+    constexpr int NW = THREADS / WAVE;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const u32 ia = wave_incl_scan(a, lane), ib = wave_incl_scan(b, lane);
+    if (lane == WAVE - 1) {
+        sm[wave] = ia;
+        sm[NW + wave] = ib;
+    }
+    __syncthreads();
+    u32 oa = 0, ob = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+        if (w < wave) {
+            oa += sm[w];
+            ob += sm[NW + w];
+        }
+    ea = oa + ia - a;
+    eb = ob + ib - b;
+}
+
+// LDS words of a pass: per-wave digit counters, later overlaid by the tile's keys and values in digit order; the place
+// of every digit's run; scan scratch
+template <int THREADS>
+struct PassLds {
+    static constexpr int NW = THREADS / WAVE;
+    static constexpr int counters = NW * TN_RADIX_MAX_ND;
+    static constexpr int staged = 2 * TN_RADIX_TILE;
+    static constexpr int words = (counters > staged ? counters : staged) + TN_RADIX_MAX_ND + 2 * NW + 2;
+};
+
+// block `block` of a counted pass; a chained one draws its tile
+template <int THREADS, bool CHAINED>
+__device__ __forceinline__ void prep_pass(const PrepPass &a, int block, u32 *lds)
+{
+    typedef PassLds<THREADS> L;
+    constexpr int IPT = TN_RADIX_TILE / THREADS;
+    constexpr int PER = (TN_RADIX_MAX_ND + THREADS - 1) / THREADS;    // digits per thread
+    u32 *whp = lds;                                                   // [NW][nd]
+    u32 *skey = lds, *sval = lds + TN_RADIX_TILE;
+    u32 *dbase = lds + (L::counters > L::staged ? L::counters : L::staged);
+    u32 *sm = dbase + TN_RADIX_MAX_ND;
+    const int nd = 1 << a.bits;
+    const u32 dmask = (u32)nd - 1u;
+    const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
+    int tile = CHAINED ? take_ticket(a.ticket, sm) : block;
+    const int pr = tile < a.p[1].tiles ? 1 : 0;                       // the in-side list's tiles come first
+    if (pr == 0) tile -= a.p[1].tiles;
+    const PrepPassList &P = a.p[pr];
+    if (tile >= P.tiles) return;                                      // not reached: as many workgroups as tiles
+    const int n = P.n;
+
+    // a wave owns IPT * 64 consecutive keys
+    const int wbase = tile * TN_RADIX_TILE + wave * (IPT * WAVE);
+    u32 key[IPT], val[IPT], loc[IPT];
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+        const int idx = wbase + it * WAVE + lane;
+        key[it] = idx < n ? P.kin[idx] : 0u;
+        val[it] = a.first ? (u32)idx : (idx < n ? P.vin[idx] : 0u);
+    }
+    const int d0 = threadIdx.x * PER;
+    u32 total[PER], below[PER];                 // keys per digit: in the list, in the lower tiles
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        total[j] = below[j] = 0;
+        if (d0 + j < nd) {
+            if (CHAINED) {
+                total[j] = P.hist[d0 + j];
+            } else {
+                const int group = tile / TN_PREP_GROUP, groups = (P.tiles + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
+#pragma unroll 8
+                for (int t = 0; t < groups; ++t) {
+                    const u32 v = P.hist[(size_t)t * nd + d0 + j];
+                    total[j] += v;
+                    below[j] += t < group ? v : 0u;
+                }
+#pragma unroll 8
+                for (int t = group * TN_PREP_GROUP; t < tile; ++t) below[j] += P.state[(size_t)t * nd + d0 + j];
+            }
+        }
+    }
+    for (int d = threadIdx.x; d < L::NW * nd; d += THREADS) whp[d] = 0;
+    __syncthreads();
+    const u64 lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+        const bool valid = wbase + it * WAVE + lane < n;
+        const u32 d = (key[it] >> a.shift) & dmask;
+        u64 m = __ballot(valid);
+        for (int bit = 0; bit < a.bits; ++bit) {
+            const bool on = (d >> bit) & 1u;
+            const u64 bal = __ballot(valid && on);
+            m &= on ? bal : ~bal;
+        }
+        const u32 rank = (u32)__popcll(m & lt);
+        u32 old = 0;
+        if (valid) old = whp[wave * nd + d];
+        if (valid && rank == 0) whp[wave * nd + d] = old + (u32)__popcll(m);
+        loc[it] = old + rank;
+    }
+    __syncthreads();
+    // per digit: counts of the lower waves of the tile, the tile's count (published at once)
+    u32 count[PER], st = 0, sc = 0;
+    u32 *mine = P.state + (size_t)tile * nd;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        u32 run = 0;
+        if (d0 + j < nd) {
+#pragma unroll
+            for (int w = 0; w < L::NW; ++w) {
+                const u32 c = whp[w * nd + d0 + j];
+                whp[w * nd + d0 + j] = run;
+                run += c;
+            }
+            if (CHAINED) post(&mine[d0 + j], tile == 0 ? PREP_INCL + run : 1u + run);
+        }
+        count[j] = run;
+        st += total[j];
+        sc += run;
+    }
+    u32 et, ec;                                 // keys of smaller digits: in the list, in the tile
+    prep_scan2<THREADS>(st, sc, et, ec, sm);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int d = d0 + j;
+        if (d < nd) {
+            for (int t = CHAINED ? tile - 1 : -1; t >= 0;) {
+                u32 v[PREP_LOOK];
+#pragma unroll
+                for (int i = 0; i < PREP_LOOK; ++i) v[i] = t - i >= 0 ? peek(P.state + (size_t)(t - i) * nd + d) : PREP_INCL;
+                bool open = true;               // every nearer word was there and not yet a sum
+                bool done = false;
+                int used = 0;
+#pragma unroll
+                for (int i = 0; i < PREP_LOOK; ++i) {
+                    if (open) {
+                        if (v[i] == 0u) {
+                            open = false;
+                        } else if (v[i] >= PREP_INCL) {
+                            below[j] += v[i] - PREP_INCL;
+                            open = false;
+                            done = true;
+                        } else {
+                            below[j] += v[i] - 1u;
+                            ++used;
+                        }
+                    }
+                }
+                if (done) break;
+                t -= used;
+                if (used == 0) __builtin_amdgcn_s_sleep(1);
+            }
+            if (CHAINED && tile > 0) post(&mine[d], PREP_INCL + below[j] + count[j]);
+            dbase[d] = et + below[j] - ec;         // where the tile's i-th key in digit order goes: dbase[digit] + i
+#pragma unroll
+            for (int w = 0; w < L::NW; ++w) whp[w * nd + d] += ec;
+        }
+        et += total[j];
+        ec += count[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) loc[it] += whp[wave * nd + ((key[it] >> a.shift) & dmask)];
+    __syncthreads();
+    // through LDS into digit order, so that a digit's keys leave as one run
+#pragma unroll
+    for (int it = 0; it < IPT; ++it)
+        if (wbase + it * WAVE + lane < n) {
+            skey[loc[it]] = key[it];
+            sval[loc[it]] = val[it];
+        }
+    __syncthreads();
+    const int here = min(TN_RADIX_TILE, n - tile * TN_RADIX_TILE);
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+        const int i = it * THREADS + (int)threadIdx.x;
+        if (i < here) {
+            const u32 k = skey[i];
+            const u32 to = dbase[(k >> a.shift) & dmask] + (u32)i;
+            P.kout[to] = k;
+            P.vout[to] = sval[i];
+        }
+    }
+}
+
+// The digits of every tile and, summed, of every group of tiles, for a counted pass.
+template <int THREADS>
+__device__ __forceinline__ void prep_count(const PrepPass &a, int block, u32 *lds)
+{
+    constexpr int IPT = TN_RADIX_TILE / THREADS;
+    const int nd = 1 << a.bits;
+    const u32 dmask = (u32)nd - 1u;
+    const int pr = block < a.p[1].tiles ? 1 : 0;
+    const int tile = block - (pr ? 0 : a.p[1].tiles);
+    const PrepPassList &P = a.p[pr];
+    if (tile >= P.tiles) return;
+    for (int d = threadIdx.x; d < nd; d += THREADS) lds[d] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+        const int i = tile * TN_RADIX_TILE + it * THREADS + (int)threadIdx.x;
+        if (i < P.n) atomicAdd(&lds[(P.kin[i] >> a.shift) & dmask], 1u);
+    }
+    __syncthreads();
+    for (int d = threadIdx.x; d < nd; d += THREADS) {
+        const u32 c = lds[d];
+        P.state[(size_t)tile * nd + d] = c;
+        if (c) atomicAdd(&P.hist[(size_t)(tile / TN_PREP_GROUP) * nd + d], c);
+    }
+}
+
+// ---------------------------------------------------------------- segments
+__device__ __forceinline__ u64 wave_sum64(u64 x)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += (u64)__shfl_xor((unsigned long long)x, o, WAVE);
+    return x;
+}
+
+// sum of what the tiles below `tile` publish (called by one whole wave; word of tile t: words[t])
+__device__ __forceinline__ u64 prep_below(const u64 *words, int tile, int lane)
+{
+    u64 below = 0;
+    for (int t = tile - 1; t >= 0;) {
+        const u64 v = t - lane >= 0 ? peek(words + (t - lane)) : PREP_SEG_INCL;
+        const u64 there = __ballot((v >> 62) != 0ull), incl = __ballot((v >> 62) == 2ull);
+        // lanes that count: from the nearest tile down to the first sum, if all of them have been published
+        const int first = incl ? (int)__builtin_ctzll(incl) : WAVE - 1;
+        const u64 need = first == WAVE - 1 ? ~0ull : ((2ull << first) - 1ull);
+        if ((there & need) != need) {
+            __builtin_amdgcn_s_sleep(1);
+            continue;
+        }
+        below += wave_sum64(lane <= first ? (v & PREP_SEG_VALUE) : 0ull);
+        if (incl) break;
+        t -= WAVE;
+    }
+    return below;
+}
+
+// Row index (0..U-1) of every sorted entry, first entry of every row, unique row ids, their number, and -- on request
+// -- the segment offsets: entries before a row (out-side), pairs before it (in-side: an entry is a center and weighs
+// its pair count).  Also leaves the digit histograms zero for the next mini-batch of this set.
+// CHAINED: the rows of the lower tiles by the chained scan; else HEADS counts them per tile in a launch of its own
+// (nothing else is written), and the launch after it adds them up.
+template <int THREADS, bool CHAINED, bool HEADS>
+__device__ __forceinline__ void prep_segments(const PrepSegments &a, int block, u32 *lds)
+{
+    constexpr int NW = THREADS / WAVE, IPT = TN_SCAN_TILE / THREADS;
+    const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
+    int tile = CHAINED ? take_ticket(a.ticket, lds) : block;
+    const int pr = tile < a.p[1].tiles ? 1 : 0;
+    if (pr == 0) tile -= a.p[1].tiles;
+    const PrepSegmentsList &p = a.p[pr];
+    if (tile >= p.tiles) return;                // not reached: as many workgroups as tiles
+    if (tile == 0 && !HEADS) {
+        if (threadIdx.x == 0) *p.long_cnt = 0;
+        if (CHAINED && pr == 1)
+            for (int i = threadIdx.x; i < a.n_hist; i += THREADS) a.hist[i] = 0;
+    }
+    const bool weighted = pr == 1 && p.seg_offsets != nullptr;   // the out-side offsets are positions
+
+    const int wbase = tile * TN_SCAN_TILE + wave * (IPT * WAVE);
+    u32 key[IPT];
+    u64 head[IPT];
+    u32 before[IPT];                            // weight of the entries before this one, within the wave
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+        const int i = wbase + it * WAVE + lane;
+        key[it] = i < p.n ? p.keys[i] : 0u;
+    }
+    u32 last = (wbase > 0 && wbase <= p.n) ? p.keys[wbase - 1] : 0u;
+    u32 heads = 0, weight = 0;
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+        const int i = wbase + it * WAVE + lane;
+        const u32 up = (u32)__shfl_up((int)key[it], 1, WAVE);
+        head[it] = __ballot(i < p.n && (i == 0 || key[it] != (lane == 0 ? last : up)));
+        last = (u32)rd_lane((int)key[it], WAVE - 1);
+        heads += (u32)__popcll(head[it]);
+        before[it] = 0;
+        if (weighted) {
+            u32 x = 0;
+            if (i < p.n) {
+                const i64 pos = a.begin + (i64)p.vals[i];
+                const i64 left = pos < a.w ? pos : a.w, right = (a.T - 1 - pos) < a.w ? (a.T - 1 - pos) : a.w;
+                x = (u32)(left + right);
+            }
+            const u32 incl = wave_incl_scan(x, lane);
+            before[it] = weight + incl - x;
+            weight += (u32)rd_lane((int)incl, WAVE - 1);
+        }
+    }
+    u32 *sm = lds, *below = lds + 2 * NW;       // wave totals; what the lower tiles hold
+    if (lane == 0) {
+        sm[wave] = heads;
+        sm[NW + wave] = weight;
+    }
+    __syncthreads();
+    u32 h_tile = 0, w_tile = 0, h0 = 0, w0 = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave) {
+            h0 += sm[w];
+            w0 += sm[NW + w];
+        }
+        h_tile += sm[w];
+        w_tile += sm[NW + w];
+    }
+    if constexpr (HEADS) {
+        if (threadIdx.x == 0) {
+            p.state[tile] = h_tile;
+            if (weighted) p.state[p.tiles + tile] = w_tile;
+        }
+        return;
+    }
+    if (wave == 0) {
+        u64 hb = 0, wb = 0;
+        if (CHAINED) {
+            if (tile > 0) {
+                if (lane == 0) {
+                    post(p.state + tile, PREP_SEG_OWN | (u64)h_tile);
+                    if (weighted) post(p.state + p.tiles + tile, PREP_SEG_OWN | (u64)w_tile);
+                }
+                hb = prep_below(p.state, tile, lane);
+                if (weighted) wb = prep_below(p.state + p.tiles, tile, lane);
+            }
+            if (lane == 0) {
+                post(p.state + tile, PREP_SEG_INCL | (hb + h_tile));
+                if (weighted) post(p.state + p.tiles + tile, PREP_SEG_INCL | (wb + w_tile));
+            }
+        } else {
+#pragma unroll 8
+            for (int t = lane; t < tile; t += WAVE) hb += p.state[t];
+            if (weighted)
+                for (int t = lane; t < tile; t += WAVE) wb += p.state[p.tiles + t];
+            hb = wave_sum64(hb);
+            wb = wave_sum64(wb);
+        }
+        if (lane == 0) {
+            below[0] = (u32)hb;
+            below[1] = (u32)wb;
+        }
+    }
+    __syncthreads();
+    u32 rows = below[0] + h0;                   // rows that begin before this wave's entries
+    const u32 wrun = below[1] + w0;
+    const u64 upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+        const int i = wbase + it * WAVE + lane;
+        const int seg = (int)(rows + (u32)__popcll(head[it] & upto)) - 1;
+        if (i < p.n) {
+            p.seg_of[i] = seg;
+            const int off = weighted ? (int)(wrun + before[it]) : i;
+            if ((head[it] >> lane) & 1ull) {
+                p.seg_start[seg] = i;
+                if ((i64)seg < p.capacity) {
+                    p.row_ids[seg] = (int)key[it];
+                    if (p.seg_offsets) p.seg_offsets[seg] = off;
+                } else {
+                    atomicOr(a.status, ST_OVERFLOW);
+                }
+            }
+            if (i == p.n - 1) {
+                p.seg_start[seg + 1] = p.n;
+                int U = seg + 1;
+                if ((i64)U > p.capacity) U = (int)p.capacity;
+                *p.n_rows = U;
+                if (p.seg_offsets && (i64)(seg + 1) <= p.capacity) {
+                    int all = p.n;
+                    if (weighted) {             // the last center's own weight on top
+                        const i64 pos = a.begin + (i64)p.vals[i];
+                        const i64 left = pos < a.w ? pos : a.w, right = (a.T - 1 - pos) < a.w ? (a.T - 1 - pos) : a.w;
+                        all = off + (int)(left + right);
+                    }
+                    p.seg_offsets[seg + 1] = all;
+                }
+            }
+        }
+        rows += (u32)__popcll(head[it]);
+    }
+}
+
+// ---------------------------------------------------------------- a phase, as a kernel's or a rider's workgroup
+template <int THREADS>
+struct PrepLds {
+    static constexpr int keys = 2 * TN_RADIX_MAX_PASSES_ND;
+    static constexpr int words = PassLds<THREADS>::words > keys ? PassLds<THREADS>::words : keys;
+};
+
+// the phases of a chained preparation
+template <int THREADS>
+__device__ __forceinline__ void prep_block(const PrepPhase &x, int block, u32 *lds)
+{
+    if (x.kind == PREP_KEYS) prep_keys<THREADS>(x.keys, block, x.blocks, lds);
+    else if (x.kind == PREP_PASS) prep_pass<THREADS, true>(x.pass, block, lds);
+    else prep_segments<THREADS, true, false>(x.seg, block, lds);
+}

@@ -135,6 +135,22 @@ def test_sgns_grad_parity_with_resampled_negatives(case):
     _grad_parity(case, resample=True)
 
 
+# sizes at the edges of the preparation's kernels: key widths at which the sort takes one pass more (9, 18 bits) or
+# another digit width, tiles of 2048 keys just full, just begun and all but one key full on either list, and the number
+# of tiles (128 on both lists together) from which the passes are counted instead of chained
+PREP_EDGE_CASES = [(V, 8, 8, 20_000, 1.1, w, N, Bc, 700, "f32")
+                   for V, w, N, Bc in ((512, 8, 15, 8), (513, 8, 15, 8), (512, 8, 15, 9), (2, 4, 7, 31),
+                                       (1 << 18, 8, 15, 128), ((1 << 18) + 1, 8, 15, 127), ((1 << 18) + 1, 1, 0, 2048),
+                                       (90, 1, 0, 2049), (3000, 1, 1, 4097),
+                                       (700, 8, 15, 1016), (700, 8, 15, 1017), (1 << 18, 8, 15, 1017), ((1 << 18) + 1, 8, 15, 1016),
+                                       ((1 << 18) + 1, 8, 15, 2304))]
+
+
+@pytest.mark.parametrize("case", PREP_EDGE_CASES, ids=lambda c: f"V{c[0]}_w{c[5]}_N{c[6]}_B{c[7]}")
+def test_sgns_grad_parity_at_the_edges_of_the_preparation(case):
+    _grad_parity(case)
+
+
 def _random_grad_cases(n, seed):
     """Seeded shapes: narrow to wide rows, windows 1..6, 0..12 negatives, batches from one center up, streams
     from flat to steep, vocabularies from two words up, batches at the start, inside and at the end of the
