@@ -76,14 +76,14 @@ struct PrepLayout {
     size_t tile0, per_pass, tile_out;        // words of the tiles of pass i: from tile0 + i * per_pass
     size_t clear, words;                     // what the keys clear, from the start; all
 };
-PrepLayout prep_layout(const Sizes &s, int O, int n)
+PrepLayout prep_layout(const Sizes &s, int O, int n, bool chained)
 {
     PrepLayout l;
+    l.chained = chained;
     const size_t ti = (size_t)tn_prep_tiles(n), to = (size_t)tn_prep_tiles(O);
     l.seg_in = PREP_TICKETS;
     l.seg_out = l.seg_in + 2 * (2 * (size_t)tn_prep_seg_tiles(n));
     l.pass0 = l.seg_out + 2 * (size_t)tn_prep_seg_tiles(O);
-    l.chained = ti + to <= TN_PREP_CHAIN_MAX;
     const size_t gi = l.chained ? 0 : (ti + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
     const size_t go = l.chained ? 0 : (to + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
     l.groups = (gi + go) * s.nd;
@@ -107,11 +107,12 @@ Sizes sizes_of(const tensair_config &c)
     s.key_bits = kb;
     tn_radix_shape(kb, &s.passes, &s.bits);
     s.nd = 1 << s.bits;
-    const PrepLayout l = prep_layout(s, (int)s.Omax, (int)s.Bmax);
-    s.pub_words = l.words;
-    if (!l.chained) {   // a smaller mini-batch may be chained, which takes more per tile
-        const size_t most = l.pass0 + (size_t)s.passes * TN_PREP_CHAIN_MAX * s.nd;
-        if (s.pub_words < most) s.pub_words = most;
+    {   // a mini-batch may be prepared either way as long as it has at most TN_PREP_CHAIN_MAX tiles
+        const PrepLayout l = prep_layout(s, (int)s.Omax, (int)s.Bmax, false);
+        i64 tiles = (i64)tn_prep_tiles((int)s.Omax) + tn_prep_tiles((int)s.Bmax);
+        if (tiles > TN_PREP_CHAIN_MAX) tiles = TN_PREP_CHAIN_MAX;
+        const size_t chained = l.pass0 + (size_t)s.passes * (size_t)tiles * s.nd;
+        s.pub_words = l.words > chained ? l.words : chained;
     }
     s.tiles_out = (int)((s.Omax + tn_seg_tile(s.Omax) - 1) / tn_seg_tile(s.Omax));   // worst case over n <= Omax
     if (s.Omax > 65536 && s.tiles_out < 65536 / 8) s.tiles_out = 65536 / 8;
@@ -151,7 +152,9 @@ struct BatchSet {
 // A mini-batch announced by tensair_prefetch.
 struct Prefetched {
     bool valid = false;
-    bool unprepared = false;   // announced, but left for the consuming call to prepare
+    bool chained = false;      // how it is (to be) prepared: riding in the launches of the call before, phase by phase ...
+    int phase = 0;             // ... phases of its preparation that are enqueued; the consuming call does the rest
+    bool on_side = false;      // ... or as a whole on the second stream (ev_prep)
     const int32_t *tokens = nullptr;
     i64 n_tokens = 0, begin = 0, P = 0;
     int n_centers = 0;
@@ -161,6 +164,12 @@ struct Prefetched {
         return valid && tokens == t && n_tokens == nt && begin == b && n_centers == n && epoch == e &&
                worker_id == w;
     }
+};
+
+// A bucket of the alias table; the two lie side by side, so that a draw reads both with one access.
+struct Draw {
+    uint32_t thr;
+    int32_t alias;
 };
 
 struct tensair_model {
@@ -180,28 +189,23 @@ struct tensair_model {
                                // the one the next step will index can be cleared while this step still reads its own
     bool mask_clean[2] = {false, false};   // buffer b is all zeros (or will be when everything enqueued so far has run)
     u32 *wbase[2], *wblk[2];   // tensair_grad_add: place of every 64-row word in the summed gradient
-    std::vector<uint32_t> h_thr;
-    std::vector<int32_t> h_alias;
+    std::vector<Draw> h_draw;  // the same on the host
     // second stream, forked from and joined to the caller's stream with events: it runs what can go
     // on next to the caller's stream (the forward pass beside the sort, the index of the coming table
     // update beside the reductions, the preparation of announced mini-batches)
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_fwd = nullptr;
     // mini-batch sets: `busy` is the one the most recent gradient call reads; announced mini-batches are
-    // prepared into the other one on the second stream (ev_prep recorded behind them)
+    // prepared into the other one, riding in the launches of that call or on the second stream (ev_prep recorded
+    // behind them)
     int busy = 1;
-    Prefetched pend;               // prepared (or being prepared) in set 1 - busy
-    Prefetched next;               // announced after `pend`: prepared when `pend` is consumed
+    Prefetched pend;               // prepared, or being prepared, or to be prepared in set 1 - busy
+    Prefetched next;               // announced after `pend`: prepared from when `pend` is consumed
     hipEvent_t ev_prep = nullptr, ev_reduced = nullptr;
-    // a preparation enqueued beside a gradient calculation may still be running when its mini-batch is
-    // consumed: its keys get an event of their own, so that the forward pass (which only needs the keys)
-    // can start while the sort and the segment scan finish
-    hipEvent_t ev_keys = nullptr;
-    bool pend_late = false;
     bool side_follows = false;     // the second stream has waited for the start of the latest gradient call
     // every event recorded on the second stream takes a ticket; the caller's stream is behind all of
     // them up to main_ticket, so a prepared set with prep_ticket <= main_ticket needs no wait
-    u64 side_ticket = 0, main_ticket = 0, prep_ticket = 0, keys_ticket = 0;
+    u64 side_ticket = 0, main_ticket = 0, prep_ticket = 0;
     // set by tensair_step: the index of the coming apply is built by extra workgroups at the front of the
     // forward pass (clearing) and of the segmented reduction (the id lists), on the caller's stream
     ApplyArgs *fused_apply = nullptr;
@@ -275,17 +279,15 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
 // probability is below 1 keep floor(p * 2^32) as acceptance threshold and hand the rest
 // of their mass to a donor; work lists are filled in ascending id order and consumed
 // from the back, so the table is a deterministic function of the counts.
-bool build_alias(const uint64_t *counts, i64 V, std::vector<uint32_t> &thr,
-                 std::vector<int32_t> &alias)
+bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw)
 {
-    thr.assign((size_t)V, 0xFFFFFFFFu);
-    alias.resize((size_t)V);
+    draw.resize((size_t)V);
     std::vector<double> prob((size_t)V);
     double total = 0.0;
     for (i64 i = 0; i < V; ++i) {
         prob[(size_t)i] = std::pow((double)counts[i], 0.75);
         total += prob[(size_t)i];
-        alias[(size_t)i] = (int32_t)i;
+        draw[(size_t)i] = {0xFFFFFFFFu, (int32_t)i};
     }
     if (!(total > 0.0)) return false;
     std::vector<int32_t> lo, hi;
@@ -304,8 +306,7 @@ bool build_alias(const uint64_t *counts, i64 V, std::vector<uint32_t> &thr,
         const int32_t rich = hi.back();
         hi.pop_back();
         const double t = std::floor(prob[(size_t)poor] * two32);
-        thr[(size_t)poor] = t >= two32 ? 0xFFFFFFFFu : (uint32_t)t;
-        alias[(size_t)poor] = rich;
+        draw[(size_t)poor] = {t >= two32 ? 0xFFFFFFFFu : (uint32_t)t, rich};
         const double rest = (prob[(size_t)rich] + prob[(size_t)poor]) - 1.0;
         prob[(size_t)rich] = rest;
         (rest < 1.0 ? lo : hi).push_back(rich);
@@ -430,18 +431,17 @@ int tensair_model_init(tensair_model **out, const tensair_config *cfg, void *w_i
     m->w_in = w_in;
     m->w_out = w_out;
     carve(*cfg, sz, (char *)workspace, m);
-    if (!build_alias(unigram_counts, cfg->vocab, m->h_thr, m->h_alias)) {
+    if (!build_alias(unigram_counts, cfg->vocab, m->h_draw)) {
         delete m;
         return fail(TENSAIR_EINVAL, "unigram_counts has no positive entry");
     }
     hipStream_t st = (hipStream_t)stream;
-    // threshold and alias of a bucket side by side: a draw reads both with one access
-    std::vector<uint32_t> draw(2 * (size_t)cfg->vocab);
-    for (i64 i = 0; i < cfg->vocab; ++i) {
-        draw[2 * (size_t)i] = m->h_thr[(size_t)i];
-        draw[2 * (size_t)i + 1] = (uint32_t)m->h_alias[(size_t)i];
+    // in pieces of 4 MB: longer copies from pageable memory take another, slower way (8 MB: 7 ms more)
+    hipError_t e = hipSuccess;
+    for (size_t at = 0, n = (size_t)cfg->vocab; at < n && e == hipSuccess; at += (size_t)1 << 19) {
+        const size_t k = n - at < ((size_t)1 << 19) ? n - at : (size_t)1 << 19;
+        e = hipMemcpyAsync(m->draw + at, m->h_draw.data() + at, k * sizeof(Draw), hipMemcpyHostToDevice, st);
     }
-    hipError_t e = hipMemcpyAsync(m->draw, draw.data(), (size_t)cfg->vocab * 8, hipMemcpyHostToDevice, st);
     int zero[4] = {0, 0, 0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(m->status, zero, sizeof(zero), hipMemcpyHostToDevice, st);
     if (e == hipSuccess && fill_tables) {
@@ -457,7 +457,6 @@ int tensair_model_init(tensair_model **out, const tensair_config *cfg, void *w_i
         hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&m->ev_fwd, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&m->ev_prep, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&m->ev_keys, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&m->ev_reduced, hipEventDisableTiming) != hipSuccess) {
         tensair_model_destroy(m);
         return fail(TENSAIR_EHIP, "model_init: cannot create the side stream");
@@ -480,8 +479,10 @@ int tensair_model_rebind(tensair_model *m, void *w_in, void *w_out, uint32_t wor
 int tensair_model_alias(const tensair_model *m, uint32_t *thr, int32_t *alias)
 {
     if (!m || !thr || !alias) return fail(TENSAIR_EINVAL, "NULL pointer argument");
-    memcpy(thr, m->h_thr.data(), (size_t)m->cfg.vocab * 4);
-    memcpy(alias, m->h_alias.data(), (size_t)m->cfg.vocab * 4);
+    for (size_t i = 0; i < (size_t)m->cfg.vocab; ++i) {
+        thr[i] = m->h_draw[i].thr;
+        alias[i] = m->h_draw[i].alias;
+    }
     return TENSAIR_OK;
 }
 
@@ -520,9 +521,9 @@ static BatchWork batch_work(const tensair_config &c, const int32_t *tokens, i64 
     return w;
 }
 
-// Whether the preparation of a mini-batch is a chained one, and its phases: the keys, the sort (per pass one, or a
+// Tiles of a mini-batch's two key lists together, and the phases of its preparation: the keys, the sort (per pass one, or a
 // count and a pass), the segments (one, or the heads and the segments).
-static bool prep_chained(const BatchWork &w) { return tn_prep_tiles((int)w.O) + tn_prep_tiles(w.b.n_centers) <= TN_PREP_CHAIN_MAX; }
+static int prep_tiles(const tensair_config &c, i64 P, int n_centers) { return tn_prep_tiles((int)(P * (c.negatives + 1))) + tn_prep_tiles(n_centers); }
 static int prep_phases(const Sizes &s, bool chained) { return chained ? s.passes + 2 : 2 * s.passes + 3; }
 static int prep_sort_end(const Sizes &s, bool chained) { return prep_phases(s, chained) - (chained ? 1 : 2); }
 
@@ -546,12 +547,12 @@ static SortedSide sorted_side(const tensair_model *m, const BatchSet &S, int sid
 
 // One phase as it is launched.  Key lists: out-side occurrences at [0, O), in-side centers at [Omax, Omax + n_centers);
 // the unsorted keys in keys[0] are never written again (the forward pass reads them); the passes go 0 -> 1 -> 2 -> 1.
-static void make_prep_phase(tensair_model *m, BatchSet &S, const BatchWork &w, int phase, const RowIndexDst &in,
-                            const RowIndexDst &out, int32_t *negatives_dbg, PrepPhase &x)
+static void make_prep_phase(tensair_model *m, BatchSet &S, const BatchWork &w, bool chained, int phase,
+                            const RowIndexDst &in, const RowIndexDst &out, int32_t *negatives_dbg, PrepPhase &x)
 {
     const tensair_config &c = m->cfg;
     const Sizes &s = m->sz;
-    const PrepLayout l = prep_layout(s, (int)w.O, w.b.n_centers);
+    const PrepLayout l = prep_layout(s, (int)w.O, w.b.n_centers, chained);
     memset(&x, 0, sizeof(x));
     const int n[2] = {(int)w.O, w.b.n_centers};
     const size_t at[2] = {0, (size_t)s.Omax};
@@ -559,7 +560,7 @@ static void make_prep_phase(tensair_model *m, BatchSet &S, const BatchWork &w, i
         PrepKeys &k = x.keys;
         x.kind = PREP_KEYS;
         const i64 slots = (i64)w.b.n_centers * 2 * c.window * (c.negatives + 1);
-        x.blocks = (int)((slots + 256 * PREP_KEYS_ITEMS - 1) / (256 * PREP_KEYS_ITEMS));
+        x.blocks = (int)((slots + PREP_KEYS_SLOTS - 1) / PREP_KEYS_SLOTS);
         k.b = w.b;
         k.V = c.vocab;
         k.draw = m->draw;
@@ -646,15 +647,23 @@ static void before_prep_phase(tensair_model *m, BatchSet &S, int kind, hipStream
 }
 
 // the phases [from, to) as launches of their own
-static void enqueue_prep(tensair_model *m, BatchSet &S, const BatchWork &w, int from, int to, const RowIndexDst &in,
-                         const RowIndexDst &out, int32_t *negatives_dbg, hipStream_t st)
+static void enqueue_prep(tensair_model *m, BatchSet &S, const BatchWork &w, bool chained, int from, int to,
+                         const RowIndexDst &in, const RowIndexDst &out, int32_t *negatives_dbg, hipStream_t st)
 {
     for (int phase = from; phase < to; ++phase) {
         PrepPhase x;
-        make_prep_phase(m, S, w, phase, in, out, negatives_dbg, x);
+        make_prep_phase(m, S, w, chained, phase, in, out, negatives_dbg, x);
         before_prep_phase(m, S, x.kind, st);
         tn_launch_prep(x, st);
     }
+}
+
+// where a mini-batch that is prepared ahead leaves its row index
+static void set_row_index(const tensair_model *m, const BatchSet &S, RowIndexDst &in, RowIndexDst &out)
+{
+    const tensair_config &c = m->cfg;
+    in = {S.ids_in, S.n_rows, S.off_in, tensair_capacity_in(&c, c.max_centers)};
+    out = {S.ids_out, S.n_rows + 1, S.off_out, tensair_capacity_out(&c, c.max_centers)};
 }
 
 static int check_batch(const tensair_model *m, const int32_t *tokens, i64 n_tokens, i64 center_begin, int n_centers,
@@ -670,41 +679,59 @@ static int check_batch(const tensair_model *m, const int32_t *tokens, i64 n_toke
     return TENSAIR_OK;
 }
 
-// Enqueue the preparation of an announced mini-batch on the second stream, into the set that the
-// latest gradient call does not read.  The second stream must already be behind that set's last readers.
-// late: the preparation may still be running when the mini-batch is consumed (it was not tucked under a
-// long table update), so its keys are made available on their own.
-// A preparation that runs beside the forward pass and the reductions of a step pays only where those kernels
-// leave the chip idle between their round trips, i.e. for small mini-batches (measured: 1 k and 10 k pairs per
-// step 6 % and 18 % faster with it, 262 k pairs 4 % slower: there both sides fight for the caches).  Larger
-// mini-batches are prepared ahead only under a long table update; otherwise the consuming call prepares them.
+// Where an announced mini-batch is prepared.
+//   Riding: phase by phase at the front of the launches of the gradient call before the one that consumes it (forward
+//     pass, reduction, chaining, table update), whose latencies hide it: no launch, event or stream of its own.  An
+//     event between two streams costs the host 15 us and the waiting stream 4 to 7, a launch 3 to 5: steps of 60 000
+//     occurrences took 80 us of host time with the preparation on the second stream and 65 us in all riding.  Up to
+//     TN_PREP_CHAIN_RIDE tiles.
+//   On the second stream under a table update that is long enough (tensair_step decides), for larger ones; or at once
+//     when announced with nothing before it, up to TN_BESIDE_MAX_OCC occurrences.
+//   Else not ahead: beside a forward pass of cache-resident tables both fight for the caches (262 000 pairs per step
+//     4 % slower).
 #ifndef TN_BESIDE_MAX_OCC
 #define TN_BESIDE_MAX_OCC (1 << 20)
 #endif
-static bool worth_preparing_beside(const tensair_model *m, const Prefetched &d)
+static bool rides(const tensair_model *m, const Prefetched &d)
 {
-    return d.P * (m->cfg.negatives + 1) <= TN_BESIDE_MAX_OCC;
+    return prep_tiles(m->cfg, d.P, d.n_centers) <= TN_PREP_CHAIN_RIDE;
 }
 
-static int enqueue_prepare(tensair_model *m, const Prefetched &d, bool late)
+// The next phase of the announced mini-batch m->pend, if it is one that rides and is not done: the caller attaches it
+// to the launch that it makes next on `st`.  The keys ride with a forward pass, the others with whatever follows it.
+static bool next_rider(tensair_model *m, bool forward, PrepPhase &x, hipStream_t st)
+{
+    Prefetched &d = m->pend;
+    if (!d.valid || !d.chained || d.on_side || (d.phase == 0) != forward || d.phase >= prep_phases(m->sz, true)) return false;
+    BatchSet &S = m->set[1 - m->busy];
+    const BatchWork w = batch_work(m->cfg, d.tokens, d.n_tokens, d.begin, d.n_centers, d.epoch, d.P);
+    RowIndexDst in, out;
+    set_row_index(m, S, in, out);
+    make_prep_phase(m, S, w, true, d.phase, in, out, nullptr, x);
+    before_prep_phase(m, S, x.kind, st);
+    ++d.phase;
+    return true;
+}
+
+// Enqueue the preparation of an announced mini-batch on the second stream, into the set that the
+// latest gradient call does not read.  The second stream must already be behind that set's last readers.
+static int enqueue_prepare(tensair_model *m, const Prefetched &d)
 {
     const tensair_config &c = m->cfg;
     BatchSet &S = m->set[1 - m->busy];
     const BatchWork w = batch_work(c, d.tokens, d.n_tokens, d.begin, d.n_centers, d.epoch, d.P);
-    const RowIndexDst in = {S.ids_in, S.n_rows, S.off_in, tensair_capacity_in(&c, c.max_centers)};
-    const RowIndexDst out = {S.ids_out, S.n_rows + 1, S.off_out, tensair_capacity_out(&c, c.max_centers)};
-    enqueue_prep(m, S, w, 0, 1, in, out, nullptr, m->side);
-    if (late) {
-        HIP_TRY(hipEventRecord(m->ev_keys, m->side));
-        m->keys_ticket = ++m->side_ticket;
-    }
-    m->pend_late = late;
-    enqueue_prep(m, S, w, 1, prep_phases(m->sz, prep_chained(w)), in, out, nullptr, m->side);
+    RowIndexDst in, out;
+    set_row_index(m, S, in, out);
+    const bool chained = prep_tiles(c, d.P, d.n_centers) <= TN_PREP_CHAIN_OWN;
+    const int phases = prep_phases(m->sz, chained);
+    enqueue_prep(m, S, w, chained, 0, phases, in, out, nullptr, m->side);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(m->ev_prep, m->side));
     m->prep_ticket = ++m->side_ticket;
     m->pend = d;
-    m->pend.unprepared = false;
+    m->pend.chained = chained;
+    m->pend.phase = phases;
+    m->pend.on_side = true;
     return TENSAIR_OK;
 }
 
@@ -716,7 +743,6 @@ static void abandon_side_work(tensair_model *m)
 {
     if (m->side) (void)hipStreamSynchronize(m->side);
     m->pend.valid = m->next.valid = m->deferred.valid = false;
-    m->pend_late = false;
     m->side_follows = false;
     m->main_ticket = m->side_ticket;
     m->fused_apply = nullptr;
@@ -746,9 +772,9 @@ int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, 
         m->next = d;
         return TENSAIR_OK;
     }
-    if (!worth_preparing_beside(m, d)) {   // kept as an announcement: the consuming call prepares it itself
-        m->pend = d;
-        m->pend.unprepared = true;
+    const int tiles = prep_tiles(c, d.P, n_centers);
+    if (tiles <= TN_PREP_CHAIN_OWN || d.P * (c.negatives + 1) > TN_BESIDE_MAX_OCC) {
+        m->pend = d;               // kept as an announcement: the consuming call prepares it itself
         return TENSAIR_OK;
     }
     // The set being filled was last read by the gradient call before the latest one.  If the second
@@ -760,7 +786,7 @@ int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, 
         HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
         m->side_follows = true;
     }
-    const int rc2 = enqueue_prepare(m, d, true);
+    const int rc2 = enqueue_prepare(m, d);
     if (rc2 == TENSAIR_EHIP) abandon_side_work(m);
     return rc2;
 }
@@ -789,46 +815,49 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     const BatchWork w = batch_work(c, tokens, n_tokens, center_begin, n_centers, epoch, P);
 
     // Streams.  The sort and the segment scan only need the keys, the forward pass the keys and the
-    // tables, the reductions both.  Without a prefetch the chain that the apply waits for (keys, sort,
-    // segments, reductions) stays on the caller's stream, so that none of its links is a cross-stream
-    // wait, and the forward pass runs next to the sort on the library's second stream.  With a matching
-    // prefetch the keys, the sorted order and the segments are already there (made on the second stream
-    // while the previous step ran) and the caller's stream starts with the forward pass.  The small jobs
-    // around them -- the prepared row index to the caller's buffers, and inside tensair_step the index of
-    // the coming table update -- ride at the front of the forward and the reduction launches: every event
-    // between streams idles the waiting stream for microseconds, and a launch of their own is not worth
-    // one.  When every stage is being timed (profile level 2) everything is serialised on the caller's
-    // stream in launches of its own.
+    // tables, the reductions both.  Everything runs on the caller's stream, with these exceptions: a large
+    // mini-batch that nobody prepared has its forward pass on the library's second stream, next to its sort,
+    // and one that a long table update of the call before could hide was prepared there.  What is small rides
+    // at the front of other launches: the phases that are still missing of this mini-batch's preparation and
+    // those of the announced one after it, the prepared row index to the caller's buffers, and inside
+    // tensair_step the index of the coming table update.  An event between streams costs the host 15 us and
+    // idles the waiting stream for microseconds, a launch of its own 3 to 5 us.  When every stage is being
+    // timed (profile level 2) everything is serialised on the caller's stream in launches of its own.
     const bool overlap = m->prof_level < 2;
     const bool fuse = overlap && m->fused_apply != nullptr;
     const bool announced = overlap && negatives_dbg == nullptr &&
                            m->pend.is(tokens, n_tokens, center_begin, n_centers, epoch, c.worker_id);
-    const bool prepared = announced && !m->pend.unprepared;
-    m->pend.valid = false;
+    const Prefetched own = announced ? m->pend : Prefetched();
     // the announced mini-batch after this one is prepared during this call; announcements that this
     // call does not follow are dropped
     const Prefetched following = announced ? m->next : Prefetched();
+    m->pend.valid = false;
     m->next.valid = false;
     m->deferred.valid = false;
     // this call takes the set that announced mini-batches are prepared into; one that does not match
     // is overwritten, after its preparation has finished
     const int u = 1 - m->busy;
     BatchSet &S = m->set[u];
-    // a prepared set that may not be finished yet: the forward pass waits for its keys only, the reductions
-    // for the rest (below); otherwise the caller's stream gets behind the whole preparation here
-    const bool split = prepared && m->pend_late && m->prep_ticket > m->main_ticket;
-    if (split) {
-        if (m->keys_ticket > m->main_ticket) {
-            HIP_TRY(hipStreamWaitEvent(st, m->ev_keys, 0));
-            m->main_ticket = m->keys_ticket;
-        }
-    } else if (m->prep_ticket > m->main_ticket) {
+    if (m->prep_ticket > m->main_ticket) {
         HIP_TRY(hipStreamWaitEvent(st, m->ev_prep, 0));
         m->main_ticket = m->prep_ticket;
     }
-    const u64 consumed_prep_ticket = m->prep_ticket;   // enqueue_prepare below moves on to the following mini-batch
     m->busy = u;
     m->side_follows = false;
+    // how far this mini-batch is prepared, and how the rest is done
+    int phase = own.phase;
+    const bool chained = phase > 0 ? own.chained : prep_tiles(c, P, n_centers) <= TN_PREP_CHAIN_OWN;
+    const int phases = prep_phases(s, chained), sorted = prep_sort_end(s, chained);
+    const bool prepared = phase == phases;
+    // the one after it: under a long table update that follows (tensair_step decides), riding, or left to its own call
+    if (following.valid) {
+        if (fuse && m->prepare_under_apply && !rides(m, following)) {
+            m->deferred = following;
+        } else {
+            m->pend = following;
+            m->pend.chained = rides(m, following);
+        }
+    }
     mark(m, PF_BEGIN_GRAD, st);
 
     FwdArgs f;
@@ -864,7 +893,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         }
         for (int t = 0; t < 2; ++t) fa.mask[t] = pick ? m->mask_alt[t] : m->mask[t];
         m->mask_clean[pick] = false;
-        const bool own_early = prepared && !split;   // the own id lists exist when the forward pass starts
+        const bool own_early = prepared;             // the own id lists exist when the forward pass starts
         tn_aux_add_index(aux_fwd, fa, own_early ? 0 : 1, fa.n_src);
         if (!own_early) tn_aux_add_index(aux_red, fa, 0, 1);
         if (!m->mask_clean[1 - pick]) {
@@ -875,17 +904,18 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         m->fused_index_done = true;
     }
 
+    const RowIndexDst in = {grad_out->in.row_ids, grad_out->in.n_rows, seg_offsets_in, grad_out->in.capacity};
+    const RowIndexDst out = {grad_out->out.row_ids, grad_out->out.n_rows, seg_offsets_out, grad_out->out.capacity};
+    PrepPhase x;
     if (prepared) {
-        // this mini-batch's row index goes to the caller's buffers with the forward pass -- with the
-        // reductions if the forward pass starts on the keys alone, before the sort has finished
+        // this mini-batch's row index goes to the caller's buffers with the forward pass
         RowIndexCopy rc2;
         rc2.side[0] = {S.ids_in, S.n_rows, S.off_in, grad_out->in.row_ids, grad_out->in.n_rows, seg_offsets_in};
         rc2.side[1] = {S.ids_out, S.n_rows + 1, S.off_out, grad_out->out.row_ids, grad_out->out.n_rows,
                        seg_offsets_out};
-        tn_aux_add_copy(split ? aux_red : aux_fwd, rc2, tensair_capacity_out(&c, n_centers));
-        if (fuse) {   // the own id lists are indexed where they are, whichever launch copies them
-            AuxWork &ix = split ? aux_red : aux_fwd;
-            ApplySrc &o_in = ix.apply.src[0][0], &o_out = ix.apply.src[1][0];
+        tn_aux_add_copy(aux_fwd, rc2, tensair_capacity_out(&c, n_centers));
+        if (fuse) {   // the own id lists are indexed where they are
+            ApplySrc &o_in = aux_fwd.apply.src[0][0], &o_out = aux_fwd.apply.src[1][0];
             o_in.ids = S.ids_in;
             o_in.n_rows = S.n_rows;
             o_in.capacity = tensair_capacity_in(&c, c.max_centers);
@@ -893,75 +923,46 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
             o_out.n_rows = S.n_rows + 1;
             o_out.capacity = tensair_capacity_out(&c, c.max_centers);
         }
-        // Where a long table update follows (tensair_step decides), the following mini-batch is prepared
-        // under that update, which is bound by HBM bandwidth and loses little to it; otherwise next to this
-        // call's forward pass, for which the second stream gets behind the caller's stream here.
-        const bool under_apply = fuse && m->prepare_under_apply;
-        if (following.valid && !under_apply) {
-            HIP_TRY(hipEventRecord(m->ev_fork, st));
-            HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
-            m->side_follows = true;
-        }
-        tn_launch_forward(f, &aux_fwd, st);
-        if (mean_loss) tn_launch_loss(m->center_loss, n_centers, f.inv_P, mean_loss, st);
-        if (split) {   // the sorted order and the segments of this mini-batch
-            HIP_TRY(hipStreamWaitEvent(st, m->ev_prep, 0));
-            if (consumed_prep_ticket > m->main_ticket) m->main_ticket = consumed_prep_ticket;
-        }
-        if (following.valid) {
-            if (under_apply) {
-                m->deferred = following;
-            } else if (worth_preparing_beside(m, following)) {
-                if ((rc = enqueue_prepare(m, following, true))) return rc;
-            } else {
-                m->pend = following;
-                m->pend.unprepared = true;
-            }
-        }
-    } else {
+    } else if (phase == 0) {
         // 1. keys
-        const RowIndexDst in = {grad_out->in.row_ids, grad_out->in.n_rows, seg_offsets_in, grad_out->in.capacity};
-        const RowIndexDst out = {grad_out->out.row_ids, grad_out->out.n_rows, seg_offsets_out,
-                                 grad_out->out.capacity};
-        enqueue_prep(m, S, w, 0, 1, in, out, negatives_dbg, st);
-        mark(m, PF_KEYS, st);
-        hipStream_t s_fwd = st;
-        if (overlap) {
-            HIP_TRY(hipEventRecord(m->ev_fork, st));
-            HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
-            m->side_follows = true;
-            s_fwd = m->side;
+        enqueue_prep(m, S, w, chained, 0, 1, in, out, negatives_dbg, st);
+        phase = 1;
+    }
+    mark(m, PF_KEYS, st);
+    // 2. forward on the unsorted keys (the sort never writes their buffer): g per occurrence, per-center share of the
+    //    W_in gradient, loss terms
+    const bool aside = overlap && !chained && !prepared;
+    if (aside) {
+        HIP_TRY(hipEventRecord(m->ev_fork, st));
+        HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
+        m->side_follows = true;
+    } else if (overlap) {
+        if (phase < phases) {
+            make_prep_phase(m, S, w, chained, phase, in, out, nullptr, x);
+            before_prep_phase(m, S, x.kind, st);
+            ++phase;
+            tn_aux_add_prep(aux_fwd, x);
         }
-        // 2. forward on the unsorted keys (the sort never writes their buffer): g per occurrence,
-        //    per-center share of the W_in gradient, loss terms
-        tn_launch_forward(f, &aux_fwd, s_fwd);
-        if (mean_loss) tn_launch_loss(m->center_loss, n_centers, f.inv_P, mean_loss, s_fwd);
-        mark(m, PF_FORWARD, st);
-        u64 fwd_ticket = 0;
-        if (overlap) {
-            HIP_TRY(hipEventRecord(m->ev_fwd, m->side));
-            fwd_ticket = ++m->side_ticket;
-        }
-        if (following.valid) {   // this mini-batch was announced but not prepared; the one after it may be
-            if (fuse && m->prepare_under_apply) {
-                m->deferred = following;
-            } else if (worth_preparing_beside(m, following)) {
-                if ((rc = enqueue_prepare(m, following, true))) return rc;   // behind the forward pass
-            } else {
-                m->pend = following;
-                m->pend.unprepared = true;
-            }
-        }
-        // 3./4. sort and segments, row index straight into the caller's buffers
-        const int sorted = prep_sort_end(s, prep_chained(w));
-        enqueue_prep(m, S, w, 1, sorted, in, out, nullptr, st);
-        mark(m, PF_SORT, st);
-        enqueue_prep(m, S, w, sorted, prep_phases(s, prep_chained(w)), in, out, nullptr, st);
-        mark(m, PF_SEGMENTS, st);
-        if (overlap) {   // behind the forward pass (not behind a preparation enqueued after it)
-            HIP_TRY(hipStreamWaitEvent(st, m->ev_fwd, 0));
-            if (fwd_ticket > m->main_ticket) m->main_ticket = fwd_ticket;
-        }
+        if (next_rider(m, true, x, st)) tn_aux_add_prep(aux_fwd, x);
+    }
+    tn_launch_forward(f, &aux_fwd, aside ? m->side : st);
+    mark(m, PF_FORWARD, st);
+    u64 fwd_ticket = 0;
+    if (aside) {
+        HIP_TRY(hipEventRecord(m->ev_fwd, m->side));
+        fwd_ticket = ++m->side_ticket;
+    }
+    // 3./4. what is missing of sort and segments, row index straight into the caller's buffers
+    if (phase < sorted) {
+        enqueue_prep(m, S, w, chained, phase, sorted, in, out, nullptr, st);
+        phase = sorted;
+    }
+    mark(m, PF_SORT, st);
+    enqueue_prep(m, S, w, chained, phase, phases, in, out, nullptr, st);
+    mark(m, PF_SEGMENTS, st);
+    if (aside) {
+        HIP_TRY(hipStreamWaitEvent(st, m->ev_fwd, 0));
+        if (fwd_ticket > m->main_ticket) m->main_ticket = fwd_ticket;
     }
 
     // 5. segmented reductions: duplicates of a row summed in sorted (= occurrence) order
@@ -1000,11 +1001,16 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     r_out.dtype = c.dtype;
     r_out.stride = c.row_stride;
     if (overlap) {   // both sides in one launch
-        tn_launch_segreduce(&r_out, &r_in, &aux_red, st);
+        if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, n_centers, f.inv_P, mean_loss);
+        if (next_rider(m, false, x, st)) tn_aux_add_prep(aux_red, x);
+        PrepPhase y;
+        const bool rider = tn_seg_chains(r_out.n) + tn_seg_chains(r_in.n) > 0 && next_rider(m, false, y, st);
+        tn_launch_segreduce(&r_out, &r_in, &aux_red, rider ? &y : nullptr, st);
     } else {         // one after the other, so that each can be timed
-        tn_launch_segreduce(nullptr, &r_in, nullptr, st);
+        if (mean_loss) tn_launch_loss(m->center_loss, n_centers, f.inv_P, mean_loss, st);
+        tn_launch_segreduce(nullptr, &r_in, nullptr, nullptr, st);
         mark(m, PF_REDUCE_IN, st);
-        tn_launch_segreduce(&r_out, nullptr, nullptr, st);
+        tn_launch_segreduce(&r_out, nullptr, nullptr, nullptr, st);
     }
     mark(m, PF_REDUCE_OUT, st);
     HIP_TRY(hipGetLastError());
@@ -1036,7 +1042,7 @@ static int enqueue_deferred_prepare(tensair_model *m, hipEvent_t ev, hipStream_t
     }
     HIP_TRY(hipStreamWaitEvent(m->side, ev, 0));
     m->side_follows = true;
-    return enqueue_prepare(m, d, false);
+    return enqueue_prepare(m, d);
 }
 
 // peers are fp32 gradients (`peers`) or bfloat16 messages (`packed`), never both
@@ -1089,7 +1095,7 @@ static int apply_impl(tensair_model *m, const tensair_sparse_grad *own, const te
     tn_launch_apply_clear(a, st);
     tn_launch_apply_index(a, 0, a.n_src, st);
     mark(m, PF_APPLY_INDEX, st);
-    tn_launch_apply_update(a, st);
+    tn_launch_apply_update(a, nullptr, st);
     ++m->apply_serial;
     mark(m, PF_APPLY_UPDATE, st);
     HIP_TRY(hipGetLastError());
@@ -1249,7 +1255,9 @@ static int step_impl(tensair_model *m, const int32_t *tokens, int64_t n_tokens, 
     // the event that opens the timing of the table update also lets the second stream go
     const hipEvent_t ev = mark(m, PF_APPLY_INDEX, st);
     if ((rc = enqueue_deferred_prepare(m, ev, st))) return rc;
-    tn_launch_apply_update(a, st);
+    PrepPhase x;
+    const bool rider = m->prof_level < 2 && tn_apply_carries(a.D) && next_rider(m, false, x, st);
+    tn_launch_apply_update(a, rider ? &x : nullptr, st);
     ++m->apply_serial;
     mark(m, PF_APPLY_UPDATE, st);
     HIP_TRY(hipGetLastError());
@@ -1424,7 +1432,6 @@ int tensair_model_destroy(tensair_model *m)
         if (m->ev_fork) (void)hipEventDestroy(m->ev_fork);
         if (m->ev_fwd) (void)hipEventDestroy(m->ev_fwd);
         if (m->ev_prep) (void)hipEventDestroy(m->ev_prep);
-        if (m->ev_keys) (void)hipEventDestroy(m->ev_keys);
         if (m->ev_reduced) (void)hipEventDestroy(m->ev_reduced);
         if (m->side) {
             (void)hipStreamSynchronize(m->side);   // a pending prefetch still writes the workspace

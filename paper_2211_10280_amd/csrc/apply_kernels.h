@@ -1,0 +1,477 @@
+// The table update's kernels and the choice among them.  They come twice: alone (apply.hip), and with a phase of the
+// coming mini-batch's preparation riding at the front of the grid (apply_ride.hip), whose code takes registers -- and
+// with them waves -- that the update alone makes use of (4 M words, few touched: 259 us at 7 waves per SIMD, 279 at 6).
+#pragma once
+#include <type_traits>
+
+#include "aux_dev.h"
+#include "dev_common.h"
+#include "kernels.h"
+
+#ifndef APPLY_CHUNK
+#define APPLY_CHUNK 16   // consecutive workgroups kept on one XCD
+#endif
+
+struct NoRider {
+    static constexpr bool narrow = false;
+    __device__ __forceinline__ bool block() const { return false; }
+    __host__ __device__ __forceinline__ int blocks() const { return 0; }
+    unsigned lds_bytes() const { return 0; }
+};
+struct PhaseRider {
+    static constexpr bool narrow = true;    // rides with rows of at most 512 elements (tn_apply_carries)
+    PrepPhase x;
+    __device__ __forceinline__ bool block() const
+    {
+        if ((int)blockIdx.x >= x.blocks) return false;
+        prep_block<BLOCK, false>(x, (int)blockIdx.x, ride_lds);
+        return true;
+    }
+    __host__ __device__ __forceinline__ int blocks() const { return x.blocks; }
+    unsigned lds_bytes() const { return ride_lds_bytes(x); }
+};
+
+// ---------------------------------------------------------------- apply
+#ifndef APPLY_G
+#define APPLY_G 4   // vocabulary rows per wave (measured: 16 -> 4 rows gains 4 %)
+#endif
+#ifndef APPLY_G_SPARSE
+#define APPLY_G_SPARSE 16   // the same where few of the vocabulary's rows are touched
+#endif
+
+// Stochastic rounding of one fp32 value to bfloat16: 16 random bits are added below the bfloat16 mantissa
+// and the sum is truncated, so the value goes up with probability (discarded bits)/2^16; infinities and
+// NaN are kept.
+__device__ __forceinline__ u32 sr_bf16(float f, u32 rnd)
+{
+    const u32 u = __float_as_uint(f);
+    if ((u & 0x7F800000u) == 0x7F800000u) return (u >> 16) | ((u & 0xFFFFu) ? 0x40u : 0u);
+    return (u + (rnd & 0xFFFFu)) >> 16;
+}
+struct SrArgs {
+    int on;
+    u32 k0, k1, serial, tag;   // Philox key, counter words 2 and 3 ('SRND' + table)
+};
+
+// Sum of the sources of one row (bits of S, ascending: own first, then peers), W <- W - lr * sum.
+// lane 32*tb + k holds the position `pos` of the row in source k and that source's row pointer.
+// STREAM: the accesses go around the caches (non-temporal), for tables far larger than the caches.  Of a
+// table row only the cache lines it fills completely are loaded that way: a row of 1200 bytes shares its
+// first and last line with its neighbours, and with those two lines loaded through the caches the
+// neighbour (mostly touched too, by the next wave) finds them there (measured: update 0.728 -> 0.685 ms;
+// the same treatment of the stores, or of the gradient rows, gains less or loses).
+// PACKED: the peers' rows are bfloat16 messages.  The own row (lane `own`) is fp32 and is loaded ahead of
+// the loop, so that every load inside the loop has the same type and no branch separates them.
+// (Measured on bf16 rows: widened right after each load the update ran 0.77 ms where the fp32 messages
+// take 0.69 ms -- every load was followed by a wait for its data.)
+template <typename T, int ITERS, bool STREAM, bool PACKED>
+__device__ __forceinline__ void update_row(T *wrow, u64 S, u64 rows_ptr, u32 pos, int D, int C4, int lane,
+                                           float neg_lr, int own, u64 chunk0, const SrArgs &sr, bf16_t *msg_row)
+{
+    typedef typename std::conditional<PACKED, bf16_t, float>::type G;
+    // table row and source rows stay as loaded (bf16 not yet widened) until every load of the batch is out
+    typename Raw4<T>::type wraw[ITERS];
+    float4 acc[ITERS];
+    load_row_raw<T, ITERS, STREAM ? 2 : 0>(wraw, wrow, C4, lane);
+    zero_row<ITERS>(acc);
+    float4 x0[ITERS];
+    bool own_pending = PACKED;
+    if (PACKED) {
+        if ((S >> own) & 1ull) {
+            const float *src = (const float *)rd_lane64(rows_ptr, own) + (size_t)(u32)rd_lane((int)pos, own) * D;
+            load_row_raw<float, ITERS, STREAM ? 1 : 0>(x0, src, C4, lane);
+        } else {
+            zero_row<ITERS>(x0);
+        }
+        S &= ~(1ull << own);
+    }
+    while (S || own_pending) {
+        typename Raw4<G>::type x[4][ITERS];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (S) {
+                const int k = (int)__builtin_ctzll(S);
+                S &= S - 1ull;
+                const G *src = (const G *)rd_lane64(rows_ptr, k) + (size_t)(u32)rd_lane((int)pos, k) * D;
+                load_row_raw<G, ITERS, STREAM ? 1 : 0>(x[j], src, C4, lane);
+            } else {
+                zero_row_raw<ITERS>(x[j]);
+            }
+        }
+        if (PACKED && own_pending) add_row<ITERS>(acc, x0);   // the own row first, once the peers' loads are out
+        own_pending = false;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) add_row_raw<ITERS>(acc, x[j]);
+    }
+    // the own row on its way out as a bfloat16 message (its load has long arrived by now)
+    if (PACKED && msg_row != nullptr) store_row_s<bf16_t, ITERS>(msg_row, x0, C4, lane);
+    float4 w[ITERS];
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+        w[it] = widen4(wraw[it]);
+        w[it].x = fmaf(neg_lr, acc[it].x, w[it].x);
+        w[it].y = fmaf(neg_lr, acc[it].y, w[it].y);
+        w[it].z = fmaf(neg_lr, acc[it].z, w[it].z);
+        w[it].w = fmaf(neg_lr, acc[it].w, w[it].w);
+    }
+    if constexpr (sizeof(T) == 2) {
+        if (sr.on) {
+            // the variant: element i = row*D + col takes the low half of word (i mod 4) of
+            // Philox(counter = (i/4 low, i/4 high, serial, 'SRND' + table), key = seed); chunk0 = row*D/4
+#pragma unroll
+            for (int it = 0; it < ITERS; ++it) {
+                const int c = lane + WAVE * it;
+                if (c < C4) {
+                    const u64 blk = chunk0 + (u64)c;
+                    const philox_out o = philox4x32_10((u32)blk, (u32)(blk >> 32), sr.serial, sr.tag, sr.k0, sr.k1);
+                    v2u p;
+                    p.x = sr_bf16(w[it].x, o.r0) | (sr_bf16(w[it].y, o.r1) << 16);
+                    p.y = sr_bf16(w[it].z, o.r2) | (sr_bf16(w[it].w, o.r3) << 16);
+                    if (STREAM) __builtin_nontemporal_store(p, (GLOBAL_AS v2u *)(wrow + 4 * c));
+                    else *reinterpret_cast<v2u *>(wrow + 4 * c) = p;
+                }
+            }
+            return;
+        }
+    }
+    if (STREAM) store_row_s<T, ITERS>(wrow, w, C4, lane);
+    else store_row<T, ITERS>(wrow, w, C4, lane);
+}
+
+// occupancy cap, so that the kernels of the second stream (the preparation of the next mini-batch) find wave
+// slots next to this one; measured with table rows on 128-byte lines: 5 / 6 / 7 / 8 waves per SIMD give a step of
+// 0.846 / 0.836 / 0.823 / 0.828 ms at a million words, and no difference at two million (3.46-3.49 ms)
+#ifndef APPLY_MAX_WAVES
+#define APPLY_MAX_WAVES 7
+#endif
+template <typename T, int ITERS, int G, bool STREAM, bool PACKED, typename Rider>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, APPLY_MAX_WAVES)))
+k_apply(ApplyArgs a, int nblocks, Rider rider)
+{
+    if (rider.block()) return;
+    // keep runs of APPLY_CHUNK consecutive workgroups on one XCD (workgroups are dealt
+    // round-robin to the 8 XCDs), so that neighbouring rows -- which share cache lines when
+    // the row size is not a multiple of the line -- meet in the same L2
+    int bid = (int)blockIdx.x - rider.blocks();
+    {
+        const int per_round = 8 * APPLY_CHUNK;
+        int full = (nblocks / per_round) * per_round;
+        if (bid < full) {
+            int round = bid / per_round, r = bid - round * per_round;
+            int xcd = r & 7, slot = r >> 3;
+            bid = round * per_round + xcd * APPLY_CHUNK + slot;
+        }
+    }
+    constexpr int GPW = 64 / G;
+    const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
+    const int gw = bid * WAVES_PER_BLOCK + wave;
+    const int word = gw / GPW, sub = gw - word * GPW;
+    const int words = (int)((a.V + 63) >> 6);
+    if (word >= words) return;
+    const int ns = a.n_src;
+    const int C4 = a.D >> 2;
+
+    // lanes 0..31 hold W_in's sources, lanes 32..63 W_out's: lane 32*tb + k has source k's rows
+    // inside this wave's group of rows of table tb
+    u64 m = 0;
+    u32 st = 0;
+    int U = 0;
+    u64 rows_ptr = 0;
+    {
+        const int tb = lane >> 5, k = lane & 31;
+        if (k < ns) {
+            const ApplySrc &s = a.src[tb][k];
+            if (s.ids != nullptr) {
+                u64 mk = a.mask[tb][idx_at(words, k, word)];
+                st = a.start[tb][idx_at(words, k, word)];
+                const int lo = sub * G;
+                st += (u32)__popcll(mk & ((1ull << lo) - 1ull));
+                m = (G == 64) ? mk : ((mk >> lo) & ((1ull << (G & 63)) - 1ull));
+                U = *s.n_rows;
+                if ((i64)U > s.capacity) U = (int)s.capacity;
+                rows_ptr = (u64)s.rows;
+                if (PACKED && k == 0 && gw == 0 && a.msg_n[tb] != nullptr) *a.msg_n[tb] = U < 0 ? 0 : U;
+            }
+        }
+    }
+    const float neg_lr = -a.lr;
+    const i64 row0 = (i64)word * 64 + sub * G;
+
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb) {
+        const bool mine = (lane >> 5) == tb;
+        u64 um;
+        {
+            u32 lo32 = (u32)uniform((int)wave_or(mine ? (u32)m : 0u));
+            u32 hi32 = (G > 32) ? (u32)uniform((int)wave_or(mine ? (u32)(m >> 32) : 0u)) : 0u;
+            um = ((u64)hi32 << 32) | lo32;
+        }
+        T *table = (T *)a.table[tb];
+        while (um) {
+            const int b = (int)__builtin_ctzll(um);
+            um &= um - 1ull;
+            const i64 r = row0 + b;
+            if (r >= a.V) break;   // only reachable with a corrupt index (flagged input)
+            // per lane: position of row r in its source (if present and in bounds)
+            const u32 pos = st + (u32)__popcll(m & ((1ull << b) - 1ull));
+            const bool ok = mine && ((m >> b) & 1ull) && (pos < (u32)U);
+            const u64 S = __ballot(ok);   // bit 32*tb + k: source k has row r
+            const SrArgs sr = {a.sr, a.sr_k0, a.sr_k1, a.sr_serial, 0x53524E44u + (u32)tb};
+            bf16_t *msg_row = nullptr;
+            if (PACKED && a.msg_rows[tb] != nullptr && ((S >> (32 * tb)) & 1ull)) {
+                const u32 at = (u32)rd_lane((int)pos, 32 * tb);          // place of row r in the own gradient
+                msg_row = (bf16_t *)a.msg_rows[tb] + (size_t)at * a.D;
+                if (lane == 32 * tb) a.msg_ids[tb][at] = (int)r;
+            }
+            update_row<T, ITERS, STREAM, PACKED>(table + (size_t)r * a.stride, S, rows_ptr, pos, a.D, C4, lane, neg_lr,
+                                                 32 * tb, (u64)r * (u64)C4, sr, msg_row);
+        }
+    }
+}
+
+// The same update for rows of at most 32 chunks (D <= 128).  A whole wave per row would leave most of its lanes
+// without a chunk, and the update's rate follows the number of row loads a wave issues, not their width
+// (measured at a million words and 7 peers with whole-wave rows: 4.1 TB/s at D = 128 and 1.5 TB/s at D = 32 against
+// 5.9 TB/s at D = 256; update 0.36 and 0.25 ms, with this kernel 0.31 and 0.09 ms).  Here a wave updates 64/SUB
+// rows at a time, one per group of SUB lanes: each pass takes the next rows of the wave's share that any source
+// has, the lanes that hold the sources' (start, mask) hand every group its row's positions through lane
+// shuffles, and a group walks its own row's sources, four loads in flight, in source order -- every row is
+// summed exactly as in k_apply.  ROWS: vocabulary rows per group and wave (more where few rows are touched, see
+// launch_apply_sub).  Gradient messages in bfloat16 (PACKED) stay with k_apply.
+#ifndef APPLY_SUB_ROWS
+#define APPLY_SUB_ROWS 4   // rows per group of lanes and wave
+#endif
+template <typename T, int SUB, int ROWS, bool STREAM, typename Rider>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, APPLY_MAX_WAVES)))
+k_apply_sub(ApplyArgs a, int nblocks, Rider rider)
+{
+    if (rider.block()) return;
+    constexpr int RPW = WAVE / SUB;   // rows in one pass of a wave
+    constexpr int G = (ROWS * RPW > 32) ? 32 : ROWS * RPW;   // vocabulary rows per wave
+    constexpr int GPW = 64 / G;
+    int bid = (int)blockIdx.x - rider.blocks();
+    {
+        const int per_round = 8 * APPLY_CHUNK;
+        int full = (nblocks / per_round) * per_round;
+        if (bid < full) {
+            int round = bid / per_round, r = bid - round * per_round;
+            int xcd = r & 7, slot = r >> 3;
+            bid = round * per_round + xcd * APPLY_CHUNK + slot;
+        }
+    }
+    const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
+    const int gw = bid * WAVES_PER_BLOCK + wave;
+    const int word = gw / GPW, sub = gw - word * GPW;
+    const int words = (int)((a.V + 63) >> 6);
+    if (word >= words) return;
+    const int ns = a.n_src;
+    const int C4 = a.D >> 2;
+    const int slot = lane / SUB, sl = lane - slot * SUB;   // group of the lane, chunk of the row it holds
+
+    // lane 32*tb + k: source k's rows inside this wave's share of table tb, as in k_apply
+    u32 m = 0, st = 0;
+    int U = 0;
+    u64 rows_ptr = 0;
+    {
+        const int tb = lane >> 5, k = lane & 31;
+        if (k < ns) {
+            const ApplySrc &s = a.src[tb][k];
+            if (s.ids != nullptr) {
+                const u64 mk = a.mask[tb][idx_at(words, k, word)];
+                const int lo = sub * G;
+                st = a.start[tb][idx_at(words, k, word)] + (u32)__popcll(mk & ((1ull << lo) - 1ull));
+                m = (u32)((mk >> lo) & ((1ull << G) - 1ull));
+                U = *s.n_rows;
+                if ((i64)U > s.capacity) U = (int)s.capacity;
+                rows_ptr = (u64)s.rows;
+            }
+        }
+    }
+    const int ptr_lo = (int)(u32)rows_ptr, ptr_hi = (int)(u32)(rows_ptr >> 32);
+    const float neg_lr = -a.lr;
+    const i64 row0 = (i64)word * 64 + sub * G;
+
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb) {
+        const bool mine = (lane >> 5) == tb;
+        u32 um = (u32)uniform((int)wave_or(mine ? m : 0u));
+        T *table = (T *)a.table[tb];
+        while (um) {
+            // the next RPW rows: lane 32*tb + k works out source k's position of each, group s keeps row s
+            int pos_s[RPW];
+            u32 S_my = 0;
+            int b_my = -1;
+#pragma unroll
+            for (int s = 0; s < RPW; ++s) {
+                pos_s[s] = 0;
+                if (um) {
+                    const int b = (int)__builtin_ctz(um);
+                    um &= um - 1u;
+                    if (row0 + b >= a.V) {   // only reachable with a corrupt index (flagged input)
+                        um = 0;
+                    } else {
+                        const u32 pos = st + (u32)__popc(m & ((1u << b) - 1u));
+                        const bool ok = mine && ((m >> b) & 1u) && (pos < (u32)U);
+                        const u64 S = __ballot(ok);
+                        pos_s[s] = (int)pos;
+                        if (slot == s) {
+                            S_my = (u32)(S >> (32 * tb));
+                            b_my = b;
+                        }
+                    }
+                }
+            }
+            const bool act = (b_my >= 0) && (sl < C4);
+            const i64 r = row0 + (b_my >= 0 ? b_my : 0);
+            T *wrow = table + (size_t)r * a.stride;
+            T *wp = wrow + 4 * sl;
+            typename Raw4<T>::type wraw;
+            zero_raw(wraw);
+            bool around = STREAM;
+            if (STREAM) {   // a 128-byte line shared with the neighbouring rows goes through the caches
+                const uintptr_t lo = (uintptr_t)wrow, hi = lo + (size_t)C4 * 4 * sizeof(T);
+                const uintptr_t line = (uintptr_t)wp & ~(uintptr_t)127;
+                around = line >= lo && line + 128 <= hi;
+            }
+            if (act) {
+                if (around) wraw = ldraw_s(wp);
+                else wraw = ldraw(wp);
+            }
+            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            u32 S_it = S_my;
+            while (__ballot(S_it != 0u)) {
+                float4 x[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool valid = S_it != 0u;
+                    const int k = valid ? (int)__builtin_ctz(S_it) : 0;
+                    S_it &= S_it - 1u;
+                    const int from = 32 * tb + k;
+                    int pos = 0;
+#pragma unroll
+                    for (int s = 0; s < RPW; ++s) {
+                        const int v = __shfl(pos_s[s], from, WAVE);
+                        pos = (slot == s) ? v : pos;
+                    }
+                    const u64 ptr = ((u64)(u32)__shfl(ptr_hi, from, WAVE) << 32) | (u64)(u32)__shfl(ptr_lo, from, WAVE);
+                    x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (valid && act) {
+                        const float *src = (const float *)ptr + (size_t)(u32)pos * a.D + 4 * sl;
+                        x[j] = STREAM ? ld4s(src) : ld4(src);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    acc.x += x[j].x;
+                    acc.y += x[j].y;
+                    acc.z += x[j].z;
+                    acc.w += x[j].w;
+                }
+            }
+            float4 w = widen4(wraw);
+            w.x = fmaf(neg_lr, acc.x, w.x);
+            w.y = fmaf(neg_lr, acc.y, w.y);
+            w.z = fmaf(neg_lr, acc.z, w.z);
+            w.w = fmaf(neg_lr, acc.w, w.w);
+            if (!act) continue;
+            if constexpr (sizeof(T) == 2) {
+                if (a.sr) {   // the variant: the same draw per element as in update_row
+                    const u64 blk = (u64)r * (u64)C4 + (u64)sl;
+                    const philox_out o = philox4x32_10((u32)blk, (u32)(blk >> 32), a.sr_serial, 0x53524E44u + (u32)tb,
+                                                       a.sr_k0, a.sr_k1);
+                    v2u p;
+                    p.x = sr_bf16(w.x, o.r0) | (sr_bf16(w.y, o.r1) << 16);
+                    p.y = sr_bf16(w.z, o.r2) | (sr_bf16(w.w, o.r3) << 16);
+                    if (STREAM) __builtin_nontemporal_store(p, (GLOBAL_AS v2u *)wp);
+                    else *reinterpret_cast<v2u *>(wp) = p;
+                    continue;
+                }
+            }
+            if (STREAM) st4s(wp, w);
+            else st4(wp, w);
+        }
+    }
+}
+
+template <typename T, int SUB, int ROWS, bool STREAM, typename Rider>
+static void launch_apply_sub_r(const ApplyArgs &a, const Rider &rider, hipStream_t st)
+{
+    const int words = (int)((a.V + 63) >> 6);
+    constexpr int G = (ROWS * (WAVE / SUB) > 32) ? 32 : ROWS * (WAVE / SUB);
+    const i64 nwaves = (i64)words * (64 / G);
+    const int nblocks = (int)((nwaves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+    hipLaunchKernelGGL((k_apply_sub<T, SUB, ROWS, STREAM, Rider>), dim3(rider.blocks() + nblocks), dim3(BLOCK), rider.lds_bytes(), st, a, nblocks, rider);
+}
+
+// few of the vocabulary's rows touched, going by the sources' capacities (see launch_apply_t)
+static bool sparse_union(const ApplyArgs &a)
+{
+    i64 cap = 0;
+    for (int k = 0; k < a.n_src; ++k)
+        if (a.src[1][k].ids != nullptr) cap += a.src[1][k].capacity;
+    return 4 * cap < 3 * a.V;
+}
+
+// 4 rows per group of lanes and wave, or 32 rows per wave where few rows are touched (8 M words, D = 128, bf16:
+// update 0.67 -> 0.42 ms; 16 M words, D = 64: 0.58 -> 0.40 ms)
+template <typename T, int SUB, bool STREAM, typename Rider>
+static void launch_apply_sub(const ApplyArgs &a, const Rider &rider, hipStream_t st)
+{
+    if (SUB > 8 && sparse_union(a)) launch_apply_sub_r<T, SUB, 16, STREAM>(a, rider, st);
+    else launch_apply_sub_r<T, SUB, APPLY_SUB_ROWS, STREAM>(a, rider, st);
+}
+
+template <typename T, int G, bool STREAM, bool PACKED, typename Rider>
+static void launch_apply_g(const ApplyArgs &a, const Rider &rider, hipStream_t st)
+{
+    const int iters = (a.D / 4 + WAVE - 1) / WAVE;
+    const int words = (int)((a.V + 63) >> 6);
+    const i64 nwaves = (i64)words * (64 / G);
+    const int nblocks = (int)((nwaves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+    dim3 grid(rider.blocks() + nblocks), blk(BLOCK);
+    switch (iters) {
+    case 1: hipLaunchKernelGGL((k_apply<T, 1, G, STREAM, PACKED, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider); break;
+    case 2: hipLaunchKernelGGL((k_apply<T, 2, G, STREAM, PACKED, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider); break;
+    default:
+        if constexpr (!Rider::narrow) {
+            if (iters == 3) hipLaunchKernelGGL((k_apply<T, 3, G, STREAM, PACKED, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider);
+            else hipLaunchKernelGGL((k_apply<T, 4, G, STREAM, PACKED, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider);
+        }
+    }
+}
+
+// Rows per wave.  Where most vocabulary rows are touched, 4 rows per wave are best (16: -4 % at a million words and
+// 7 peers, two thirds of the rows touched); where few are, most waves of such a grid find nothing, and 16 rows per
+// wave win (same gradients, update at 2 / 4 / 8 million words: 0.85 / 1.11 / 1.49 ms with 4 rows, 0.86 / 1.01 / 1.16 ms
+// with 16, 64 rows no better).  How many rows the union has is only known on the device; the sources' capacities
+// bound it, and below three quarters of a row of capacity per vocabulary row the sparse shape is taken.
+template <typename T, bool STREAM, bool PACKED, typename Rider>
+static void launch_apply_t(const ApplyArgs &a, const Rider &rider, hipStream_t st)
+{
+    if (sparse_union(a)) launch_apply_g<T, APPLY_G_SPARSE, STREAM, PACKED>(a, rider, st);
+    else launch_apply_g<T, APPLY_G, STREAM, PACKED>(a, rider, st);
+}
+
+template <typename T, bool STREAM, typename Rider>
+static void launch_apply_p(const ApplyArgs &a, const Rider &rider, hipStream_t st)
+{
+    const int C4 = a.D / 4;
+    if (a.packed) launch_apply_t<T, STREAM, true>(a, rider, st);
+    else if (C4 > 32) launch_apply_t<T, STREAM, false>(a, rider, st);
+    else if (C4 > 16) launch_apply_sub<T, 32, STREAM>(a, rider, st);
+    else if (C4 > 8) launch_apply_sub<T, 16, STREAM>(a, rider, st);
+    else launch_apply_sub<T, 8, STREAM>(a, rider, st);
+}
+
+template <typename Rider>
+static void launch_apply(const ApplyArgs &a, const Rider &rider, hipStream_t st)
+{
+    // Tables that dwarf the caches (256 MB memory-side, 32 MB of L2) are updated around them: a row
+    // touched here is not touched again before megabytes of others have passed, and what the gradient
+    // calculation left in the caches (the frequent rows, which its next pass reads again) survives the
+    // update.  Measured at a 2 x 1.2 GB model: step 0.953 -> 0.930 ms.  Small tables stay cached.
+    const i64 elem = a.dtype == 0 ? 4 : 2;
+    const bool stream = 2 * a.V * (i64)a.stride * elem > ((i64)1 << 30);
+    if (a.dtype == 0) stream ? launch_apply_p<float, true>(a, rider, st) : launch_apply_p<float, false>(a, rider, st);
+    else stream ? launch_apply_p<bf16_t, true>(a, rider, st) : launch_apply_p<bf16_t, false>(a, rider, st);
+}

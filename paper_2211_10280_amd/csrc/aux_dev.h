@@ -1,4 +1,4 @@
-// Small integer jobs of a worker step -- clearing and building the per-word index of the table update,
+// Small jobs of a worker step -- phases of the coming mini-batch's preparation, the mean loss, clearing and building the per-word index of the table update,
 // handing a prepared mini-batch's row index to the caller's buffers -- as device functions, so that they
 // can run either as kernels of their own or as extra workgroups at the front of the grid of a kernel that
 // is launched at that point of the step anyway (the forward pass, the segmented reduction): there they
@@ -6,6 +6,7 @@
 #pragma once
 #include "dev_common.h"
 #include "kernels.h"
+#include "prep_dev.h"
 
 #ifndef AUX_INDEX_UNROLL
 #define AUX_INDEX_UNROLL 4
@@ -112,9 +113,47 @@ __device__ __forceinline__ void aux_copy_row_index(const RowIndexCopy::Side &s, 
     }
 }
 
-// The jobs that ride at the front of a launch (see AuxWork): workgroup b of x.total.
-__device__ __forceinline__ void aux_block(const AuxWork &x, int b)
+__device__ __forceinline__ void aux_mean_loss(const float *center_loss, int n, float inv_P, float *mean_loss, float *sm)
 {
+    float s = 0.f;
+    for (int i = threadIdx.x; i < n; i += BLOCK) s += center_loss[i];
+    s = wave_sum(s);
+    if (lane_id() == 0) sm[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t = sm[0];
+#pragma unroll
+        for (int w = 1; w < WAVES_PER_BLOCK; ++w) t += sm[w];
+        *mean_loss = t * inv_P;
+    }
+}
+
+// LDS of those jobs
+static inline unsigned aux_lds_bytes(const AuxWork &x)
+{
+    const unsigned a = ride_lds_bytes(x.prep[0]);
+    return a ? a : x.mean_loss ? 4u * WAVES_PER_BLOCK : 0u;
+}
+
+// The jobs that ride at the front of a launch (see AuxWork): workgroup b of x.total.  lds: PrepLds<BLOCK>::words words.
+// PREP: phases of a preparation may be among them; KEYS: the keys too
+template <bool PREP, bool KEYS>
+__device__ __forceinline__ void aux_block(const AuxWork &x, int b, u32 *lds)
+{
+    const int prep = PREP ? x.prep[0].blocks + x.prep[1].blocks : 0;
+    if (PREP && b < prep) {      // the longest jobs first
+        const bool second = b >= x.prep[0].blocks;
+        prep_block<BLOCK, KEYS>(second ? x.prep[1] : x.prep[0], second ? b - x.prep[0].blocks : b, lds);
+        return;
+    }
+    b -= prep;
+    if (x.mean_loss) {
+        if (b == 0) {
+            aux_mean_loss(x.center_loss, x.n_centers, x.inv_P, x.mean_loss, (float *)lds);
+            return;
+        }
+        --b;
+    }
     if (b < x.clear_blocks) {
         aux_clear_masks(x.clear_mask[0], x.clear_mask[1], x.clear_n, b);
         return;

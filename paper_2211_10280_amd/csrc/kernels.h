@@ -47,7 +47,7 @@ struct BatchDesc {
 };
 
 // ---- preparation of a mini-batch (prep_dev.h): one launch per phase -- keys, the passes of the sort, segments
-#define PREP_KEYS_ITEMS 4   // slots per thread
+#define PREP_KEYS_SLOTS 1024   // slots per workgroup
 struct PrepKeys {
     BatchDesc b;
     i64 V;
@@ -107,9 +107,13 @@ struct PrepPhase {
     };
 };
 #define TN_PREP_GROUP 64       // tiles per group of a counted pass
-#ifndef TN_PREP_CHAIN_MAX
-#define TN_PREP_CHAIN_MAX 128  // most tiles of a chained pass
+// Most tiles of a chained preparation: as launches of its own (longer ones are faster counted), and riding in other
+// launches, where its latency is hidden.
+#define TN_PREP_CHAIN_OWN 128
+#ifndef TN_PREP_CHAIN_RIDE
+#define TN_PREP_CHAIN_RIDE 512
 #endif
+#define TN_PREP_CHAIN_MAX (TN_PREP_CHAIN_OWN > TN_PREP_CHAIN_RIDE ? TN_PREP_CHAIN_OWN : TN_PREP_CHAIN_RIDE)
 static inline int tn_prep_tiles(int n) { return (n + TN_RADIX_TILE - 1) / TN_RADIX_TILE; }
 static inline int tn_prep_seg_tiles(int n) { return (n + TN_SCAN_TILE - 1) / TN_SCAN_TILE; }
 void tn_launch_prep(const PrepPhase &x, hipStream_t st);   // the phase as a launch of its own
@@ -163,8 +167,16 @@ struct SegReduceArgs {
     int dtype, stride;
     const float *center_part;
 };
-// the W_out-side and the W_in-side problem of a mini-batch in one launch (either may be NULL)
-void tn_launch_segreduce(const SegReduceArgs *out, const SegReduceArgs *in, const AuxWork *aux, hipStream_t st);
+// the W_out-side and the W_in-side problem of a mini-batch in one launch (either may be NULL); `rider` (may be NULL):
+// rides with the launch that chains the long rows, if there is one (tn_seg_chains)
+void tn_launch_segreduce(const SegReduceArgs *out, const SegReduceArgs *in, const AuxWork *aux, const PrepPhase *rider,
+                         hipStream_t st);
+// workgroups that chain long rows: they exist only where a problem has more than one tile
+static inline int tn_seg_chains(i64 n)
+{
+    const i64 tiles = (n + tn_seg_tile(n) - 1) / tn_seg_tile(n);
+    return tiles > 1 ? (int)(tiles < 1024 ? tiles : 1024) : 0;
+}
 
 void tn_launch_loss(const float *center_loss, int n_centers, float inv_P, float *mean_loss,
                     hipStream_t st);
@@ -198,11 +210,17 @@ struct ApplyArgs {
     u32 sr_k0, sr_k1, sr_serial;
 };
 // Small jobs that ride at the front of the grid of the forward pass or of the segmented reduction
-// (workgroups [0, total) of that launch): clearing the masks of the table update's index, copying a
-// prepared mini-batch's row index to the caller's buffers, indexing the sources [k_begin, k_end) of the
-// coming table update.  Clearing and indexing must not share a launch (the index needs cleared masks).
+// (workgroups [0, total) of that launch): phases of a mini-batch's preparation, the mean loss, clearing the masks of
+// the table update's index, copying a prepared mini-batch's row index to the caller's buffers, indexing the sources
+// [k_begin, k_end) of the coming table update.  Clearing and indexing must not share a launch (the index needs
+// cleared masks); of two phases neither may need the other's result.
 struct AuxWork {
-    int total;               // clear_blocks + 2 * copy_blocks + 2 * (k_end - k_begin) * index_blocks
+    int total;               // prep + loss + clear_blocks + 2 * copy_blocks + 2 * (k_end - k_begin) * index_blocks
+    PrepPhase prep[2];
+    const float *center_loss;   // mean loss: sum of [n_centers] terms times inv_P
+    float *mean_loss;           // NULL: not wanted
+    int n_centers;
+    float inv_P;
     int clear_blocks;
     u64 *clear_mask[2];      // masks to zero (both tables), clear_n entries each -- not necessarily apply's
     size_t clear_n;
@@ -213,13 +231,17 @@ struct AuxWork {
     ApplyArgs apply;
 };
 void tn_aux_none(AuxWork &x);
+void tn_aux_add_prep(AuxWork &x, const PrepPhase &p);   // twice at most
+void tn_aux_add_loss(AuxWork &x, const float *center_loss, int n_centers, float inv_P, float *mean_loss);
 void tn_aux_add_clear(AuxWork &x, u64 *mask_in, u64 *mask_out, size_t n);
 void tn_aux_add_copy(AuxWork &x, const RowIndexCopy &c, i64 max_rows);
 void tn_aux_add_index(AuxWork &x, const ApplyArgs &a, int k_begin, int k_end);
 
 void tn_launch_apply_clear(const ApplyArgs &a, hipStream_t st);
 void tn_launch_apply_index(const ApplyArgs &a, int k_begin, int k_end, hipStream_t st);
-void tn_launch_apply_update(const ApplyArgs &a, hipStream_t st);
+static inline bool tn_apply_carries(int D) { return D <= 512; }   // whether a phase can ride with the update
+void tn_launch_apply_update(const ApplyArgs &a, const PrepPhase *rider, hipStream_t st);   // rider may be NULL
+void tn_launch_apply_update_riding(const ApplyArgs &a, const PrepPhase &rider, hipStream_t st);
 
 // ---- sum of sparse gradients: out = src_0 + src_1 + ... on the union of their rows
 struct GradSumArgs {

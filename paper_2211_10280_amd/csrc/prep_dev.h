@@ -32,7 +32,7 @@
 // A tile's published word, for counts (32 bits): 0 nothing yet; 1 + count of the tile; PREP_INCL + count of all
 // tiles up to and including it.  Counts of a tile are at most TN_RADIX_TILE < PREP_INCL - 1.
 #define PREP_INCL 4096u
-#define PREP_LOOK 8       // words of lower tiles that a thread has in flight
+#define PREP_LOOK 4       // words of lower tiles that a thread has in flight (more would cost the launches that passes ride in a wave per SIMD)
 // ... and for the segment scan (64 bits): state in the top two bits (0 nothing, 1 the tile's own, 2 up to it)
 #define PREP_SEG_OWN (1ull << 62)
 #define PREP_SEG_INCL (2ull << 62)
@@ -57,12 +57,12 @@ __device__ __forceinline__ int take_ticket(u32 *counter, u32 *word)
 // Slot s of the mini-batch is (center i, offset index q, k): k = 0 is the context, k = 1..N are the negatives.
 // Writes the out-side key list [pair][N+1] (pair-major, the order of the occurrence list), the in-side key of every
 // center, the center token of every pair and (for chained passes) the digit counts of both lists; clears the words that the sort's and
-// the segment scan's workgroups will publish, and their tickets.  A thread takes PREP_KEYS_ITEMS slots, one of every
-// THREADS, so that their table lookups are in flight together.
+// the segment scan's workgroups will publish, and their tickets.  A workgroup takes PREP_KEYS_SLOTS slots, a thread one of
+// every THREADS, so that their table lookups are in flight together.
 template <int THREADS>
 __device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblocks, u32 *lds)
 {
-    constexpr int ITEMS = PREP_KEYS_ITEMS;
+    constexpr int ITEMS = PREP_KEYS_SLOTS / THREADS;
     const BatchDesc &b = a.b;
     const int nd = 1 << a.bits, nhist = a.passes * nd;   // counters of one list
     const u32 dmask = (u32)nd - 1u;
@@ -537,11 +537,17 @@ struct PrepLds {
     static constexpr int words = PassLds<THREADS>::words > keys ? PassLds<THREADS>::words : keys;
 };
 
-// the phases of a chained preparation
-template <int THREADS>
+// a phase of a chained preparation; KEYS: it may be the keys (which ride with the forward pass only)
+template <int THREADS, bool KEYS>
 __device__ __forceinline__ void prep_block(const PrepPhase &x, int block, u32 *lds)
 {
-    if (x.kind == PREP_KEYS) prep_keys<THREADS>(x.keys, block, x.blocks, lds);
+    if (KEYS && x.kind == PREP_KEYS) prep_keys<THREADS>(x.keys, block, x.blocks, lds);
     else if (x.kind == PREP_PASS) prep_pass<THREADS, true>(x.pass, block, lds);
     else prep_segments<THREADS, true, false>(x.seg, block, lds);
 }
+
+// LDS of the launches that phases ride in: dynamic, and asked for only where one does, so that a launch without riders
+// leaves the LDS to the kernels of another stream (a forward pass that held 18 KB per workgroup kept the sort beside
+// it off the chip: step with hot rows 581 -> 615 us).
+extern __shared__ u32 ride_lds[];
+static inline unsigned ride_lds_bytes(const PrepPhase &x) { return x.blocks ? 4u * PrepLds<BLOCK>::words : 0u; }

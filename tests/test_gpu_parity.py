@@ -1161,6 +1161,50 @@ def test_prefetch_gives_the_same_bits():
     m.close()
 
 
+@pytest.mark.parametrize("V", [300, 5000, 300_000])      # one, two and three passes of the sort
+@pytest.mark.parametrize("D", [36, 520])                  # the table update carries a phase, or is too wide to
+@pytest.mark.parametrize("call", ["step", "grad"])        # four launches for phases to ride in, or three
+def test_phases_that_ride_give_the_same_bits(V, D, call):
+    """Mini-batches of all sizes announced two deep, so that their preparation rides phase by phase in the launches of
+    the call before -- none, some or all of its phases done when they are consumed -- against calls without
+    announcements; announcements that are dropped half prepared; a mini-batch too large for chained passes (2 w (N+1) =
+    256 occurrences per center, 1200 centers) before a small one."""
+    T, w, N = 30_000, 8, 15
+    tok = W.zipf_stream(V, 1.1, T, 5)
+    counts = W.unigram_counts(tok, V)
+    Wi, Wo = _random_tables(V, D, D, "f32", seed=11)
+    dtok = torch.from_numpy(tok).cuda()
+    batches = [(0, 3, 0), (100, 8, 0), (300, 40, 1), (5000, 300, 1), (9000, 1200, 2), (T - 60, 60, 2), (700, 9, 3), (2000, 120, 3)]
+    runs = []
+    for ahead in (False, True):
+        m = B.Model(V, D, B.F32, w, N, 1200, 0, 77, counts, worker_id=2,
+                    tables=(_tables_to_dev(Wi, "f32"), _tables_to_dev(Wo, "f32")))
+        g = m.grad_buffers()
+        loss = torch.zeros(1, device="cuda")
+        got = []
+        for i, (begin, n, epoch) in enumerate(batches):
+            if ahead and i == 0:
+                m.prefetch(dtok, begin, n, epoch)
+            if ahead and i + 1 < len(batches):
+                m.prefetch(dtok, *batches[i + 1])
+            if ahead and i == 3:       # a call for something else: both announcements go, one of them half prepared
+                other = m.grad_buffers()
+                m.sgns_grad(dtok, 50, 5, 9, other)
+                m.prefetch(dtok, begin, n, epoch)
+                m.prefetch(dtok, *batches[i + 1])
+            if call == "step":
+                m.step(dtok, begin, n, epoch, [], 0.5, g, loss)
+            else:
+                m.sgns_grad(dtok, begin, n, epoch, g, mean_loss=loss)
+            got.append(_grad_snapshot(g, loss))
+        m.status()
+        got.append([_tables_to_host(t, "f32") for t in (m.w_in, m.w_out)])
+        runs.append(got)
+        m.close()
+    for i, (a, b) in enumerate(zip(*runs)):
+        assert _same(a, b), i
+
+
 @pytest.mark.parametrize("name,idx,kw", [
     ("cfg3_pf", 3, dict(vocab=20_000, tokens=300_000, batch=256)),
     ("cfg5_pf", 5, dict(vocab=20_000, tokens=300_000, batch=256)),
