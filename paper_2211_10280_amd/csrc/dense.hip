@@ -15,7 +15,10 @@
 // a thread takes one chunk of 4 elements; the gradients of the chunk are loaded DENSE_INFLIGHT
 // sources at a time and summed in source order
 #define DENSE_INFLIGHT 4
-// STREAM: all accesses around the caches, for models far larger than them (+9 % at 300 M parameters)
+// what does not fit the 256 MB memory-side cache goes around the caches (f32, 8 gradients: 25 M parameters, 1 GB, 190 ->
+// 173 us; 12 M, 0.48 GB, 92 -> 83; bf16 25 M 166 -> 149; 6 M and fewer parameters stay cached)
+#define DENSE_STREAM_BYTES ((i64)256 << 20)
+// STREAM: all accesses around the caches
 template <typename T, bool STREAM>
 __global__ void __launch_bounds__(BLOCK) k_dense_apply(DenseApplyArgs a)
 {
@@ -73,7 +76,7 @@ void tn_launch_dense_apply(const DenseApplyArgs &a, hipStream_t st)
     i64 want = (n4 + BLOCK - 1) / BLOCK;
     if (want < 1) want = 1;
     const int blocks = (int)want;
-    const bool stream = a.n * (a.dtype == 0 ? 4 : 2) + (i64)a.n_grads * a.n * 4 > ((i64)1 << 30);
+    const bool stream = a.n * (a.dtype == 0 ? 4 : 2) + (i64)a.n_grads * a.n * 4 > DENSE_STREAM_BYTES;
     if (a.dtype == 0) {
         if (stream) hipLaunchKernelGGL((k_dense_apply<float, true>), dim3(blocks), dim3(BLOCK), 0, st, a);
         else hipLaunchKernelGGL((k_dense_apply<float, false>), dim3(blocks), dim3(BLOCK), 0, st, a);
