@@ -35,6 +35,8 @@ struct PhaseRider {
 #ifndef APPLY_G
 #define APPLY_G 4   // vocabulary rows per wave (measured: 16 -> 4 rows gains 4 %)
 #endif
+#define APPLY_SMALL_V 16384          // see launch_apply_t
+#define APPLY_SPARSE_MIN_V 786432
 #ifndef APPLY_G_SPARSE
 #define APPLY_G_SPARSE 16   // the same where few of the vocabulary's rows are touched
 #endif
@@ -409,15 +411,18 @@ static bool sparse_union(const ApplyArgs &a)
     i64 cap = 0;
     for (int k = 0; k < a.n_src; ++k)
         if (a.src[1][k].ids != nullptr) cap += a.src[1][k].capacity;
-    return 4 * cap < 3 * a.V;
+    return a.V >= APPLY_SPARSE_MIN_V && 4 * cap < 3 * a.V;
 }
 
 // 4 rows per group of lanes and wave, or 32 rows per wave where few rows are touched (8 M words, D = 128, bf16:
-// update 0.67 -> 0.42 ms; 16 M words, D = 64: 0.58 -> 0.40 ms)
+// update 0.67 -> 0.42 ms; 16 M words, D = 64: 0.58 -> 0.40 ms); one row per group where the vocabulary is too small to
+// give every wave slot of the chip work with four (1 000 words, D = 32: 32 waves of 64 rows and 12 us became 128 waves;
+// step 34.6 -> 28.8 us; no difference from 16 384 words at D = 128 on)
 template <typename T, int SUB, bool STREAM, typename Rider>
 static void launch_apply_sub(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
     if (SUB > 8 && sparse_union(a)) launch_apply_sub_r<T, SUB, 16, STREAM>(a, rider, st);
+    else if (!STREAM && a.V < APPLY_SMALL_V * (WAVE / SUB)) launch_apply_sub_r<T, SUB, 1, STREAM>(a, rider, st);
     else launch_apply_sub_r<T, SUB, APPLY_SUB_ROWS, STREAM>(a, rider, st);
 }
 
@@ -444,11 +449,16 @@ static void launch_apply_g(const ApplyArgs &a, const Rider &rider, hipStream_t s
 // 7 peers, two thirds of the rows touched); where few are, most waves of such a grid find nothing, and 16 rows per
 // wave win (same gradients, update at 2 / 4 / 8 million words: 0.85 / 1.11 / 1.49 ms with 4 rows, 0.86 / 1.01 / 1.16 ms
 // with 16, 64 rows no better).  How many rows the union has is only known on the device; the sources' capacities
-// bound it, and below three quarters of a row of capacity per vocabulary row the sparse shape is taken.
+// bound it, and below three quarters of a row of capacity per vocabulary row the sparse shape is taken.  In a small
+// vocabulary it never is: there the few waves that hold the frequent words, all of whose rows are touched, work on
+// long after the others (whole call at 100 000 words, 120 centers 37 us with 16 rows, 21 with 4; 300 000 words, 64 centers
+// 38 and 31; 2 million, 512 centers 64 and 152).  Below 16 384 words a grid of 4 rows per wave leaves wave slots empty:
+// one row per wave (1 000 words, D = 300: step 60.8 -> 58.4 us).
 template <typename T, bool STREAM, bool PACKED, typename Rider>
 static void launch_apply_t(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
     if (sparse_union(a)) launch_apply_g<T, APPLY_G_SPARSE, STREAM, PACKED>(a, rider, st);
+    else if (!STREAM && a.V < APPLY_SMALL_V) launch_apply_g<T, 1, STREAM, PACKED>(a, rider, st);
     else launch_apply_g<T, APPLY_G, STREAM, PACKED>(a, rider, st);
 }
 

@@ -294,6 +294,17 @@ def test_dasgd_apply_parity_few_rows_of_a_large_vocabulary(dtype, V, D, stride, 
     _apply_parity(dtype, V, D, stride, K, True, thin=40)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V,D,stride,K,thin", [
+    # few rows touched: from 786 432 words on more vocabulary rows per wave, below it as many as elsewhere
+    (786_431, 132, 132, 2, 400), (786_432, 132, 160, 2, 400), (800_011, 100, 104, 3, 400), (800_011, 36, 36, 1, 400),
+    # small vocabularies: one row per wave or group of lanes, up to 16 384 words (times rows per wave)
+    (16_383, 132, 132, 3, 1), (16_384, 132, 132, 3, 1), (32_767, 100, 100, 2, 1), (32_768, 100, 100, 2, 1),
+    (131_071, 32, 32, 1, 10), (1, 8, 8, 1, 1)])
+def test_dasgd_apply_parity_at_the_borders_of_its_shapes(dtype, V, D, stride, K, thin):
+    _apply_parity(dtype, V, D, stride, K, True, thin=thin)
+
+
 def _random_apply_shapes(n, seed):
     """Seeded shapes off the beaten track: every lane grouping of the table update (D <= 32, <= 64, <= 128, one to
     four chunk passes of a whole wave), dimensions just below and above the borders between them, padded and
