@@ -138,7 +138,10 @@ struct FwdArgs {
     float *center_part;    // [n_centers][D] out
     float *center_loss;    // [n_centers] out (sum of the loss terms, not yet divided by P)
     float inv_P;
+    int repeats;           // a position's tasks are expected to name the same words many times over (and are at most
+                           // TN_REPEAT_MAX_TASKS): a hint, rows of up to 320 elements heed it
 };
+#define TN_REPEAT_MAX_TASKS 512
 struct AuxWork;
 void tn_launch_forward(const FwdArgs &a, const AuxWork *aux, hipStream_t st);   // aux may be NULL
 

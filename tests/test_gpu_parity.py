@@ -151,6 +151,21 @@ def test_sgns_grad_parity_at_the_edges_of_the_preparation(case):
     _grad_parity(case)
 
 
+# positions whose tasks repeat words (the forward pass then works on the different ones): every row shape it has, both
+# sizes of its table and their edges (256 and 512 tasks per position, one more goes the plain way), clipped windows
+REPEAT_CASES = [
+    (60, 256, 256, 3_000, 1.3, 8, 15, 300, 0, "f32"), (60, 300, 320, 3_000, 1.3, 8, 15, 200, 2_800, "f32"),
+    (60, 36, 36, 3_000, 1.3, 8, 15, 200, 100, "bf16"), (40, 320, 320, 3_000, 1.2, 8, 31, 120, 0, "bf16"),
+    (40, 128, 128, 3_000, 1.2, 8, 31, 120, 2_880, "f32"), (300, 64, 64, 3_000, 1.5, 2, 64, 100, 50, "f32"),
+    (300, 64, 64, 3_000, 1.5, 3, 85, 70, 0, "f32"), (40, 64, 64, 3_000, 1.5, 1, 8, 100, 50, "f32"), (1, 16, 16, 500, 1.0, 8, 31, 60, 0, "f32"),
+]
+
+
+@pytest.mark.parametrize("case", REPEAT_CASES, ids=lambda c: f"V{c[0]}_D{c[1]}_w{c[5]}_N{c[6]}_{c[9]}")
+def test_sgns_grad_parity_where_words_repeat(case):
+    _grad_parity(case)
+
+
 def _random_grad_cases(n, seed):
     """Seeded shapes: narrow to wide rows, windows 1..6, 0..12 negatives, batches from one center up, streams
     from flat to steep, vocabularies from two words up, batches at the start, inside and at the end of the
