@@ -271,22 +271,23 @@ int tensair_step_packed(tensair_model *m, const int32_t *tokens, int64_t n_token
 
 /* Announces a coming mini-batch, so that the part of its tensair_sgns_grad / tensair_step
  * call that does not depend on the tables -- pair enumeration, negatives, sort by row id,
- * segments, unique row ids -- is prepared ahead of time on the library's own stream, next to
+ * segments, unique row ids -- is prepared ahead of time, next to
  * whatever the caller's stream is doing (in TensAIR's dataflow, Section 3, mini-batches queue
  * up at the Model operator: the coming ones are known while the current one trains).
- * Up to two announcements are kept, in order.  When the first is prepared is the library's choice: at
- * once if the mini-batch is small (up to 2^20 context and negative occurrences: its sort is bound by
- * latency and fits beside whatever runs), else by the gradient call that consumes it.  A second one is
- * prepared during the gradient call that consumes the first -- under that call's table update if
- * tensair_step expects a long one, else beside its forward pass if small; a third replaces the second.
+ * Up to two announcements are kept, in order.  When and where one is prepared is the library's choice: a
+ * second one, of up to 512 tiles of 2048 occurrences (about 2^20), phase by phase in the launches of the
+ * gradient call that consumes the first; a larger one under that call's table update if tensair_step expects
+ * a long one; one that is announced with none before it at once, on the library's own stream, if it has
+ * between 128 and 512 tiles; whatever is left is done by the gradient call that consumes it.  A third
+ * replaces the second.
  * A gradient call on this model uses the
  * prepared data if its (tokens, n_tokens, center_begin, n_centers, epoch) and the model's
  * worker id are those of the oldest announcement -- its results are then bit-identical to
  * those of a call without prefetch -- and otherwise drops every announcement.
  * A mini-batch without pairs is not recorded.
- * Ordering: the preparation may start as soon as everything enqueued on `stream` before
- * the START of the most recent gradient call on this model has finished (before this call,
- * if the library's stream has not followed that call), so the token range must be ready by
+ * Ordering: on the library's own stream the preparation may start as soon as everything enqueued on
+ * `stream` before the START of the most recent gradient call on this model has finished (before this
+ * call, if the library's stream has not followed that call), so the token range must be ready by
  * then and must stay unchanged until the consuming call has run.
  * Same argument checks and error codes as tensair_sgns_grad. */
 int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, int64_t center_begin,

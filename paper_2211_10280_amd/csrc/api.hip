@@ -3,6 +3,7 @@
 // Call names follow the Model operator of TensAIR (arXiv 2211.10280), Algorithm 1.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -191,9 +192,8 @@ struct tensair_model {
     u32 *wbase[2], *wblk[2];   // tensair_grad_add: place of every 64-row word in the summed gradient
     std::vector<Draw> h_draw;  // the same on the host
     double different = 1.0;    // share of a position's negatives that are different words, as expected
-    // second stream, forked from and joined to the caller's stream with events: it runs what can go
-    // on next to the caller's stream (the forward pass beside the sort, the index of the coming table
-    // update beside the reductions, the preparation of announced mini-batches)
+    // second stream, forked from and joined to the caller's stream with events: the forward pass beside the sort of a
+    // large mini-batch that was not prepared, the preparation of an announced one under a long table update
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_fwd = nullptr;
     // mini-batch sets: `busy` is the one the most recent gradient call reads; announced mini-batches are
@@ -296,11 +296,12 @@ bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double 
     lo.reserve((size_t)V);
     hi.reserve((size_t)V);
     const double scale = (double)V;
+    const double per_word = n / scale;
     double met = 0.0;
     for (i64 i = 0; i < V; ++i) {
         double q = prob[(size_t)i] * scale / total;
         prob[(size_t)i] = q;
-        const double x = q * n / scale < 1.0 ? q * n / scale : 1.0;   // 1 - exp(-x), nearly
+        const double x = std::min(q * per_word, 1.0);   // 1 - exp(-x), nearly
         met += x - 0.37 * x * x;
         (q < 1.0 ? lo : hi).push_back((int32_t)i);
     }
@@ -505,12 +506,11 @@ int64_t tensair_pair_count(const tensair_model *m, int64_t n_tokens, int64_t cen
     return pair_count(m->cfg, n_tokens, center_begin, n_centers);
 }
 
-// The table-independent part of a mini-batch, split in two so that other work can be enqueued in
-// between: keys (pairs, negatives), then sort + segments.
+// A mini-batch as its preparation and its gradient calculation take it.
 struct BatchWork {
     BatchDesc b;
     i64 P, O;
-    u32 epoch;
+    u32 epoch, worker_id;
 };
 
 static BatchWork batch_work(const tensair_config &c, const int32_t *tokens, i64 n_tokens, i64 center_begin,
@@ -528,6 +528,7 @@ static BatchWork batch_work(const tensair_config &c, const int32_t *tokens, i64 
     w.P = P;
     w.O = P * (c.negatives + 1);
     w.epoch = epoch;
+    w.worker_id = c.worker_id;
     return w;
 }
 
@@ -576,7 +577,7 @@ static void make_prep_phase(tensair_model *m, BatchSet &S, const BatchWork &w, b
         k.draw = m->draw;
         k.k0 = (u32)(c.seed & 0xFFFFFFFFu);
         k.k1 = (u32)(c.seed >> 32);
-        k.ctr3 = c.worker_id + 65536u * w.epoch;
+        k.ctr3 = w.worker_id + 65536u * w.epoch;
         k.resample = (c.flags & TENSAIR_RESAMPLE_NEGATIVES) != 0;
         k.out_keys = S.keys[0];
         k.in_keys = S.keys[0] + s.Omax;
@@ -714,7 +715,8 @@ static bool next_rider(tensair_model *m, bool forward, PrepPhase &x, hipStream_t
     Prefetched &d = m->pend;
     if (!d.valid || !d.chained || d.on_side || (d.phase == 0) != forward || d.phase >= prep_phases(m->sz, true)) return false;
     BatchSet &S = m->set[1 - m->busy];
-    const BatchWork w = batch_work(m->cfg, d.tokens, d.n_tokens, d.begin, d.n_centers, d.epoch, d.P);
+    BatchWork w = batch_work(m->cfg, d.tokens, d.n_tokens, d.begin, d.n_centers, d.epoch, d.P);
+    w.worker_id = d.worker_id;     // the id it was announced under
     RowIndexDst in, out;
     set_row_index(m, S, in, out);
     make_prep_phase(m, S, w, true, d.phase, in, out, nullptr, x);
@@ -729,7 +731,8 @@ static int enqueue_prepare(tensair_model *m, const Prefetched &d)
 {
     const tensair_config &c = m->cfg;
     BatchSet &S = m->set[1 - m->busy];
-    const BatchWork w = batch_work(c, d.tokens, d.n_tokens, d.begin, d.n_centers, d.epoch, d.P);
+    BatchWork w = batch_work(c, d.tokens, d.n_tokens, d.begin, d.n_centers, d.epoch, d.P);
+    w.worker_id = d.worker_id;     // the id it was announced under
     RowIndexDst in, out;
     set_row_index(m, S, in, out);
     const bool chained = prep_tiles(c, d.P, d.n_centers) <= TN_PREP_CHAIN_OWN;
