@@ -275,9 +275,11 @@ k_forward_repeats(FwdArgs a, AuxWork aux)
             const float n1 = (float)(n & 0xFFFFu), n0 = (float)(n >> 16);
             sum = fmaf(n1, g1, n0 * g0);
             if (LOSS) {
-                // loss terms: softplus(-s) for a context, softplus(s) for a negative
+                // loss terms: softplus(-s) for a context, softplus(s) for a negative; one that does not occur is left
+                // out, not taken zero times (it is infinite where the dot product has overflowed)
                 const float tail = log1pf(expf(-fabsf(s_l)));
-                loss += n1 * (fmaxf(-s_l, 0.f) + tail) + n0 * (fmaxf(s_l, 0.f) + tail);
+                if (n & 0xFFFFu) loss += n1 * (fmaxf(-s_l, 0.f) + tail);
+                if (n >> 16) loss += n0 * (fmaxf(s_l, 0.f) + tail);
             }
         }
 #pragma unroll

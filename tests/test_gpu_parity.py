@@ -166,6 +166,36 @@ def test_sgns_grad_parity_where_words_repeat(case):
     _grad_parity(case)
 
 
+@pytest.mark.parametrize("w,N", [(8, 15), (3, 84), (3, 85)])      # 256, 510 and 516 tasks per position: the last goes the plain way
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_mean_loss_where_scores_overflow(w, N, dtype):
+    """A word whose dot products overflow to +inf loses nothing as a context, one with -inf nothing as a negative: the
+    loss is that of the other words (whose scores are zero: ln 2 each), whatever forward pass is taken."""
+    V, D, T, Bc = 40, 16, 2_000, 90
+    rng = np.random.default_rng(w + N)
+    tok = rng.integers(0, 20, T).astype(np.int32)                  # words 0..19 are met as contexts only ...
+    counts = np.zeros(V, np.uint64)
+    counts[20:] = 50                                                # ... and 20..39 as negatives only
+    Wi = torch.full((V, D), 1e20)
+    Wo = torch.zeros((V, D))
+    Wo[:10], Wo[20:30] = 1e20, -1e20                                # dot products of +-1.6e41; the others are zero
+    m = B.Model(V, D, DT[dtype][0], w, N, Bc, 0, 5, counts, tables=(Wi.cuda().to(DT[dtype][2]), Wo.cuda().to(DT[dtype][2])))
+    P = m.pair_count(T, 300, Bc)
+    g, loss = m.grad_buffers(), torch.zeros(1, device="cuda")
+    neg = torch.full((P * N,), -1, dtype=torch.int32, device="cuda")
+    m.sgns_grad(torch.from_numpy(tok).cuda(), 300, Bc, 0, g, mean_loss=loss, negatives_dbg=neg)
+    m.status()
+    contexts = sum(int((tok[i - w:i + w + 1] >= 10).sum()) - int(tok[i] >= 10) for i in range(300, 300 + Bc))
+    negatives = int((neg >= 30).sum())
+    assert 0 < contexts < P and 0 < negatives < P * N
+    want = (contexts + negatives) * np.log(2.0) / P
+    _say(f"   loss {float(loss.item())} expected {want}")
+    assert abs(float(loss.item()) - want) <= TOL_LOSS * want
+    (_, rows_in), (_, rows_out) = g.to_host()
+    assert np.isfinite(rows_in).all() and np.isfinite(rows_out).all()
+    m.close()
+
+
 def _random_grad_cases(n, seed):
     """Seeded shapes: narrow to wide rows, windows 1..6, 0..12 negatives, batches from one center up, streams
     from flat to steep, vocabularies from two words up, batches at the start, inside and at the end of the
