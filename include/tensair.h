@@ -31,6 +31,10 @@
  *   - A model handle keeps host-side state between calls (announced mini-batches, the order of
  *     work on the library's stream): calls on one handle must not overlap in time on the host;
  *     different handles are independent.
+ *   - Calls may be recorded into a HIP graph.  From the first gradient call, step, update or gradient sum that
+ *     is, the handle keeps nothing prepared from one call to the next, since a replay may run at any time:
+ *     tensair_prefetch then records nothing.  (A recorded tensair_step draws the same numbers for stochastic
+ *     rounding at every replay.)  Replays count as calls on the model: one stream, none beside another call.
  *   - Data errors seen by kernels (a peer gradient whose ids are out of range or not
  *     strictly ascending) never fault: the offending rows are skipped, a device
  *     status word is set, and tensair_status() reports TENSAIR_EDATA.
@@ -284,7 +288,7 @@ int tensair_step_packed(tensair_model *m, const int32_t *tokens, int64_t n_token
  * prepared data if its (tokens, n_tokens, center_begin, n_centers, epoch) and the model's
  * worker id are those of the oldest announcement -- its results are then bit-identical to
  * those of a call without prefetch -- and otherwise drops every announcement.
- * A mini-batch without pairs is not recorded.
+ * A mini-batch without pairs is not recorded, nor is any once a call on the model was recorded into a HIP graph.
  * Ordering: on the library's own stream the preparation may start as soon as everything enqueued on
  * `stream` before the START of the most recent gradient call on this model has finished (before this
  * call, if the library's stream has not followed that call), so the token range must be ready by

@@ -213,6 +213,7 @@ struct tensair_model {
     bool fused_index_done = false;
     bool prepare_under_apply = false;   // tensair_step: the table update is long enough to hide a preparation
     Prefetched deferred;                // the mini-batch to prepare under that update (enqueued by tensair_step)
+    bool captured = false;              // a call on this handle was recorded into a HIP graph (see note_capture)
     u32 apply_serial = 0;               // table updates enqueued so far (stochastic rounding draws from it)
     // stage timing (tensair_profile): events recorded on the caller's stream
     int prof_level = 0;
@@ -351,6 +352,28 @@ hipEvent_t mark(tensair_model *m, int tag, hipStream_t st)
     if (hipEventRecord(ev, st) != hipSuccess) return nullptr;
     m->prof_marks.emplace_back(tag, ev);
     return ev;
+}
+
+// A call that is being recorded into a HIP graph does not run now, and may run again at any time later: what it leaves
+// in the workspace (zeroed digit counts and masks, a mini-batch that is prepared, wholly or in part) is not there when
+// the host says so, and what other calls left there is gone after a replay.  From the first such call on, every call on
+// the handle therefore starts from nothing: it prepares its own mini-batch and clears what it needs cleared.
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) != hipSuccess) {   // another thread's capture: this stream takes no part in it
+        (void)hipGetLastError();
+        return false;
+    }
+    return s == hipStreamCaptureStatusActive;
+}
+void note_capture(tensair_model *m, hipStream_t st)
+{
+    if (!m->captured && !capturing(st)) return;
+    m->captured = true;
+    m->pend.valid = m->next.valid = m->deferred.valid = false;
+    m->mask_clean[0] = m->mask_clean[1] = false;
+    m->set[0].hist_clean = m->set[1].hist_clean = false;
 }
 
 i64 pair_count(const tensair_config &c, i64 T, i64 begin, int n)
@@ -781,6 +804,8 @@ int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, 
     d.P = pair_count(c, n_tokens, center_begin, n_centers);
     if (d.P == 0) return TENSAIR_OK;   // nothing to prepare
     d.valid = true;
+    note_capture(m, (hipStream_t)stream);
+    if (m->captured) return TENSAIR_OK;
     if (m->pend.valid) {   // one mini-batch is waiting already: this one is prepared when that is consumed
         m->next = d;
         return TENSAIR_OK;
@@ -824,6 +849,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         HIP_TRY(hipGetLastError());
         return TENSAIR_OK;
     }
+    note_capture(m, st);
     const int Np1 = c.negatives + 1;
     const BatchWork w = batch_work(c, tokens, n_tokens, center_begin, n_centers, epoch, P);
 
@@ -1104,6 +1130,7 @@ static int apply_impl(tensair_model *m, const tensair_sparse_grad *own, const te
     if (rc) return rc;
     if (!own && n_peers == 0) return TENSAIR_OK;
     hipStream_t st = (hipStream_t)stream;
+    note_capture(m, st);
     mark(m, PF_BEGIN_APPLY, st);
     m->mask_clean[0] = false;
     tn_launch_apply_clear(a, st);
@@ -1202,6 +1229,7 @@ int tensair_grad_add(tensair_model *m, const tensair_sparse_grad *a, const tensa
         g.wblk[t] = m->wblk[t];
     }
     hipStream_t st = (hipStream_t)stream;
+    note_capture(m, st);
     mark(m, PF_BEGIN_ADD, st);
     m->mask_clean[0] = false;
     tn_launch_grad_sum_index(g, st);

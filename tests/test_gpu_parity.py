@@ -1261,6 +1261,62 @@ def test_phases_that_ride_give_the_same_bits(V, D, call):
         assert _same(a, b), i
 
 
+@pytest.mark.parametrize("n", [60, 1500])                 # chained preparation; counted, forward pass on the second stream
+@pytest.mark.parametrize("call", ["step", "grad"])
+def test_a_captured_call_replays_between_eager_ones(n, call):
+    """A call recorded into a HIP graph and replayed several times, with eager calls (announced ones too) in between,
+    against the same calls made eagerly: the same bits at every replay and in every call."""
+    V, D, T, w, N = 5000, 64, 30_000, 8, 15
+    tok = W.zipf_stream(V, 1.1, T, 5)
+    counts = W.unigram_counts(tok, V)
+    Wi, Wo = _random_tables(V, D, D, "f32", seed=12)
+    dtok = torch.from_numpy(tok).cuda()
+    models = [B.Model(V, D, B.F32, w, N, n, 0, 77, counts, tables=(_tables_to_dev(Wi, "f32"), _tables_to_dev(Wo, "f32")))
+              for _ in range(2)]
+    bufs, losses = [m.grad_buffers() for m in models], [torch.zeros(1, device="cuda") for _ in models]
+
+    def run(i, batch):
+        m, g, loss = models[i], bufs[i], losses[i]
+        if call == "step":
+            m.step(dtok, *batch, [], 0.5, g, loss)
+        else:
+            m.sgns_grad(dtok, *batch, g, mean_loss=loss)
+
+    def same(what):
+        torch.cuda.synchronize()
+        assert _same(_grad_snapshot(bufs[0], losses[0]), _grad_snapshot(bufs[1], losses[1])), what
+        assert torch.equal(models[0].w_in, models[1].w_in) and torch.equal(models[0].w_out, models[1].w_out), what
+
+    recorded = (7 * n, n, 3)
+    run(0, (0, n, 0))
+    run(1, (0, n, 0))
+    same("before")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run(0, recorded)
+    run(0, (n, n, 0))                       # not replayed yet
+    run(1, (n, n, 0))
+    same("after the capture")
+    for k in range(4):
+        _say("   replay", k)
+        graph.replay()
+        run(1, recorded)
+        same(f"replay {k}")
+        for j in range(k):
+            batch = ((2 + j) * n, n, k)
+            models[0].prefetch(dtok, *batch)
+            models[0].prefetch(dtok, (3 + j) * n, n, k)
+            if j == 1:
+                graph.replay()              # between an announcement and its call
+                run(1, recorded)
+            run(0, batch)
+            run(1, batch)
+            same(f"eager call {j} after replay {k}")
+    for m in models:
+        m.status()
+        m.close()
+
+
 @pytest.mark.parametrize("name,idx,kw", [
     ("cfg3_pf", 3, dict(vocab=20_000, tokens=300_000, batch=256)),
     ("cfg5_pf", 5, dict(vocab=20_000, tokens=300_000, batch=256)),

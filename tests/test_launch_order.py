@@ -1,0 +1,74 @@
+"""What calls enqueue, read from the library's host side run against stand-ins of the HIP runtime (launch_trace.py,
+hip_trace.c): no GPU needed, nothing is executed."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_2211_10280_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def trace(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("hip_trace") / "hip_trace.so")
+    subprocess.check_call(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "hip_trace.c")])
+    lib = os.environ.get("TENSAIR_TRACED_LIB", B.LIB_PATH)
+
+    def run(calls, tokens=1_000_000, **model):
+        model = {"row_stride": model["dim"], "dtype": B.F32, "max_peers": 0, "worker_id": 0, "seed": 7, "flags": 0, **model}
+        r = subprocess.run([sys.executable, os.path.join(HERE, "launch_trace.py"), lib, so], capture_output=True, text=True,
+                           input=json.dumps({"model": model, "tokens": tokens, "calls": calls}), timeout=120)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout)
+
+    return run
+
+
+def launches(did):
+    """[(kernel, workgroups, stream)] of one call, kernels without namespace and types"""
+    out = []
+    for d in did:
+        if d[0] == "launch":
+            n = int("".join(c for c in d[1][2:5] if c.isdigit()))            # _Z<length><name>...
+            out.append((d[1][2 + len(str(n)):][:n], int(d[2]), d[4]))
+    return out
+
+
+def names(did):
+    return [k for k, _, _ in launches(did)]
+
+
+# 60 centers: chained preparation (8 tiles); 1500 centers: counted (188 tiles), forward pass on the second stream
+SMALL = dict(vocab=50_000, dim=64, window=8, negatives=15, max_centers=6000)
+
+
+@pytest.mark.parametrize("n", [60, 1500])
+@pytest.mark.parametrize("kind", ["grad", "step"])
+def test_calls_after_a_capture_rely_on_nothing_that_was_left(trace, kind, n):
+    """A recorded call has not run when the next one is enqueued, and runs again later: neither may count on counters,
+    masks or a mini-batch that the other is to leave in the workspace."""
+    batch = lambda i: [i * n, n, 0]                                            # noqa: E731
+    call = lambda i: [kind] + batch(i) + ([0] if kind == "step" else [])       # noqa: E731
+    calls = [["prefetch"] + batch(0), ["prefetch"] + batch(1), call(0), ["capture", 1], call(1), ["capture", 0]]
+    calls += [c for i in range(2, 8) for c in (["prefetch"] + batch(i), ["prefetch"] + batch(i + 1), call(i))]
+    got = trace(calls, **SMALL)
+    assert all(c["rc"] == 0 for c in got)
+    assert [c["call"][0] for c in got[:4]] == ["prefetch", "prefetch", kind, kind]
+    for c in got[3:]:
+        did = names(c["did"])
+        if c["call"][0] == "prefetch":
+            assert did == []
+        else:
+            assert did.index("k_prep_clear") < did.index("k_prep_keys")        # digit counts zeroed by the call itself
+            assert ("k_apply_clear" in did) == (kind == "step")                # and the masks of the update's index
+
+
+def test_an_update_that_is_captured_leaves_no_mask_clean(trace):
+    got = trace([["step", 0, 60, 0, 0], ["step", 60, 60, 0, 0], ["capture", 1], ["apply", 60, 900, 0], ["capture", 0],
+                 ["step", 120, 60, 0, 0], ["step", 180, 60, 0, 0]], **SMALL)
+    assert "k_apply_clear" not in names(got[1]["did"])                         # cleared during the step before
+    assert all("k_apply_clear" in names(c["did"]) for c in got[3:])
