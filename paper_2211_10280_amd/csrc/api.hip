@@ -1298,7 +1298,7 @@ static int step_impl(tensair_model *m, const int32_t *tokens, int64_t n_tokens, 
     const hipEvent_t ev = mark(m, PF_APPLY_INDEX, st);
     if ((rc = enqueue_deferred_prepare(m, ev, st))) return rc;
     PrepPhase x;
-    const bool rider = m->prof_level < 2 && tn_apply_carries(a.D) && next_rider(m, false, x, st);
+    const bool rider = m->prof_level < 2 && tn_apply_carries(a.D, a.V) && next_rider(m, false, x, st);
     tn_launch_apply_update(a, rider ? &x : nullptr, st);
     ++m->apply_serial;
     mark(m, PF_APPLY_UPDATE, st);

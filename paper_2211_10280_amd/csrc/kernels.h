@@ -242,7 +242,9 @@ void tn_aux_add_index(AuxWork &x, const ApplyArgs &a, int k_begin, int k_end);
 
 void tn_launch_apply_clear(const ApplyArgs &a, hipStream_t st);
 void tn_launch_apply_index(const ApplyArgs &a, int k_begin, int k_end, hipStream_t st);
-static inline bool tn_apply_carries(int D) { return D <= 512; }   // whether a phase can ride with the update
+// whether a phase can ride with the update: its workgroups come on top of those for the rows (of 16 vocabulary rows
+// each, at least), and one launch has to hold them all
+static inline bool tn_apply_carries(int D, i64 V) { return D <= 512 && (V + 15) / 16 + TN_PREP_CHAIN_RIDE <= TN_MAX_BLOCKS; }
 void tn_launch_apply_update(const ApplyArgs &a, const PrepPhase *rider, hipStream_t st);   // rider may be NULL
 void tn_launch_apply_update_riding(const ApplyArgs &a, const PrepPhase &rider, hipStream_t st);
 

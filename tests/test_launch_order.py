@@ -72,3 +72,16 @@ def test_an_update_that_is_captured_leaves_no_mask_clean(trace):
                  ["step", 120, 60, 0, 0], ["step", 180, 60, 0, 0]], **SMALL)
     assert "k_apply_clear" not in names(got[1]["did"])                         # cleared during the step before
     assert all("k_apply_clear" in names(c["did"]) for c in got[3:])
+
+
+@pytest.mark.parametrize("V", [B.MAX_VOCAB, B.MAX_VOCAB - 16 * 600])
+def test_no_launch_grows_beyond_its_limit_in_the_largest_vocabulary(trace, V):
+    """2^32 threads: the update of the largest vocabulary fills a launch, so a phase rides with it only where there is
+    room (each of the two sizes is on its side of that)."""
+    step = lambda i: ["step", 1000 * i, 1000, 0, 0]                            # noqa: E731
+    calls = [step(0), ["prefetch", 1000, 1000, 0], ["prefetch", 2000, 1000, 0], step(1), ["prefetch", 3000, 1000, 0], step(2)]
+    got = trace(calls, vocab=V, dim=256, window=8, negatives=15, max_centers=800_000, dtype=B.BF16)
+    grids = [g for c in got if c["call"][0] == "step" for k, g, _ in launches(c["did"]) if k == "k_apply"]
+    assert len(grids) == 3 and grids[0] == (V + 63) // 64 * 4
+    assert all(d[0] != "launch" or int(d[2]) * int(d[3]) < 1 << 32 for c in got for d in c["did"])
+    assert (grids[2] > grids[0]) == (V < B.MAX_VOCAB)                          # a phase rode along
