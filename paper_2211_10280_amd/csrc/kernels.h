@@ -114,8 +114,8 @@ struct PrepPhase {
 #define TN_PREP_CHAIN_RIDE 512
 #endif
 #define TN_PREP_CHAIN_MAX (TN_PREP_CHAIN_OWN > TN_PREP_CHAIN_RIDE ? TN_PREP_CHAIN_OWN : TN_PREP_CHAIN_RIDE)
-static inline int tn_prep_tiles(int n) { return (n + TN_RADIX_TILE - 1) / TN_RADIX_TILE; }
-static inline int tn_prep_seg_tiles(int n) { return (n + TN_SCAN_TILE - 1) / TN_SCAN_TILE; }
+static inline int tn_prep_tiles(i64 n) { return (int)((n + TN_RADIX_TILE - 1) / TN_RADIX_TILE); }   // n: up to 2^31 - 1
+static inline int tn_prep_seg_tiles(i64 n) { return (int)((n + TN_SCAN_TILE - 1) / TN_SCAN_TILE); }
 void tn_launch_prep(const PrepPhase &x, hipStream_t st);   // the phase as a launch of its own
 void tn_launch_prep_clear(u32 *hist, int n, hipStream_t st);
 

@@ -43,6 +43,9 @@ def test_host_side_argument_checks():
     assert B.tensair_workspace_bytes(B.Config(B.MAX_VOCAB, 4, 4, B.F32, 1, 0, 1, 0, 0, 7)) > 0
     with pytest.raises(B.TensairError):
         B.tensair_workspace_bytes(B.Config(B.MAX_VOCAB + 1, 4, 4, B.F32, 1, 0, 1, 0, 0, 7))
+    # the largest mini-batches (2^31 - 2 occurrences and centers together) need more than slightly smaller ones
+    sizes = [B.tensair_workspace_bytes(B.Config(1000, 4, 4, B.F32, 181, n, 95, 0, 0, 7)) for n in (62_443, 62_444)]
+    assert 0 < sizes[1] - sizes[0] < 0.001 * sizes[0]
     for bad in (B.Config(0, 32, 32, B.F32, 2, 5, 64, 0, 0, 7),      # vocab
                 B.Config(1000, 30, 32, B.F32, 2, 5, 64, 0, 0, 7),    # dim not a multiple of 4
                 B.Config(1000, 32, 28, B.F32, 2, 5, 64, 0, 0, 7),    # stride < dim
