@@ -1001,6 +1001,10 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     enqueue_prep(m, S, w, chained, phase, phases, in, out, nullptr, st);
     mark(m, PF_SEGMENTS, st);
     if (aside) {
+        // the keys of the announced mini-batch after this one, in a launch of their own: a forward pass on the second
+        // stream carries none, and without them none of its other phases could ride with what follows (nor could any
+        // mini-batch's after it: each would be left to its own call, with the forward pass aside again)
+        if (next_rider(m, true, x, st)) tn_launch_prep(x, st);
         HIP_TRY(hipStreamWaitEvent(st, m->ev_fwd, 0));
         if (fwd_ticket > m->main_ticket) m->main_ticket = fwd_ticket;
     }

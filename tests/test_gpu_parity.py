@@ -1261,6 +1261,41 @@ def test_phases_that_ride_give_the_same_bits(V, D, call):
         assert _same(a, b), i
 
 
+@pytest.mark.parametrize("call", ["step", "grad"])
+def test_mini_batches_too_large_to_ride_among_others_give_the_same_bits(call):
+    """Mini-batches of 628 and more tiles (prepared by their own calls, forward pass on the second stream) among ones
+    of 201, 126 and 8 tiles (whose phases ride, the first of them begun beside a large one), announced two deep, against
+    the same calls without announcements."""
+    V, D, T, w, N = 50_000, 64, 60_000, 8, 15
+    tok = W.zipf_stream(V, 1.1, T, 5)
+    counts = W.unigram_counts(tok, V)
+    Wi, Wo = _random_tables(V, D, D, "f32", seed=11)
+    dtok = torch.from_numpy(tok).cuda()
+    sizes = [5000, 1600, 1600, 1600, 5200, 5000, 60, 1600, 1000, 5000]
+    batches = [(4700 * i, n, i % 3) for i, n in enumerate(sizes)]
+    runs = []
+    for ahead in (False, True):
+        m = B.Model(V, D, B.F32, w, N, 5200, 0, 77, counts, tables=(_tables_to_dev(Wi, "f32"), _tables_to_dev(Wo, "f32")))
+        g, loss, got = m.grad_buffers(), torch.zeros(1, device="cuda"), []
+        if ahead:
+            m.prefetch(dtok, *batches[0])
+        for i, batch in enumerate(batches):
+            if ahead and i + 1 < len(batches):
+                m.prefetch(dtok, *batches[i + 1])
+            if call == "step":
+                m.step(dtok, *batch, [], 0.5, g, loss)
+            else:
+                m.sgns_grad(dtok, *batch, g, mean_loss=loss)
+            if i % 4 == 3:           # the others stay in the queue together
+                got.append(_grad_snapshot(g, loss))
+        m.status()
+        got.append(_grad_snapshot(g, loss) + [_tables_to_host(t, "f32") for t in (m.w_in, m.w_out)])
+        runs.append(got)
+        m.close()
+    for i, (a, b) in enumerate(zip(*runs)):
+        assert _same(a, b), i
+
+
 @pytest.mark.parametrize("n", [60, 1500])                 # chained preparation; counted, forward pass on the second stream
 @pytest.mark.parametrize("call", ["step", "grad"])
 def test_a_captured_call_replays_between_eager_ones(n, call):

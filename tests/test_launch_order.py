@@ -85,3 +85,21 @@ def test_no_launch_grows_beyond_its_limit_in_the_largest_vocabulary(trace, V):
     assert len(grids) == 3 and grids[0] == (V + 63) // 64 * 4
     assert all(d[0] != "launch" or int(d[2]) * int(d[3]) < 1 << 32 for c in got for d in c["did"])
     assert (grids[2] > grids[0]) == (V < B.MAX_VOCAB)                          # a phase rode along
+
+
+@pytest.mark.parametrize("kind", ["grad", "step"])
+def test_riding_goes_on_after_a_mini_batch_too_large_to_ride(trace, kind):
+    """628 tiles, then 201 each, announced two deep: the first is prepared by its own call; from there on the next one
+    rides in the launches of the call before, and a call has nothing, or little, of its own left to prepare."""
+    sizes = [5000, 5000] + [1600] * 5
+    calls = []
+    for i, n in enumerate(sizes):
+        calls += [["prefetch", 5000 * (i + 1), m, 0] for m in sizes[i + 1:i + 2]]
+        calls.append([kind, 5000 * i, n, 0] + ([0] if kind == "step" else []))
+    calls.insert(0, ["prefetch", 0, 5000, 0])
+    got = [c for c in trace(calls, **SMALL) if c["call"][0] == kind]
+    prep = [[k for k in names(c["did"]) if k.startswith("k_prep")] for c in got]
+    assert prep[0].count("k_prep_count") == 2 and prep[1].count("k_prep_count") == 2
+    assert prep[1].count("k_prep_keys") == 2                                   # its own, and the next one's
+    for p in prep[2:]:
+        assert p == [] or (kind == "grad" and p == ["k_prep_segments"]), p
