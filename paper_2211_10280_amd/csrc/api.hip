@@ -153,9 +153,10 @@ struct BatchSet {
 // A mini-batch announced by tensair_prefetch.
 struct Prefetched {
     bool valid = false;
-    bool chained = false;      // how it is (to be) prepared: riding in the launches of the call before, phase by phase ...
-    int phase = 0;             // ... phases of its preparation that are enqueued; the consuming call does the rest
-    bool on_side = false;      // ... or as a whole on the second stream (ev_prep)
+    bool chained = false;      // how it is (to be) prepared: on the caller's stream, most often riding in the launches ...
+    int phase = 0;             // ... of the call before; phases that are enqueued, the consuming call does the rest;
+    bool on_side = false;      // or as a whole on the second stream (ev_prep),
+    bool late = false;         // where it may still be running when it is consumed: its keys have an event of their own
     const int32_t *tokens = nullptr;
     i64 n_tokens = 0, begin = 0, P = 0;
     int n_centers = 0;
@@ -202,11 +203,11 @@ struct tensair_model {
     int busy = 1;
     Prefetched pend;               // prepared, or being prepared, or to be prepared in set 1 - busy
     Prefetched next;               // announced after `pend`: prepared from when `pend` is consumed
-    hipEvent_t ev_prep = nullptr, ev_reduced = nullptr;
+    hipEvent_t ev_prep = nullptr, ev_keys = nullptr, ev_reduced = nullptr;
     bool side_follows = false;     // the second stream has waited for the start of the latest gradient call
     // every event recorded on the second stream takes a ticket; the caller's stream is behind all of
     // them up to main_ticket, so a prepared set with prep_ticket <= main_ticket needs no wait
-    u64 side_ticket = 0, main_ticket = 0, prep_ticket = 0;
+    u64 side_ticket = 0, main_ticket = 0, prep_ticket = 0, keys_ticket = 0;
     // set by tensair_step: the index of the coming apply is built by extra workgroups at the front of the
     // forward pass (clearing) and of the segmented reduction (the id lists), on the caller's stream
     ApplyArgs *fused_apply = nullptr;
@@ -491,6 +492,7 @@ int tensair_model_init(tensair_model **out, const tensair_config *cfg, void *w_i
         hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&m->ev_fwd, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&m->ev_prep, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&m->ev_keys, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&m->ev_reduced, hipEventDisableTiming) != hipSuccess) {
         tensair_model_destroy(m);
         return fail(TENSAIR_EHIP, "model_init: cannot create the side stream");
@@ -719,8 +721,14 @@ static int check_batch(const tensair_model *m, const int32_t *tokens, i64 n_toke
 //     event between two streams costs the host 15 us and the waiting stream 4 to 7, a launch 3 to 5: steps of 60 000
 //     occurrences took 80 us of host time with the preparation on the second stream and 65 us in all riding.  Up to
 //     TN_PREP_CHAIN_RIDE tiles.
-//   On the second stream under a table update that is long enough (tensair_step decides), for larger ones; or at once
-//     when announced with nothing before it, up to TN_BESIDE_MAX_OCC occurrences.
+//   On the second stream under a table update that is long enough (tensair_step decides), for larger ones.
+//   At once, when it is announced with nothing before it: there is no call whose launches it could ride in, and the
+//     GPU may have nothing else to do until it is consumed.  On the caller's stream up to TN_PREP_CHAIN_OWN tiles, all
+//     but the segments, which ride with the consuming call's forward pass; on the second stream up to TN_BESIDE_MAX_OCC
+//     occurrences, where the consuming call's forward pass waits for the keys alone and runs beside the sort.  Step
+//     after a pause, announced before it / not announced: 31 tiles 68 / 110 us, 108 tiles 94 / 142, 160 tiles 111 / 191,
+//     222 tiles 843 / 925; without a pause 91 / 89, 131 / 121, 179 / 160, 911 / 891 (all of the small ones' preparation
+//     at once 99 and 137; waiting for the large ones' sort before the forward pass 198 and 935).
 //   Else not ahead: beside a forward pass of cache-resident tables both fight for the caches (262 000 pairs per step
 //     4 % slower).
 #ifndef TN_BESIDE_MAX_OCC
@@ -748,26 +756,34 @@ static bool next_rider(tensair_model *m, bool forward, PrepPhase &x, hipStream_t
     return true;
 }
 
-// Enqueue the preparation of an announced mini-batch on the second stream, into the set that the
-// latest gradient call does not read.  The second stream must already be behind that set's last readers.
-static int enqueue_prepare(tensair_model *m, const Prefetched &d)
+// Enqueue the preparation of an announced mini-batch in launches of its own, into the set that the latest gradient call
+// does not read: on the second stream, which must already be behind that set's last readers, or on the caller's.
+// late: it may still be running when the mini-batch is consumed, so its keys are made available on their own.
+static int enqueue_prepare(tensair_model *m, const Prefetched &d, bool on_side, bool late, hipStream_t st)
 {
-    const tensair_config &c = m->cfg;
     BatchSet &S = m->set[1 - m->busy];
-    BatchWork w = batch_work(c, d.tokens, d.n_tokens, d.begin, d.n_centers, d.epoch, d.P);
+    BatchWork w = batch_work(m->cfg, d.tokens, d.n_tokens, d.begin, d.n_centers, d.epoch, d.P);
     w.worker_id = d.worker_id;     // the id it was announced under
     RowIndexDst in, out;
     set_row_index(m, S, in, out);
-    const bool chained = prep_tiles(c, d.P, d.n_centers) <= TN_PREP_CHAIN_OWN;
-    const int phases = prep_phases(m->sz, chained);
-    enqueue_prep(m, S, w, chained, 0, phases, in, out, nullptr, m->side);
+    const bool chained = !on_side;                       // what goes to the second stream is too long for chained passes
+    const int phases = prep_phases(m->sz, chained) - (chained ? 1 : 0);   // the segments: with the consuming call's forward pass
+    enqueue_prep(m, S, w, chained, 0, 1, in, out, nullptr, st);
+    if (late) {
+        HIP_TRY(hipEventRecord(m->ev_keys, st));
+        m->keys_ticket = ++m->side_ticket;
+    }
+    enqueue_prep(m, S, w, chained, 1, phases, in, out, nullptr, st);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipEventRecord(m->ev_prep, m->side));
-    m->prep_ticket = ++m->side_ticket;
+    if (on_side) {
+        HIP_TRY(hipEventRecord(m->ev_prep, st));
+        m->prep_ticket = ++m->side_ticket;
+    }
     m->pend = d;
     m->pend.chained = chained;
     m->pend.phase = phases;
-    m->pend.on_side = true;
+    m->pend.on_side = on_side;
+    m->pend.late = late;
     return TENSAIR_OK;
 }
 
@@ -810,21 +826,21 @@ int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, 
         m->next = d;
         return TENSAIR_OK;
     }
-    const int tiles = prep_tiles(c, d.P, n_centers);
-    if (tiles <= TN_PREP_CHAIN_OWN || d.P * (c.negatives + 1) > TN_BESIDE_MAX_OCC) {
+    if (d.P * (c.negatives + 1) > TN_BESIDE_MAX_OCC) {
         m->pend = d;               // kept as an announcement: the consuming call prepares it itself
         return TENSAIR_OK;
     }
+    hipStream_t st = (hipStream_t)stream;
+    const bool on_side = prep_tiles(c, d.P, n_centers) > TN_PREP_CHAIN_OWN;
     // The set being filled was last read by the gradient call before the latest one.  If the second
     // stream has waited for the start of the latest call it is already behind those readers; if not,
     // it is put behind everything enqueued on the caller's stream so far.
-    if (!m->side_follows) {
-        hipStream_t st = (hipStream_t)stream;
+    if (on_side && !m->side_follows) {
         HIP_TRY(hipEventRecord(m->ev_fork, st));
         HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
         m->side_follows = true;
     }
-    const int rc2 = enqueue_prepare(m, d);
+    const int rc2 = enqueue_prepare(m, d, on_side, on_side, on_side ? m->side : st);
     if (rc2 == TENSAIR_EHIP) abandon_side_work(m);
     return rc2;
 }
@@ -877,7 +893,14 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     // is overwritten, after its preparation has finished
     const int u = 1 - m->busy;
     BatchSet &S = m->set[u];
-    if (m->prep_ticket > m->main_ticket) {
+    // its preparation may still be running: the forward pass waits for its keys only, the reductions for the rest
+    const bool split = own.late && m->prep_ticket > m->main_ticket;
+    if (split) {
+        if (m->keys_ticket > m->main_ticket) {
+            HIP_TRY(hipStreamWaitEvent(st, m->ev_keys, 0));
+            m->main_ticket = m->keys_ticket;
+        }
+    } else if (m->prep_ticket > m->main_ticket) {
         HIP_TRY(hipStreamWaitEvent(st, m->ev_prep, 0));
         m->main_ticket = m->prep_ticket;
     }
@@ -933,7 +956,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         }
         for (int t = 0; t < 2; ++t) fa.mask[t] = pick ? m->mask_alt[t] : m->mask[t];
         m->mask_clean[pick] = false;
-        const bool own_early = prepared;             // the own id lists exist when the forward pass starts
+        const bool own_early = prepared && !split;   // the own id lists exist when the forward pass starts
         tn_aux_add_index(aux_fwd, fa, own_early ? 0 : 1, fa.n_src);
         if (!own_early) tn_aux_add_index(aux_red, fa, 0, 1);
         if (!m->mask_clean[1 - pick]) {
@@ -948,14 +971,16 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     const RowIndexDst out = {grad_out->out.row_ids, grad_out->out.n_rows, seg_offsets_out, grad_out->out.capacity};
     PrepPhase x;
     if (prepared) {
-        // this mini-batch's row index goes to the caller's buffers with the forward pass
+        // this mini-batch's row index goes to the caller's buffers with the forward pass -- with the reductions if the
+        // forward pass starts on the keys alone
+        AuxWork &with = split ? aux_red : aux_fwd;
         RowIndexCopy rc2;
         rc2.side[0] = {S.ids_in, S.n_rows, S.off_in, grad_out->in.row_ids, grad_out->in.n_rows, seg_offsets_in};
         rc2.side[1] = {S.ids_out, S.n_rows + 1, S.off_out, grad_out->out.row_ids, grad_out->out.n_rows,
                        seg_offsets_out};
-        tn_aux_add_copy(aux_fwd, rc2, tensair_capacity_out(&c, n_centers));
+        tn_aux_add_copy(with, rc2, tensair_capacity_out(&c, n_centers));
         if (fuse) {   // the own id lists are indexed where they are
-            ApplySrc &o_in = aux_fwd.apply.src[0][0], &o_out = aux_fwd.apply.src[1][0];
+            ApplySrc &o_in = with.apply.src[0][0], &o_out = with.apply.src[1][0];
             o_in.ids = S.ids_in;
             o_in.n_rows = S.n_rows;
             o_in.capacity = tensair_capacity_in(&c, c.max_centers);
@@ -1007,6 +1032,10 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         if (next_rider(m, true, x, st)) tn_launch_prep(x, st);
         HIP_TRY(hipStreamWaitEvent(st, m->ev_fwd, 0));
         if (fwd_ticket > m->main_ticket) m->main_ticket = fwd_ticket;
+    }
+    if (split) {
+        HIP_TRY(hipStreamWaitEvent(st, m->ev_prep, 0));
+        m->main_ticket = m->prep_ticket;
     }
 
     // 5. segmented reductions: duplicates of a row summed in sorted (= occurrence) order
@@ -1086,7 +1115,7 @@ static int enqueue_deferred_prepare(tensair_model *m, hipEvent_t ev, hipStream_t
     }
     HIP_TRY(hipStreamWaitEvent(m->side, ev, 0));
     m->side_follows = true;
-    return enqueue_prepare(m, d);
+    return enqueue_prepare(m, d, true, false, m->side);
 }
 
 // peers are fp32 gradients (`peers`) or bfloat16 messages (`packed`), never both
@@ -1478,6 +1507,7 @@ int tensair_model_destroy(tensair_model *m)
         if (m->ev_fork) (void)hipEventDestroy(m->ev_fork);
         if (m->ev_fwd) (void)hipEventDestroy(m->ev_fwd);
         if (m->ev_prep) (void)hipEventDestroy(m->ev_prep);
+        if (m->ev_keys) (void)hipEventDestroy(m->ev_keys);
         if (m->ev_reduced) (void)hipEventDestroy(m->ev_reduced);
         if (m->side) {
             (void)hipStreamSynchronize(m->side);   // a pending prefetch still writes the workspace

@@ -1296,6 +1296,47 @@ def test_mini_batches_too_large_to_ride_among_others_give_the_same_bits(call):
         assert _same(a, b), i
 
 
+@pytest.mark.parametrize("D,peers", [(64, 2), (300, 0)])
+@pytest.mark.parametrize("V", [300, 50_000, 300_000])
+def test_mini_batches_announced_one_at_a_time_give_the_same_bits(V, D, peers):
+    """Prepared when they are announced: on the caller's stream all but the segments, on the library's stream (from 129
+    tiles on) with the consuming call's forward pass beside the sort, or not at all (5000 centers, 628 tiles); with and
+    without a pause before the call, with peers' gradients in the same step."""
+    T, w, N = 60_000, 8, 15
+    tok = W.zipf_stream(V, 1.1, T, 5)
+    counts = W.unigram_counts(tok, V)
+    Wi, Wo = _random_tables(V, D, D, "f32", seed=11)
+    dtok = torch.from_numpy(tok).cuda()
+    sizes = [60, 1600, 1015, 1016, 1017, 1600, 5000, 3, 1600, 60, 4000]
+    batches = [(4700 * i, n, i % 3) for i, n in enumerate(sizes)]
+    runs = []
+    for ahead in (False, True):
+        m = B.Model(V, D, B.F32, w, N, 5000, peers, 77, counts, tables=(_tables_to_dev(Wi, "f32"), _tables_to_dev(Wo, "f32")))
+        g, loss, got, others = m.grad_buffers(), torch.zeros(1, device="cuda"), [], []
+        for k in range(peers):
+            others.append(m.grad_buffers())
+            m.sgns_grad(dtok, 1000 * k, 700, 9, others[-1])
+        seg_in, seg_out = (torch.zeros(c + 1, dtype=torch.int32, device="cuda") for c in (g.cap_in, g.cap_out))
+        for i, batch in enumerate(batches):
+            if ahead:
+                m.prefetch(dtok, *batch)
+                if i % 3 == 2:
+                    torch.cuda.synchronize()
+            if i % 2:
+                m.sgns_grad(dtok, *batch, g, mean_loss=loss, seg_offsets_in=seg_in, seg_offsets_out=seg_out)
+                got.append(_grad_snapshot(g, loss, seg_in, seg_out))
+            else:
+                m.step(dtok, *batch, others, 0.5, g, loss)
+                if i % 4 == 0:
+                    got.append(_grad_snapshot(g, loss))
+        m.status()
+        got.append(_grad_snapshot(g, loss) + [_tables_to_host(t, "f32") for t in (m.w_in, m.w_out)])
+        runs.append(got)
+        m.close()
+    for i, (a, b) in enumerate(zip(*runs)):
+        assert _same(a, b), i
+
+
 @pytest.mark.parametrize("n", [60, 1500])                 # chained preparation; counted, forward pass on the second stream
 @pytest.mark.parametrize("call", ["step", "grad"])
 def test_a_captured_call_replays_between_eager_ones(n, call):

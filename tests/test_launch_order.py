@@ -103,3 +103,31 @@ def test_riding_goes_on_after_a_mini_batch_too_large_to_ride(trace, kind):
     assert prep[1].count("k_prep_keys") == 2                                   # its own, and the next one's
     for p in prep[2:]:
         assert p == [] or (kind == "grad" and p == ["k_prep_segments"]), p
+
+
+@pytest.mark.parametrize("kind", ["grad", "step"])
+def test_what_is_announced_one_at_a_time_is_prepared_at_once(trace, kind):
+    """60 centers (8 tiles): on the caller's stream, all but the last phase, without an event.  1500 (188 tiles): on the
+    library's stream; the forward pass that consumes it waits for its keys, the reduction for the rest."""
+    calls = []
+    for i, n in enumerate([60, 1500] * 2):
+        calls += [["prefetch", 2000 * i, n, 0], [kind, 2000 * i, n, 0] + ([0] if kind == "step" else [])]
+    got = trace(calls, **SMALL)
+    for ahead, call in zip(got[::2], got[1::2]):
+        did, events = launches(ahead["did"]), [d for d in ahead["did"] if d[0] != "launch"]
+        prep = [k for k, _, _ in did if k != "k_prep_clear"]
+        assert not any(k.startswith("k_prep") for k in names(call["did"]))     # the segments ride
+        forward = next(i for i, d in enumerate(call["did"]) if d[0] == "launch" and "k_forward" in d[1])
+        reduction = next(i for i, d in enumerate(call["did"]) if d[0] == "launch" and "k_segreduce" in d[1])
+        waits = [(i, d[2]) for i, d in enumerate(call["did"]) if d[0] == "wait"]
+        if ahead["call"][2] == 60:
+            assert prep == ["k_prep_keys", "k_prep_pass", "k_prep_pass"] and {s for _, _, s in did} == {"0"}
+            assert not events and not waits
+        else:
+            assert prep == ["k_prep_keys"] + ["k_prep_count", "k_prep_pass"] * 2 + ["k_prep_segments"] * 2
+            assert len({s for _, _, s in did}) == 1 and "0" not in {s for _, _, s in did}
+            order = ["event" if d[0] == "event" else d[1] for d in ahead["did"] if d[0] != "wait"]
+            recorded = [d[1] for d in events if d[0] == "event"]               # fork, keys, all
+            assert len(recorded) == 3 and "k_prep_keys" in order[order.index("event", 1) - 1]
+            assert [w for _, w in waits] == recorded[1:]
+            assert waits[0][0] < forward < waits[1][0] < reduction
