@@ -278,12 +278,15 @@ int tensair_step_packed(tensair_model *m, const int32_t *tokens, int64_t n_token
  * segments, unique row ids -- is prepared ahead of time, next to
  * whatever the caller's stream is doing (in TensAIR's dataflow, Section 3, mini-batches queue
  * up at the Model operator: the coming ones are known while the current one trains).
- * Up to two announcements are kept, in order.  When and where one is prepared is the library's choice: a
- * second one, of up to 512 tiles of 2048 occurrences (about 2^20), phase by phase in the launches of the
- * gradient call that consumes the first; a larger one under that call's table update if tensair_step expects
- * a long one; one that is announced with none before it at once, on `stream` if it has up to 128 tiles, on the
- * library's own stream if it has up to 512; whatever is left is done by the gradient call that consumes it.
- * A third replaces the second.
+ * Up to two announcements are kept, in order.  When and where one is prepared is the library's choice.
+ *   A second one, of up to 256 tiles of 2048 occurrences (512 where tensair_step expects a very long table
+ *   update), phase by phase in the launches of the gradient call that consumes the first; a larger one on the
+ *   library's own stream, under that call's table update if a long one is expected, else beside its forward
+ *   pass if it has up to 2^20 occurrences.
+ *   One that is announced with none before it at once: on `stream` if it has up to 128 tiles, on the library's
+ *   own stream if it has up to 2^20 occurrences.
+ *   Whatever is left is done by the gradient call that consumes it.
+ * A third announcement replaces the second.
  * A gradient call on this model uses the
  * prepared data if its (tokens, n_tokens, center_begin, n_centers, epoch) and the model's
  * worker id are those of the oldest announcement -- its results are then bit-identical to

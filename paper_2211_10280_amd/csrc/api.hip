@@ -194,7 +194,7 @@ struct tensair_model {
     std::vector<Draw> h_draw;  // the same on the host
     double different = 1.0;    // share of a position's negatives that are different words, as expected
     // second stream, forked from and joined to the caller's stream with events: the forward pass beside the sort of a
-    // large mini-batch that was not prepared, the preparation of an announced one under a long table update
+    // large mini-batch that was not prepared, the preparation of an announced one that is too large to ride
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_fwd = nullptr;
     // mini-batch sets: `busy` is the one the most recent gradient call reads; announced mini-batches are
@@ -212,7 +212,8 @@ struct tensair_model {
     // forward pass (clearing) and of the segmented reduction (the id lists), on the caller's stream
     ApplyArgs *fused_apply = nullptr;
     bool fused_index_done = false;
-    bool prepare_under_apply = false;   // tensair_step: the table update is long enough to hide a preparation
+    bool prepare_under_apply = false;   // tensair_step: the table update is long enough to hide a preparation ...
+    bool ride_long_update = false;      // ... many times over
     Prefetched deferred;                // the mini-batch to prepare under that update (enqueued by tensair_step)
     bool captured = false;              // a call on this handle was recorded into a HIP graph (see note_capture)
     u32 apply_serial = 0;               // table updates enqueued so far (stochastic rounding draws from it)
@@ -720,8 +721,9 @@ static int check_batch(const tensair_model *m, const int32_t *tokens, i64 n_toke
 //     pass, reduction, chaining, table update), whose latencies hide it: no launch, event or stream of its own.  An
 //     event between two streams costs the host 15 us and the waiting stream 4 to 7, a launch 3 to 5: steps of 60 000
 //     occurrences took 80 us of host time with the preparation on the second stream and 65 us in all riding.  Up to
-//     TN_PREP_CHAIN_RIDE tiles.
-//   On the second stream under a table update that is long enough (tensair_step decides), for larger ones.
+//     TN_PREP_CHAIN_RIDE tiles, TN_PREP_CHAIN_MAX where a very long table update follows.
+//   On the second stream for larger ones: under a table update that is long enough (tensair_step decides), else beside
+//     the forward pass and the reductions, up to TN_BESIDE_MAX_OCC occurrences.
 //   At once, when it is announced with nothing before it: there is no call whose launches it could ride in, and the
 //     GPU may have nothing else to do until it is consumed.  On the caller's stream up to TN_PREP_CHAIN_OWN tiles, all
 //     but the segments, which ride with the consuming call's forward pass; on the second stream up to TN_BESIDE_MAX_OCC
@@ -734,9 +736,9 @@ static int check_batch(const tensair_model *m, const int32_t *tokens, i64 n_toke
 #ifndef TN_BESIDE_MAX_OCC
 #define TN_BESIDE_MAX_OCC (1 << 20)
 #endif
-static bool rides(const tensair_model *m, const Prefetched &d)
+static bool rides(const tensair_model *m, const Prefetched &d, bool long_update)
 {
-    return prep_tiles(m->cfg, d.P, d.n_centers) <= TN_PREP_CHAIN_RIDE;
+    return prep_tiles(m->cfg, d.P, d.n_centers) <= (long_update ? TN_PREP_CHAIN_MAX : TN_PREP_CHAIN_RIDE);
 }
 
 // The next phase of the announced mini-batch m->pend, if it is one that rides and is not done: the caller attaches it
@@ -872,7 +874,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     // Streams.  The sort and the segment scan only need the keys, the forward pass the keys and the
     // tables, the reductions both.  Everything runs on the caller's stream, with these exceptions: a large
     // mini-batch that nobody prepared has its forward pass on the library's second stream, next to its sort,
-    // and one that a long table update of the call before could hide was prepared there.  What is small rides
+    // and an announced one that is too large to ride is prepared there.  What is small rides
     // at the front of other launches: the phases that are still missing of this mini-batch's preparation and
     // those of the announced one after it, the prepared row index to the caller's buffers, and inside
     // tensair_step the index of the coming table update.  An event between streams costs the host 15 us and
@@ -911,13 +913,19 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     const bool chained = phase > 0 ? own.chained : prep_tiles(c, P, n_centers) <= TN_PREP_CHAIN_OWN;
     const int phases = prep_phases(s, chained), sorted = prep_sort_end(s, chained);
     const bool prepared = phase == phases;
-    // the one after it: under a long table update that follows (tensair_step decides), riding, or left to its own call
+    // the one after it: riding, under a long table update that follows (tensair_step decides), beside this call's
+    // forward pass, or left to its own call
+    bool beside = false;
     if (following.valid) {
-        if (fuse && m->prepare_under_apply && !rides(m, following)) {
+        if (rides(m, following, fuse && m->ride_long_update)) {
+            m->pend = following;
+            m->pend.chained = true;
+        } else if (fuse && m->prepare_under_apply) {
             m->deferred = following;
+        } else if (following.P * Np1 <= TN_BESIDE_MAX_OCC) {
+            beside = true;
         } else {
             m->pend = following;
-            m->pend.chained = rides(m, following);
         }
     }
     mark(m, PF_BEGIN_GRAD, st);
@@ -997,11 +1005,12 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     // 2. forward on the unsorted keys (the sort never writes their buffer): g per occurrence, per-center share of the
     //    W_in gradient, loss terms
     const bool aside = overlap && !chained && !prepared;
-    if (aside) {
+    if (aside || beside) {
         HIP_TRY(hipEventRecord(m->ev_fork, st));
         HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
         m->side_follows = true;
-    } else if (overlap) {
+    }
+    if (overlap && !aside) {
         if (phase < phases) {
             make_prep_phase(m, S, w, chained, phase, in, out, nullptr, x);
             before_prep_phase(m, S, x.kind, st);
@@ -1017,6 +1026,11 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         HIP_TRY(hipEventRecord(m->ev_fwd, m->side));
         fwd_ticket = ++m->side_ticket;
     }
+    if (split) {    // the rest of this mini-batch's preparation
+        HIP_TRY(hipStreamWaitEvent(st, m->ev_prep, 0));
+        m->main_ticket = m->prep_ticket;
+    }
+    if (beside && (rc = enqueue_prepare(m, following, true, true, m->side))) return rc;   // behind a forward pass aside
     // 3./4. what is missing of sort and segments, row index straight into the caller's buffers
     if (phase < sorted) {
         enqueue_prep(m, S, w, chained, phase, sorted, in, out, nullptr, st);
@@ -1032,10 +1046,6 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         if (next_rider(m, true, x, st)) tn_launch_prep(x, st);
         HIP_TRY(hipStreamWaitEvent(st, m->ev_fwd, 0));
         if (fwd_ticket > m->main_ticket) m->main_ticket = fwd_ticket;
-    }
-    if (split) {
-        HIP_TRY(hipStreamWaitEvent(st, m->ev_prep, 0));
-        m->main_ticket = m->prep_ticket;
     }
 
     // 5. segmented reductions: duplicates of a row summed in sorted (= occurrence) order
@@ -1315,6 +1325,7 @@ static int step_impl(tensair_model *m, const int32_t *tokens, int64_t n_tokens, 
         const double t_apply = src_bytes * rows * c.dim / 5e12;
         const double t_prepare = occ * 0.2e-9 + 60e-6;
         m->prepare_under_apply = t_apply >= 2.0 * t_prepare;
+        m->ride_long_update = t_apply >= TN_PREP_RIDE_LONG_UPDATE * t_prepare;
     }
     rc = sgns_grad_impl(m, tokens, n_tokens, center_begin, n_centers, epoch, own_out, mean_loss, nullptr,
                         nullptr, nullptr, stream);

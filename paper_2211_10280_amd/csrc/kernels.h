@@ -108,12 +108,17 @@ struct PrepPhase {
 };
 #define TN_PREP_GROUP 64       // tiles per group of a counted pass
 // Most tiles of a chained preparation: as launches of its own (longer ones are faster counted), and riding in other
-// launches, where its latency is hidden.
+// launches, where its latency is hidden.  Beyond 256 tiles the tickets alone hold those launches up, and a counted
+// preparation on a stream of its own beside them is faster (step riding / beside: 222 tiles 131 / 146 us at 300 000
+// words, D = 64, 315 / 318 at a million, D = 300; 260 tiles 155 / 146 and 369 / 366; 440 tiles 230 / 208 and 606 / 580).
+// Under a table update that takes at least TN_PREP_RIDE_LONG_UPDATE times as long as the preparation it is the other way
+// round up to 512 tiles (2 million words in bfloat16, D = 512, 440 tiles: 15 peers 3 665 / 3 700 us, 11 peers 2 946 / 2 953,
+// 300 tiles 2 789 / 2 826 and 2 226 / 2 251; at a ratio of 11 to 14: 15 peers, D = 256, 1 680 / 1 664, D = 300 in fp32
+// 2 304 / 2 287, 7 peers, D = 512, 2 191 / 2 190).
 #define TN_PREP_CHAIN_OWN 128
-#ifndef TN_PREP_CHAIN_RIDE
-#define TN_PREP_CHAIN_RIDE 512
-#endif
-#define TN_PREP_CHAIN_MAX (TN_PREP_CHAIN_OWN > TN_PREP_CHAIN_RIDE ? TN_PREP_CHAIN_OWN : TN_PREP_CHAIN_RIDE)
+#define TN_PREP_CHAIN_RIDE 256
+#define TN_PREP_CHAIN_MAX 512
+#define TN_PREP_RIDE_LONG_UPDATE 16.0
 static inline int tn_prep_tiles(i64 n) { return (int)((n + TN_RADIX_TILE - 1) / TN_RADIX_TILE); }   // n: up to 2^31 - 1
 static inline int tn_prep_seg_tiles(i64 n) { return (int)((n + TN_SCAN_TILE - 1) / TN_SCAN_TILE); }
 void tn_launch_prep(const PrepPhase &x, hipStream_t st);   // the phase as a launch of its own
@@ -244,7 +249,7 @@ void tn_launch_apply_clear(const ApplyArgs &a, hipStream_t st);
 void tn_launch_apply_index(const ApplyArgs &a, int k_begin, int k_end, hipStream_t st);
 // whether a phase can ride with the update: its workgroups come on top of those for the rows (of 16 vocabulary rows
 // each, at least), and one launch has to hold them all
-static inline bool tn_apply_carries(int D, i64 V) { return D <= 512 && (V + 15) / 16 + TN_PREP_CHAIN_RIDE <= TN_MAX_BLOCKS; }
+static inline bool tn_apply_carries(int D, i64 V) { return D <= 512 && (V + 15) / 16 + TN_PREP_CHAIN_MAX <= TN_MAX_BLOCKS; }
 void tn_launch_apply_update(const ApplyArgs &a, const PrepPhase *rider, hipStream_t st);   // rider may be NULL
 void tn_launch_apply_update_riding(const ApplyArgs &a, const PrepPhase &rider, hipStream_t st);
 

@@ -1223,8 +1223,8 @@ def test_prefetch_gives_the_same_bits():
 def test_phases_that_ride_give_the_same_bits(V, D, call):
     """Mini-batches of all sizes announced two deep, so that their preparation rides phase by phase in the launches of
     the call before -- none, some or all of its phases done when they are consumed -- against calls without
-    announcements; announcements that are dropped half prepared; a mini-batch too large for chained passes (2 w (N+1) =
-    256 occurrences per center, 1200 centers) before a small one."""
+    announcements; announcements that are dropped half prepared; a mini-batch of 151 tiles, too many for chained
+    passes in launches of their own (2 w (N+1) = 256 occurrences per center, 1200 centers), before a small one."""
     T, w, N = 30_000, 8, 15
     tok = W.zipf_stream(V, 1.1, T, 5)
     counts = W.unigram_counts(tok, V)
@@ -1261,18 +1261,19 @@ def test_phases_that_ride_give_the_same_bits(V, D, call):
         assert _same(a, b), i
 
 
+@pytest.mark.parametrize("sizes", [(5000, 1600, 1600, 1600, 5200, 5000, 60, 1600, 1000, 5000),
+                                   (2400, 2400, 2400, 60, 4000, 1600, 2400, 5000, 2400, 2400, 2040, 2041, 2400)])
 @pytest.mark.parametrize("call", ["step", "grad"])
-def test_mini_batches_too_large_to_ride_among_others_give_the_same_bits(call):
-    """Mini-batches of 628 and more tiles (prepared by their own calls, forward pass on the second stream) among ones
-    of 201, 126 and 8 tiles (whose phases ride, the first of them begun beside a large one), announced two deep, against
-    the same calls without announcements."""
+def test_mini_batches_too_large_to_ride_among_others_give_the_same_bits(call, sizes):
+    """Mini-batches of 628 and more tiles (prepared by their own calls, forward pass on the second stream) and of 257 to
+    512 (prepared on the second stream beside the call before) among smaller ones (whose phases ride, also beside a
+    large one), announced two deep, against the same calls without announcements."""
     V, D, T, w, N = 50_000, 64, 60_000, 8, 15
     tok = W.zipf_stream(V, 1.1, T, 5)
     counts = W.unigram_counts(tok, V)
     Wi, Wo = _random_tables(V, D, D, "f32", seed=11)
     dtok = torch.from_numpy(tok).cuda()
-    sizes = [5000, 1600, 1600, 1600, 5200, 5000, 60, 1600, 1000, 5000]
-    batches = [(4700 * i, n, i % 3) for i, n in enumerate(sizes)]
+    batches = [(4400 * i, n, i % 3) for i, n in enumerate(sizes)]
     runs = []
     for ahead in (False, True):
         m = B.Model(V, D, B.F32, w, N, 5200, 0, 77, counts, tables=(_tables_to_dev(Wi, "f32"), _tables_to_dev(Wo, "f32")))

@@ -106,6 +106,27 @@ def test_riding_goes_on_after_a_mini_batch_too_large_to_ride(trace, kind):
 
 
 @pytest.mark.parametrize("kind", ["grad", "step"])
+def test_mini_batches_of_medium_size_are_prepared_beside_the_call_before(trace, kind):
+    """302 tiles, announced two deep, no long update to follow: on the library's stream, which starts with the forward
+    pass of the call before; the call that consumes one waits for its keys, and before the reduction for the rest."""
+    batch = lambda i: [2400 * i, 2400, 0]                                      # noqa: E731
+    calls = [["prefetch"] + batch(0)]
+    for i in range(5):
+        calls += [["prefetch"] + batch(i + 1), [kind] + batch(i) + ([0] if kind == "step" else [])]
+    got = [c["did"] for c in trace(calls, **SMALL) if c["call"][0] == kind]
+    for i, did in enumerate(got[:-1]):
+        side = [k for k, _, s in launches(did) if s != "0"]
+        assert side == ["k_prep_clear"] * (i < 1) + ["k_prep_keys"] + ["k_prep_count", "k_prep_pass"] * 2 + ["k_prep_segments"] * 2
+        assert not any(k.startswith("k_prep") for k, _, s in launches(did) if s == "0")
+        at = {k: j for j, d in enumerate(did) if d[0] == "launch" and d[4] == "0" for k in ("forward", "segreduce") if k in d[1]}
+        keys = next(j for j, d in enumerate(did) if d[0] == "launch" and "k_prep_keys" in d[1])
+        fork = next(j for j, d in enumerate(did) if d[0] == "wait" and d[1] != "0")
+        assert fork < at["forward"] and fork < keys
+        mine = [j for j, d in enumerate(did) if d[0] == "wait" and d[1] == "0"]
+        assert mine[0] < at["forward"] < mine[1] < keys and mine[1] < at["segreduce"]
+
+
+@pytest.mark.parametrize("kind", ["grad", "step"])
 def test_what_is_announced_one_at_a_time_is_prepared_at_once(trace, kind):
     """60 centers (8 tiles): on the caller's stream, all but the last phase, without an event.  1500 (188 tiles): on the
     library's stream; the forward pass that consumes it waits for its keys, the reduction for the rest."""
