@@ -85,8 +85,8 @@ PrepLayout prep_layout(const Sizes &s, int O, int n, bool chained)
     l.seg_in = PREP_TICKETS;
     l.seg_out = l.seg_in + 2 * (2 * (size_t)tn_prep_seg_tiles(n));
     l.pass0 = l.seg_out + 2 * (size_t)tn_prep_seg_tiles(O);
-    const size_t gi = l.chained ? 0 : (ti + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
-    const size_t go = l.chained ? 0 : (to + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
+    const size_t gi = l.chained ? 0 : (size_t)tn_prep_groups((int)ti) + 1;      // and a row for the sum of all
+    const size_t go = l.chained ? 0 : (size_t)tn_prep_groups((int)to) + 1;
     l.groups = (gi + go) * s.nd;
     l.group_out = gi * s.nd;
     l.tile0 = l.pass0 + s.passes * l.groups;
@@ -636,6 +636,7 @@ static void make_prep_phase(tensair_model *m, BatchSet &S, const BatchWork &w, b
         p.ticket = S.pub + i;
         p.shift = i * s.bits;
         p.bits = s.bits;
+        p.scanned = !l.chained && std::max(tn_prep_groups(p.p[0].tiles), tn_prep_groups(p.p[1].tiles)) > TN_PREP_GROUPS_OWN;
         p.first = i == 0;
         S.kb = kout;
         S.cur = (i & 1) ^ 1;

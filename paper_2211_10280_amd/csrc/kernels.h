@@ -65,13 +65,14 @@ struct PrepPassList {
     const u32 *kin, *vin;  // vin: not read by the first pass, whose values are the entries' places
     u32 *kout, *vout;
     u32 *state;            // [tiles][2^bits] published words (chained), digit counts (counted)
-    u32 *hist;             // [2^bits] keys per digit (chained); [groups][2^bits] per group of tiles (counted)
+    u32 *hist;             // [2^bits] keys per digit (chained); [groups + 1][2^bits] per group of tiles (counted)
     int n, tiles;
 };
 struct PrepPass {
     PrepPassList p[2];     // out-side, in-side
     u32 *ticket;
     int shift, bits, first;
+    int scanned;           // counted: hist holds the keys of the lower groups, in the row after the last all keys
 };
 struct PrepSegmentsList {
     const u32 *keys;       // sorted keys
@@ -107,6 +108,12 @@ struct PrepPhase {
     };
 };
 #define TN_PREP_GROUP 64       // tiles per group of a counted pass
+// Most groups whose counts every tile of a counted pass adds up by itself.  With more of them that would be the pass
+// (its reads grow with the square of the tiles), so a launch before it sums them once (262 000 words, each tile by
+// itself / summed once: 4.2 M occurrences, 32 groups, gradient 0.769 / 0.774 ms; 6.3 M 1.16 / 1.13; 34 M 8.5 / 7.1;
+// 134 M 48 / 21.6; at 2.1 M, 16 groups, no difference).
+#define TN_PREP_GROUPS_OWN 40
+static inline int tn_prep_groups(int tiles) { return (tiles + TN_PREP_GROUP - 1) / TN_PREP_GROUP; }
 // Most tiles of a chained preparation: as launches of its own (longer ones are faster counted), and riding in other
 // launches, where its latency is hidden.  Beyond 256 tiles the tickets alone hold those launches up, and a counted
 // preparation on a stream of its own beside them is faster (step riding / beside: 222 tiles 131 / 146 us at 300 000

@@ -23,7 +23,8 @@
 //     bytes, and launches fewer are what counts: count, scan and scatter as launches of their own took 19 us per
 //     pass of 61 000 keys, this takes 14 and rides in another launch.
 //   counted (many tiles): a launch before the pass counts the digits of every tile and sums them over groups of
-//     tiles; a tile adds up the groups below its own and the tiles of its group below itself.  Tickets cost 55 ns
+//     tiles; a tile adds up the groups below its own and the tiles of its group below itself (where the groups are
+//     many, one more launch has added them up).  Tickets cost 55 ns
 //     each, one after the other (a single word that all XCDs add to): 110 us at 2 000 tiles.
 #pragma once
 #include "dev_common.h"
@@ -216,11 +217,16 @@ __device__ __forceinline__ void prep_pass(const PrepPass &a, int block, u32 *lds
                 total[j] = P.hist[d0 + j];
             } else {
                 const int group = tile / TN_PREP_GROUP, groups = (P.tiles + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
+                if (a.scanned) {
+                    total[j] = P.hist[(size_t)groups * nd + d0 + j];
+                    below[j] = P.hist[(size_t)group * nd + d0 + j];
+                } else {
 #pragma unroll 8
-                for (int t = 0; t < groups; ++t) {
-                    const u32 v = P.hist[(size_t)t * nd + d0 + j];
-                    total[j] += v;
-                    below[j] += t < group ? v : 0u;
+                    for (int t = 0; t < groups; ++t) {
+                        const u32 v = P.hist[(size_t)t * nd + d0 + j];
+                        total[j] += v;
+                        below[j] += t < group ? v : 0u;
+                    }
                 }
 #pragma unroll 8
                 for (int t = group * TN_PREP_GROUP; t < tile; ++t) below[j] += P.state[(size_t)t * nd + d0 + j];
@@ -355,6 +361,26 @@ __device__ __forceinline__ void prep_count(const PrepPass &a, int block, u32 *ld
         P.state[(size_t)tile * nd + d] = c;
         if (c) atomicAdd(&P.hist[(size_t)(tile / TN_PREP_GROUP) * nd + d], c);
     }
+}
+
+// The groups' counts of digit `d` of a list become those of the groups below, and a row more that of all: one thread per
+// digit, the groups' rows one after the other (coalesced over the digits; independent loads, so several are in flight).
+__device__ __forceinline__ void prep_scan_groups(const PrepPassList &P, int nd, int d)
+{
+    const int groups = (P.tiles + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
+    u32 *row = P.hist + d;
+    u32 run = 0;
+    for (int t0 = 0; t0 < groups; t0 += 16) {
+        u32 v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = t0 + i < groups ? row[(size_t)(t0 + i) * nd] : 0u;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            if (t0 + i < groups) row[(size_t)(t0 + i) * nd] = run;
+            run += v[i];
+        }
+    }
+    row[(size_t)groups * nd] = run;
 }
 
 // ---------------------------------------------------------------- segments

@@ -22,6 +22,13 @@ __global__ void __launch_bounds__(BLOCK) k_prep_count(PrepPhase x)
     prep_count<BLOCK>(x.pass, (int)blockIdx.x, lds);
 }
 
+// grid: (digits / WAVE, 2 lists)
+__global__ void __launch_bounds__(WAVE) k_prep_scan(PrepPhase x)
+{
+    const int nd = 1 << x.pass.bits, d = (int)(blockIdx.x * WAVE + threadIdx.x);
+    if (d < nd) prep_scan_groups(x.pass.p[blockIdx.y], nd, d);
+}
+
 template <bool CHAINED, bool HEADS>
 __global__ void __launch_bounds__(BLOCK) k_prep_segments(PrepPhase x)
 {
@@ -36,7 +43,10 @@ void tn_launch_prep(const PrepPhase &x, hipStream_t st)
     case PREP_KEYS: hipLaunchKernelGGL(k_prep_keys, grid, blk, 0, st, x); break;
     case PREP_PASS: hipLaunchKernelGGL(k_prep_pass<true>, grid, blk, 0, st, x); break;
     case PREP_SEGMENTS: hipLaunchKernelGGL((k_prep_segments<true, false>), grid, blk, 0, st, x); break;
-    case PREP_COUNT: hipLaunchKernelGGL(k_prep_count, grid, blk, 0, st, x); break;
+    case PREP_COUNT:
+        hipLaunchKernelGGL(k_prep_count, grid, blk, 0, st, x);
+        if (x.pass.scanned) hipLaunchKernelGGL(k_prep_scan, dim3(((1 << x.pass.bits) + WAVE - 1) / WAVE, 2), dim3(WAVE), 0, st, x);
+        break;
     case PREP_PASS_COUNTED: hipLaunchKernelGGL(k_prep_pass<false>, grid, blk, 0, st, x); break;
     case PREP_HEADS: hipLaunchKernelGGL((k_prep_segments<false, true>), grid, blk, 0, st, x); break;
     default: hipLaunchKernelGGL((k_prep_segments<false, false>), grid, blk, 0, st, x); break;

@@ -151,6 +151,15 @@ def test_sgns_grad_parity_at_the_edges_of_the_preparation(case):
     _grad_parity(case)
 
 
+# numbers of groups of 64 tiles (40) from which their counts are summed in a launch of their own, in one to three passes
+GROUP_EDGE_CASES = [(V, 4, 4, 30_000, 1.1, 8, 15, Bc, 700, "f32") for V, Bc in ((500, 20481), (70_000, 20480), (70_000, 20481), (300_000, 20481))]
+
+
+@pytest.mark.parametrize("case", GROUP_EDGE_CASES, ids=lambda c: f"V{c[0]}_B{c[7]}")
+def test_sgns_grad_parity_at_the_edge_of_the_groups_of_tiles(case):
+    _grad_parity(case)
+
+
 # positions whose tasks repeat words (the forward pass then works on the different ones): every row shape it has, both
 # sizes of its table and their edges (256 and 512 tasks per position, one more goes the plain way), clipped windows
 REPEAT_CASES = [

@@ -152,3 +152,13 @@ def test_what_is_announced_one_at_a_time_is_prepared_at_once(trace, kind):
             assert len(recorded) == 3 and "k_prep_keys" in order[order.index("event", 1) - 1]
             assert [w for _, w in waits] == recorded[1:]
             assert waits[0][0] < forward < waits[1][0] < reduction
+
+
+def test_long_key_lists_are_not_counted_by_every_tile(trace):
+    """From 41 groups of tiles on, the groups' counts are summed once per pass, in a launch of their own: work per
+    occurrence does not grow with the mini-batch."""
+    model = dict(SMALL, max_centers=80_000)
+    got = trace([["grad", 100, n, 0] for n in (20_480, 20_481, 80_000)], **model)
+    prep = [[k for k in names(c["did"]) if k in ("k_prep_count", "k_prep_scan", "k_prep_pass")] for c in got]
+    assert prep[0] == ["k_prep_count", "k_prep_pass"] * 2
+    assert prep[1] == prep[2] == ["k_prep_count", "k_prep_scan", "k_prep_pass"] * 2
