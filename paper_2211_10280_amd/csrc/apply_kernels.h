@@ -36,7 +36,6 @@ struct PhaseRider {
 #define APPLY_G 4   // vocabulary rows per wave (measured: 16 -> 4 rows gains 4 %)
 #endif
 #define APPLY_SMALL_V 16384          // see launch_apply_t
-#define APPLY_SPARSE_MIN_V 786432
 #ifndef APPLY_G_SPARSE
 #define APPLY_G_SPARSE 16   // the same where few of the vocabulary's rows are touched
 #endif
@@ -406,22 +405,24 @@ static void launch_apply_sub_r(const ApplyArgs &a, const Rider &rider, hipStream
 }
 
 // few of the vocabulary's rows touched, going by the sources' capacities (see launch_apply_t)
-static bool sparse_union(const ApplyArgs &a)
+static bool sparse_union(const ApplyArgs &a, i64 min_v)
 {
     i64 cap = 0;
     for (int k = 0; k < a.n_src; ++k)
         if (a.src[1][k].ids != nullptr) cap += a.src[1][k].capacity;
-    return a.V >= APPLY_SPARSE_MIN_V && 4 * cap < 3 * a.V;
+    return a.V >= min_v && 4 * cap < 3 * a.V;
 }
 
 // 4 rows per group of lanes and wave, or 32 rows per wave where few rows are touched (8 M words, D = 128, bf16:
-// update 0.67 -> 0.42 ms; 16 M words, D = 64: 0.58 -> 0.40 ms); one row per group where the vocabulary is too small to
+// update 0.67 -> 0.42 ms; 16 M words, D = 64: 0.58 -> 0.40 ms), from 655 360 words on (whole call with 32 rows per wave /
+// 4 per group, means over 64 to 2 048 centers and 0 to 3 peers: D = 128 at 550 000 words 1 / 0.90, 650 000 0.98, 780 000
+// 1.08; D = 64 at 600 000 0.94, 800 000 1.03; up to 1.9 times as long below 200 000 words); one row per group where the vocabulary is too small to
 // give every wave slot of the chip work with four (1 000 words, D = 32: 32 waves of 64 rows and 12 us became 128 waves;
 // step 34.6 -> 28.8 us; no difference from 16 384 words at D = 128 on)
 template <typename T, int SUB, bool STREAM, typename Rider>
 static void launch_apply_sub(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
-    if (SUB > 8 && sparse_union(a)) launch_apply_sub_r<T, SUB, 16, STREAM>(a, rider, st);
+    if (SUB > 8 && sparse_union(a, 655360)) launch_apply_sub_r<T, SUB, 16, STREAM>(a, rider, st);
     else if (!STREAM && a.V < APPLY_SMALL_V * (WAVE / SUB)) launch_apply_sub_r<T, SUB, 1, STREAM>(a, rider, st);
     else launch_apply_sub_r<T, SUB, APPLY_SUB_ROWS, STREAM>(a, rider, st);
 }
@@ -451,13 +452,19 @@ static void launch_apply_g(const ApplyArgs &a, const Rider &rider, hipStream_t s
 // with 16, 64 rows no better).  How many rows the union has is only known on the device; the sources' capacities
 // bound it, and below three quarters of a row of capacity per vocabulary row the sparse shape is taken.  In a small
 // vocabulary it never is: there the few waves that hold the frequent words, all of whose rows are touched, work on
-// long after the others (whole call at 100 000 words, 120 centers 37 us with 16 rows, 21 with 4; 300 000 words, 64 centers
-// 38 and 31; 2 million, 512 centers 64 and 152).  Below 16 384 words a grid of 4 rows per wave leaves wave slots empty:
+// long after the others, the longer the more a row takes -- against a grid four times as large, which grows with the
+// vocabulary (64 centers, no peers, 16 / 4 rows: D = 132 in fp32 23 / 20 us at 131 000 words, 22 / 26 at 262 000, 23 / 44 at
+// 600 000; D = 300 27 / 20, 28 / 27, 37 / 47).  Whole call with 4 rows as a share of 16, mean over 64 to 2 048 centers
+// and 0 to 3 peers: fp32 D = 256 0.91 at 262 000 words, 1.07 at 330 000; D = 300 0.86 at 330 000, 0.92 at 420 000, 1.13 at
+// 600 000; D = 512 0.89 at 420 000; D = 768 0.85 at 400 000, 1.03 at 600 000; bfloat16, whose rows take half the time,
+// D = 200 0.96 at 197 000, 1.17 at 300 000; D = 400 0.99 at 300 000; D = 1024 1.03 at 400 000; bfloat16 messages, D = 64,
+// 0.96 at 197 000; 2 million words, 512 centers, D = 256 98 us against 64.  Below 16 384 words a grid of 4 rows per wave leaves wave slots empty:
 // one row per wave (1 000 words, D = 300: step 60.8 -> 58.4 us).
 template <typename T, bool STREAM, bool PACKED, typename Rider>
 static void launch_apply_t(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
-    if (sparse_union(a)) launch_apply_g<T, APPLY_G_SPARSE, STREAM, PACKED>(a, rider, st);
+    const i64 unit = sizeof(T) == 2 || PACKED ? 73728 : 131072;
+    if (sparse_union(a, unit * ((a.D / 4 + WAVE - 1) / WAVE + 1))) launch_apply_g<T, APPLY_G_SPARSE, STREAM, PACKED>(a, rider, st);
     else if (!STREAM && a.V < APPLY_SMALL_V) launch_apply_g<T, 1, STREAM, PACKED>(a, rider, st);
     else launch_apply_g<T, APPLY_G, STREAM, PACKED>(a, rider, st);
 }

@@ -359,6 +359,15 @@ def test_dasgd_apply_parity_at_the_borders_of_its_shapes(dtype, V, D, stride, K,
     _apply_parity(dtype, V, D, stride, K, True, thin=thin)
 
 
+@pytest.mark.parametrize("dtype,V,D,stride,K", [
+    # few rows touched: on both sides of the vocabulary from which more of its rows are taken per wave
+    ("f32", 262_143, 132, 132, 2), ("f32", 262_144, 132, 132, 2), ("f32", 393_215, 300, 300, 1), ("f32", 393_216, 300, 304, 1),
+    ("bf16", 147_455, 132, 136, 2), ("bf16", 147_456, 132, 136, 2), ("bf16", 294_911, 516, 516, 1), ("bf16", 294_912, 516, 516, 1),
+    ("f32", 655_359, 100, 100, 2), ("f32", 655_360, 100, 100, 2), ("bf16", 655_360, 36, 36, 2), ("f32", 655_360, 32, 32, 2)])
+def test_dasgd_apply_parity_at_the_borders_of_its_sparse_shape(dtype, V, D, stride, K):
+    _apply_parity(dtype, V, D, stride, K, True, thin=400)
+
+
 def _random_apply_shapes(n, seed):
     """Seeded shapes off the beaten track: every lane grouping of the table update (D <= 32, <= 64, <= 128, one to
     four chunk passes of a whole wave), dimensions just below and above the borders between them, padded and

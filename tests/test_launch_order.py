@@ -162,3 +162,17 @@ def test_long_key_lists_are_not_counted_by_every_tile(trace):
     prep = [[k for k in names(c["did"]) if k in ("k_prep_count", "k_prep_scan", "k_prep_pass")] for c in got]
     assert prep[0] == ["k_prep_count", "k_prep_pass"] * 2
     assert prep[1] == prep[2] == ["k_prep_count", "k_prep_scan", "k_prep_pass"] * 2
+
+
+@pytest.mark.parametrize("V,D,dtype,rows", [                  # vocabulary rows per workgroup of four waves
+    (262_143, 132, B.F32, 16), (262_144, 132, B.F32, 64), (393_215, 300, B.F32, 16), (393_216, 300, B.F32, 64),
+    (655_359, 1024, B.F32, 16), (655_360, 1024, B.F32, 64), (147_455, 132, B.BF16, 16), (147_456, 132, B.BF16, 64),
+    (221_183, 300, B.BF16, 16), (221_184, 300, B.BF16, 64), (655_359, 100, B.F32, 32), (655_360, 100, B.F32, 128),
+    (655_360, 64, B.F32, 128), (4_000_000, 32, B.F32, 128)])
+def test_rows_per_wave_where_few_are_touched(trace, V, D, dtype, rows):
+    """A quarter of a row of capacity per vocabulary row: the sparse shape of the update from the vocabulary on that its
+    own and the dense shape were measured to take the same time at."""
+    model = dict(SMALL, vocab=V, dim=D, dtype=dtype, max_centers=64, max_peers=1)
+    got = launches(trace([["apply", 60, V // 8, 1]], **model)[0]["did"])[-1]
+    assert got[0] == ("k_apply" if D > 128 else "k_apply_sub")
+    assert got[1] == ((V + 63) // 64 * 64 + rows - 1) // rows
