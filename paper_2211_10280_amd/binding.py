@@ -148,11 +148,14 @@ def _ptr(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
+# the current stream's handle without a Stream object (which takes 3 us a call), where torch has it: the name is private
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    if stream is not None:
-        return C.c_void_p(stream.cuda_stream)
-    # the current stream's handle without a Stream object (3 us a call)
-    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if stream is None and _raw_stream is not None:
+        return C.c_void_p(_raw_stream(torch.cuda.current_device()))
+    return C.c_void_p((stream if stream is not None else torch.cuda.current_stream()).cuda_stream)
 
 
 # ---------------------------------------------------------------- device buffers

@@ -111,6 +111,18 @@ def test_host_side_argument_checks_of_the_further_entry_points():
     assert L.tensair_model_destroy(None) == B.OK             # destroying nothing is allowed
 
 
+def test_the_current_stream_is_found_with_and_without_the_private_name(monkeypatch):
+    class Stream:
+        cuda_stream = 4096
+
+    monkeypatch.setattr(B.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(B, "_raw_stream", lambda device: 64 * device)
+    assert B._stream().value == 192 and B._stream(Stream).value == 4096
+    monkeypatch.setattr(B, "_raw_stream", None)
+    assert B._stream().value == 4096 and B._stream(Stream).value == 4096
+
+
 def test_bench_refuses_more_than_one_gpu():
     """This build is the one-GPU worker step: bench.py says so and exits instead of pretending to scale."""
     import subprocess
