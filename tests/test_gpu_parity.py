@@ -1279,6 +1279,79 @@ def test_phases_that_ride_give_the_same_bits(V, D, call):
         assert _same(a, b), i
 
 
+@pytest.mark.parametrize("n", [60, 1600, 2400])            # ridden along (two sizes), and beside the call before
+def test_announcements_under_two_worker_ids_give_the_same_bits(n):
+    """A mini-batch is drawn under the worker id it was announced with, whatever the id is while its preparation rides:
+    two announcements under different ids, the model rebound between them and before either call."""
+    V, D, T, w, N = 50_000, 64, 30_000, 8, 15
+    tok = W.zipf_stream(V, 1.1, T, 5)
+    counts = W.unigram_counts(tok, V)
+    Wi, Wo = _random_tables(V, D, D, "f32", seed=11)
+    dtok = torch.from_numpy(tok).cuda()
+    m = B.Model(V, D, B.F32, w, N, n, 0, 77, counts, worker_id=2, tables=(_tables_to_dev(Wi, "f32"), _tables_to_dev(Wo, "f32")))
+    g, loss = m.grad_buffers(), torch.zeros(1, device="cuda")
+    batches = [(2, 100, 0), (3, 5000, 0), (4, 5000, 0)]              # worker id, first center, epoch
+
+    def call(b):
+        m.rebind(m.w_in, m.w_out, b[0])
+        m.sgns_grad(dtok, b[1], n, b[2], g, mean_loss=loss)
+        return _grad_snapshot(g, loss)
+
+    def announce(b):
+        m.rebind(m.w_in, m.w_out, b[0])
+        m.prefetch(dtok, b[1], n, b[2])
+
+    plain = [call(b) for b in batches]
+    assert not _same(plain[1], plain[2])                             # the id makes the difference
+    for other in batches[1:]:
+        announce(batches[0])
+        announce(other)
+        assert _same(call(batches[0]), plain[0])
+        assert _same(call(other), plain[batches.index(other)])
+    m.status()
+    m.close()
+
+
+def test_sgns_grad_parity_with_four_passes_of_the_sort():
+    """More than 2^27 words: four passes of seven bits, which end in other buffers than three -- chained, counted, ridden
+    along and prepared when announced.  (The library's own alias table: that it is the oracle's is tested elsewhere.)"""
+    V, D, T, w, N, seed = (1 << 27) + 1, 4, 30_000, 8, 15, 0xC0FFEE
+    if torch.cuda.mem_get_info()[0] < 16 << 30:
+        pytest.skip("needs 16 GB of device memory")
+    _say("four passes", V)
+    rng = np.random.default_rng(4)
+    tok = rng.integers(0, V, T).astype(np.int32)
+    tok[::3] = rng.choice(np.array([0, 1, 127, 128, 1 << 21, (1 << 27) - 1, 1 << 27], np.int32), tok[::3].size)
+    Wi, Wo = _random_tables(V, D, D, "bf16", seed=3)
+    m = B.Model(V, D, B.BF16, w, N, 1600, 0, seed, np.ones(V, np.uint64), worker_id=3,
+                tables=(_tables_to_dev(Wi, "bf16"), _tables_to_dev(Wo, "bf16")))
+    thr, alias = m.alias()
+    dtok = torch.from_numpy(tok).cuda()
+    g, loss = m.grad_buffers(), torch.zeros(1, device="cuda")
+    seg_in, seg_out = (torch.zeros(c + 1, dtype=torch.int32, device="cuda") for c in (g.cap_in, g.cap_out))
+    for begin, n in ((700, 60), (2_000, 1600)):                      # 8 tiles, 201 tiles
+        _say("   centers", n)
+        og = oracle.sgns_grad(tok, w, N, begin, n, D, oracle.BF16, Wi, Wo, thr, alias, seed, 3, 2)
+        got = []
+        for ahead in ("no", "alone", "behind another"):
+            if ahead == "behind another":
+                m.prefetch(dtok, 9_000, n, 2)
+            if ahead != "no":
+                m.prefetch(dtok, begin, n, 2)
+            if ahead == "behind another":
+                m.sgns_grad(dtok, 9_000, n, 2, g)
+            m.sgns_grad(dtok, begin, n, 2, g, mean_loss=loss, seg_offsets_in=seg_in, seg_offsets_out=seg_out)
+            m.status()
+            got.append(_grad_snapshot(g, loss, seg_in, seg_out))
+        assert _same(got[0], got[1]) and _same(got[0], got[2])
+        _, _, ids_in, ids_out, rows_in, rows_out, got_loss, off_in, off_out = got[0]
+        assert np.array_equal(ids_in, og.gin.ids) and np.array_equal(ids_out, og.gout.ids) and ids_out[-1] == 1 << 27
+        assert np.array_equal(off_in, og.gin.seg.astype(np.int32)) and np.array_equal(off_out, og.gout.seg.astype(np.int32))
+        assert rows_rel(rows_in, og.gin.rows) <= TOL_ROWS and rows_rel(rows_out, og.gout.rows) <= TOL_ROWS
+        assert abs(float(got_loss[0]) - og.loss) <= TOL_LOSS * og.loss
+    m.close()
+
+
 @pytest.mark.parametrize("sizes", [(5000, 1600, 1600, 1600, 5200, 5000, 60, 1600, 1000, 5000),
                                    (2400, 2400, 2400, 60, 4000, 1600, 2400, 5000, 2400, 2400, 2040, 2041, 2400)])
 @pytest.mark.parametrize("call", ["step", "grad"])
@@ -1415,7 +1488,7 @@ def test_a_captured_call_replays_between_eager_ones(n, call):
 @pytest.mark.parametrize("name,idx,kw", [
     ("cfg3_pf", 3, dict(vocab=20_000, tokens=300_000, batch=256)),
     ("cfg5_pf", 5, dict(vocab=20_000, tokens=300_000, batch=256)),
-    # mini-batches above 2^20 occurrences are not prepared beside a step; with a long table update to follow
+    # mini-batches above 2^20 occurrences neither ride nor are prepared beside a forward pass; with a long table update to follow
     # (wide rows, 15 peers) the one after the current is still prepared under that update ...
     ("cfg5_big_long_update", 5, dict(vocab=300_000, tokens=1_000_000, batch=12_000)),
     # ... and with a short one (narrow rows, 1 peer) every announcement is left to the consuming call
@@ -1452,9 +1525,9 @@ def _same_on_device(a, b):
 @pytest.mark.parametrize("idx,steps", [(1, 500), (2, 1000), (3, 200), (4, 60), (5, 16)])
 def test_long_runs_with_and_without_prefetch_are_bit_identical(idx, steps):
     """The full-size configurations for many steps, two workers side by side on one stream: one announces every
-    coming mini-batch (preparation on the library's second stream: under the table update, beside the forward
-    pass, or left to the consuming call, as the configuration has it; index jobs riding in other launches, two
-    sets of masks and workspaces taking turns), the other does not.  Anything that ran before what it depends
+    coming mini-batch (its preparation rides in the launches of the step before, or is left to the consuming call, as
+    the configuration has it; index jobs riding in other launches, two sets of masks and workspaces taking turns),
+    the other does not.  Anything that ran before what it depends
     on had finished would show as a difference in some step's gradient or in the final tables."""
     cfg = W.CONFIGS[idx]
     tok, counts = _stream(cfg)
