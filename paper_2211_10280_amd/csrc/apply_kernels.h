@@ -139,9 +139,11 @@ __device__ __forceinline__ void update_row(T *wrow, u64 S, u64 rows_ptr, u32 pos
     else store_row<T, ITERS>(wrow, w, C4, lane);
 }
 
-// occupancy cap, so that the kernels of the second stream (the preparation of the next mini-batch) find wave
-// slots next to this one; measured with table rows on 128-byte lines: 5 / 6 / 7 / 8 waves per SIMD give a step of
-// 0.846 / 0.836 / 0.823 / 0.828 ms at a million words, and no difference at two million (3.46-3.49 ms)
+// occupancy cap: wave slots for the kernels of the second stream, where a preparation too large to ride runs beside this
+// one, and a little less pressure on the memory system where nothing does; measured with table rows on 128-byte lines and
+// the preparation on the second stream: 5 / 6 / 7 / 8 waves per SIMD give a step of 0.846 / 0.836 / 0.823 / 0.828 ms at a
+// million words, and no difference at two million (3.46-3.49 ms); with the preparation riding, 4 / 5 / 6 / 7 give 0.886 /
+// 0.853 / 0.844 / 0.847 ms, and an update of few rows of 4 million words (bfloat16, D = 200) 355 / 308 / 279 / 259 us
 #ifndef APPLY_MAX_WAVES
 #define APPLY_MAX_WAVES 7
 #endif

@@ -16,7 +16,6 @@ static inline int tn_seg_tile(i64 n) { return n <= 65536 ? 8 : 32; }
 #define TN_RADIX_TILE 2048    // keys per workgroup in a pass of the sort
 #define TN_RADIX_MAX_BITS 9   // widest digit of a pass
 #define TN_RADIX_MAX_ND (1 << TN_RADIX_MAX_BITS)
-#define TN_RADIX_MAX_PASSES 4
 #define TN_RADIX_MAX_PASSES_ND (3 * TN_RADIX_MAX_ND)   // digits of all passes together, at most (28 key bits: 4 x 128)
 // Number of passes and digit width for keys of `key_bits` bits: the fewest passes.  A pass is bound by round trips to
 // memory, and a digit's keys leave a tile as one run, so wider digits cost little; 9 bits are what a tile's counters

@@ -16,7 +16,8 @@
 //
 // A tile of keys is ranked inside its workgroup; what the lower tiles hold of every digit comes in one of two ways.
 //   chained (few tiles): a pass is one launch.  Every tile publishes its digit counts, then the sums up to it, and adds
-//     up what it needs from the nearest tiles below it.  Tiles are dealt by a ticket, so a workgroup only ever waits
+//     up what it needs from the nearest tiles below it (the published single-pass scan with decoupled look-back of
+//     Merrill and Garland, 2016, per digit).  Tiles are dealt by a ticket, so a workgroup only ever waits
 //     for workgroups that have started before it and that themselves wait for none above them: every wait ends,
 //     whatever the order of dispatch.  A published word carries its value and its state together, so no fence is
 //     needed.  At 10^4..10^5 keys a pass is bound by the latency of launches and of round trips to memory, not by
