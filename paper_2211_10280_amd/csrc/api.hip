@@ -861,6 +861,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     hipStream_t st = (hipStream_t)stream;
     const Sizes &s = m->sz;
 
+    note_capture(m, st);
     const i64 P = pair_count(c, n_tokens, center_begin, n_centers);
     if (P == 0) {
         tn_launch_empty_grad(grad_out->in.n_rows, grad_out->out.n_rows, mean_loss, seg_offsets_in,
@@ -868,7 +869,6 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         HIP_TRY(hipGetLastError());
         return TENSAIR_OK;
     }
-    note_capture(m, st);
     const int Np1 = c.negatives + 1;
     const BatchWork w = batch_work(c, tokens, n_tokens, center_begin, n_centers, epoch, P);
 

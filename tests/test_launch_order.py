@@ -67,6 +67,18 @@ def test_calls_after_a_capture_rely_on_nothing_that_was_left(trace, kind, n):
             assert ("k_apply_clear" in did) == (kind == "step")                # and the masks of the update's index
 
 
+def test_a_captured_step_without_pairs_carries_no_phase(trace):
+    """The mini-batch whose phases ride is half prepared when a step of an empty one is recorded: none of them may ride
+    with its update, which does not run now."""
+    batch = lambda i: [i * 60, 60, 0]                                          # noqa: E731
+    calls = [["prefetch"] + batch(0), ["prefetch"] + batch(1), ["step"] + batch(0) + [0], ["capture", 1], ["step", 60, 0, 0, 0],
+             ["capture", 0], ["step"] + batch(1) + [0]]
+    got = trace(calls, **dict(SMALL, vocab=300_000))                           # three passes: the segments have not ridden yet
+    update = [launches(c["did"])[-1] for c in got[2:]]
+    assert update[0][1] > update[1][1] and update[1] == update[2]              # the first carried a pass
+    assert "k_prep_keys" in names(got[4]["did"])
+
+
 def test_an_update_that_is_captured_leaves_no_mask_clean(trace):
     got = trace([["step", 0, 60, 0, 0], ["step", 60, 60, 0, 0], ["capture", 1], ["apply", 60, 900, 0], ["capture", 0],
                  ["step", 120, 60, 0, 0], ["step", 180, 60, 0, 0]], **SMALL)
