@@ -306,7 +306,8 @@ int tensair_status(tensair_model *m, void *stream);
 
 /* Stage timing with HIP events on the caller's stream (a measurement aid, not part of the
  * method).  level 0: off (default); 1: one pair of events around the table-update kernel of
- * tensair_dasgd_apply / tensair_step; 2: an event after every stage of the step.
+ * tensair_dasgd_apply / tensair_step (with the phase of a coming mini-batch's preparation that may ride in its
+ * launch); 2: an event after every stage of the step.
  * tensair_profile_read waits for the last recorded event, writes up to max_records
  * (tag, milliseconds) records since the previous read and returns their number (negative =
  * error).  Tags: 1 keys+negatives, 2 forward, 3 sort, 4 segments, 5 reduce W_in side,
