@@ -115,10 +115,13 @@ Sizes sizes_of(const tensair_config &c)
         const size_t chained = l.pass0 + (size_t)s.passes * (size_t)tiles * s.nd;
         s.pub_words = l.words > chained ? l.words : chained;
     }
-    s.tiles_out = (int)((s.Omax + tn_seg_tile(s.Omax) - 1) / tn_seg_tile(s.Omax));   // worst case over n <= Omax
-    if (s.Omax > 65536 && s.tiles_out < 65536 / 8) s.tiles_out = 65536 / 8;
-    s.tiles_in = (int)((s.Bmax + tn_seg_tile(s.Bmax) - 1) / tn_seg_tile(s.Bmax));
-    if (s.Bmax > 65536 && s.tiles_in < 65536 / 8) s.tiles_in = 65536 / 8;
+    auto seg_tiles = [&](i64 most) {   // worst case over n <= most
+        i64 tiles = (most + tn_seg_tile(most, c.dim) - 1) / tn_seg_tile(most, c.dim);
+        const i64 small = 65536 / tn_seg_tile(65536, c.dim);
+        return (int)(most > 65536 && tiles < small ? small : tiles);
+    };
+    s.tiles_out = seg_tiles(s.Omax);
+    s.tiles_in = seg_tiles(s.Bmax);
     s.words = (c.vocab + 63) / 64;
     return s;
 }
@@ -1088,7 +1091,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, n_centers, f.inv_P, mean_loss);
         if (next_rider(m, false, x, st)) tn_aux_add_prep(aux_red, x);
         PrepPhase y;
-        const bool rider = tn_seg_chains(r_out.n) + tn_seg_chains(r_in.n) > 0 && next_rider(m, false, y, st);
+        const bool rider = tn_seg_chains(r_out.n, c.dim) + tn_seg_chains(r_in.n, c.dim) > 0 && next_rider(m, false, y, st);
         tn_launch_segreduce(&r_out, &r_in, &aux_red, rider ? &y : nullptr, st);
     } else {         // one after the other, so that each can be timed
         if (mean_loss) tn_launch_loss(m->center_loss, n_centers, f.inv_P, mean_loss, st);

@@ -16,6 +16,7 @@
 
 #include "aux_dev.h"
 #include "dev_common.h"
+#include "forward_dev.h"
 #include "kernels.h"
 #include "rows_dev.h"
 
@@ -55,34 +56,26 @@ k_forward(FwdArgs a, AuxWork aux)
     }
     const int i = (int)blockIdx.x - aux.total;
     const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
-    const BatchDesc &b = a.b;
-    const i64 p = b.begin + i;
     const T *w_in = (const T *)a.w_in;
     const T *w_out = (const T *)a.w_out;
-    const int Np1 = b.N + 1;
-
-    int c = b.tok[p];
-    if ((u32)c >= (u32)a.V) c = 0;   // flagged by the key kernel; stay in range
-    i64 left = p < b.w ? p : b.w;
-    i64 right = (b.T - 1 - p) < b.w ? (b.T - 1 - p) : b.w;
-    const int ntasks = (int)(left + right) * Np1;
-    const i64 occ0 = (pairs_before(p, b.T, b.w) - b.pair_base) * Np1;
+    const int Np1 = a.b.N + 1;
+    const FwdCenter at = fwd_center(a, i);
 
     Row v, acc;
-    v.load(w_in + (size_t)c * a.stride, a.D, lane);
+    v.load(w_in + (size_t)at.c * a.stride, a.D, lane);
     acc.zero();
     float loss = 0.f;   // per-lane partial (lanes 0..UNROLL-1 carry it)
 
     // wave `wave` takes tasks wave, wave+4, ...; UNROLL rows are in flight at a time.  The
     // dot products are reduced one by one, then lane x evaluates the sigmoid of task x, so the
     // transcendental code runs once per group instead of once per task.
-    for (int t0 = wave; t0 < ntasks; t0 += WAVES_PER_BLOCK * UNROLL) {
+    for (int t0 = wave; t0 < at.ntasks; t0 += WAVES_PER_BLOCK * UNROLL) {
         LoadedRow<T, NQ, TAIL> u[UNROLL];
 #pragma unroll
         for (int x = 0; x < UNROLL; ++x) {
             int t = t0 + x * WAVES_PER_BLOCK;
-            if (t < ntasks) {
-                u32 j = a.out_keys[occ0 + t];
+            if (t < at.ntasks) {
+                u32 j = a.out_keys[at.occ0 + t];
                 u[x].load(w_out + (size_t)j * a.stride, a.D, lane);
             } else {
                 u[x].zero();
@@ -95,19 +88,10 @@ k_forward(FwdArgs a, AuxWork aux)
             s_l = (lane == x) ? s : s_l;
         }
         const int t_l = t0 + lane * WAVES_PER_BLOCK;
-        const bool live = (lane < UNROLL) && (t_l < ntasks);
-        const bool pos = (t_l % Np1) == 0;
-        // sigmoid(s) - label without cancellation: label 1: -1/(1+e^s), label 0: 1/(1+e^-s)
-        const float z = pos ? s_l : -s_l;
-        float gg = 1.0f / (1.0f + expf(z));
-        gg = pos ? -gg : gg;
-        const float g_l = live ? gg * a.inv_P : 0.f;
-        if (live) a.g[occ0 + t_l] = g_l;
-        if (LOSS) {
-            // loss term: softplus(-s) for the context, softplus(s) for a negative
-            const float y = -z;
-            if (live) loss += fmaxf(y, 0.f) + log1pf(expf(-fabsf(y)));
-        }
+        const bool live = (lane < UNROLL) && (t_l < at.ntasks);
+        const float g_t = task_g<LOSS>((t_l % Np1) == 0, s_l, a.inv_P, loss, live);
+        const float g_l = live ? g_t : 0.f;
+        if (live) a.g[at.occ0 + t_l] = g_l;
 #pragma unroll
         for (int x = 0; x < UNROLL; ++x) acc.axpy(rd_lane(g_l, x), u[x]);
     }
@@ -133,28 +117,7 @@ k_forward(FwdArgs a, AuxWork aux)
     }
 }
 
-// ---------------------------------------------------------------- forward where words repeat
-// Where few words are frequent, a position's tasks name the same word over and over (10 000 words, Zipf exponent 1.5,
-// 256 tasks: 126 different ones): every word is gathered and multiplied once here, and its row added once, scaled by
-// what its contexts and its negatives receive together.  The workgroup finds the different words with a hash table in
-// LDS; they are worked on in the order of their first task, so the result does not depend on the order of insertion.
-// g is stored per task as before (the same bits: one dot product, the same lanes).  The pass is bound by the row
-// gathers out of L2, and half of them go; what the table costs (two barriers and some LDS traffic per position) is
-// more than that where most words are different, so the host asks for it by the noise distribution (FwdArgs::repeats).
-// 16 384 centers, 10 000 words, D = 256: 250 -> 175 us beside the sort (step 576 -> 511 us); 500 centers, 2 000 words, D = 32: step
-// 60.5 -> 55.7; no gain where nine tenths of the words are different (5 000 words, 60 tasks: step 40.4 -> 40.6).
-struct RepeatLds {
-    int slots, tasks;      // slots: a power of two, at least twice the tasks
-    __host__ __device__ int words() const { return 3 * slots + 4 * tasks + 2 * WAVES_PER_BLOCK; }
-};
-__host__ __device__ static inline RepeatLds repeat_lds(int tasks)
-{
-    RepeatLds l;
-    l.tasks = tasks;
-    l.slots = tasks <= 256 ? 512 : 1024;
-    return l;
-}
-
+// ---------------------------------------------------------------- forward where words repeat (see RepeatList)
 template <typename T, int NQ, bool TAIL, bool LOSS, bool PREP>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8)))
 k_forward_repeats(FwdArgs a, AuxWork aux)
@@ -162,100 +125,30 @@ k_forward_repeats(FwdArgs a, AuxWork aux)
     typedef WaveRow<NQ, TAIL> Row;
     constexpr int UNROLL = FwdShape<T, NQ, TAIL>::unroll;
     constexpr int ROW = FwdShape<T, NQ, TAIL>::row;
-    constexpr int PER = TN_REPEAT_MAX_TASKS / BLOCK;      // tasks per thread
     if ((int)blockIdx.x < aux.total) {
         aux_block<PREP, PREP>(aux, (int)blockIdx.x, ride_lds);
         return;
     }
     float (*red)[ROW] = (float (*)[ROW])ride_lds;
     float *lred = (float *)ride_lds + WAVES_PER_BLOCK * ROW;
-    const BatchDesc &b = a.b;
-    const int Np1 = b.N + 1;
-    const RepeatLds l = repeat_lds(2 * b.w * Np1);
-    u32 *key = ride_lds + WAVES_PER_BLOCK * ROW + WAVES_PER_BLOCK;   // [slots] word
-    u32 *first = key + l.slots;        // [slots] first task that names it, later its place in the list
-    u32 *cnt = first + l.slots;        // [slots] contexts + 65536 * negatives
-    u32 *ukey = cnt + l.slots, *ucnt = ukey + l.tasks;               // [tasks] the list: word, counts,
-    float *gp = (float *)(ucnt + l.tasks), *gn = gp + l.tasks;       // g of a context and of a negative
-    u32 *wn = (u32 *)(gn + l.tasks);   // [PER][waves] different words per wave and round
     const int i = (int)blockIdx.x - aux.total;
     const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
-    const i64 p = b.begin + i;
     const T *w_in = (const T *)a.w_in;
     const T *w_out = (const T *)a.w_out;
-
-    int c = b.tok[p];
-    if ((u32)c >= (u32)a.V) c = 0;   // flagged by the key kernel; stay in range
-    const i64 left = p < b.w ? p : b.w;
-    const i64 right = (b.T - 1 - p) < b.w ? (b.T - 1 - p) : b.w;
-    const int ntasks = (int)(left + right) * Np1;         // <= l.tasks <= TN_REPEAT_MAX_TASKS
-    const i64 occ0 = (pairs_before(p, b.T, b.w) - b.pair_base) * Np1;
+    const FwdCenter at = fwd_center(a, i);
 
     Row v, acc;
-    v.load(w_in + (size_t)c * a.stride, a.D, lane);
+    v.load(w_in + (size_t)at.c * a.stride, a.D, lane);
     acc.zero();
-    u32 mine[PER];
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = r * BLOCK + (int)threadIdx.x;
-        mine[r] = t < ntasks ? a.out_keys[occ0 + t] : 0u;
-    }
-    for (int s = threadIdx.x; s < l.slots; s += BLOCK) {
-        key[s] = 0xFFFFFFFFu;          // no word: ids stay below 2^28
-        first[s] = 0xFFFFFFFFu;
-        cnt[s] = 0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = r * BLOCK + (int)threadIdx.x;
-        if (t < ntasks) {
-            const u32 k = mine[r];
-            // a free slot or the word's own is found: there are at least twice as many slots as tasks
-            u32 s = (k * 0x9E3779B1u) >> 22;
-            for (;; ++s) {
-                s &= (u32)l.slots - 1u;
-                const u32 was = atomicCAS(&key[s], 0xFFFFFFFFu, k);
-                if (was == 0xFFFFFFFFu || was == k) break;
-            }
-            atomicMin(&first[s], (u32)t);
-            atomicAdd(&cnt[s], t % Np1 == 0 ? 1u : 65536u);
-            mine[r] = s;
-        }
-    }
-    __syncthreads();
-    // the list of different words, in the order of their first tasks
-    u64 own[PER];
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = r * BLOCK + (int)threadIdx.x;
-        own[r] = __ballot(t < ntasks && first[mine[r]] == (u32)t);
-        if (lane == 0) wn[r * WAVES_PER_BLOCK + wave] = (u32)__popcll(own[r]);
-    }
-    __syncthreads();
-    int nu = 0;
-#pragma unroll
-    for (int r = 0; r < PER; ++r)
-#pragma unroll
-        for (int w = 0; w < WAVES_PER_BLOCK; ++w) {
-            if (w == wave && ((own[r] >> lane) & 1ull)) {
-                const int at = nu + (int)__popcll(own[r] & ((1ull << lane) - 1ull));
-                const u32 s = mine[r];
-                ukey[at] = key[s];
-                ucnt[at] = cnt[s];
-                first[s] = (u32)at;
-            }
-            nu += (int)wn[r * WAVES_PER_BLOCK + w];
-        }
-    nu = uniform(nu);
-    __syncthreads();
+    RepeatList words;
+    words.build(a, at, ride_lds + WAVES_PER_BLOCK * ROW + WAVES_PER_BLOCK);
     float loss = 0.f;
-    for (int t0 = wave; t0 < nu; t0 += WAVES_PER_BLOCK * UNROLL) {
+    for (int t0 = wave; t0 < words.n; t0 += WAVES_PER_BLOCK * UNROLL) {
         LoadedRow<T, NQ, TAIL> u[UNROLL];
 #pragma unroll
         for (int x = 0; x < UNROLL; ++x) {
             const int t = t0 + x * WAVES_PER_BLOCK;
-            if (t < nu) u[x].load(w_out + (size_t)uniform((int)ukey[t]) * a.stride, a.D, lane);
+            if (t < words.n) u[x].load(w_out + (size_t)uniform((int)words.ukey[t]) * a.stride, a.D, lane);
             else u[x].zero();
         }
         float s_l = 0.f;
@@ -266,22 +159,7 @@ k_forward_repeats(FwdArgs a, AuxWork aux)
         }
         const int t_l = t0 + lane * WAVES_PER_BLOCK;
         float sum = 0.f;
-        if (lane < UNROLL && t_l < nu) {
-            // sigmoid(s) - label without cancellation: label 1: -1/(1+e^s), label 0: 1/(1+e^-s)
-            const float g1 = -(1.0f / (1.0f + expf(s_l))) * a.inv_P, g0 = 1.0f / (1.0f + expf(-s_l)) * a.inv_P;
-            gp[t_l] = g1;
-            gn[t_l] = g0;
-            const u32 n = ucnt[t_l];
-            const float n1 = (float)(n & 0xFFFFu), n0 = (float)(n >> 16);
-            sum = fmaf(n1, g1, n0 * g0);
-            if (LOSS) {
-                // loss terms: softplus(-s) for a context, softplus(s) for a negative; one that does not occur is left
-                // out, not taken zero times (it is infinite where the dot product has overflowed)
-                const float tail = log1pf(expf(-fabsf(s_l)));
-                if (n & 0xFFFFu) loss += n1 * (fmaxf(-s_l, 0.f) + tail);
-                if (n >> 16) loss += n0 * (fmaxf(s_l, 0.f) + tail);
-            }
-        }
+        if (lane < UNROLL && t_l < words.n) sum = words.template scale<LOSS>(t_l, s_l, a.inv_P, loss);
 #pragma unroll
         for (int x = 0; x < UNROLL; ++x) acc.axpy(rd_lane(sum, x), u[x]);
     }
@@ -292,14 +170,7 @@ k_forward_repeats(FwdArgs a, AuxWork aux)
         if (lane == 0) lred[wave] = loss;
     }
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = r * BLOCK + (int)threadIdx.x;
-        if (t < ntasks) {
-            const u32 at = first[mine[r]];
-            a.g[occ0 + t] = t % Np1 == 0 ? gp[at] : gn[at];
-        }
-    }
+    words.store_g(a, at);
     float *dst = a.center_part + (size_t)i * a.D;
     for (int e = threadIdx.x; e < a.D; e += BLOCK) {
         float s = red[0][e];
@@ -363,6 +234,10 @@ void tn_launch_forward(const FwdArgs &a, const AuxWork *aux, hipStream_t st)
     if (!aux) {
         tn_aux_none(none);
         aux = &none;
+    }
+    if (a.D <= TN_SUB_MAX_DIM) {
+        tn_launch_forward_sub(a, *aux, st);
+        return;
     }
     const bool loss = a.center_loss != nullptr;
     if (a.dtype == 0) loss ? launch_forward_t<float, true>(a, *aux, st) : launch_forward_t<float, false>(a, *aux, st);

@@ -9,10 +9,13 @@ typedef uint64_t u64;
 typedef int64_t i64;
 
 #define TN_MAX_SRC 32     // own + up to 31 peers
+#define TN_SUB_MAX_DIM 128   // rows of at most this many elements (16 bytes for at most 32 lanes): several to a wave
 #define TN_MAX_BLOCKS ((1 << 24) - 1)   // workgroups of 256 threads that one launch may have (2^32 threads in all)
 // sorted entries per wave in the segmented reduction: small problems get small tiles so that
 // enough waves exist to hide the latency of the row loads
-static inline int tn_seg_tile(i64 n) { return n <= 65536 ? 8 : 32; }
+// (a wave that sums several entries side by side gets more of them: SEG_SUB_TILE)
+#define SEG_SUB_TILE 16
+static inline int tn_seg_tile(i64 n, int D) { return n > 65536 ? 32 : D <= TN_SUB_MAX_DIM ? SEG_SUB_TILE : 8; }
 #define TN_RADIX_TILE 2048    // keys per workgroup in a pass of the sort
 #define TN_RADIX_MAX_BITS 9   // widest digit of a pass
 #define TN_RADIX_MAX_ND (1 << TN_RADIX_MAX_BITS)
@@ -155,6 +158,7 @@ struct FwdArgs {
 #define TN_REPEAT_MAX_TASKS 512
 struct AuxWork;
 void tn_launch_forward(const FwdArgs &a, const AuxWork *aux, hipStream_t st);   // aux may be NULL
+void tn_launch_forward_sub(const FwdArgs &a, const AuxWork &aux, hipStream_t st);
 
 // ---- stage 5: segmented reduction of rows (duplicates summed in sorted order)
 struct SegReduceArgs {
@@ -185,10 +189,18 @@ struct SegReduceArgs {
 // rides with the launch that chains the long rows, if there is one (tn_seg_chains)
 void tn_launch_segreduce(const SegReduceArgs *out, const SegReduceArgs *in, const AuxWork *aux, const PrepPhase *rider,
                          hipStream_t st);
+// The W_out-side and the W_in-side reduction of a mini-batch are independent: one launch runs both
+// (workgroups [0, blocks_in) take the in-side problem, the rest the out-side one), so that the small
+// in-side problem costs no launch of its own and its few workgroups start first.
+struct SegReducePair {
+    SegReduceArgs out, in;
+    int blocks_in;    // workgroups of the in-side problem at the front of the grid
+};
+void tn_launch_segreduce_sub(SegReducePair &p, const AuxWork &aux, const PrepPhase &rider, hipStream_t st);
 // workgroups that chain long rows: they exist only where a problem has more than one tile
-static inline int tn_seg_chains(i64 n)
+static inline int tn_seg_chains(i64 n, int D)
 {
-    const i64 tiles = (n + tn_seg_tile(n) - 1) / tn_seg_tile(n);
+    const i64 tiles = (n + tn_seg_tile(n, D) - 1) / tn_seg_tile(n, D);
     return tiles > 1 ? (int)(tiles < 1024 ? tiles : 1024) : 0;
 }
 

@@ -205,6 +205,18 @@ def test_mean_loss_where_scores_overflow(w, N, dtype):
     m.close()
 
 
+# rows of at most 128 elements, several to a wave: both edges of every group size, tiles of 16 entries and (from 65 537
+# occurrences on) of 32, rows of a few entries and rows that run through many tiles
+NARROW_CASES = [(V, D, D + pad, 20_000, z, w, N, Bc, 300, dt)
+                for D, pad, dt in ((4, 0, "bf16"), (32, 8, "f32"), (36, 0, "f32"), (64, 0, "bf16"), (68, 4, "bf16"), (128, 0, "f32"))
+                for V, z, w, N, Bc in ((30_000, 1.0, 2, 3, 77), (50, 1.3, 3, 9, 1092), (50, 1.3, 3, 9, 1093), (9_000, 1.2, 4, 7, 2000))]
+
+
+@pytest.mark.parametrize("case", NARROW_CASES, ids=lambda c: f"V{c[0]}_D{c[1]}_B{c[7]}_{c[9]}")
+def test_sgns_grad_parity_of_narrow_rows(case):
+    _grad_parity(case)
+
+
 def _random_grad_cases(n, seed):
     """Seeded shapes: narrow to wide rows, windows 1..6, 0..12 negatives, batches from one center up, streams
     from flat to steep, vocabularies from two words up, batches at the start, inside and at the end of the
