@@ -115,10 +115,11 @@ Sizes sizes_of(const tensair_config &c)
         const size_t chained = l.pass0 + (size_t)s.passes * (size_t)tiles * s.nd;
         s.pub_words = l.words > chained ? l.words : chained;
     }
-    auto seg_tiles = [&](i64 most) {   // worst case over n <= most
-        i64 tiles = (most + tn_seg_tile(most, c.dim) - 1) / tn_seg_tile(most, c.dim);
-        const i64 small = 65536 / tn_seg_tile(65536, c.dim);
-        return (int)(most > 65536 && tiles < small ? small : tiles);
+    auto seg_tiles = [&](i64 most) {   // worst case over n <= most: at most, and at the last n of every tile size
+        i64 tiles = tn_seg_tiles(most, c.dim);
+        for (i64 n : {(i64)8192, (i64)32768})
+            if (n < most) tiles = std::max(tiles, tn_seg_tiles(n, c.dim));
+        return (int)tiles;
     };
     s.tiles_out = seg_tiles(s.Omax);
     s.tiles_in = seg_tiles(s.Bmax);
@@ -600,7 +601,9 @@ static void make_prep_phase(tensair_model *m, BatchSet &S, const BatchWork &w, b
         PrepKeys &k = x.keys;
         x.kind = PREP_KEYS;
         const i64 slots = (i64)w.b.n_centers * 2 * c.window * (c.negatives + 1);
-        x.blocks = (int)((slots + PREP_KEYS_SLOTS - 1) / PREP_KEYS_SLOTS);
+        const int per_block = tn_prep_keys_slots(slots);
+        x.blocks = (int)((slots + per_block - 1) / per_block);
+        k.items = per_block / BLOCK;
         k.b = w.b;
         k.V = c.vocab;
         k.draw = m->draw;
@@ -1091,7 +1094,12 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, n_centers, f.inv_P, mean_loss);
         if (next_rider(m, false, x, st)) tn_aux_add_prep(aux_red, x);
         PrepPhase y;
-        const bool rider = tn_seg_chains(r_out.n, c.dim) + tn_seg_chains(r_in.n, c.dim) > 0 && next_rider(m, false, y, st);
+        // the chaining of long rows is short (4 us where a pass of the sort takes 9): a phase rides with it only where there
+        // are more left than the table update and the next forward pass can take (1 024 centers, 50 000 words: step 54.6
+        // -> 49.0 us with the second pass under the update instead)
+        const int later = 1 + (fuse && tn_apply_carries(c.dim, c.vocab) ? 1 : 0);
+        const bool rider = tn_seg_chains(r_out.n, c.dim) + tn_seg_chains(r_in.n, c.dim) > 0 &&
+                           m->pend.phase + later < prep_phases(s, true) && next_rider(m, false, y, st);
         tn_launch_segreduce(&r_out, &r_in, &aux_red, rider ? &y : nullptr, st);
     } else {         // one after the other, so that each can be timed
         if (mean_loss) tn_launch_loss(m->center_loss, n_centers, f.inv_P, mean_loss, st);

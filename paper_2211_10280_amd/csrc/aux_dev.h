@@ -131,11 +131,13 @@ __device__ __forceinline__ void aux_mean_loss(const float *center_loss, int n, f
 // LDS of those jobs
 static inline unsigned aux_lds_bytes(const AuxWork &x)
 {
-    const unsigned a = ride_lds_bytes(x.prep[0]);
-    return a ? a : x.mean_loss ? 4u * WAVES_PER_BLOCK : 0u;
+    unsigned most = x.mean_loss ? 4u * WAVES_PER_BLOCK : 0u;
+    for (const PrepPhase &p : x.prep)
+        if (ride_lds_bytes(p) > most) most = ride_lds_bytes(p);
+    return most;
 }
 
-// The jobs that ride at the front of a launch (see AuxWork): workgroup b of x.total.  lds: PrepLds<BLOCK>::words words.
+// The jobs that ride at the front of a launch (see AuxWork): workgroup b of x.total.  lds: aux_lds_bytes(x) bytes.
 // PREP: phases of a preparation may be among them; KEYS: the keys too
 template <bool PREP, bool KEYS>
 __device__ __forceinline__ void aux_block(const AuxWork &x, int b, u32 *lds)

@@ -258,14 +258,20 @@ __device__ __forceinline__ u64 rd_lane64(u64 v, int l)
 }
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// inclusive scan of one value per lane across the wave
-__device__ __forceinline__ u32 wave_incl_scan(u32 x, int lane)
+// inclusive scan of one value per lane across the wave: within rows of 16 lanes, then the rows' last lanes are handed on
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ u32 dpp_add(u32 x)
 {
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-        u32 y = (u32)__shfl_up((int)x, o, WAVE);
-        if (lane >= o) x += y;
-    }
+    return x + (u32)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xF, false);
+}
+__device__ __forceinline__ u32 wave_incl_scan(u32 x, int)
+{
+    x = dpp_add<0x111, 0xF>(x);    // row_shr:1
+    x = dpp_add<0x112, 0xF>(x);    // row_shr:2
+    x = dpp_add<0x114, 0xF>(x);    // row_shr:4
+    x = dpp_add<0x118, 0xF>(x);    // row_shr:8
+    x = dpp_add<0x142, 0xA>(x);    // row_bcast:15 into rows 1 and 3
+    x = dpp_add<0x143, 0xC>(x);    // row_bcast:31 into rows 2 and 3
     return x;
 }
 

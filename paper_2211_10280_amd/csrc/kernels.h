@@ -11,11 +11,15 @@ typedef int64_t i64;
 #define TN_MAX_SRC 32     // own + up to 31 peers
 #define TN_SUB_MAX_DIM 128   // rows of at most this many elements (16 bytes for at most 32 lanes): several to a wave
 #define TN_MAX_BLOCKS ((1 << 24) - 1)   // workgroups of 256 threads that one launch may have (2^32 threads in all)
-// sorted entries per wave in the segmented reduction: small problems get small tiles so that
-// enough waves exist to hide the latency of the row loads
-// (a wave that sums several entries side by side gets more of them: SEG_SUB_TILE)
-#define SEG_SUB_TILE 16
-static inline int tn_seg_tile(i64 n, int D) { return n > 65536 ? 32 : D <= TN_SUB_MAX_DIM ? SEG_SUB_TILE : 8; }
+// Sorted entries per wave in the segmented reduction, 2^tn_seg_shift: small problems get small tiles so that
+// enough waves exist to hide the latency of the row loads, but every row of more than a tile is chained from partials.
+// Tiles of 8 / 16 / 32 entries, step in us: 4 100 entries, D = 460 28.4 / 29.0 / 32.5; 6 900, D = 256 (gradient) 48.3 /
+// 49.6 / 52.2; 12 200, D = 144 36.2 / 34.5 / 37.0; 21 000, D = 224 52.5 / 48.8 / 47.2; 32 500, D = 168, unannounced 69.6 /
+// 67.0 / 68.7; 52 800, D = 216 73.6 / 66.3 / 63.8.  Rows of at most TN_SUB_MAX_DIM elements, of which a wave sums several
+// side by side: 1 500 entries, D = 32 22.9 / 22.9 / 21.9; 61 400, D = 128 56.9 / 49.1 / 47.4; 63 700, D = 92 56.1 / 46.9 / 41.6.
+#define TN_SEG_MAX_TILE 32
+static inline int tn_seg_shift(i64 n, int D) { return D <= TN_SUB_MAX_DIM || n > 32768 ? 5 : n > 8192 ? 4 : 3; }
+static inline i64 tn_seg_tiles(i64 n, int D) { return (n + (1 << tn_seg_shift(n, D)) - 1) >> tn_seg_shift(n, D); }
 #define TN_RADIX_TILE 2048    // keys per workgroup in a pass of the sort
 #define TN_RADIX_MAX_BITS 9   // widest digit of a pass
 #define TN_RADIX_MAX_ND (1 << TN_RADIX_MAX_BITS)
@@ -49,7 +53,12 @@ struct BatchDesc {
 };
 
 // ---- preparation of a mini-batch (prep_dev.h): one launch per phase -- keys, the passes of the sort, segments
-#define PREP_KEYS_SLOTS 1024   // slots per workgroup
+#define PREP_KEYS_SLOTS 1024   // most slots per workgroup
+// Slots per workgroup: few where there are few (a workgroup's time is that of one slot after the other), more where the
+// workgroups' digit counts, added up in memory, would cost more (step, 1 024 / 512 / 256 slots: 1 536 slots in all 26.5 / 24.4 /
+// 23.7 us, 6 000 - / 29.9 / 29.4, gradient of 12 000 - / 41.3 / 40.0; step, 61 000 56.3 / 54.6 / 55.4, 64 000 - / 43.0 / 45.0;
+// 85 000 60.1 / 62.0, 143 000 64.5 / 66.1).
+static inline int tn_prep_keys_slots(i64 slots) { return slots <= 16384 ? 256 : slots <= 65536 ? 512 : PREP_KEYS_SLOTS; }
 struct PrepKeys {
     BatchDesc b;
     i64 V;
@@ -60,6 +69,7 @@ struct PrepKeys {
     int *pair_center, *neg_dbg, *status;
     u32 *hist;             // [2 lists][passes][2^bits] digit counts, added to: zero before (NULL: not wanted)
     int passes, bits;
+    int items;             // slots per thread of a workgroup of BLOCK threads
     u32 *clear;            // what the later phases publish into and their tickets: zeroed
     size_t n_clear;
 };
@@ -163,6 +173,7 @@ void tn_launch_forward_sub(const FwdArgs &a, const AuxWork &aux, hipStream_t st)
 // ---- stage 5: segmented reduction of rows (duplicates summed in sorted order)
 struct SegReduceArgs {
     int n;                 // sorted entries
+    int shift;             // tiles of 2^shift entries (the launcher sets it: tn_seg_shift)
     const u32 *vals;       // sorted values
     const int *seg_of;     // row index per sorted entry
     const int *seg_start;  // first sorted entry of every row; [U] = n
@@ -200,7 +211,7 @@ void tn_launch_segreduce_sub(SegReducePair &p, const AuxWork &aux, const PrepPha
 // workgroups that chain long rows: they exist only where a problem has more than one tile
 static inline int tn_seg_chains(i64 n, int D)
 {
-    const i64 tiles = (n + tn_seg_tile(n, D) - 1) / tn_seg_tile(n, D);
+    const i64 tiles = tn_seg_tiles(n, D);
     return tiles > 1 ? (int)(tiles < 1024 ? tiles : 1024) : 0;
 }
 

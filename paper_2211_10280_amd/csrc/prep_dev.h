@@ -59,12 +59,12 @@ __device__ __forceinline__ int take_ticket(u32 *counter, u32 *word)
 // Slot s of the mini-batch is (center i, offset index q, k): k = 0 is the context, k = 1..N are the negatives.
 // Writes the out-side key list [pair][N+1] (pair-major, the order of the occurrence list), the in-side key of every
 // center, the center token of every pair and (for chained passes) the digit counts of both lists; clears the words that the sort's and
-// the segment scan's workgroups will publish, and their tickets.  A workgroup takes PREP_KEYS_SLOTS slots, a thread one of
+// the segment scan's workgroups will publish, and their tickets.  A workgroup takes items * THREADS slots, a thread one of
 // every THREADS, so that their table lookups are in flight together.
 template <int THREADS>
 __device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblocks, u32 *lds)
 {
-    constexpr int ITEMS = PREP_KEYS_SLOTS / THREADS;
+    constexpr int ITEMS = PREP_KEYS_SLOTS / THREADS;     // a.items of them are used
     const BatchDesc &b = a.b;
     const int nd = 1 << a.bits, nhist = a.passes * nd;   // counters of one list
     const u32 dmask = (u32)nd - 1u;
@@ -74,7 +74,7 @@ __device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblo
     __syncthreads();
     const u32 Np1 = (u32)b.N + 1u, w = (u32)b.w, per_center = 2u * w * Np1;
     const u32 total = (u32)b.n_centers * per_center;     // fits 31 bits (checked with the configuration)
-    const u32 s0 = (u32)block * (u32)(THREADS * ITEMS) + threadIdx.x;
+    const u32 s0 = (u32)block * (u32)(THREADS * a.items) + threadIdx.x;
     u32 key[ITEMS];
     int in_key[ITEMS];      // >= 0: the slot is its center's first, and this is the center's word
 #pragma unroll
@@ -82,7 +82,7 @@ __device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblo
         key[j] = 0xFFFFFFFFu;
         in_key[j] = -1;
         const u32 t = s0 + (u32)j * THREADS;
-        if (t >= total) continue;
+        if (j >= a.items || t >= total) continue;
         const u32 i = t / per_center, rem = t - i * per_center, q = rem / Np1, k = rem - q * Np1;
         const i64 p = b.begin + (i64)i;
         int c = b.tok[p];
@@ -145,9 +145,9 @@ __device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblo
 }
 
 // ---------------------------------------------------------------- one pass of the sort
-// block-wide exclusive scan of two numbers per thread
+// block-wide exclusive scan of two numbers per thread, and their sums
 template <int THREADS>
-__device__ __forceinline__ void prep_scan2(u32 a, u32 b, u32 &ea, u32 &eb, u32 *sm)
+__device__ __forceinline__ void prep_scan2(u32 a, u32 b, u32 &ea, u32 &eb, u32 &ta, u32 &tb, u32 *sm)
 {
     constexpr int NW = THREADS / WAVE;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
@@ -157,41 +157,47 @@ __device__ __forceinline__ void prep_scan2(u32 a, u32 b, u32 &ea, u32 &eb, u32 *
         sm[NW + wave] = ib;
     }
     __syncthreads();
-    u32 oa = 0, ob = 0;
+    ea = ia - a;
+    eb = ib - b;
+    ta = tb = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
+    for (int w = 0; w < NW; ++w) {
         if (w < wave) {
-            oa += sm[w];
-            ob += sm[NW + w];
+            ea += sm[w];
+            eb += sm[NW + w];
         }
-    ea = oa + ia - a;
-    eb = ob + ib - b;
+        ta += sm[w];
+        tb += sm[NW + w];
+    }
 }
 
-// LDS words of a pass: per-wave digit counters, later overlaid by the tile's keys and values in digit order; the place
-// of every digit's run; scan scratch
+// LDS words of a pass with nd digits: per wave and digit a mask of lanes (two words) and a counter, later overlaid by the
+// tile's keys and values in digit order; the place of every digit's run; scan scratch
 template <int THREADS>
 struct PassLds {
     static constexpr int NW = THREADS / WAVE;
-    static constexpr int counters = NW * TN_RADIX_MAX_ND;
+    static constexpr int PER = (TN_RADIX_MAX_ND + THREADS - 1) / THREADS;    // digits per thread
     static constexpr int staged = 2 * TN_RADIX_TILE;
-    static constexpr int words = (counters > staged ? counters : staged) + TN_RADIX_MAX_ND + 2 * NW + 2;
+    __host__ __device__ static constexpr int dbase(int nd) { return 3 * NW * nd > staged ? 3 * NW * nd : staged; }
+    __host__ __device__ static constexpr int words(int nd) { return dbase(nd) + nd + 2 * NW * PER + 2; }
 };
 
-// block `block` of a counted pass; a chained one draws its tile
+// block `block` of a counted pass; a chained one draws its tile.  Alone, 61 000 keys in 31 tiles take 14.0 us with the
+// lanes of a digit found by ballots, bit by bit (4 of them; 1 now), and two neighbouring digits looked back for by every
+// other thread, one after the other (6; 3 now).
 template <int THREADS, bool CHAINED>
 __device__ __forceinline__ void prep_pass(const PrepPass &a, int block, u32 *lds)
 {
     typedef PassLds<THREADS> L;
-    constexpr int IPT = TN_RADIX_TILE / THREADS;
-    constexpr int PER = (TN_RADIX_MAX_ND + THREADS - 1) / THREADS;    // digits per thread
-    u32 *whp = lds;                                                   // [NW][nd]
-    u32 *skey = lds, *sval = lds + TN_RADIX_TILE;
-    u32 *dbase = lds + (L::counters > L::staged ? L::counters : L::staged);
-    u32 *sm = dbase + TN_RADIX_MAX_ND;
+    constexpr int IPT = TN_RADIX_TILE / THREADS, PER = L::PER;
     const int nd = 1 << a.bits;
+    u32 *skey = lds, *sval = lds + TN_RADIX_TILE;
+    u32 *dbase = lds + L::dbase(nd);
+    u32 *sm = dbase + nd;
     const u32 dmask = (u32)nd - 1u;
     const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
+    u64 *lanes = (u64 *)lds + wave * nd;                              // [nd] of this wave
+    u32 *whp = lds + 2 * L::NW * nd;                                  // [NW][nd]
     int tile = CHAINED ? take_ticket(a.ticket, sm) : block;
     const int pr = tile < a.p[1].tiles ? 1 : 0;                       // the in-side list's tiles come first
     if (pr == 0) tile -= a.p[1].tiles;
@@ -208,110 +214,142 @@ __device__ __forceinline__ void prep_pass(const PrepPass &a, int block, u32 *lds
         key[it] = idx < n ? P.kin[idx] : 0u;
         val[it] = a.first ? (u32)idx : (idx < n ? P.vin[idx] : 0u);
     }
-    const int d0 = threadIdx.x * PER;
     u32 total[PER], below[PER];                 // keys per digit: in the list, in the lower tiles
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
+        const int d = j * THREADS + (int)threadIdx.x;
         total[j] = below[j] = 0;
-        if (d0 + j < nd) {
+        if (d < nd) {
             if (CHAINED) {
-                total[j] = P.hist[d0 + j];
+                total[j] = P.hist[d];
             } else {
                 const int group = tile / TN_PREP_GROUP, groups = (P.tiles + TN_PREP_GROUP - 1) / TN_PREP_GROUP;
                 if (a.scanned) {
-                    total[j] = P.hist[(size_t)groups * nd + d0 + j];
-                    below[j] = P.hist[(size_t)group * nd + d0 + j];
+                    total[j] = P.hist[(size_t)groups * nd + d];
+                    below[j] = P.hist[(size_t)group * nd + d];
                 } else {
 #pragma unroll 8
                     for (int t = 0; t < groups; ++t) {
-                        const u32 v = P.hist[(size_t)t * nd + d0 + j];
+                        const u32 v = P.hist[(size_t)t * nd + d];
                         total[j] += v;
                         below[j] += t < group ? v : 0u;
                     }
                 }
 #pragma unroll 8
-                for (int t = group * TN_PREP_GROUP; t < tile; ++t) below[j] += P.state[(size_t)t * nd + d0 + j];
+                for (int t = group * TN_PREP_GROUP; t < tile; ++t) below[j] += P.state[(size_t)t * nd + d];
             }
         }
     }
-    for (int d = threadIdx.x; d < L::NW * nd; d += THREADS) whp[d] = 0;
+    for (int d = threadIdx.x; d < 3 * L::NW * nd; d += THREADS) lds[d] = 0;
     __syncthreads();
     const u64 lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    // the lanes that hold the same digit: every lane adds its bit to the digit's mask, reads it and clears it.  A wave's
+    // accesses to LDS are carried out in order, so the keys follow one another without a wait.
+    u64 same[IPT];
 #pragma unroll
     for (int it = 0; it < IPT; ++it) {
-        const bool valid = wbase + it * WAVE + lane < n;
         const u32 d = (key[it] >> a.shift) & dmask;
-        u64 m = __ballot(valid);
-        for (int bit = 0; bit < a.bits; ++bit) {
-            const bool on = (d >> bit) & 1u;
-            const u64 bal = __ballot(valid && on);
-            m &= on ? bal : ~bal;
+        same[it] = 0;
+        if (wbase + it * WAVE + lane < n) {
+            __hip_atomic_fetch_or(&lanes[d], 1ull << lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            same[it] = __hip_atomic_load(&lanes[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            __hip_atomic_store(&lanes[d], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         }
-        const u32 rank = (u32)__popcll(m & lt);
-        u32 old = 0;
-        if (valid) old = whp[wave * nd + d];
-        if (valid && rank == 0) whp[wave * nd + d] = old + (u32)__popcll(m);
-        loc[it] = old + rank;
     }
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) {
+        const u32 d = (key[it] >> a.shift) & dmask;
+        u32 *count = &whp[wave * nd + d];
+        loc[it] = 0;
+        if (wbase + it * WAVE + lane < n) {
+            loc[it] = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            if ((same[it] & lt) == 0ull)
+                __hip_atomic_fetch_add(count, (u32)__popcll(same[it]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < IPT; ++it) loc[it] += (u32)__popcll(same[it] & lt);
     __syncthreads();
     // per digit: counts of the lower waves of the tile, the tile's count (published at once)
-    u32 count[PER], st = 0, sc = 0;
+    u32 count[PER];
     u32 *mine = P.state + (size_t)tile * nd;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
+        const int d = j * THREADS + (int)threadIdx.x;
         u32 run = 0;
-        if (d0 + j < nd) {
+        if (d < nd) {
 #pragma unroll
             for (int w = 0; w < L::NW; ++w) {
-                const u32 c = whp[w * nd + d0 + j];
-                whp[w * nd + d0 + j] = run;
+                const u32 c = whp[w * nd + d];
+                whp[w * nd + d] = run;
                 run += c;
             }
-            if (CHAINED) post(&mine[d0 + j], tile == 0 ? PREP_INCL + run : 1u + run);
+            if (CHAINED) post(&mine[d], tile == 0 ? PREP_INCL + run : 1u + run);
         }
         count[j] = run;
-        st += total[j];
-        sc += run;
     }
-    u32 et, ec;                                 // keys of smaller digits: in the list, in the tile
-    prep_scan2<THREADS>(st, sc, et, ec, sm);
+    if (CHAINED) {
+        // all digits of this thread at a time; look[j]: the next tile to look at, -1 when done
+        int look[PER];
+        bool more = false;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int d = d0 + j;
-        if (d < nd) {
-            for (int t = CHAINED ? tile - 1 : -1; t >= 0;) {
-                u32 v[PREP_LOOK];
+        for (int j = 0; j < PER; ++j) {
+            look[j] = j * THREADS + (int)threadIdx.x < nd ? tile - 1 : -1;
+            more |= look[j] >= 0;
+        }
+        while (more) {
+            u32 v[PER][PREP_LOOK];
 #pragma unroll
-                for (int i = 0; i < PREP_LOOK; ++i) v[i] = t - i >= 0 ? peek(P.state + (size_t)(t - i) * nd + d) : PREP_INCL;
-                bool open = true;               // every nearer word was there and not yet a sum
-                bool done = false;
-                int used = 0;
+            for (int j = 0; j < PER; ++j)
 #pragma unroll
-                for (int i = 0; i < PREP_LOOK; ++i) {
-                    if (open) {
-                        if (v[i] == 0u) {
-                            open = false;
-                        } else if (v[i] >= PREP_INCL) {
-                            below[j] += v[i] - PREP_INCL;
-                            open = false;
-                            done = true;
-                        } else {
-                            below[j] += v[i] - 1u;
-                            ++used;
+                for (int i = 0; i < PREP_LOOK; ++i)
+                    v[j][i] = look[j] - i >= 0 ? peek(P.state + (size_t)(look[j] - i) * nd + j * THREADS + threadIdx.x) : PREP_INCL;
+            more = false;
+            bool any = false;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                if (look[j] >= 0) {
+                    bool open = true;           // every nearer word was there and not yet a sum
+                    int used = 0;
+#pragma unroll
+                    for (int i = 0; i < PREP_LOOK; ++i) {
+                        if (open) {
+                            if (v[j][i] == 0u) {
+                                open = false;
+                            } else if (v[j][i] >= PREP_INCL) {
+                                below[j] += v[j][i] - PREP_INCL;
+                                open = false;
+                                used = look[j] + 1;
+                            } else {
+                                below[j] += v[j][i] - 1u;
+                                ++used;
+                            }
                         }
                     }
+                    look[j] -= used;
+                    any |= used > 0;
+                    more |= look[j] >= 0;
+                    if (tile > 0 && look[j] < 0) post(&mine[j * THREADS + threadIdx.x], PREP_INCL + below[j] + count[j]);
                 }
-                if (done) break;
-                t -= used;
-                if (used == 0) __builtin_amdgcn_s_sleep(1);
             }
-            if (CHAINED && tile > 0) post(&mine[d], PREP_INCL + below[j] + count[j]);
-            dbase[d] = et + below[j] - ec;         // where the tile's i-th key in digit order goes: dbase[digit] + i
-#pragma unroll
-            for (int w = 0; w < L::NW; ++w) whp[w * nd + d] += ec;
+            if (!any) __builtin_amdgcn_s_sleep(1);
         }
-        et += total[j];
-        ec += count[j];
+    }
+    u32 t0 = 0, c0 = 0;                         // keys of the digits before this round's: in the list, in the tile
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int d = j * THREADS + (int)threadIdx.x;
+        if (j * THREADS < nd) {
+            u32 et, ec, tt, tc;
+            prep_scan2<THREADS>(total[j], count[j], et, ec, tt, tc, sm + 2 * L::NW * j);
+            if (d < nd) {
+                dbase[d] = t0 + et + below[j] - (c0 + ec);   // where the tile's i-th key in digit order goes: dbase[digit] + i
+#pragma unroll
+                for (int w = 0; w < L::NW; ++w) whp[w * nd + d] += c0 + ec;
+            }
+            t0 += tt;
+            c0 += tc;
+        }
     }
     __syncthreads();
 #pragma unroll
@@ -558,11 +596,17 @@ __device__ __forceinline__ void prep_segments(const PrepSegments &a, int block, 
 }
 
 // ---------------------------------------------------------------- a phase, as a kernel's or a rider's workgroup
+#define PREP_SEG_LDS 64      // LDS words of the segments
 template <int THREADS>
-struct PrepLds {
-    static constexpr int keys = 2 * TN_RADIX_MAX_PASSES_ND;
-    static constexpr int words = PassLds<THREADS>::words > keys ? PassLds<THREADS>::words : keys;
-};
+static inline unsigned prep_lds_bytes(const PrepPhase &x)
+{
+    switch (x.kind) {
+    case PREP_KEYS: return 4u * (unsigned)(2 * x.keys.passes << x.keys.bits);
+    case PREP_PASS: case PREP_PASS_COUNTED: return 4u * (unsigned)PassLds<THREADS>::words(1 << x.pass.bits);
+    case PREP_COUNT: return 4u << x.pass.bits;
+    default: return 4u * PREP_SEG_LDS;
+    }
+}
 
 // a phase of a chained preparation; KEYS: it may be the keys (which ride with the forward pass only)
 template <int THREADS, bool KEYS>
@@ -573,8 +617,9 @@ __device__ __forceinline__ void prep_block(const PrepPhase &x, int block, u32 *l
     else prep_segments<THREADS, true, false>(x.seg, block, lds);
 }
 
-// LDS of the launches that phases ride in: dynamic, and asked for only where one does, so that a launch without riders
+// LDS of these launches: dynamic, and asked for only where a phase rides, so that a launch without riders
 // leaves the LDS to the kernels of another stream (a forward pass that held 18 KB per workgroup kept the sort beside
 // it off the chip: step with hot rows 581 -> 615 us).
-extern __shared__ u32 ride_lds[];
-static inline unsigned ride_lds_bytes(const PrepPhase &x) { return x.blocks ? 4u * PrepLds<BLOCK>::words : 0u; }
+extern __shared__ __attribute__((aligned(16))) u32 ride_lds[];
+template <int THREADS = BLOCK>
+static inline unsigned ride_lds_bytes(const PrepPhase &x) { return x.blocks ? prep_lds_bytes<THREADS>(x) : 0u; }

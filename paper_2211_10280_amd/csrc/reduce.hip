@@ -27,7 +27,7 @@ __device__ __forceinline__ void entry_source(const SegReduceArgs &a, u32 val, co
     }
 }
 
-template <typename T, int NQ, bool TAIL, int MODE, int TILE>
+template <typename T, int NQ, bool TAIL, int MODE>
 __device__ __forceinline__ void segreduce_tile(const SegReduceArgs &a, int block)
 {
     typedef WaveRow<NQ, TAIL> Row;
@@ -36,11 +36,11 @@ __device__ __forceinline__ void segreduce_tile(const SegReduceArgs &a, int block
     const int tile = block * WAVES_PER_BLOCK + uniform((int)(threadIdx.x >> 6));
     const int lane = lane_id();
     SegWindow win;
-    if (!win.load<TILE>(a, tile)) return;
+    if (!win.load(a, tile)) return;
     const T *row_l = nullptr;
     float scale_l = 0.f;
     if (lane < win.avail) entry_source<T, MODE>(a, win.val_l, row_l, scale_l);
-    if (!win.split<TILE>(a)) return;
+    if (!win.split(a)) return;
     const int seg_l = win.seg_l, e_begin = win.e_begin, e_end = win.e_end;
     const u64 heads = win.heads;
     int dest = win.dest;             // of the current row: 0 out_rows, 1 part[tile][0], 2 part[tile][1]
@@ -100,7 +100,7 @@ __device__ __forceinline__ void segreduce_tile(const SegReduceArgs &a, int block
                         flush();
                         acc.zero();
                         cur = rd_lane(seg_l, hd[x]);
-                        dest = win.template row_dest<TILE>(hd[x]);
+                        dest = win.row_dest(hd[x]);
                     }
                     acc.axpy(sc[x], r[x]);
                 }
@@ -129,7 +129,7 @@ __device__ __forceinline__ void segreduce_tile(const SegReduceArgs &a, int block
                     flush();
                     acc.zero();
                     cur = sg[x];
-                    dest = win.template row_dest<TILE>(e);
+                    dest = win.row_dest(e);
                 }
                 acc.axpy(sc[x], r[x]);
             }
@@ -139,7 +139,7 @@ __device__ __forceinline__ void segreduce_tile(const SegReduceArgs &a, int block
     if (dest == 2) seg_note_long(a, tile);
 }
 
-template <typename T, int NQ, bool TAIL, int TILE_OUT, int TILE_IN>
+template <typename T, int NQ, bool TAIL>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(NQ == 1 || (NQ == 2 && sizeof(T) == 2 && !TAIL) ? 8 : NQ == 4 ? 5 : 1)))
 k_segreduce(SegReducePair p, AuxWork aux)
 {
@@ -149,28 +149,19 @@ k_segreduce(SegReducePair p, AuxWork aux)
         return;
     }
     const int b = (int)blockIdx.x - aux.total;
-    if (b < p.blocks_in) segreduce_tile<float, NQ, TAIL, 1, TILE_IN>(p.in, b);
-    else segreduce_tile<T, NQ, TAIL, 0, TILE_OUT>(p.out, b - p.blocks_in);
+    if (b < p.blocks_in) segreduce_tile<float, NQ, TAIL, 1>(p.in, b);
+    else segreduce_tile<T, NQ, TAIL, 0>(p.out, b - p.blocks_in);
 }
 
 // ITERS: float4 registers per lane of a whole row (the chaining kernels' layout); TAIL: the reduction
 // holds rows as ITERS-1 float4 and one float per lane instead (dimensions just above a multiple of 256)
-template <typename T, int ITERS, bool TAIL, int TILE_OUT, int TILE_IN>
-static void launch_segreduce_i(SegReducePair &p, const AuxWork &aux, const PrepPhase &rider, hipStream_t st)
-{
-    constexpr int NQ = TAIL ? ITERS - 1 : ITERS;
-    launch_segreduce_tiles<WideChain<ITERS>, TILE_OUT, TILE_IN>(p, rider, st, [&](int blocks) {
-        hipLaunchKernelGGL((k_segreduce<T, NQ, TAIL, TILE_OUT, TILE_IN>), dim3(aux.total + blocks), dim3(BLOCK), aux_lds_bytes(aux), st,
-                           p, aux);
-    });
-}
-
 template <typename T, int ITERS, bool TAIL>
 static void launch_segreduce_t(SegReducePair &p, const AuxWork &aux, const PrepPhase &rider, hipStream_t st)
 {
-    const bool so = tn_seg_tile(p.out.n, p.out.D) == 8, si = tn_seg_tile(p.in.n, p.in.D) == 8;
-    if (so) si ? launch_segreduce_i<T, ITERS, TAIL, 8, 8>(p, aux, rider, st) : launch_segreduce_i<T, ITERS, TAIL, 8, 32>(p, aux, rider, st);
-    else si ? launch_segreduce_i<T, ITERS, TAIL, 32, 8>(p, aux, rider, st) : launch_segreduce_i<T, ITERS, TAIL, 32, 32>(p, aux, rider, st);
+    constexpr int NQ = TAIL ? ITERS - 1 : ITERS;
+    launch_segreduce_tiles<WideChain<ITERS>>(p, rider, st, [&](int blocks) {
+        hipLaunchKernelGGL((k_segreduce<T, NQ, TAIL>), dim3(aux.total + blocks), dim3(BLOCK), aux_lds_bytes(aux), st, p, aux);
+    });
 }
 
 template <typename T>

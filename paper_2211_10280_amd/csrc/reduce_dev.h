@@ -14,14 +14,15 @@
 #define SEG_RUNS 1
 #endif
 
-// One wave per tile of TILE (<= 32) sorted entries.  A row (segment) of at most TILE entries is
+// One wave per tile of up to 32 sorted entries.  A row (segment) of at most a tile's entries is
 // "short": it is summed completely, in sorted order, by the wave whose tile contains its first
 // entry, even where it runs into the next tile, and written once.  Longer rows are "long": every
 // tile sums the part of the row that lies inside it into a partial (part[tile][0] for a row that
 // began in an earlier tile, part[tile][1] for one that begins here), and k_segfixup chains the
-// partials in tile order.  Work per wave is bounded by 2*TILE entries whatever the skew of the ids.
+// partials in tile order.  Work per wave is bounded by two tiles whatever the skew of the ids.
 struct SegWindow {
     int tile, t0, avail, tile_len;   // the tile, its first entry, entries in the window (two tiles), in the tile
+    int tile_size;
     int seg_l;                       // lane l: row and value of entry t0 + l
     u32 val_l;
     int first_start;                 // first entry of the row that entry t0 belongs to
@@ -40,22 +41,21 @@ struct SegWindow {
         if (later) return e + 1 + (int)__builtin_ctzll(later);
         return at_end ? avail : -1;
     }
-    template <int TILE>
     __device__ __forceinline__ int row_dest(int e) const   // of a row that begins at e
     {
         const int end = row_end(e);
-        return ((end < 0) || (end - e) > TILE) ? 2 : 0;
+        return ((end < 0) || (end - e) > tile_size) ? 2 : 0;
     }
     // rows and values of the window; false: no such tile
-    template <int TILE>
     __device__ __forceinline__ bool load(const SegReduceArgs &a, int tile_)
     {
-        static_assert(2 * TILE <= WAVE, "a wave keeps the metadata of two tiles in its lanes");
+        static_assert(2 * TN_SEG_MAX_TILE <= WAVE, "a wave keeps the metadata of two tiles in its lanes");
         tile = tile_;
-        t0 = tile * TILE;
+        tile_size = 1 << a.shift;
+        t0 = tile << a.shift;
         if (t0 >= a.n) return false;
-        tile_len = min(a.n, t0 + TILE) - t0;
-        avail = min(2 * TILE, a.n - t0);
+        tile_len = min(a.n, t0 + tile_size) - t0;
+        avail = min(2 * tile_size, a.n - t0);
         const int lane = lane_id();
         seg_l = -1;
         val_l = 0;
@@ -66,7 +66,6 @@ struct SegWindow {
         return true;
     }
     // false: nothing to sum
-    template <int TILE>
     __device__ __forceinline__ bool split(const SegReduceArgs &a)
     {
         const int lane = lane_id();
@@ -77,7 +76,7 @@ struct SegWindow {
         at_end = (t0 + avail == a.n);
         e_begin = dest = last_dest = 0;
         const int fe = row_end(0);
-        const bool lead_long = (fe < 0) || (t0 + fe - first_start) > TILE;
+        const bool lead_long = (fe < 0) || (t0 + fe - first_start) > tile_size;
         if (first_start < t0) {
             if (lead_long) dest = 1;
             else e_begin = fe;                          // short row owned by an earlier tile
@@ -87,7 +86,7 @@ struct SegWindow {
         const u64 in_tile = heads & ((tile_len < 64) ? ((1ull << tile_len) - 1ull) : ~0ull);
         if (in_tile) {
             const int h_last = 63 - (int)__builtin_clzll(in_tile);
-            last_dest = row_dest<TILE>(h_last);
+            last_dest = row_dest(h_last);
             e_end = last_dest ? tile_len : row_end(h_last);
         } else {
             last_dest = 1;
@@ -97,7 +96,7 @@ struct SegWindow {
         if (a.cross && (tile % TN_SEG_XBLOCK) == 0 && tile > 0 && lane == 0)
             a.xinfo[tile / TN_SEG_XBLOCK] = (first_start < t0 && dest == 1) ? 1 : 0;
         if (e_begin >= e_end) return false;
-        if (e_begin > 0) dest = row_dest<TILE>(e_begin);   // the first owned row begins at e_begin
+        if (e_begin > 0) dest = row_dest(e_begin);   // the first owned row begins at e_begin
         return true;
     }
 };
@@ -187,16 +186,16 @@ __device__ __forceinline__ void chain_store(float *dst, int D, float (*red)[Chai
 
 // Chains the partials of long rows in tile order: one workgroup per long row (grid-strided
 // over the list the reduction left), its waves sharing the chain part[tile][1], part[tile+1][0], ...
-template <typename Chain, int TILE>
+template <typename Chain>
 __device__ __forceinline__ void segfixup_rows(const SegReduceArgs &a, int first, int stride, float (*red)[Chain::row])
 {
     const int count = *a.long_cnt;
     for (int i = first; i < count; i += stride) {
         const int tile = a.long_list[i];
-        const int t1 = min(a.n, tile * TILE + TILE);
+        const int t1 = min(a.n, (tile + 1) << a.shift);
         const int row = a.seg_of[t1 - 1];
         const int end = a.seg_start[row + 1];
-        const int len = (end - 1) / TILE - tile;   // tiles after this one that hold a leading partial
+        const int len = ((end - 1) >> a.shift) - tile;   // tiles after this one that hold a leading partial
         // the chain: leading partials of the tiles up to the next border of a tile block, then one
         // partial per tile block (k_segcross), the last of which ends where the row ends
         const int b1 = tile / TN_SEG_XBLOCK + 1;
@@ -215,52 +214,52 @@ __device__ __forceinline__ void segfixup_rows(const SegReduceArgs &a, int first,
 // grouped in blocks of TN_SEG_XBLOCK; at most one long row crosses the border at the start of a block,
 // and this kernel sums that row's leading partials inside the block into cross[block], all blocks in
 // parallel.  k_segfixup then adds one partial per block instead of one per tile.
-template <typename Chain, int TILE>
+template <typename Chain>
 __device__ __forceinline__ void segcross_block(const SegReduceArgs &a, int b, float (*red)[Chain::row])
 {
     const int t0 = b * TN_SEG_XBLOCK;
-    const i64 e0 = (i64)t0 * TILE;
+    const i64 e0 = (i64)t0 << a.shift;
     if (b < 1 || e0 >= a.n || a.xinfo[b] == 0) return;
     const int row = a.seg_of[e0];
     const int start = a.seg_start[row];
     const int end = a.seg_start[row + 1];
-    if (start >= e0 || end - start <= TILE) return;   // no row crosses the border, or a short one (no partials)
-    const int last_tile = (end - 1) / TILE;
+    if (start >= e0 || end - start <= (1 << a.shift)) return;   // no row crosses the border, or a short one (no partials)
+    const int last_tile = (end - 1) >> a.shift;
     const int cnt = (last_tile < t0 + TN_SEG_XBLOCK - 1 ? last_tile : t0 + TN_SEG_XBLOCK - 1) - t0 + 1;
     Chain::sum(a.D, cnt, nullptr, [&](int j) { return a.part + (size_t)(t0 + j) * 2 * a.D; }, red);
     chain_store<Chain>(a.cross + (size_t)b * a.D, a.D, red);
 }
 
-template <typename Chain, int TILE_OUT, int TILE_IN>
+template <typename Chain>
 __global__ void __launch_bounds__(FIXUP_THREADS) k_segcross(SegReducePair p)
 {
     __shared__ float red[FIXUP_WAVES][Chain::row];
     const int b = blockIdx.x;
-    if (b < p.blocks_in) segcross_block<Chain, TILE_IN>(p.in, b, red);
-    else segcross_block<Chain, TILE_OUT>(p.out, b - p.blocks_in, red);
+    if (b < p.blocks_in) segcross_block<Chain>(p.in, b, red);
+    else segcross_block<Chain>(p.out, b - p.blocks_in, red);
 }
 
-template <typename Chain, int TILE_OUT, int TILE_IN>
+template <typename Chain>
 __global__ void __launch_bounds__(FIXUP_THREADS) k_segfixup(SegReducePair p, PrepPhase rider)
 {
-    constexpr int LDS = FIXUP_WAVES * Chain::row;
-    __shared__ __attribute__((aligned(16))) u32 lds[LDS > PrepLds<FIXUP_THREADS>::words ? LDS : PrepLds<FIXUP_THREADS>::words];
     if ((int)blockIdx.x < rider.blocks) {
-        prep_block<FIXUP_THREADS, false>(rider, (int)blockIdx.x, lds);
+        prep_block<FIXUP_THREADS, false>(rider, (int)blockIdx.x, ride_lds);
         return;
     }
-    float (*red)[Chain::row] = (float (*)[Chain::row])lds;
+    float (*red)[Chain::row] = (float (*)[Chain::row])ride_lds;
     const int b = (int)blockIdx.x - rider.blocks, blocks = (int)gridDim.x - rider.blocks;
-    if (b < p.blocks_in) segfixup_rows<Chain, TILE_IN>(p.in, b, p.blocks_in, red);
-    else segfixup_rows<Chain, TILE_OUT>(p.out, b - p.blocks_in, blocks - p.blocks_in, red);
+    if (b < p.blocks_in) segfixup_rows<Chain>(p.in, b, p.blocks_in, red);
+    else segfixup_rows<Chain>(p.out, b - p.blocks_in, blocks - p.blocks_in, red);
 }
 
-// the launches of a reduction in tiles of TILE_OUT and TILE_IN entries; reduce(workgroups of the two problems): its own
-template <typename Chain, int TILE_OUT, int TILE_IN, typename Reduce>
+// the launches of a reduction; reduce(workgroups of the two problems): its own
+template <typename Chain, typename Reduce>
 static void launch_segreduce_tiles(SegReducePair &p, const PrepPhase &rider, hipStream_t st, Reduce reduce)
 {
-    const int tiles_out = p.out.n > 0 ? (p.out.n + TILE_OUT - 1) / TILE_OUT : 0;
-    const int tiles_in = p.in.n > 0 ? (p.in.n + TILE_IN - 1) / TILE_IN : 0;
+    p.out.shift = tn_seg_shift(p.out.n, p.out.D);
+    p.in.shift = tn_seg_shift(p.in.n, p.in.D);
+    const int tiles_out = p.out.n > 0 ? (int)tn_seg_tiles(p.out.n, p.out.D) : 0;
+    const int tiles_in = p.in.n > 0 ? (int)tn_seg_tiles(p.in.n, p.in.D) : 0;
     if (tiles_out <= TN_SEG_CROSS_MIN) p.out.cross = nullptr;
     if (tiles_in <= TN_SEG_CROSS_MIN) p.in.cross = nullptr;
     const int blocks_out = (tiles_out + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
@@ -273,12 +272,13 @@ static void launch_segreduce_tiles(SegReducePair &p, const PrepPhase &rider, hip
     const int xb_in = tiles_in > TN_SEG_CROSS_MIN ? (tiles_in + TN_SEG_XBLOCK - 1) / TN_SEG_XBLOCK : 0;
     if (xb_out + xb_in > 0) {
         p.blocks_in = xb_in;
-        hipLaunchKernelGGL((k_segcross<Chain, TILE_OUT, TILE_IN>), dim3(xb_in + xb_out), dim3(FIXUP_THREADS), 0, st, p);
+        hipLaunchKernelGGL((k_segcross<Chain>), dim3(xb_in + xb_out), dim3(FIXUP_THREADS), 0, st, p);
     }
     const int fix_out = tn_seg_chains(p.out.n, p.out.D), fix_in = tn_seg_chains(p.in.n, p.in.D);
     if (fix_out + fix_in > 0) {
         p.blocks_in = fix_in;
-        hipLaunchKernelGGL((k_segfixup<Chain, TILE_OUT, TILE_IN>), dim3(rider.blocks + fix_out + fix_in), dim3(FIXUP_THREADS), 0,
-                           st, p, rider);
+        const unsigned own = 4u * FIXUP_WAVES * Chain::row, riding = ride_lds_bytes<FIXUP_THREADS>(rider);
+        hipLaunchKernelGGL((k_segfixup<Chain>), dim3(rider.blocks + fix_out + fix_in), dim3(FIXUP_THREADS),
+                           own > riding ? own : riding, st, p, rider);
     }
 }

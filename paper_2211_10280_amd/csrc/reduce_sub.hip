@@ -10,14 +10,14 @@
 #define SEG_SUB_UNROLL 4     // rows in flight per group
 #endif
 
-template <typename T, int SUB, int MODE, int TILE>
+template <typename T, int SUB, int MODE>
 __device__ __forceinline__ void segreduce_tile_sub(const SegReduceArgs &a, int block)
 {
     constexpr int RPW = WAVE / SUB, UNROLL = SEG_SUB_UNROLL;
     const int tile = block * WAVES_PER_BLOCK + uniform((int)(threadIdx.x >> 6));
     const int lane = lane_id();
     SegWindow win;
-    if (!win.load<TILE>(a, tile)) return;
+    if (!win.load(a, tile)) return;
     // where entry t0 + lane comes from: a row of the table (MODE 0) or of the centers' partial rows, and its scale
     int src_l = 0;
     float scale_l = 0.f;
@@ -30,7 +30,7 @@ __device__ __forceinline__ void segreduce_tile_sub(const SegReduceArgs &a, int b
             scale_l = 1.0f;
         }
     }
-    if (!win.split<TILE>(a)) return;
+    if (!win.split(a)) return;
     const int e_begin = win.e_begin, e_end = win.e_end;
     int seg_l = win.seg_l;
 
@@ -153,7 +153,7 @@ __device__ __forceinline__ void segreduce_tile_sub(const SegReduceArgs &a, int b
     if (win.last_dest == 2) seg_note_long(a, tile);
 }
 
-template <typename T, int SUB, int TILE_OUT, int TILE_IN>
+template <typename T, int SUB>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8)))
 k_segreduce_sub(SegReducePair p, AuxWork aux)
 {
@@ -163,26 +163,16 @@ k_segreduce_sub(SegReducePair p, AuxWork aux)
         return;
     }
     const int b = (int)blockIdx.x - aux.total;
-    if (b < p.blocks_in) segreduce_tile_sub<float, SUB, 1, TILE_IN>(p.in, b);
-    else segreduce_tile_sub<T, SUB, 0, TILE_OUT>(p.out, b - p.blocks_in);
-}
-
-template <typename T, int SUB, int TILE_OUT, int TILE_IN>
-static void launch_segreduce_i(SegReducePair &p, const AuxWork &aux, const PrepPhase &rider, hipStream_t st)
-{
-    launch_segreduce_tiles<GroupChain<SUB>, TILE_OUT, TILE_IN>(p, rider, st, [&](int blocks) {
-        hipLaunchKernelGGL((k_segreduce_sub<T, SUB, TILE_OUT, TILE_IN>), dim3(aux.total + blocks), dim3(BLOCK), aux_lds_bytes(aux), st,
-                           p, aux);
-    });
+    if (b < p.blocks_in) segreduce_tile_sub<float, SUB, 1>(p.in, b);
+    else segreduce_tile_sub<T, SUB, 0>(p.out, b - p.blocks_in);
 }
 
 template <typename T, int SUB>
 static void launch_segreduce_t(SegReducePair &p, const AuxWork &aux, const PrepPhase &rider, hipStream_t st)
 {
-    constexpr int S = SEG_SUB_TILE;
-    const bool so = tn_seg_tile(p.out.n, p.out.D) == S, si = tn_seg_tile(p.in.n, p.in.D) == S;
-    if (so) si ? launch_segreduce_i<T, SUB, S, S>(p, aux, rider, st) : launch_segreduce_i<T, SUB, S, 32>(p, aux, rider, st);
-    else si ? launch_segreduce_i<T, SUB, 32, S>(p, aux, rider, st) : launch_segreduce_i<T, SUB, 32, 32>(p, aux, rider, st);
+    launch_segreduce_tiles<GroupChain<SUB>>(p, rider, st, [&](int blocks) {
+        hipLaunchKernelGGL((k_segreduce_sub<T, SUB>), dim3(aux.total + blocks), dim3(BLOCK), aux_lds_bytes(aux), st, p, aux);
+    });
 }
 
 template <typename T>

@@ -5,21 +5,18 @@
 
 __global__ void __launch_bounds__(BLOCK) k_prep_keys(PrepPhase x)
 {
-    __shared__ u32 lds[2 * TN_RADIX_MAX_PASSES_ND];
-    prep_keys<BLOCK>(x.keys, (int)blockIdx.x, (int)gridDim.x, lds);
+    prep_keys<BLOCK>(x.keys, (int)blockIdx.x, (int)gridDim.x, ride_lds);
 }
 
 template <bool CHAINED>
 __global__ void __launch_bounds__(BLOCK) k_prep_pass(PrepPhase x)
 {
-    __shared__ u32 lds[PassLds<BLOCK>::words];
-    prep_pass<BLOCK, CHAINED>(x.pass, (int)blockIdx.x, lds);
+    prep_pass<BLOCK, CHAINED>(x.pass, (int)blockIdx.x, ride_lds);
 }
 
 __global__ void __launch_bounds__(BLOCK) k_prep_count(PrepPhase x)
 {
-    __shared__ u32 lds[TN_RADIX_MAX_ND];
-    prep_count<BLOCK>(x.pass, (int)blockIdx.x, lds);
+    prep_count<BLOCK>(x.pass, (int)blockIdx.x, ride_lds);
 }
 
 // grid: (digits / WAVE, 2 lists)
@@ -32,24 +29,24 @@ __global__ void __launch_bounds__(WAVE) k_prep_scan(PrepPhase x)
 template <bool CHAINED, bool HEADS>
 __global__ void __launch_bounds__(BLOCK) k_prep_segments(PrepPhase x)
 {
-    __shared__ u32 lds[64];
-    prep_segments<BLOCK, CHAINED, HEADS>(x.seg, (int)blockIdx.x, lds);
+    prep_segments<BLOCK, CHAINED, HEADS>(x.seg, (int)blockIdx.x, ride_lds);
 }
 
 void tn_launch_prep(const PrepPhase &x, hipStream_t st)
 {
     const dim3 grid(x.blocks), blk(BLOCK);
+    const unsigned lds = prep_lds_bytes<BLOCK>(x);
     switch (x.kind) {
-    case PREP_KEYS: hipLaunchKernelGGL(k_prep_keys, grid, blk, 0, st, x); break;
-    case PREP_PASS: hipLaunchKernelGGL(k_prep_pass<true>, grid, blk, 0, st, x); break;
-    case PREP_SEGMENTS: hipLaunchKernelGGL((k_prep_segments<true, false>), grid, blk, 0, st, x); break;
+    case PREP_KEYS: hipLaunchKernelGGL(k_prep_keys, grid, blk, lds, st, x); break;
+    case PREP_PASS: hipLaunchKernelGGL(k_prep_pass<true>, grid, blk, lds, st, x); break;
+    case PREP_SEGMENTS: hipLaunchKernelGGL((k_prep_segments<true, false>), grid, blk, lds, st, x); break;
     case PREP_COUNT:
-        hipLaunchKernelGGL(k_prep_count, grid, blk, 0, st, x);
+        hipLaunchKernelGGL(k_prep_count, grid, blk, lds, st, x);
         if (x.pass.scanned) hipLaunchKernelGGL(k_prep_scan, dim3(((1 << x.pass.bits) + WAVE - 1) / WAVE, 2), dim3(WAVE), 0, st, x);
         break;
-    case PREP_PASS_COUNTED: hipLaunchKernelGGL(k_prep_pass<false>, grid, blk, 0, st, x); break;
-    case PREP_HEADS: hipLaunchKernelGGL((k_prep_segments<false, true>), grid, blk, 0, st, x); break;
-    default: hipLaunchKernelGGL((k_prep_segments<false, false>), grid, blk, 0, st, x); break;
+    case PREP_PASS_COUNTED: hipLaunchKernelGGL(k_prep_pass<false>, grid, blk, lds, st, x); break;
+    case PREP_HEADS: hipLaunchKernelGGL((k_prep_segments<false, true>), grid, blk, lds, st, x); break;
+    default: hipLaunchKernelGGL((k_prep_segments<false, false>), grid, blk, lds, st, x); break;
     }
 }
 

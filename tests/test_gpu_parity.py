@@ -217,6 +217,17 @@ def test_sgns_grad_parity_of_narrow_rows(case):
     _grad_parity(case)
 
 
+# occurrences at which the reduction takes larger tiles (8 192, 32 768) and the keys more slots per workgroup (16 384,
+# 65 536): 64 per position, the last of each size and one position more; hot rows that run through many tiles
+TILE_CASES = [(V, 132, 132, 20_000, 1.2, 4, 7, n // 64 + more, 500, "f32")
+              for V in (40, 5_000) for n in (8_192, 16_384, 32_768, 65_536) for more in (0, 1)]
+
+
+@pytest.mark.parametrize("case", TILE_CASES, ids=lambda c: f"V{c[0]}_B{c[7]}")
+def test_sgns_grad_parity_at_the_borders_of_its_tiles(case):
+    _grad_parity(case)
+
+
 def _random_grad_cases(n, seed):
     """Seeded shapes: narrow to wide rows, windows 1..6, 0..12 negatives, batches from one center up, streams
     from flat to steep, vocabularies from two words up, batches at the start, inside and at the end of the
