@@ -222,78 +222,106 @@ __global__ void __launch_bounds__(BLOCK) k_union_offsets(GradSumArgs g)
     }
 }
 
-// one wave per G consecutive vocabulary rows of both tables, as in k_apply
-template <int ITERS, int G>
+// one wave per G consecutive vocabulary rows of both tables, as in k_apply; SWEEP: one group after the other, as there
+template <int ITERS, int G, bool SWEEP>
 __global__ void __launch_bounds__(BLOCK) k_grad_sum(GradSumArgs g, int nblocks)
 {
     const ApplyArgs &a = g.a;
     constexpr int GPW = 64 / G;
     const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
-    const int gw = blockIdx.x * WAVES_PER_BLOCK + wave;
-    const int word = gw / GPW, sub = gw - word * GPW;
     const int words = (int)((a.V + 63) >> 6);
-    if (word >= words) return;
+    const int groups = words * GPW, stride = SWEEP ? nblocks * WAVES_PER_BLOCK : groups;
+    int gw = blockIdx.x * WAVES_PER_BLOCK + wave;
+    if (gw >= groups) return;
     const int ns = a.n_src;
     const int C4 = a.D >> 2;
-    const int lo = sub * G;
 
-    u64 mk = 0;
-    u32 st = 0;
     int U = 0;
     u64 rows_ptr = 0;
+    u64 mk_next = 0, mk_after = 0;   // index words of the coming group and, in a sweep, of the one after it
+    u32 st_next = 0, st_after = 0, base_next = 0, base_after = 0;
+    const u64 *masks = nullptr;
+    const u32 *starts = nullptr;
+    const u32 *bases = g.wbase[lane >> 5];
     {
         const int tb = lane >> 5, k = lane & 31;
         if (k < ns) {
             const ApplySrc &s = a.src[tb][k];
             if (s.ids != nullptr) {
-                mk = a.mask[tb][idx_at(words, k, word)];
-                st = a.start[tb][idx_at(words, k, word)];
+                masks = a.mask[tb] + idx_at(words, k, 0);
+                starts = a.start[tb] + idx_at(words, k, 0);
+                mk_next = masks[gw / GPW];
+                st_next = starts[gw / GPW];
+                if (SWEEP && gw + stride < groups) {
+                    mk_after = masks[(gw + stride) / GPW];
+                    st_after = starts[(gw + stride) / GPW];
+                }
                 U = *s.n_rows;
                 if ((i64)U > s.capacity) U = (int)s.capacity;
                 rows_ptr = (u64)s.rows;
             }
         }
     }
-    const i64 row0 = (i64)word * 64;
-#pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-        const bool mine = (lane >> 5) == tb;
-        // rows of the word that any source has
-        const u32 ulo = (u32)uniform((int)wave_or(mine ? (u32)mk : 0u));
-        const u32 uhi = (u32)uniform((int)wave_or(mine ? (u32)(mk >> 32) : 0u));
-        const u64 uw = ((u64)uhi << 32) | ulo;
-        u64 um = (G == 64) ? uw : ((uw >> lo) & ((1ull << (G & 63)) - 1ull));
-        const u32 base = g.wbase[tb][word];
-        while (um) {
-            const int b = lo + (int)__builtin_ctzll(um);
-            um &= um - 1ull;
-            const i64 r = row0 + b;
-            const i64 dst = (i64)base + __popcll(uw & ((1ull << b) - 1ull));
-            if (r >= a.V || dst >= g.out_cap[tb]) break;   // corrupt index or overflow (both flagged)
-            const u32 pos = st + (u32)__popcll(mk & ((1ull << b) - 1ull));
-            const bool ok = mine && ((mk >> b) & 1ull) && (pos < (u32)U);
-            u64 S = __ballot(ok);
-            float4 acc[ITERS];
-            zero_row<ITERS>(acc);
-            while (S) {
-                float4 x[4][ITERS];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (S) {
-                        const int k = (int)__builtin_ctzll(S);
-                        S &= S - 1ull;
-                        const float *src = (const float *)rd_lane64(rows_ptr, k) + (size_t)(u32)rd_lane((int)pos, k) * a.D;
-                        load_row_s<float, ITERS>(x[j], src, C4, lane);   // read once: around the caches
-                    } else {
-                        zero_row<ITERS>(x[j]);
-                    }
+    base_next = bases[gw / GPW];
+    if (SWEEP && gw + stride < groups) base_after = bases[(gw + stride) / GPW];
+    for (;; gw += stride) {
+        const int word = gw / GPW, lo = (gw - word * GPW) * G;
+        const u64 mk = mk_next;
+        const u32 st = st_next, base_l = base_next;
+        if (SWEEP) {
+            mk_next = mk_after;
+            st_next = st_after;
+            base_next = base_after;
+            if (gw + 2 * (i64)stride < groups) {
+                if (masks != nullptr) {
+                    mk_after = masks[(gw + 2 * stride) / GPW];
+                    st_after = starts[(gw + 2 * stride) / GPW];
                 }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) add_row<ITERS>(acc, x[j]);
+                base_after = bases[(gw + 2 * stride) / GPW];
             }
-            store_row_s<float, ITERS>(g.out_rows[tb] + (size_t)dst * a.D, acc, C4, lane);
-            if (lane == 0) g.out_ids[tb][dst] = (int)r;
         }
+        const i64 row0 = (i64)word * 64;
+        u32 u_lo[2], u_hi[2];               // rows of the word that any source has
+        half_or((u32)mk, u_lo[0], u_lo[1]);
+        half_or((u32)(mk >> 32), u_hi[0], u_hi[1]);
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+            const bool mine = (lane >> 5) == tb;
+            const u64 uw = ((u64)u_hi[tb] << 32) | u_lo[tb];
+            u64 um = (G == 64) ? uw : ((uw >> lo) & ((1ull << (G & 63)) - 1ull));
+            const u32 base = (u32)rd_lane((int)base_l, 32 * tb);
+            while (um) {
+                const int b = lo + (int)__builtin_ctzll(um);
+                um &= um - 1ull;
+                const i64 r = row0 + b;
+                const i64 dst = (i64)base + __popcll(uw & ((1ull << b) - 1ull));
+                if (r >= a.V || dst >= g.out_cap[tb]) break;   // corrupt index or overflow (both flagged)
+                const u32 pos = st + (u32)__popcll(mk & ((1ull << b) - 1ull));
+                const bool ok = mine && ((mk >> b) & 1ull) && (pos < (u32)U);
+                u64 S = __ballot(ok);
+                float4 acc[ITERS];
+                zero_row<ITERS>(acc);
+                while (S) {
+                    float4 x[4][ITERS];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (S) {
+                            const int k = (int)__builtin_ctzll(S);
+                            S &= S - 1ull;
+                            const float *src = (const float *)rd_lane64(rows_ptr, k) + (size_t)(u32)rd_lane((int)pos, k) * a.D;
+                            load_row_s<float, ITERS>(x[j], src, C4, lane);   // read once: around the caches
+                        } else {
+                            zero_row<ITERS>(x[j]);
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) add_row<ITERS>(acc, x[j]);
+                }
+                store_row_s<float, ITERS>(g.out_rows[tb] + (size_t)dst * a.D, acc, C4, lane);
+                if (lane == 0) g.out_ids[tb][dst] = (int)r;
+            }
+        }
+        if (!SWEEP || gw + stride >= groups) break;
     }
 }
 
@@ -309,18 +337,31 @@ void tn_launch_grad_sum_index(const GradSumArgs &g, hipStream_t st)
     hipLaunchKernelGGL(k_union_offsets, dim3(sblocks, 2), dim3(BLOCK), 0, st, g);
 }
 
-void tn_launch_grad_sum_rows(const GradSumArgs &g, hipStream_t st)
+template <int G, bool SWEEP>
+static void launch_grad_sum(const GradSumArgs &g, hipStream_t st)
 {
     const ApplyArgs &a = g.a;
     const int words = (int)((a.V + 63) >> 6);
     const int iters = (a.D / 4 + WAVE - 1) / WAVE;
-    const i64 nwaves = (i64)words * (64 / GRADSUM_G);
-    const int nblocks = (int)((nwaves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+    const i64 nwaves = (i64)words * (64 / G);
+    int nblocks = (int)((nwaves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+    if (SWEEP) nblocks = sweep_blocks(nblocks);
     dim3 grid(nblocks), blk(BLOCK);
     switch (iters) {
-    case 1: hipLaunchKernelGGL((k_grad_sum<1, GRADSUM_G>), grid, blk, 0, st, g, nblocks); break;
-    case 2: hipLaunchKernelGGL((k_grad_sum<2, GRADSUM_G>), grid, blk, 0, st, g, nblocks); break;
-    case 3: hipLaunchKernelGGL((k_grad_sum<3, GRADSUM_G>), grid, blk, 0, st, g, nblocks); break;
-    default: hipLaunchKernelGGL((k_grad_sum<4, GRADSUM_G>), grid, blk, 0, st, g, nblocks); break;
+    case 1: hipLaunchKernelGGL((k_grad_sum<1, G, SWEEP>), grid, blk, 0, st, g, nblocks); break;
+    case 2: hipLaunchKernelGGL((k_grad_sum<2, G, SWEEP>), grid, blk, 0, st, g, nblocks); break;
+    case 3: hipLaunchKernelGGL((k_grad_sum<3, G, SWEEP>), grid, blk, 0, st, g, nblocks); break;
+    default: hipLaunchKernelGGL((k_grad_sum<4, G, SWEEP>), grid, blk, 0, st, g, nblocks); break;
     }
+}
+
+// Where few of a large vocabulary's rows are touched a sweep, as for the table update; buffer and message, whole calls,
+// sweep in groups of 8 / of 4 / no sweep: 200 000 words, D = 256 36.1 / 31.7 / 34.8 us; 500 000 44.2 / 43.1 / 49.1; a million
+// 52.6 / 57.1 / 70.9 and, more touched, 108 / 114 / 126; 2 million 47.2 / 63.7 / 88.6 and 150 / 165 / 190; D = 64 43.8 / 61.9 /
+// 83.8 and 86.6 / 101 / 132.
+void tn_launch_grad_sum_rows(const GradSumArgs &g, hipStream_t st)
+{
+    if (!sweep_union(g.a)) launch_grad_sum<GRADSUM_G, false>(g, st);
+    else if (g.a.V < 524288) launch_grad_sum<4, true>(g, st);
+    else launch_grad_sum<8, true>(g, st);
 }

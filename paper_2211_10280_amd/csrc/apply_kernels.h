@@ -139,6 +139,21 @@ __device__ __forceinline__ void update_row(T *wrow, u64 S, u64 rows_ptr, u32 pos
     else store_row<T, ITERS>(wrow, w, C4, lane);
 }
 
+// keep runs of APPLY_CHUNK consecutive workgroups on one XCD (workgroups are dealt
+// round-robin to the 8 XCDs), so that neighbouring rows -- which share cache lines when
+// the row size is not a multiple of the line -- meet in the same L2
+__device__ __forceinline__ int apply_block(int bid, int nblocks)
+{
+    const int per_round = 8 * APPLY_CHUNK;
+    const int full = (nblocks / per_round) * per_round;
+    if (bid < full) {
+        const int round = bid / per_round, r = bid - round * per_round;
+        const int xcd = r & 7, slot = r >> 3;
+        bid = round * per_round + xcd * APPLY_CHUNK + slot;
+    }
+    return bid;
+}
+
 // occupancy cap: wave slots for the kernels of the second stream, where a preparation too large to ride runs beside this
 // one, and a little less pressure on the memory system where nothing does; measured with table rows on 128-byte lines and
 // the preparation on the second stream: 5 / 6 / 7 / 8 waves per SIMD give a step of 0.846 / 0.836 / 0.823 / 0.828 ms at a
@@ -147,49 +162,43 @@ __device__ __forceinline__ void update_row(T *wrow, u64 S, u64 rows_ptr, u32 pos
 #ifndef APPLY_MAX_WAVES
 #define APPLY_MAX_WAVES 7
 #endif
-template <typename T, int ITERS, int G, bool STREAM, bool PACKED, typename Rider>
+// SWEEP: a wave takes one group of rows after the other, `stride` apart (see launch_apply_t); else one.
+template <typename T, int ITERS, int G, bool STREAM, bool PACKED, bool SWEEP, typename Rider>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, APPLY_MAX_WAVES)))
 k_apply(ApplyArgs a, int nblocks, Rider rider)
 {
     if (rider.block()) return;
-    // keep runs of APPLY_CHUNK consecutive workgroups on one XCD (workgroups are dealt
-    // round-robin to the 8 XCDs), so that neighbouring rows -- which share cache lines when
-    // the row size is not a multiple of the line -- meet in the same L2
-    int bid = (int)blockIdx.x - rider.blocks();
-    {
-        const int per_round = 8 * APPLY_CHUNK;
-        int full = (nblocks / per_round) * per_round;
-        if (bid < full) {
-            int round = bid / per_round, r = bid - round * per_round;
-            int xcd = r & 7, slot = r >> 3;
-            bid = round * per_round + xcd * APPLY_CHUNK + slot;
-        }
-    }
+    const int bid = SWEEP ? (int)blockIdx.x - rider.blocks() : apply_block((int)blockIdx.x - rider.blocks(), nblocks);
     constexpr int GPW = 64 / G;
     const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
-    const int gw = bid * WAVES_PER_BLOCK + wave;
-    const int word = gw / GPW, sub = gw - word * GPW;
     const int words = (int)((a.V + 63) >> 6);
-    if (word >= words) return;
+    const int groups = words * GPW, stride = SWEEP ? nblocks * WAVES_PER_BLOCK : groups;
+    int gw = bid * WAVES_PER_BLOCK + wave;
+    if (gw >= groups) return;
     const int ns = a.n_src;
     const int C4 = a.D >> 2;
 
     // lanes 0..31 hold W_in's sources, lanes 32..63 W_out's: lane 32*tb + k has source k's rows
     // inside this wave's group of rows of table tb
-    u64 m = 0;
-    u32 st = 0;
     int U = 0;
     u64 rows_ptr = 0;
+    u64 mk_next = 0, mk_after = 0;   // index words of the coming group and, in a sweep, of the one after it
+    u32 st_next = 0, st_after = 0;
+    const u64 *masks = nullptr;      // of this lane's source, by word
+    const u32 *starts = nullptr;
     {
         const int tb = lane >> 5, k = lane & 31;
         if (k < ns) {
             const ApplySrc &s = a.src[tb][k];
             if (s.ids != nullptr) {
-                u64 mk = a.mask[tb][idx_at(words, k, word)];
-                st = a.start[tb][idx_at(words, k, word)];
-                const int lo = sub * G;
-                st += (u32)__popcll(mk & ((1ull << lo) - 1ull));
-                m = (G == 64) ? mk : ((mk >> lo) & ((1ull << (G & 63)) - 1ull));
+                masks = a.mask[tb] + idx_at(words, k, 0);
+                starts = a.start[tb] + idx_at(words, k, 0);
+                mk_next = masks[gw / GPW];
+                st_next = starts[gw / GPW];
+                if (SWEEP && gw + stride < groups) {
+                    mk_after = masks[(gw + stride) / GPW];
+                    st_after = starts[(gw + stride) / GPW];
+                }
                 U = *s.n_rows;
                 if ((i64)U > s.capacity) U = (int)s.capacity;
                 rows_ptr = (u64)s.rows;
@@ -198,37 +207,50 @@ k_apply(ApplyArgs a, int nblocks, Rider rider)
         }
     }
     const float neg_lr = -a.lr;
-    const i64 row0 = (i64)word * 64 + sub * G;
 
-#pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-        const bool mine = (lane >> 5) == tb;
-        u64 um;
-        {
-            u32 lo32 = (u32)uniform((int)wave_or(mine ? (u32)m : 0u));
-            u32 hi32 = (G > 32) ? (u32)uniform((int)wave_or(mine ? (u32)(m >> 32) : 0u)) : 0u;
-            um = ((u64)hi32 << 32) | lo32;
-        }
-        T *table = (T *)a.table[tb];
-        while (um) {
-            const int b = (int)__builtin_ctzll(um);
-            um &= um - 1ull;
-            const i64 r = row0 + b;
-            if (r >= a.V) break;   // only reachable with a corrupt index (flagged input)
-            // per lane: position of row r in its source (if present and in bounds)
-            const u32 pos = st + (u32)__popcll(m & ((1ull << b) - 1ull));
-            const bool ok = mine && ((m >> b) & 1ull) && (pos < (u32)U);
-            const u64 S = __ballot(ok);   // bit 32*tb + k: source k has row r
-            const SrArgs sr = {a.sr, a.sr_k0, a.sr_k1, a.sr_serial, 0x53524E44u + (u32)tb};
-            bf16_t *msg_row = nullptr;
-            if (PACKED && a.msg_rows[tb] != nullptr && ((S >> (32 * tb)) & 1ull)) {
-                const u32 at = (u32)rd_lane((int)pos, 32 * tb);          // place of row r in the own gradient
-                msg_row = (bf16_t *)a.msg_rows[tb] + (size_t)at * a.D;
-                if (lane == 32 * tb) a.msg_ids[tb][at] = (int)r;
+    for (;; gw += stride) {
+        const int word = gw / GPW, lo = (gw - word * GPW) * G;
+        const u64 mk = mk_next;
+        const u32 st = st_next + (u32)__popcll(mk & ((1ull << lo) - 1ull));
+        const u64 m = (G == 64) ? mk : ((mk >> lo) & ((1ull << (G & 63)) - 1ull));
+        if (SWEEP) {    // two groups ahead of the rows that are worked on
+            mk_next = mk_after;
+            st_next = st_after;
+            if (masks != nullptr && gw + 2 * (i64)stride < groups) {
+                mk_after = masks[(gw + 2 * stride) / GPW];
+                st_after = starts[(gw + 2 * stride) / GPW];
             }
-            update_row<T, ITERS, STREAM, PACKED>(table + (size_t)r * a.stride, S, rows_ptr, pos, a.D, C4, lane, neg_lr,
-                                                 32 * tb, (u64)r * (u64)C4, sr, msg_row);
         }
+        const i64 row0 = (i64)word * 64 + lo;
+        u32 um_lo[2], um_hi[2] = {0, 0};    // rows that any source has, per table
+        half_or((u32)m, um_lo[0], um_lo[1]);
+        if (G > 32) half_or((u32)(m >> 32), um_hi[0], um_hi[1]);
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+            const bool mine = (lane >> 5) == tb;
+            u64 um = ((u64)um_hi[tb] << 32) | um_lo[tb];
+            T *table = (T *)a.table[tb];
+            while (um) {
+                const int b = (int)__builtin_ctzll(um);
+                um &= um - 1ull;
+                const i64 r = row0 + b;
+                if (r >= a.V) break;   // only reachable with a corrupt index (flagged input)
+                // per lane: position of row r in its source (if present and in bounds)
+                const u32 pos = st + (u32)__popcll(m & ((1ull << b) - 1ull));
+                const bool ok = mine && ((m >> b) & 1ull) && (pos < (u32)U);
+                const u64 S = __ballot(ok);   // bit 32*tb + k: source k has row r
+                const SrArgs sr = {a.sr, a.sr_k0, a.sr_k1, a.sr_serial, 0x53524E44u + (u32)tb};
+                bf16_t *msg_row = nullptr;
+                if (PACKED && a.msg_rows[tb] != nullptr && ((S >> (32 * tb)) & 1ull)) {
+                    const u32 at = (u32)rd_lane((int)pos, 32 * tb);          // place of row r in the own gradient
+                    msg_row = (bf16_t *)a.msg_rows[tb] + (size_t)at * a.D;
+                    if (lane == 32 * tb) a.msg_ids[tb][at] = (int)r;
+                }
+                update_row<T, ITERS, STREAM, PACKED>(table + (size_t)r * a.stride, S, rows_ptr, pos, a.D, C4, lane, neg_lr,
+                                                     32 * tb, (u64)r * (u64)C4, sr, msg_row);
+            }
+        }
+        if (!SWEEP || gw + stride >= groups) break;
     }
 }
 
@@ -244,7 +266,7 @@ k_apply(ApplyArgs a, int nblocks, Rider rider)
 #ifndef APPLY_SUB_ROWS
 #define APPLY_SUB_ROWS 4   // rows per group of lanes and wave
 #endif
-template <typename T, int SUB, int ROWS, bool STREAM, typename Rider>
+template <typename T, int SUB, int ROWS, bool STREAM, bool SWEEP, typename Rider>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, APPLY_MAX_WAVES)))
 k_apply_sub(ApplyArgs a, int nblocks, Rider rider)
 {
@@ -252,38 +274,36 @@ k_apply_sub(ApplyArgs a, int nblocks, Rider rider)
     constexpr int RPW = WAVE / SUB;   // rows in one pass of a wave
     constexpr int G = (ROWS * RPW > 32) ? 32 : ROWS * RPW;   // vocabulary rows per wave
     constexpr int GPW = 64 / G;
-    int bid = (int)blockIdx.x - rider.blocks();
-    {
-        const int per_round = 8 * APPLY_CHUNK;
-        int full = (nblocks / per_round) * per_round;
-        if (bid < full) {
-            int round = bid / per_round, r = bid - round * per_round;
-            int xcd = r & 7, slot = r >> 3;
-            bid = round * per_round + xcd * APPLY_CHUNK + slot;
-        }
-    }
+    const int bid = SWEEP ? (int)blockIdx.x - rider.blocks() : apply_block((int)blockIdx.x - rider.blocks(), nblocks);
     const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
-    const int gw = bid * WAVES_PER_BLOCK + wave;
-    const int word = gw / GPW, sub = gw - word * GPW;
     const int words = (int)((a.V + 63) >> 6);
-    if (word >= words) return;
+    const int groups = words * GPW, stride = SWEEP ? nblocks * WAVES_PER_BLOCK : groups;
+    int gw = bid * WAVES_PER_BLOCK + wave;
+    if (gw >= groups) return;
     const int ns = a.n_src;
     const int C4 = a.D >> 2;
     const int slot = lane / SUB, sl = lane - slot * SUB;   // group of the lane, chunk of the row it holds
 
     // lane 32*tb + k: source k's rows inside this wave's share of table tb, as in k_apply
-    u32 m = 0, st = 0;
     int U = 0;
     u64 rows_ptr = 0;
+    u64 mk_next = 0, mk_after = 0;   // index words of the coming group and, in a sweep, of the one after it
+    u32 st_next = 0, st_after = 0;
+    const u64 *masks = nullptr;
+    const u32 *starts = nullptr;
     {
         const int tb = lane >> 5, k = lane & 31;
         if (k < ns) {
             const ApplySrc &s = a.src[tb][k];
             if (s.ids != nullptr) {
-                const u64 mk = a.mask[tb][idx_at(words, k, word)];
-                const int lo = sub * G;
-                st = a.start[tb][idx_at(words, k, word)] + (u32)__popcll(mk & ((1ull << lo) - 1ull));
-                m = (u32)((mk >> lo) & ((1ull << G) - 1ull));
+                masks = a.mask[tb] + idx_at(words, k, 0);
+                starts = a.start[tb] + idx_at(words, k, 0);
+                mk_next = masks[gw / GPW];
+                st_next = starts[gw / GPW];
+                if (SWEEP && gw + stride < groups) {
+                    mk_after = masks[(gw + stride) / GPW];
+                    st_after = starts[(gw + stride) / GPW];
+                }
                 U = *s.n_rows;
                 if ((i64)U > s.capacity) U = (int)s.capacity;
                 rows_ptr = (u64)s.rows;
@@ -292,128 +312,164 @@ k_apply_sub(ApplyArgs a, int nblocks, Rider rider)
     }
     const int ptr_lo = (int)(u32)rows_ptr, ptr_hi = (int)(u32)(rows_ptr >> 32);
     const float neg_lr = -a.lr;
-    const i64 row0 = (i64)word * 64 + sub * G;
 
+    for (;; gw += stride) {
+        const int word = gw / GPW, lo = (gw - word * GPW) * G;
+        const u64 mk = mk_next;
+        const u32 st = st_next + (u32)__popcll(mk & ((1ull << lo) - 1ull));
+        const u32 m = (u32)((mk >> lo) & ((1ull << G) - 1ull));
+        if (SWEEP) {
+            mk_next = mk_after;
+            st_next = st_after;
+            if (masks != nullptr && gw + 2 * (i64)stride < groups) {
+                mk_after = masks[(gw + 2 * stride) / GPW];
+                st_after = starts[(gw + 2 * stride) / GPW];
+            }
+        }
+        const i64 row0 = (i64)word * 64 + lo;
+        u32 um_tb[2];
+        half_or(m, um_tb[0], um_tb[1]);
 #pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-        const bool mine = (lane >> 5) == tb;
-        u32 um = (u32)uniform((int)wave_or(mine ? m : 0u));
-        T *table = (T *)a.table[tb];
-        while (um) {
-            // the next RPW rows: lane 32*tb + k works out source k's position of each, group s keeps row s
-            int pos_s[RPW];
-            u32 S_my = 0;
-            int b_my = -1;
+        for (int tb = 0; tb < 2; ++tb) {
+            const bool mine = (lane >> 5) == tb;
+            u32 um = um_tb[tb];
+            T *table = (T *)a.table[tb];
+            while (um) {
+                // the next RPW rows: lane 32*tb + k works out source k's position of each, group s keeps row s (handing the
+                // groups (start, mask) to work it out themselves lengthens the chain: step of 378 centers, D = 44 28.1 -> 30.6 us)
+                int pos_s[RPW];
+                u32 S_my = 0;
+                int b_my = -1;
 #pragma unroll
-            for (int s = 0; s < RPW; ++s) {
-                pos_s[s] = 0;
-                if (um) {
-                    const int b = (int)__builtin_ctz(um);
-                    um &= um - 1u;
-                    if (row0 + b >= a.V) {   // only reachable with a corrupt index (flagged input)
-                        um = 0;
-                    } else {
-                        const u32 pos = st + (u32)__popc(m & ((1u << b) - 1u));
-                        const bool ok = mine && ((m >> b) & 1u) && (pos < (u32)U);
-                        const u64 S = __ballot(ok);
-                        pos_s[s] = (int)pos;
-                        if (slot == s) {
-                            S_my = (u32)(S >> (32 * tb));
-                            b_my = b;
+                for (int s = 0; s < RPW; ++s) {
+                    pos_s[s] = 0;
+                    if (um) {
+                        const int b = (int)__builtin_ctz(um);
+                        um &= um - 1u;
+                        if (row0 + b >= a.V) {   // only reachable with a corrupt index (flagged input)
+                            um = 0;
+                        } else {
+                            const u32 pos = st + (u32)__popc(m & ((1u << b) - 1u));
+                            const bool ok = mine && ((m >> b) & 1u) && (pos < (u32)U);
+                            pos_s[s] = (int)pos;
+                            const u64 S = __ballot(ok);
+                            if (slot == s) {
+                                S_my = (u32)(S >> (32 * tb));
+                                b_my = b;
+                            }
                         }
                     }
                 }
-            }
-            const bool act = (b_my >= 0) && (sl < C4);
-            const i64 r = row0 + (b_my >= 0 ? b_my : 0);
-            T *wrow = table + (size_t)r * a.stride;
-            T *wp = wrow + 4 * sl;
-            typename Raw4<T>::type wraw;
-            zero_raw(wraw);
-            bool around = STREAM;
-            if (STREAM) {   // a 128-byte line shared with the neighbouring rows goes through the caches
-                const uintptr_t lo = (uintptr_t)wrow, hi = lo + (size_t)C4 * 4 * sizeof(T);
-                const uintptr_t line = (uintptr_t)wp & ~(uintptr_t)127;
-                around = line >= lo && line + 128 <= hi;
-            }
-            if (act) {
-                if (around) wraw = ldraw_s(wp);
-                else wraw = ldraw(wp);
-            }
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-            u32 S_it = S_my;
-            while (__ballot(S_it != 0u)) {
-                float4 x[4];
+                const bool act = (b_my >= 0) && (sl < C4);
+                const i64 r = row0 + (b_my >= 0 ? b_my : 0);
+                T *wrow = table + (size_t)r * a.stride;
+                T *wp = wrow + 4 * sl;
+                typename Raw4<T>::type wraw;
+                zero_raw(wraw);
+                bool around = STREAM;
+                if (STREAM) {   // a 128-byte line shared with the neighbouring rows goes through the caches
+                    const uintptr_t lo = (uintptr_t)wrow, hi = lo + (size_t)C4 * 4 * sizeof(T);
+                    const uintptr_t line = (uintptr_t)wp & ~(uintptr_t)127;
+                    around = line >= lo && line + 128 <= hi;
+                }
+                if (act) {
+                    if (around) wraw = ldraw_s(wp);
+                    else wraw = ldraw(wp);
+                }
+                float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+                u32 S_it = S_my;
+                while (__ballot(S_it != 0u)) {
+                    float4 x[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const bool valid = S_it != 0u;
-                    const int k = valid ? (int)__builtin_ctz(S_it) : 0;
-                    S_it &= S_it - 1u;
-                    const int from = 32 * tb + k;
-                    int pos = 0;
+                    for (int j = 0; j < 4; ++j) {
+                        const bool valid = S_it != 0u;
+                        const int k = valid ? (int)__builtin_ctz(S_it) : 0;
+                        S_it &= S_it - 1u;
+                        const int from = 32 * tb + k;
+                        int pos = 0;
 #pragma unroll
-                    for (int s = 0; s < RPW; ++s) {
-                        const int v = __shfl(pos_s[s], from, WAVE);
-                        pos = (slot == s) ? v : pos;
+                        for (int s = 0; s < RPW; ++s) {
+                            const int v = __shfl(pos_s[s], from, WAVE);
+                            pos = (slot == s) ? v : pos;
+                        }
+                        const u64 ptr = ((u64)(u32)__shfl(ptr_hi, from, WAVE) << 32) | (u64)(u32)__shfl(ptr_lo, from, WAVE);
+                        x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                        if (valid && act) {
+                            const float *src = (const float *)ptr + (size_t)(u32)pos * a.D + 4 * sl;
+                            x[j] = STREAM ? ld4s(src) : ld4(src);
+                        }
                     }
-                    const u64 ptr = ((u64)(u32)__shfl(ptr_hi, from, WAVE) << 32) | (u64)(u32)__shfl(ptr_lo, from, WAVE);
-                    x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (valid && act) {
-                        const float *src = (const float *)ptr + (size_t)(u32)pos * a.D + 4 * sl;
-                        x[j] = STREAM ? ld4s(src) : ld4(src);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        acc.x += x[j].x;
+                        acc.y += x[j].y;
+                        acc.z += x[j].z;
+                        acc.w += x[j].w;
                     }
                 }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc.x += x[j].x;
-                    acc.y += x[j].y;
-                    acc.z += x[j].z;
-                    acc.w += x[j].w;
+                float4 w = widen4(wraw);
+                w.x = fmaf(neg_lr, acc.x, w.x);
+                w.y = fmaf(neg_lr, acc.y, w.y);
+                w.z = fmaf(neg_lr, acc.z, w.z);
+                w.w = fmaf(neg_lr, acc.w, w.w);
+                if (!act) continue;
+                if constexpr (sizeof(T) == 2) {
+                    if (a.sr) {   // the variant: the same draw per element as in update_row
+                        const u64 blk = (u64)r * (u64)C4 + (u64)sl;
+                        const philox_out o = philox4x32_10((u32)blk, (u32)(blk >> 32), a.sr_serial, 0x53524E44u + (u32)tb,
+                                                           a.sr_k0, a.sr_k1);
+                        v2u p;
+                        p.x = sr_bf16(w.x, o.r0) | (sr_bf16(w.y, o.r1) << 16);
+                        p.y = sr_bf16(w.z, o.r2) | (sr_bf16(w.w, o.r3) << 16);
+                        if (STREAM) __builtin_nontemporal_store(p, (GLOBAL_AS v2u *)wp);
+                        else *reinterpret_cast<v2u *>(wp) = p;
+                        continue;
+                    }
                 }
+                if (STREAM) st4s(wp, w);
+                else st4(wp, w);
             }
-            float4 w = widen4(wraw);
-            w.x = fmaf(neg_lr, acc.x, w.x);
-            w.y = fmaf(neg_lr, acc.y, w.y);
-            w.z = fmaf(neg_lr, acc.z, w.z);
-            w.w = fmaf(neg_lr, acc.w, w.w);
-            if (!act) continue;
-            if constexpr (sizeof(T) == 2) {
-                if (a.sr) {   // the variant: the same draw per element as in update_row
-                    const u64 blk = (u64)r * (u64)C4 + (u64)sl;
-                    const philox_out o = philox4x32_10((u32)blk, (u32)(blk >> 32), a.sr_serial, 0x53524E44u + (u32)tb,
-                                                       a.sr_k0, a.sr_k1);
-                    v2u p;
-                    p.x = sr_bf16(w.x, o.r0) | (sr_bf16(w.y, o.r1) << 16);
-                    p.y = sr_bf16(w.z, o.r2) | (sr_bf16(w.w, o.r3) << 16);
-                    if (STREAM) __builtin_nontemporal_store(p, (GLOBAL_AS v2u *)wp);
-                    else *reinterpret_cast<v2u *>(wp) = p;
-                    continue;
-                }
-            }
-            if (STREAM) st4s(wp, w);
-            else st4(wp, w);
         }
+        if (!SWEEP || gw + stride >= groups) break;
     }
 }
 
-template <typename T, int SUB, int ROWS, bool STREAM, typename Rider>
+// workgroups of a sweep: as many as are on the chip at a time
+#define APPLY_SWEEP_BLOCKS (256 * APPLY_MAX_WAVES)
+static int sweep_blocks(int nblocks) { return nblocks < APPLY_SWEEP_BLOCKS ? nblocks : APPLY_SWEEP_BLOCKS; }
+
+template <typename T, int SUB, int ROWS, bool STREAM, bool SWEEP, typename Rider>
 static void launch_apply_sub_r(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
     const int words = (int)((a.V + 63) >> 6);
     constexpr int G = (ROWS * (WAVE / SUB) > 32) ? 32 : ROWS * (WAVE / SUB);
     const i64 nwaves = (i64)words * (64 / G);
-    const int nblocks = (int)((nwaves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
-    hipLaunchKernelGGL((k_apply_sub<T, SUB, ROWS, STREAM, Rider>), dim3(rider.blocks() + nblocks), dim3(BLOCK), rider.lds_bytes(), st, a, nblocks, rider);
+    int nblocks = (int)((nwaves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+    if (SWEEP) nblocks = sweep_blocks(nblocks);
+    hipLaunchKernelGGL((k_apply_sub<T, SUB, ROWS, STREAM, SWEEP, Rider>), dim3(rider.blocks() + nblocks), dim3(BLOCK), rider.lds_bytes(), st, a, nblocks, rider);
 }
 
 // few of the vocabulary's rows touched, going by the sources' capacities (see launch_apply_t)
-static bool sparse_union(const ApplyArgs &a, i64 min_v)
+static i64 union_rows(const ApplyArgs &a)
 {
     i64 cap = 0;
     for (int k = 0; k < a.n_src; ++k)
         if (a.src[1][k].ids != nullptr) cap += a.src[1][k].capacity;
-    return a.V >= min_v && 4 * cap < 3 * a.V;
+    return cap;
 }
+static bool sparse_union(const ApplyArgs &a, i64 min_v) { return a.V >= min_v && 4 * union_rows(a) < 3 * a.V; }
+// less than a fifth of a row of capacity per vocabulary row: a launch that stays on the chip and sweeps over the vocabulary,
+// with the index words of the next two groups of rows on their way while the rows of one are worked on, so that a wave's
+// start and its look-ups are paid once and not per group; the groups are small (the few waves with the frequent words would
+// work on long after the others).  Against the shapes below, sweep / no sweep, whole calls with 3 peers: 200 000 words,
+// D = 256 19.9 / 22.6 us, 400 000 25.8 / 37.5, 800 000 50.0 / 54.7, 1.2 million 69.0 / 66.4, 2 million 82.5 / 74.6, 4 million
+// 120.6 / 128.9; bfloat16 D = 200, 2 million 65.8 / 67.5, 4 million 91.7 / 115.6 and, more touched, 210.7 / 236.0; rows of
+// 128 elements in bfloat16 200 000 words 16.8 / 18.0, 800 000 26.9 / 45.6, 1.2 million 51.7 / 52.4, 2 million 81.5 / 72.5;
+// of 64 100 000 14.7 / 17.7, 800 000 24.5 / 30.9, 1.6 million 33.0 / 33.0; of 32 100 000 14.9 / 13.5, 200 000 16.4 / 20.7,
+// 800 000 20.5 / 21.9, 1.6 million 29.6 / 27.8.  Groups: 4 / 8 rows 400 000 words, D = 256 25.8 / 30.7, 800 000 in bfloat16,
+// D = 400 60.9 / 50.9; 8 / 16 rows 4 million, bfloat16 99.5 / 91.7
+#define SWEEP_MIN_V 131072
+static bool sweep_union(const ApplyArgs &a) { return a.V >= SWEEP_MIN_V && 5 * union_rows(a) < a.V; }
 
 // 4 rows per group of lanes and wave, or 32 rows per wave where few rows are touched (8 M words, D = 128, bf16:
 // update 0.67 -> 0.42 ms; 16 M words, D = 64: 0.58 -> 0.40 ms), from 655 360 words on (whole call with 32 rows per wave /
@@ -424,26 +480,30 @@ static bool sparse_union(const ApplyArgs &a, i64 min_v)
 template <typename T, int SUB, bool STREAM, typename Rider>
 static void launch_apply_sub(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
-    if (SUB > 8 && sparse_union(a, 655360)) launch_apply_sub_r<T, SUB, 16, STREAM>(a, rider, st);
-    else if (!STREAM && a.V < APPLY_SMALL_V * (WAVE / SUB)) launch_apply_sub_r<T, SUB, 1, STREAM>(a, rider, st);
-    else launch_apply_sub_r<T, SUB, APPLY_SUB_ROWS, STREAM>(a, rider, st);
+    if (sweep_union(a) && a.V < 1000000) {
+        if (SUB < 32 || a.V < 393216) launch_apply_sub_r<T, SUB, 2, STREAM, true>(a, rider, st);
+        else launch_apply_sub_r<T, SUB, 4, STREAM, true>(a, rider, st);
+    } else if (SUB > 8 && sparse_union(a, 655360)) launch_apply_sub_r<T, SUB, 16, STREAM, false>(a, rider, st);
+    else if (!STREAM && a.V < APPLY_SMALL_V * (WAVE / SUB)) launch_apply_sub_r<T, SUB, 1, STREAM, false>(a, rider, st);
+    else launch_apply_sub_r<T, SUB, APPLY_SUB_ROWS, STREAM, false>(a, rider, st);
 }
 
-template <typename T, int G, bool STREAM, bool PACKED, typename Rider>
+template <typename T, int G, bool STREAM, bool PACKED, bool SWEEP, typename Rider>
 static void launch_apply_g(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
     const int iters = (a.D / 4 + WAVE - 1) / WAVE;
     const int words = (int)((a.V + 63) >> 6);
     const i64 nwaves = (i64)words * (64 / G);
-    const int nblocks = (int)((nwaves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+    int nblocks = (int)((nwaves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
+    if (SWEEP) nblocks = sweep_blocks(nblocks);
     dim3 grid(rider.blocks() + nblocks), blk(BLOCK);
     switch (iters) {
-    case 1: hipLaunchKernelGGL((k_apply<T, 1, G, STREAM, PACKED, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider); break;
-    case 2: hipLaunchKernelGGL((k_apply<T, 2, G, STREAM, PACKED, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider); break;
+    case 1: hipLaunchKernelGGL((k_apply<T, 1, G, STREAM, PACKED, SWEEP, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider); break;
+    case 2: hipLaunchKernelGGL((k_apply<T, 2, G, STREAM, PACKED, SWEEP, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider); break;
     default:
         if constexpr (!Rider::narrow) {
-            if (iters == 3) hipLaunchKernelGGL((k_apply<T, 3, G, STREAM, PACKED, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider);
-            else hipLaunchKernelGGL((k_apply<T, 4, G, STREAM, PACKED, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider);
+            if (iters == 3) hipLaunchKernelGGL((k_apply<T, 3, G, STREAM, PACKED, SWEEP, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider);
+            else hipLaunchKernelGGL((k_apply<T, 4, G, STREAM, PACKED, SWEEP, Rider>), grid, blk, rider.lds_bytes(), st, a, nblocks, rider);
         }
     }
 }
@@ -466,9 +526,13 @@ template <typename T, bool STREAM, bool PACKED, typename Rider>
 static void launch_apply_t(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
     const i64 unit = sizeof(T) == 2 || PACKED ? 73728 : 131072;
-    if (sparse_union(a, unit * ((a.D / 4 + WAVE - 1) / WAVE + 1))) launch_apply_g<T, APPLY_G_SPARSE, STREAM, PACKED>(a, rider, st);
-    else if (!STREAM && a.V < APPLY_SMALL_V) launch_apply_g<T, 1, STREAM, PACKED>(a, rider, st);
-    else launch_apply_g<T, APPLY_G, STREAM, PACKED>(a, rider, st);
+    if (sweep_union(a) && (a.V < 1000000 || a.V >= 3000000)) {
+        if (a.V < 655360) launch_apply_g<T, 4, STREAM, PACKED, true>(a, rider, st);
+        else if (a.V < 1000000) launch_apply_g<T, 8, STREAM, PACKED, true>(a, rider, st);
+        else launch_apply_g<T, 16, STREAM, PACKED, true>(a, rider, st);
+    } else if (sparse_union(a, unit * ((a.D / 4 + WAVE - 1) / WAVE + 1))) launch_apply_g<T, APPLY_G_SPARSE, STREAM, PACKED, false>(a, rider, st);
+    else if (!STREAM && a.V < APPLY_SMALL_V) launch_apply_g<T, 1, STREAM, PACKED, false>(a, rider, st);
+    else launch_apply_g<T, APPLY_G, STREAM, PACKED, false>(a, rider, st);
 }
 
 template <typename T, bool STREAM, typename Rider>

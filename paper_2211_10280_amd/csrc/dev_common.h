@@ -238,11 +238,26 @@ __device__ __forceinline__ float wave_sum_dpp(float x)
     x += dpp_get<0x143, 0xC>(x);   // row_bcast:31 into rows 2 and 3: lane 63 holds the total
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
+// or over the lanes 0..31 and over the lanes 32..63, by row moves
+__device__ __forceinline__ u32 dpp_or_rows(u32 x)
+{
+    x |= (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
+    x |= (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
+    x |= (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false);   // row_half_mirror
+    x |= (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, false);   // row_mirror: every lane of a row holds the row's
+    return x;
+}
+__device__ __forceinline__ void half_or(u32 x, u32 &lo, u32 &hi)
+{
+    x = dpp_or_rows(x);
+    lo = (u32)(__builtin_amdgcn_readlane((int)x, 0) | __builtin_amdgcn_readlane((int)x, 16));
+    hi = (u32)(__builtin_amdgcn_readlane((int)x, 32) | __builtin_amdgcn_readlane((int)x, 48));
+}
 __device__ __forceinline__ u32 wave_or(u32 x)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x |= (u32)__shfl_xor((int)x, o, WAVE);
-    return x;
+    u32 lo, hi;
+    half_or(x, lo, hi);
+    return lo | hi;
 }
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 __device__ __forceinline__ int rd_lane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }

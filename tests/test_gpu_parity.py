@@ -391,6 +391,15 @@ def test_dasgd_apply_parity_at_the_borders_of_its_sparse_shape(dtype, V, D, stri
     _apply_parity(dtype, V, D, stride, K, True, thin=400)
 
 
+@pytest.mark.parametrize("dtype,V,D,K", [
+    # less than a fifth of a row of capacity per vocabulary row: from 131 072 words on the update sweeps over the vocabulary,
+    # in small groups of rows (other sizes from 393 216 and 655 360 words on), up to a million words
+    ("f32", 131_071, 132, 3), ("f32", 131_072, 132, 3), ("bf16", 655_361, 132, 1), ("f32", 131_072, 8, 2),
+    ("bf16", 400_037, 64, 3), ("bf16", 393_215, 128, 3), ("f32", 393_217, 100, 1), ("f32", 999_999, 36, 2), ("f32", 1_000_000, 36, 2)])
+def test_dasgd_apply_parity_where_it_sweeps_over_the_vocabulary(dtype, V, D, K):
+    _apply_parity(dtype, V, D, D, K, True, thin=60)
+
+
 def _random_apply_shapes(n, seed):
     """Seeded shapes off the beaten track: every lane grouping of the table update (D <= 32, <= 64, <= 128, one to
     four chunk passes of a whole wave), dimensions just below and above the borders between them, padded and
@@ -946,6 +955,18 @@ def test_grad_pack_parity(V, D, ui, uo):
     assert np.array_equal(bi, oracle.grad_pack_rows(gi[1])) and np.array_equal(bo, oracle.grad_pack_rows(go[1]))
     assert (msg.in_rows[ui:].cpu().numpy() == 0x1234).all()
     m.close()
+
+
+@pytest.mark.parametrize("dtype,V,D,K", [                  # messages take the whole-wave shape at every dimension: its groups
+    ("f32", 131_072, 8, 3), ("bf16", 655_359, 8, 3), ("f32", 655_360, 36, 1), ("bf16", 999_999, 8, 2), ("f32", 3_000_001, 8, 3)])
+def test_dasgd_apply_packed_parity_where_it_sweeps_over_the_vocabulary(dtype, V, D, K):
+    test_dasgd_apply_packed_parity(dtype, V, D, D, K, True, 60)
+
+
+@pytest.mark.parametrize("V,ua,ub", [(131_072, (500, 9_000), (77, 4_000)), (524_287, (5, 30_001), (4_000, 70_000)),
+                                     (524_288, (0, 20_000), (1, 0)), (1_000_003, (100_000, 3), (70_000, 150_000))])
+def test_grad_add_parity_where_it_sweeps_over_the_vocabulary(V, ua, ub):
+    test_grad_add_parity(V, 12, ua, ub)
 
 
 @pytest.mark.parametrize("K", [0, 3])
