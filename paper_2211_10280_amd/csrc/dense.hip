@@ -180,15 +180,16 @@ void tn_launch_cosine_diff(const CosineArgs &a, hipStream_t st)
 }
 
 // ---------------------------------------------------------------- gradient message in bfloat16
-// grid (blocks, 2 tables).  The rows of a sparse gradient are dense, [n][D], so the conversion is flat: a
-// workgroup rounds PACK_CHUNKS * 256 consecutive chunks of 4 elements (to nearest even), a thread one
+// The first `blocks_in` workgroups take W_in's rows, the others W_out's.  The rows of a sparse gradient are dense, [n][D], so
+// the conversion is flat: a workgroup rounds PACK_CHUNKS * 256 consecutive chunks of 4 elements (to nearest even), a thread one
 // chunk of every 256, all its loads issued before the first store; the row ids are copied by the threads
 // whose chunk index is below n.  The launch covers the capacity (n is only known on the device);
 // workgroups beyond the n rows that are there leave at once.
 #define PACK_CHUNKS 4
-__global__ void __launch_bounds__(BLOCK) k_grad_pack(GradPackArgs a)
+__global__ void __launch_bounds__(BLOCK) k_grad_pack(GradPackArgs a, int blocks_in)
 {
-    const int tb = blockIdx.y;
+    const int tb = (int)blockIdx.x < blocks_in ? 0 : 1;
+    const int block = (int)blockIdx.x - (tb ? blocks_in : 0), blocks = tb ? (int)gridDim.x - blocks_in : blocks_in;
     i64 n = *a.n[tb];
     if (n < 0) n = 0;
     bool over = false;
@@ -200,14 +201,13 @@ __global__ void __launch_bounds__(BLOCK) k_grad_pack(GradPackArgs a)
         n = a.out_cap[tb];
         over = true;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (block == 0 && threadIdx.x == 0) {
         *a.out_n[tb] = (int)n;
         if (over) atomicOr(a.status, ST_OVERFLOW);
     }
     const i64 chunks = n * (a.D >> 2);
-    const i64 step = (i64)gridDim.x * BLOCK * PACK_CHUNKS;
-    // one pass unless the gradient is larger than the largest grid
-    for (i64 base = (i64)blockIdx.x * BLOCK * PACK_CHUNKS + threadIdx.x; base < chunks; base += step) {
+    const i64 step = (i64)blocks * BLOCK * PACK_CHUNKS;
+    for (i64 base = (i64)block * BLOCK * PACK_CHUNKS + threadIdx.x; base < chunks; base += step) {
         float4 v[PACK_CHUNKS];
 #pragma unroll
         for (int j = 0; j < PACK_CHUNKS; ++j) {
@@ -223,14 +223,18 @@ __global__ void __launch_bounds__(BLOCK) k_grad_pack(GradPackArgs a)
     }
 }
 
+// Workgroups per table, at most: the launch covers the capacity, and dispatching one that finds nothing takes as long as
+// dispatching another (sum of two gradients and its message at a million words, D = 300: a grid of 66 000 for either table
+// 309 us, one of each table's own 300, at most 16 384 292, at most 4 096 297)
+#define PACK_MAX_BLOCKS 16384
 void tn_launch_grad_pack(const GradPackArgs &a, hipStream_t st)
 {
-    i64 chunks = 1;
+    int blocks[2];
     for (int tb = 0; tb < 2; ++tb) {
         const i64 rows = a.cap[tb] < a.out_cap[tb] ? a.cap[tb] : a.out_cap[tb];
-        if (rows * (a.D >> 2) > chunks) chunks = rows * (a.D >> 2);
+        const i64 chunks = rows * (a.D >> 2) > 1 ? rows * (a.D >> 2) : 1;
+        const i64 want = (chunks + BLOCK * PACK_CHUNKS - 1) / (BLOCK * PACK_CHUNKS);
+        blocks[tb] = (int)(want > PACK_MAX_BLOCKS ? PACK_MAX_BLOCKS : want);
     }
-    i64 want = (chunks + BLOCK * PACK_CHUNKS - 1) / (BLOCK * PACK_CHUNKS);
-    const int blocks = (int)(want > (1 << 22) ? (1 << 22) : want);
-    hipLaunchKernelGGL(k_grad_pack, dim3(blocks, 2), dim3(BLOCK), 0, st, a);
+    hipLaunchKernelGGL(k_grad_pack, dim3(blocks[0] + blocks[1]), dim3(BLOCK), 0, st, a, blocks[0]);
 }
