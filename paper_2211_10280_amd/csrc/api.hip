@@ -44,6 +44,7 @@ struct Sizes {
     size_t pub_words;          // what the preparation's workgroups publish, and their tickets (prep_layout)
     int tiles_out, tiles_in;   // segmented-reduction tiles
     i64 words;
+    bool group;                // mini-batches may be large enough to go by pairs of words (group.hip), as far as the sizes go
 };
 
 bool config_ok(const tensair_config *c, const char **why)
@@ -124,6 +125,7 @@ Sizes sizes_of(const tensair_config &c)
     s.tiles_out = seg_tiles(s.Omax);
     s.tiles_in = seg_tiles(s.Bmax);
     s.words = (c.vocab + 63) / 64;
+    s.group = c.vocab <= TN_GROUP_MAX_VOCAB && s.Omax > TN_GROUP_MIN_OCC && 2 * c.window * (c.negatives + 1) <= TN_REPEAT_MAX_TASKS;
     return s;
 }
 
@@ -194,6 +196,10 @@ struct tensair_model {
     u64 *mask_alt[2];          // a second set (buffer 1): inside tensair_step the two are used in turn, so that
                                // the one the next step will index can be cleared while this step still reads its own
     bool mask_clean[2] = {false, false};   // buffer b is all zeros (or will be when everything enqueued so far has run)
+    u64 *group_masks = nullptr;        // see GroupArgs
+    u64 *group_any = nullptr;
+    unsigned short *group_starts = nullptr;
+    int4 *group_meta = nullptr;
     u32 *wbase[2], *wblk[2];   // tensair_grad_add: place of every 64-row word in the summed gradient
     std::vector<Draw> h_draw;  // the same on the host
     double different = 1.0;    // share of a position's negatives that are different words, as expected
@@ -273,6 +279,13 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
     p = take((size_t)(s.tiles_in / TN_SEG_XBLOCK + 2) * D * 4); if (m) m->cross_in = (float *)p;
     p = take((size_t)(s.tiles_out / TN_SEG_XBLOCK + 2) * 4); if (m) m->xinfo_out = (int *)p;
     p = take((size_t)(s.tiles_in / TN_SEG_XBLOCK + 2) * 4); if (m) m->xinfo_in = (int *)p;
+    if (s.group) {
+        const size_t pitch = (size_t)tn_group_pitch(c.vocab, s.Bmax);
+        p = take((size_t)s.words * 8); if (m) m->group_any = (u64 *)p;
+        p = take((size_t)s.words * pitch * 8); if (m) m->group_masks = (u64 *)p;
+        p = take((size_t)s.words * pitch * 2); if (m) m->group_starts = (unsigned short *)p;
+        p = take(pitch * 16); if (m) m->group_meta = (int4 *)p;
+    }
     for (int t = 0; t < 2; ++t) {
         p = take((size_t)(s.words + 1) * K1 * 4); if (m) m->start[t] = (u32 *)p;
         p = take((size_t)s.words * K1 * 8); if (m) m->mask[t] = (u64 *)p;
@@ -812,6 +825,12 @@ static void abandon_side_work(tensair_model *m)
     m->set[0].hist_clean = m->set[1].hist_clean = false;
 }
 
+// Whether the gradient of a mini-batch goes by pairs of words (group.hip).  Such a mini-batch is prepared by its own call.
+static bool goes_by_pairs(const tensair_model *m, i64 P)
+{
+    return m->sz.group && m->different <= TN_REPEATS_BELOW && P * (m->cfg.negatives + 1) > TN_GROUP_MIN_OCC;
+}
+
 int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, int64_t center_begin,
                      int32_t n_centers, uint32_t epoch, void *stream)
 {
@@ -917,6 +936,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     m->side_follows = false;
     // how far this mini-batch is prepared, and how the rest is done
     int phase = own.phase;
+    const bool by_pairs = phase == 0 && goes_by_pairs(m, P) && !negatives_dbg && !seg_offsets_in && !seg_offsets_out;
     const bool chained = phase > 0 ? own.chained : prep_tiles(c, P, n_centers) <= TN_PREP_CHAIN_OWN;
     const int phases = prep_phases(s, chained), sorted = prep_sort_end(s, chained);
     const bool prepared = phase == phases;
@@ -927,7 +947,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         if (rides(m, following, fuse && m->ride_long_update)) {
             m->pend = following;
             m->pend.chained = true;
-        } else if (fuse && m->prepare_under_apply) {
+        } else if (fuse && m->prepare_under_apply && !goes_by_pairs(m, following.P)) {
             m->deferred = following;
         } else if (following.P * Np1 <= TN_BESIDE_MAX_OCC) {
             beside = true;
@@ -973,7 +993,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         m->mask_clean[pick] = false;
         const bool own_early = prepared && !split;   // the own id lists exist when the forward pass starts
         tn_aux_add_index(aux_fwd, fa, own_early ? 0 : 1, fa.n_src);
-        if (!own_early) tn_aux_add_index(aux_red, fa, 0, 1);
+        if (!own_early && !by_pairs) tn_aux_add_index(aux_red, fa, 0, 1);
         if (!m->mask_clean[1 - pick]) {
             const size_t all = (size_t)s.words * (size_t)(c.max_peers + 1 > 2 ? c.max_peers + 1 : 2);
             tn_aux_add_clear(aux_red, pick ? m->mask[0] : m->mask_alt[0], pick ? m->mask[1] : m->mask_alt[1], all);
@@ -985,6 +1005,53 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     const RowIndexDst in = {grad_out->in.row_ids, grad_out->in.n_rows, seg_offsets_in, grad_out->in.capacity};
     const RowIndexDst out = {grad_out->out.row_ids, grad_out->out.n_rows, seg_offsets_out, grad_out->out.capacity};
     PrepPhase x;
+    if (by_pairs) {
+        // the positions sorted by their center's word, then the gradient itself
+        BatchWork centers = w;
+        centers.O = 0;
+        for (int i = 0; i < prep_phases(s, false); ++i) {
+            make_prep_phase(m, S, centers, false, i, in, out, nullptr, x);
+            before_prep_phase(m, S, x.kind, st);
+            tn_launch_prep(x, st);
+            if (i == 0) mark(m, PF_KEYS, st);
+        }
+        mark(m, PF_SORT, st);
+        if (beside) {
+            HIP_TRY(hipEventRecord(m->ev_fork, st));
+            HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
+            m->side_follows = true;
+            if ((rc = enqueue_prepare(m, following, true, true, m->side))) return rc;
+        }
+        if (next_rider(m, true, x, st)) tn_launch_prep(x, st);
+        const SortedSide si = sorted_side(m, S, 1);
+        GroupArgs ga;
+        memset(&ga, 0, sizeof(ga));
+        ga.f = f;
+        ga.vals = si.vals;
+        ga.seg_of = si.seg_of;
+        ga.seg_start = si.seg_start;
+        ga.n_in = grad_out->in.n_rows;
+        ga.words = (int)s.words;
+        ga.pitch = (int)tn_group_pitch(c.vocab, n_centers);
+        ga.per_center = 2 * c.window * Np1;
+        ga.positions = tn_group_positions(ga.per_center);
+        ga.list = S.keys[1];      // only the in-side list is sorted: the other's room is free
+        ga.counts = S.keys[2];
+        ga.any = m->group_any;
+        ga.masks = m->group_masks;
+        ga.starts = m->group_starts;
+        ga.meta = m->group_meta;
+        ga.in_rows = grad_out->in.row_grads;
+        ga.out_rows = grad_out->out.row_grads;
+        ga.out_ids = grad_out->out.row_ids;
+        ga.out_n = grad_out->out.n_rows;
+        if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, n_centers, f.inv_P, mean_loss);
+        tn_launch_group(ga, aux_fwd, aux_red, st);
+        if (fuse) tn_launch_apply_index(*m->fused_apply, 0, 1, st);
+        mark(m, PF_REDUCE_OUT, st);
+        HIP_TRY(hipGetLastError());
+        return TENSAIR_OK;
+    }
     if (prepared) {
         // this mini-batch's row index goes to the caller's buffers with the forward pass -- with the reductions if the
         // forward pass starts on the keys alone

@@ -215,6 +215,31 @@ static inline int tn_seg_chains(i64 n, int D)
     return tiles > 1 ? (int)(tiles < 1024 ? tiles : 1024) : 0;
 }
 
+// ---- stages 4 and 5 of a very large mini-batch over a small vocabulary whose words repeat (group.hip)
+// up to TN_GROUP_MAX_VOCAB words (a counter each in LDS) and more than TN_GROUP_MIN_OCC occurrences
+#define TN_GROUP_MAX_VOCAB 32768
+#define TN_GROUP_MIN_OCC (1 << 20)
+// positions of a center word that are counted together: their tasks' counts fit 16 bits (step of 16 384 centers, 256 tasks
+// each, with 64 / 128 positions 338 / 325 us)
+static inline int tn_group_positions(int per_center) { return per_center <= 256 ? 128 : 64; }   // per_center <= TN_REPEAT_MAX_TASKS
+struct GroupArgs {
+    FwdArgs f;               // g: scales of the chunks' words, in the place of their list entries; center_part and center_loss by sorted position
+    const u32 *vals;         // positions in the order of their center words
+    const int *seg_of, *seg_start, *n_in;
+    int words, pitch;        // 64-word groups of the vocabulary; chunks that there is room for
+    int positions, per_center;   // of a chunk, at most; tasks of a position, at most
+    u32 *list, *counts;      // [positions in all][per_center] the chunks' words, from their first position's place on
+    u64 *any;                // [words] words that occur
+    u64 *masks;              // [words][pitch] words of a chunk
+    unsigned short *starts;  // [words][pitch] words of the chunk before these
+    int4 *meta;              // [pitch] center word, first sorted position, words
+    float *in_rows, *out_rows;
+    int *out_ids, *out_n;
+};
+static inline i64 tn_group_pitch(i64 V, i64 n_centers) { return ((n_centers < V ? n_centers : V) + n_centers / 64 + 64) & ~(i64)63; }
+struct AuxWork;
+void tn_launch_group(GroupArgs &a, const AuxWork &with_rows, const AuxWork &with_sums, hipStream_t st);
+
 void tn_launch_loss(const float *center_loss, int n_centers, float inv_P, float *mean_loss,
                     hipStream_t st);
 void tn_launch_empty_grad(int *n_in, int *n_out, float *mean_loss, int *seg_in, int *seg_out,
