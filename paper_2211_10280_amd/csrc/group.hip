@@ -37,11 +37,42 @@ struct GroupShape {
 template <int THREADS>
 __device__ __forceinline__ float sum_waves(const float *red, int row, int e)
 {
-    float s = red[e];
+    double s = red[e];
 #pragma unroll
     for (int w = 1; w < THREADS / WAVE; ++w) s += red[w * row + e];
-    return s;
+    return (float)s;
 }
+
+// A wave's row of long sums.  Hundreds of chunks are added up for a frequent word, and in one chain of fp32 additions that
+// loses accuracy (rows against 64 bits 2.6e-7; sums of eight rows added up in fp32 1.3e-7; in double 0.6e-7 to 0.9e-7; the
+// reduction of sorted occurrences, whose sums meet in a tree, 0.7e-7 to 1.0e-7).
+template <int NQ, bool TAIL>
+struct LongRow {
+    double q[NQ][4], t;
+    __device__ __forceinline__ void zero()
+    {
+#pragma unroll
+        for (int it = 0; it < NQ; ++it) q[it][0] = q[it][1] = q[it][2] = q[it][3] = 0.0;
+        t = 0.0;
+    }
+    __device__ __forceinline__ void add(const WaveRow<NQ, TAIL> &x)
+    {
+#pragma unroll
+        for (int it = 0; it < NQ; ++it) {
+            q[it][0] += x.q[it].x;
+            q[it][1] += x.q[it].y;
+            q[it][2] += x.q[it].z;
+            q[it][3] += x.q[it].w;
+        }
+        if (TAIL) t += x.t;
+    }
+    __device__ __forceinline__ void round(WaveRow<NQ, TAIL> &x) const
+    {
+#pragma unroll
+        for (int it = 0; it < NQ; ++it) x.q[it] = make_float4((float)q[it][0], (float)q[it][1], (float)q[it][2], (float)q[it][3]);
+        x.t = (float)t;
+    }
+};
 
 // the chunk that begins at sorted position e, the i-th of row r, is number r + (first position of r) / positions + i: the
 // chunks of a row are neighbours, and at most one number per row stays unused.  lds: a counter per word, then what the
@@ -180,8 +211,11 @@ k_group_rows(GroupArgs a, AuxWork aux)
             sum = pair_scale<LOSS>(count[t_l], s_l, f.inv_P, loss, g1, g0);
             f.g[base + t_l] = sum;
         }
+        Row part;       // sums of sums: one long chain of additions loses accuracy
+        part.zero();
 #pragma unroll
-        for (int x = 0; x < UNROLL; ++x) acc.axpy(rd_lane(sum, x), u[x]);
+        for (int x = 0; x < UNROLL; ++x) part.axpy(rd_lane(sum, x), u[x]);
+        acc.axpy(1.0f, part);
     }
     acc.spill(red + wave * ROW, lane);
     if (LOSS) {
@@ -231,17 +265,23 @@ __global__ void __launch_bounds__(SUM_THREADS) k_group_reduce(GroupArgs a, AuxWo
         for (int i = wave; i < chunks; i += SUM_WAVES) {
             const int n = uniform(a.meta[b + s0 / a.positions + i].z);
             const int shares = (n + a.per_center - 1) / a.per_center;
-            const float *part = f.center_part + (size_t)(s0 + i * a.positions) * f.D;
+            const float *rows = f.center_part + (size_t)(s0 + i * a.positions) * f.D;
+            Row of_chunk;
+            of_chunk.zero();
             for (int q0 = 0; q0 < shares; q0 += 4) {
                 LoadedRow<float, NQ, TAIL> x[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    if (q0 + j < shares) x[j].load(part + (size_t)(q0 + j) * f.D, f.D, lane);
+                    if (q0 + j < shares) x[j].load(rows + (size_t)(q0 + j) * f.D, f.D, lane);
                     else x[j].zero();
                 }
+                Row part;
+                part.zero();
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc.axpy(1.0f, x[j]);
+                for (int j = 0; j < 4; ++j) part.axpy(1.0f, x[j]);
+                of_chunk.axpy(1.0f, part);
             }
+            acc.axpy(1.0f, of_chunk);
         }
         dst = a.in_rows + (size_t)b * f.D;
     } else {                                // a word: the chunks that have it
@@ -264,6 +304,8 @@ __global__ void __launch_bounds__(SUM_THREADS) k_group_reduce(GroupArgs a, AuxWo
         if (!here) return;
         if (threadIdx.x == 0) a.out_ids[n] = b;
         const int chunks = U + f.b.n_centers / a.positions;      // numbers in use and the few between them
+        LongRow<NQ, TAIL> total;
+        total.zero();
         for (int c0 = wave * WAVE; c0 < chunks; c0 += SUM_WAVES * WAVE) {
             u64 mk = 0;
             int4 meta = make_int4(0, 0, 0, 0);
@@ -287,11 +329,15 @@ __global__ void __launch_bounds__(SUM_THREADS) k_group_reduce(GroupArgs a, AuxWo
                         x[j].load((const T *)f.w_in + (size_t)rd_lane(meta.x, at[j]) * f.stride, f.D, lane);
                     }
                 }
+                Row part;
+                part.zero();
 #pragma unroll
                 for (int j = 0; j < UNROLL; ++j)
-                    if (at[j] >= 0) acc.axpy(rd_lane(s_l, at[j]), x[j]);
+                    if (at[j] >= 0) part.axpy(rd_lane(s_l, at[j]), x[j]);
+                total.add(part);
             }
         }
+        total.round(acc);
         dst = a.out_rows + (size_t)n * f.D;
     }
     acc.spill(red + wave * ROW, lane);
