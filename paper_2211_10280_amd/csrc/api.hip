@@ -125,7 +125,8 @@ Sizes sizes_of(const tensair_config &c)
     s.tiles_out = seg_tiles(s.Omax);
     s.tiles_in = seg_tiles(s.Bmax);
     s.words = (c.vocab + 63) / 64;
-    s.group = c.vocab <= TN_GROUP_MAX_VOCAB && s.Omax > TN_GROUP_MIN_OCC && 2 * c.window * (c.negatives + 1) <= TN_REPEAT_MAX_TASKS;
+    const i64 per_center = (i64)2 * c.window * (c.negatives + 1);
+    s.group = c.vocab <= TN_GROUP_MAX_VOCAB && s.Omax > TN_GROUP_MIN_OCC && per_center >= TN_GROUP_MIN_TASKS && per_center <= TN_REPEAT_MAX_TASKS;
     return s;
 }
 
@@ -346,6 +347,10 @@ bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double 
 // measured at expected shares of 0.45 to 0.9, it gains below 0.9 (0.87: step 306 against 310 us) and loses nothing above
 // but the table's cost (0.6 % at 0.9).
 #define TN_REPEATS_BELOW 0.85
+// The same for going by pairs of words (group.hip): rows of more than 128 elements gain wherever words repeat (expected
+// share 0.84: step 332 -> 255 us), narrow ones, whose gathers weigh less, a little (D = 64: 0.84 231 -> 247, 0.82 298 -> 284,
+// 0.67 251 -> 237, 0.44 179 -> 164).
+static double pairs_below(int D) { return D <= TN_SUB_MAX_DIM ? 0.8 : TN_REPEATS_BELOW; }
 // Stage tags of tensair_profile_read.  A tag's duration runs from the previous mark to its own.
 enum { PF_BEGIN_GRAD = 0, PF_KEYS, PF_FORWARD, PF_SORT, PF_SEGMENTS, PF_REDUCE_IN, PF_REDUCE_OUT,
        PF_BEGIN_APPLY, PF_APPLY_INDEX, PF_APPLY_UPDATE, PF_BEGIN_ADD, PF_ADD_INDEX, PF_ADD_ROWS,
@@ -828,7 +833,7 @@ static void abandon_side_work(tensair_model *m)
 // Whether the gradient of a mini-batch goes by pairs of words (group.hip).  Such a mini-batch is prepared by its own call.
 static bool goes_by_pairs(const tensair_model *m, i64 P)
 {
-    return m->sz.group && m->different <= TN_REPEATS_BELOW && P * (m->cfg.negatives + 1) > TN_GROUP_MIN_OCC;
+    return m->sz.group && m->different <= pairs_below(m->cfg.dim) && P * (m->cfg.negatives + 1) > TN_GROUP_MIN_OCC;
 }
 
 int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, int64_t center_begin,

@@ -217,8 +217,12 @@ static inline int tn_seg_chains(i64 n, int D)
 
 // ---- stages 4 and 5 of a very large mini-batch over a small vocabulary whose words repeat (group.hip)
 // up to TN_GROUP_MAX_VOCAB words (a counter each in LDS) and more than TN_GROUP_MIN_OCC occurrences
-#define TN_GROUP_MAX_VOCAB 32768
+// (three workgroups' counters fit a compute unit's LDS up to here; step of 8 192 centers, 256 tasks each, 3 peers, D = 256,
+// by occurrences / by pairs: 1 323 words 263 / 163 us, 2 000 220 / 166, 5 000 332 / 255, 10 000 400 / 296, 331 / 246 and 303 / 234 with
+// Zipf exponents of 1.1, 1.3 and 1.45; 32 000 words, one workgroup per compute unit, 419 / 574 and 303 / 451)
+#define TN_GROUP_MAX_VOCAB 12288
 #define TN_GROUP_MIN_OCC (1 << 20)
+#define TN_GROUP_MIN_TASKS 128   // per position: a chunk's counters are cleared and listed whatever it holds
 // positions of a center word that are counted together: their tasks' counts fit 16 bits (step of 16 384 centers, 256 tasks
 // each, with 64 / 128 positions 338 / 325 us)
 static inline int tn_group_positions(int per_center) { return per_center <= 256 ? 128 : 64; }   // per_center <= TN_REPEAT_MAX_TASKS
