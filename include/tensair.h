@@ -180,8 +180,11 @@ int64_t tensair_pair_count(const tensair_model *m, int64_t n_tokens, int64_t cen
  * worker_id + 65536*epoch), key = seed): word 0 picks the bucket by multiply-high,
  * word 1 is compared with the bucket's threshold.  Per pair and j in {context,
  * negatives}: s = <W_in[c], W_out[j]>, g = (sigmoid(s) - label)/P; Gin[c] += g W_out[j],
- * Gout[j] += g W_in[c] (fp32 accumulation in a fixed order, duplicates summed by
- * sort and segmented reduction, no atomics).
+ * Gout[j] += g W_in[c] (accumulation in fp32 or better, in a fixed order, no atomics: duplicates
+ * are summed by sort and segmented reduction; where a mini-batch of more than 2^20 occurrences
+ * meets a small vocabulary, by pairs of words).  The order is a function of the configuration, the
+ * unigram counts and the mini-batch: the same call gives the same bits, whatever optional outputs
+ * are asked for.
  * grad_out: capacities >= tensair_capacity_in/out(n_centers); receives n_rows, the
  * ascending unique row ids and the summed rows.
  * Optional DEVICE outputs (NULL to skip): mean_loss float[1] (mean over the P pairs);
@@ -285,7 +288,8 @@ int tensair_step_packed(tensair_model *m, const int32_t *tokens, int64_t n_token
  *   pass if it has up to 2^20 occurrences.
  *   One that is announced with none before it at once: on `stream` if it has up to 128 tiles, on the library's
  *   own stream if it has up to 2^20 occurrences.
- *   Whatever is left is done by the gradient call that consumes it.
+ *   Whatever is left is done by the gradient call that consumes it, and all of a mini-batch of more than 2^20
+ *   occurrences whose gradient goes by pairs of words.
  * A third announcement replaces the second.
  * A gradient call on this model uses the
  * prepared data if its (tokens, n_tokens, center_begin, n_centers, epoch) and the model's

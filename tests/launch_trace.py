@@ -3,8 +3,9 @@ enqueued, as JSON.  A process of its own, without torch, whose own HIP runtime w
 
     python launch_trace.py LIBRARY STAND_INS < calls.json
 
-calls.json: {"model": {...fields of tensair_config...}, "tokens": T, "calls": [[name, ...], ...]} with the calls
-    ["grad", begin, n, epoch]   ["step", begin, n, epoch, peers]   ["prefetch", begin, n, epoch]   ["rebind", worker]
+calls.json: {"model": {...fields of tensair_config...}, "tokens": T, "counts": unigram counts (64 words once if absent),
+"calls": [[name, ...], ...]} with the calls
+    ["grad", begin, n, epoch, output...] (optional outputs: "negatives", "offsets_in", "offsets_out")   ["step", begin, n, epoch, peers]   ["prefetch", begin, n, epoch]   ["rebind", worker]
     ["apply", rows_in, rows_out, peers]   ["capture", 0 | 1]   ["profile", level]
 Every pointer is made up: nothing reads or writes them."""
 import ctypes as C
@@ -46,8 +47,8 @@ def main():
         return at[0]
 
     counts = (C.c_uint64 * cfg.vocab)()      # zeros, and a few words of the noise distribution
-    for i in range(0, min(cfg.vocab, 64)):
-        counts[i] = 1
+    for i, n in enumerate(job.get("counts") or [1] * min(cfg.vocab, 64)):
+        counts[i] = n
     h = vp()
     workspace, stream, T = pointer(64), None, job["tokens"]
     rc = lib.tensair_model_init(C.byref(h), C.byref(cfg), vp(pointer()), vp(pointer()), 0, counts, vp(workspace),
@@ -78,7 +79,8 @@ def main():
             if name == "prefetch":
                 rc = lib.tensair_prefetch(*batch, stream)
             elif name == "grad":
-                rc = lib.tensair_sgns_grad(*batch, C.byref(own), None, None, None, None, stream)
+                dbg = [vp(pointer()) if o in a[3:] else None for o in ("negatives", "offsets_in", "offsets_out")]
+                rc = lib.tensair_sgns_grad(*batch, C.byref(own), None, *dbg, stream)
             else:
                 peers = (Grad * max(a[3], 1))(*[grad(own.in_.capacity, own.out.capacity) for _ in range(a[3])])
                 rc = lib.tensair_step(*batch, peers, i32(a[3]), C.c_float(0.1), C.byref(own), None, stream)

@@ -18,10 +18,10 @@ def trace(tmp_path_factory):
     subprocess.check_call(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "hip_trace.c")])
     lib = os.environ.get("TENSAIR_TRACED_LIB", B.LIB_PATH)
 
-    def run(calls, tokens=1_000_000, **model):
+    def run(calls, tokens=1_000_000, counts=None, **model):
         model = {"row_stride": model["dim"], "dtype": B.F32, "max_peers": 0, "worker_id": 0, "seed": 7, "flags": 0, **model}
         r = subprocess.run([sys.executable, os.path.join(HERE, "launch_trace.py"), lib, so], capture_output=True, text=True,
-                           input=json.dumps({"model": model, "tokens": tokens, "calls": calls}), timeout=120)
+                           input=json.dumps({"model": model, "tokens": tokens, "counts": counts, "calls": calls}), timeout=120)
         assert r.returncode == 0, r.stderr
         return json.loads(r.stdout)
 
@@ -188,3 +188,13 @@ def test_rows_per_wave_where_few_are_touched(trace, V, D, dtype, rows):
     got = launches(trace([["apply", 60, V // 8, 1]], **model)[0]["did"])[-1]
     assert got[0] == ("k_apply" if D > 128 else "k_apply_sub")
     assert got[1] == ((V + 63) // 64 * 64 + rows - 1) // rows
+
+
+@pytest.mark.parametrize("outputs", [[], ["negatives"], ["offsets_in"], ["offsets_out"], ["negatives", "offsets_in", "offsets_out"]])
+def test_optional_outputs_do_not_choose_the_gradients_form(trace, outputs):
+    """A large mini-batch over a small vocabulary goes by pairs of words whatever else is asked for; its occurrences are
+    sorted only for their offsets."""
+    did = launches(trace([["grad", 100, 5000, 0] + outputs], vocab=300, dim=64, window=8, negatives=15, max_centers=5000)[0]["did"])
+    assert "k_group_rows" in [k for k, _, _ in did] and not any("forward" in k or "segreduce" in k for k, _, _ in did)
+    tiles = [g for k, g, _ in did if k == "k_prep_pass"]
+    assert tiles == [3 + (625 if "offsets_out" in outputs else 0)]
