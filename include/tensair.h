@@ -314,8 +314,8 @@ int tensair_status(tensair_model *m, void *stream);
  * launch); 2: an event after every stage of the step.
  * tensair_profile_read waits for the last recorded event, writes up to max_records
  * (tag, milliseconds) records since the previous read and returns their number (negative =
- * error).  Tags: 1 keys+negatives, 2 forward, 3 sort, 4 segments, 5 reduce W_in side,
- * 6 reduce W_out side, 8 apply index, 9 apply table update, 11 index and scan of
+ * error).  Tags: 1 keys+negatives, 2 forward (by pairs of words, where it comes after the segments: counting
+ * the pairs and working on them), 3 sort, 4 segments, 5 reduce W_in side, 6 reduce W_out side, 8 apply index, 9 apply table update, 11 index and scan of
  * tensair_grad_add, 12 its row kernel (level 1 also brackets that one), 14 the kernel of
  * tensair_grad_pack (level 1 too); a tag's time runs from
  * the previous event to its own.  At most 65536 events are kept between reads. */

@@ -1021,8 +1021,9 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
             before_prep_phase(m, S, x.kind, st);
             tn_launch_prep(x, st);
             if (i == 0) mark(m, PF_KEYS, st);
+            if (i + 1 == prep_sort_end(s, false)) mark(m, PF_SORT, st);
         }
-        mark(m, PF_SORT, st);
+        mark(m, PF_SEGMENTS, st);
         if (beside) {
             HIP_TRY(hipEventRecord(m->ev_fork, st));
             HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
@@ -1052,8 +1053,17 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         ga.out_rows = grad_out->out.row_grads;
         ga.out_ids = grad_out->out.row_ids;
         ga.out_n = grad_out->out.n_rows;
-        if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, n_centers, f.inv_P, mean_loss);
-        tn_launch_group(ga, aux_fwd, aux_red, st);
+        tn_launch_group(ga, GROUP_ROWS, aux_fwd, st);
+        mark(m, PF_FORWARD, st);
+        if (overlap) {
+            if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, n_centers, f.inv_P, mean_loss);
+            tn_launch_group(ga, GROUP_SUMS_IN | GROUP_SUMS_OUT, aux_red, st);
+        } else {         // one after the other, so that each can be timed
+            if (mean_loss) tn_launch_loss(m->center_loss, n_centers, f.inv_P, mean_loss, st);
+            tn_launch_group(ga, GROUP_SUMS_IN, aux_red, st);
+            mark(m, PF_REDUCE_IN, st);
+            tn_launch_group(ga, GROUP_SUMS_OUT, aux_red, st);
+        }
         if (fuse) tn_launch_apply_index(*m->fused_apply, 0, 1, st);
         mark(m, PF_REDUCE_OUT, st);
         HIP_TRY(hipGetLastError());

@@ -19,6 +19,7 @@
 #include "forward_dev.h"
 #include "kernels.h"
 #include "rows_dev.h"
+#include <algorithm>
 
 #define GROUP_THREADS 512
 #define GROUP_WAVES (GROUP_THREADS / WAVE)
@@ -346,41 +347,43 @@ __global__ void __launch_bounds__(SUM_THREADS) k_group_reduce(GroupArgs a, AuxWo
 }
 
 template <typename T, int NQ, bool TAIL>
-static void launch_group_k(GroupArgs &a, const AuxWork &with_rows, const AuxWork &with_sums, hipStream_t st)
+static void launch_group_k(const GroupArgs &a, int what, const AuxWork &aux, hipStream_t st)
 {
-    const int n = a.f.b.n_centers;
-    hipLaunchKernelGGL(k_group_count, dim3((n + GROUP_RANGE - 1) / GROUP_RANGE), dim3(GROUP_THREADS), 4u * (unsigned)(65 * a.words + 1), st, a);
-    const dim3 grid(with_rows.total + n), blk(BLOCK);
-    if (a.f.center_loss) hipLaunchKernelGGL((k_group_rows<T, NQ, TAIL, true>), grid, blk, 0, st, a, with_rows);
-    else hipLaunchKernelGGL((k_group_rows<T, NQ, TAIL, false>), grid, blk, 0, st, a, with_rows);
-    hipLaunchKernelGGL(k_group_any, dim3(a.words), dim3(BLOCK), 0, st, a);
-    const int blocks_in = (int)(n < a.f.V ? n : a.f.V);
-    hipLaunchKernelGGL((k_group_reduce<T, NQ, TAIL>), dim3(with_sums.total + blocks_in + (int)a.f.V), dim3(SUM_THREADS), 0, st, a, with_sums,
-                       blocks_in);
+    const int n = a.f.b.n_centers, V = (int)a.f.V;
+    if (what == GROUP_ROWS) {
+        hipLaunchKernelGGL(k_group_count, dim3((n + GROUP_RANGE - 1) / GROUP_RANGE), dim3(GROUP_THREADS), 4u * (unsigned)(65 * a.words + 1), st, a);
+        const dim3 grid(aux.total + n), blk(BLOCK);
+        if (a.f.center_loss) hipLaunchKernelGGL((k_group_rows<T, NQ, TAIL, true>), grid, blk, 0, st, a, aux);
+        else hipLaunchKernelGGL((k_group_rows<T, NQ, TAIL, false>), grid, blk, 0, st, a, aux);
+        return;
+    }
+    const int blocks_in = what & GROUP_SUMS_IN ? std::min(n, V) : 0, blocks_out = what & GROUP_SUMS_OUT ? V : 0;
+    if (blocks_out) hipLaunchKernelGGL(k_group_any, dim3(a.words), dim3(BLOCK), 0, st, a);
+    hipLaunchKernelGGL((k_group_reduce<T, NQ, TAIL>), dim3(aux.total + blocks_in + blocks_out), dim3(SUM_THREADS), 0, st, a, aux, blocks_in);
 }
 
 template <typename T>
-static void launch_group_t(GroupArgs &a, const AuxWork &x, const AuxWork &y, hipStream_t st)
+static void launch_group_t(const GroupArgs &a, int what, const AuxWork &x, hipStream_t st)
 {
     const int full = a.f.D / (4 * WAVE), rest = a.f.D - full * 4 * WAVE;   // as in the forward pass
     if (rest > 0 && rest <= WAVE && full >= 1) {
         switch (full) {
-        case 1: launch_group_k<T, 1, true>(a, x, y, st); break;
-        case 2: launch_group_k<T, 2, true>(a, x, y, st); break;
-        default: launch_group_k<T, 3, true>(a, x, y, st); break;
+        case 1: launch_group_k<T, 1, true>(a, what, x, st); break;
+        case 2: launch_group_k<T, 2, true>(a, what, x, st); break;
+        default: launch_group_k<T, 3, true>(a, what, x, st); break;
         }
         return;
     }
     switch ((a.f.D / 4 + WAVE - 1) / WAVE) {
-    case 1: launch_group_k<T, 1, false>(a, x, y, st); break;
-    case 2: launch_group_k<T, 2, false>(a, x, y, st); break;
-    case 3: launch_group_k<T, 3, false>(a, x, y, st); break;
-    default: launch_group_k<T, 4, false>(a, x, y, st); break;
+    case 1: launch_group_k<T, 1, false>(a, what, x, st); break;
+    case 2: launch_group_k<T, 2, false>(a, what, x, st); break;
+    case 3: launch_group_k<T, 3, false>(a, what, x, st); break;
+    default: launch_group_k<T, 4, false>(a, what, x, st); break;
     }
 }
 
-void tn_launch_group(GroupArgs &a, const AuxWork &with_rows, const AuxWork &with_sums, hipStream_t st)
+void tn_launch_group(const GroupArgs &a, int what, const AuxWork &aux, hipStream_t st)
 {
-    if (a.f.dtype == 0) launch_group_t<float>(a, with_rows, with_sums, st);
-    else launch_group_t<bf16_t>(a, with_rows, with_sums, st);
+    if (a.f.dtype == 0) launch_group_t<float>(a, what, aux, st);
+    else launch_group_t<bf16_t>(a, what, aux, st);
 }

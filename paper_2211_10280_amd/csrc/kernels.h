@@ -242,7 +242,9 @@ struct GroupArgs {
 };
 static inline i64 tn_group_pitch(i64 V, i64 n_centers) { return ((n_centers < V ? n_centers : V) + n_centers / 64 + 64) & ~(i64)63; }
 struct AuxWork;
-void tn_launch_group(GroupArgs &a, const AuxWork &with_rows, const AuxWork &with_sums, hipStream_t st);
+// what: the pairs and their rows, or one of the tables' sums or both; `aux` rides with the rows, with the sums
+enum { GROUP_ROWS = 0, GROUP_SUMS_IN = 1, GROUP_SUMS_OUT = 2 };
+void tn_launch_group(const GroupArgs &a, int what, const AuxWork &aux, hipStream_t st);
 
 void tn_launch_loss(const float *center_loss, int n_centers, float inv_P, float *mean_loss,
                     hipStream_t st);

@@ -267,6 +267,12 @@ def test_sgns_grad_by_pairs_of_words_whatever_outputs_are_asked_for(case):
             assert np.array_equal(gi, wi), list(asked)
             assert np.array_equal(gr, wr), list(asked)
         assert loss.item() == loss_w.item()
+    B.tensair_profile(m.h, 2)                           # every stage by itself: the same sums again
+    m.sgns_grad(t, begin, n, 0, got, mean_loss=loss)
+    m.status()
+    assert [tag for tag, _ in B.tensair_profile_read(m.h)] == [B.PROFILE_TAGS[i] for i in (1, 3, 4, 2, 5, 6)]
+    for (gi, gr), (wi, wr) in zip(got.to_host(), want.to_host()):
+        assert np.array_equal(gi, wi) and np.array_equal(gr, wr)
     m.close()
 
 

@@ -198,3 +198,16 @@ def test_optional_outputs_do_not_choose_the_gradients_form(trace, outputs):
     assert "k_group_rows" in [k for k, _, _ in did] and not any("forward" in k or "segreduce" in k for k, _, _ in did)
     tiles = [g for k, g, _ in did if k == "k_prep_pass"]
     assert tiles == [3 + (625 if "offsets_out" in outputs else 0)]
+
+
+def test_stages_of_the_gradient_by_pairs_are_timed_one_by_one(trace):
+    """Profile level 2: an event before the first stage and after every one, each in launches of its own."""
+    did = trace([["profile", 2], ["grad", 100, 5000, 0]], vocab=300, dim=64, window=8, negatives=15, max_centers=5000)[1]["did"]
+    stages = [[]]
+    for d in did:
+        if d[0] == "event":
+            stages.append([])
+        else:
+            stages[-1] += names([d])
+    assert stages == [[], ["k_prep_clear", "k_prep_keys"], ["k_prep_count", "k_prep_pass"], ["k_prep_segments"] * 2,
+                      ["k_group_count", "k_group_rows"], ["k_group_reduce"], ["k_group_any", "k_group_reduce"], []]
