@@ -204,6 +204,7 @@ struct tensair_model {
     u32 *wbase[2], *wblk[2];   // tensair_grad_add: place of every 64-row word in the summed gradient
     std::vector<Draw> h_draw;  // the same on the host
     double different = 1.0;    // share of a position's negatives that are different words, as expected
+    double hottest = 0.0;      // share of the most frequent word among all negatives
     // second stream, forked from and joined to the caller's stream with events: the forward pass beside the sort of a
     // large mini-batch that was not prepared, the preparation of an announced one that is too large to ride
     hipStream_t side = nullptr;
@@ -301,8 +302,8 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
 // probability is below 1 keep floor(p * 2^32) as acceptance threshold and hand the rest
 // of their mass to a donor; work lists are filled in ascending id order and consumed
 // from the back, so the table is a deterministic function of the counts.
-// *different: how many of n draws are different words, as a share of n, roughly.
-bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double n, double *different)
+// *different: how many of n draws are different words, as a share of n, roughly; *hottest: the largest probability.
+bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double n, double *different, double *hottest)
 {
     draw.resize((size_t)V);
     std::vector<double> prob((size_t)V);
@@ -313,6 +314,7 @@ bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double 
         draw[(size_t)i] = {0xFFFFFFFFu, (int32_t)i};
     }
     if (!(total > 0.0)) return false;
+    *hottest = *std::max_element(prob.begin(), prob.end()) / total;
     std::vector<int32_t> lo, hi;
     lo.reserve((size_t)V);
     hi.reserve((size_t)V);
@@ -351,6 +353,10 @@ bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double 
 // share 0.84: step 332 -> 255 us), narrow ones, whose gathers weigh less, a little (D = 64: 0.84 231 -> 247, 0.82 298 -> 284,
 // 0.67 251 -> 237, 0.44 179 -> 164).
 static double pairs_below(int D) { return D <= TN_SUB_MAX_DIM ? 0.8 : TN_REPEATS_BELOW; }
+// ... and only where no word is most of the negatives: the occurrences of a word are counted one after the other (step, 256
+// tasks each, D = 32, by occurrences / by pairs: one word, 4 200 centers 103 / 185 us, 65 536 centers 817 / 1 961; a share of
+// 0.63 96 / 110 and 722 / 979; of 0.42 92 / 94 and 672 / 597).
+#define TN_GROUP_MAX_SHARE 0.5
 // Stage tags of tensair_profile_read.  A tag's duration runs from the previous mark to its own.
 enum { PF_BEGIN_GRAD = 0, PF_KEYS, PF_FORWARD, PF_SORT, PF_SEGMENTS, PF_REDUCE_IN, PF_REDUCE_OUT,
        PF_BEGIN_APPLY, PF_APPLY_INDEX, PF_APPLY_UPDATE, PF_BEGIN_ADD, PF_ADD_INDEX, PF_ADD_ROWS,
@@ -489,7 +495,7 @@ int tensair_model_init(tensair_model **out, const tensair_config *cfg, void *w_i
     m->w_in = w_in;
     m->w_out = w_out;
     carve(*cfg, sz, (char *)workspace, m);
-    if (!build_alias(unigram_counts, cfg->vocab, m->h_draw, 2.0 * cfg->window * cfg->negatives, &m->different)) {
+    if (!build_alias(unigram_counts, cfg->vocab, m->h_draw, 2.0 * cfg->window * cfg->negatives, &m->different, &m->hottest)) {
         delete m;
         return fail(TENSAIR_EINVAL, "unigram_counts has no positive entry");
     }
@@ -833,7 +839,8 @@ static void abandon_side_work(tensair_model *m)
 // Whether the gradient of a mini-batch goes by pairs of words (group.hip).  Such a mini-batch is prepared by its own call.
 static bool goes_by_pairs(const tensair_model *m, i64 P)
 {
-    return m->sz.group && m->different <= pairs_below(m->cfg.dim) && P * (m->cfg.negatives + 1) > TN_GROUP_MIN_OCC;
+    return m->sz.group && m->different <= pairs_below(m->cfg.dim) && m->hottest <= TN_GROUP_MAX_SHARE &&
+           P * (m->cfg.negatives + 1) > TN_GROUP_MIN_OCC;
 }
 
 int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, int64_t center_begin,

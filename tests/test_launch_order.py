@@ -211,3 +211,11 @@ def test_stages_of_the_gradient_by_pairs_are_timed_one_by_one(trace):
             stages[-1] += names([d])
     assert stages == [[], ["k_prep_clear", "k_prep_keys"], ["k_prep_count", "k_prep_pass"], ["k_prep_segments"] * 2,
                       ["k_group_count", "k_group_rows"], ["k_group_reduce"], ["k_group_any", "k_group_reduce"], []]
+
+
+# by pairs of words: the most frequent word's share of the negatives is counts^0.75 / sum
+@pytest.mark.parametrize("counts,pairs", [([7], False), ([1, 1], True), ([2, 1], False), ([100, 46, 30, 22], True), ([2000] + [1] * 200, False),
+                                          ([20] + [1] * 299, True)])
+def test_a_word_that_is_most_of_the_negatives_is_not_counted_by_pairs(trace, counts, pairs):
+    did = names(trace([["grad", 100, 5000, 0]], counts=counts, vocab=len(counts), dim=64, window=8, negatives=15, max_centers=5000)[0]["did"])
+    assert ("k_group_rows" in did) == pairs and any("forward" in k for k in did) != pairs
