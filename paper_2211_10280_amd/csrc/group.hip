@@ -45,8 +45,9 @@ __device__ __forceinline__ float sum_waves(const float *red, int row, int e)
 }
 
 // A wave's row of long sums.  Hundreds of chunks are added up for a frequent word, and in one chain of fp32 additions that
-// loses accuracy (rows against 64 bits 2.6e-7; sums of eight rows added up in fp32 1.3e-7; in double 0.6e-7 to 0.9e-7; the
-// reduction of sorted occurrences, whose sums meet in a tree, 0.7e-7 to 1.0e-7).
+// loses accuracy (rows of W_out against 64 bits 2.6e-7; sums of four or eight rows added up in fp32 1.3e-7; in double 0.6e-7 to
+// 0.9e-7; the reduction of sorted occurrences, whose sums meet in a tree, 0.7e-7 to 1.0e-7.  The shares of a center word are as
+// many as it has chunks: 500 000 centers of 2 words 1.5e-7 in fp32, 0.9e-7 in double).
 template <int NQ, bool TAIL>
 struct LongRow {
     double q[NQ][4], t;
@@ -257,8 +258,8 @@ __global__ void __launch_bounds__(SUM_THREADS) k_group_reduce(GroupArgs a, AuxWo
     const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
     const int U = *a.n_in;
     int b = (int)blockIdx.x - aux.total;
-    Row acc;
-    acc.zero();
+    LongRow<NQ, TAIL> total;
+    total.zero();
     float *dst;
     if (b < blocks_in) {                    // a center word: the shares of its chunks, a chunk per wave
         if (b >= U) return;
@@ -282,7 +283,7 @@ __global__ void __launch_bounds__(SUM_THREADS) k_group_reduce(GroupArgs a, AuxWo
                 for (int j = 0; j < 4; ++j) part.axpy(1.0f, x[j]);
                 of_chunk.axpy(1.0f, part);
             }
-            acc.axpy(1.0f, of_chunk);
+            total.add(of_chunk);
         }
         dst = a.in_rows + (size_t)b * f.D;
     } else {                                // a word: the chunks that have it
@@ -305,8 +306,6 @@ __global__ void __launch_bounds__(SUM_THREADS) k_group_reduce(GroupArgs a, AuxWo
         if (!here) return;
         if (threadIdx.x == 0) a.out_ids[n] = b;
         const int chunks = U + f.b.n_centers / a.positions;      // numbers in use and the few between them
-        LongRow<NQ, TAIL> total;
-        total.zero();
         for (int c0 = wave * WAVE; c0 < chunks; c0 += SUM_WAVES * WAVE) {
             u64 mk = 0;
             int4 meta = make_int4(0, 0, 0, 0);
@@ -338,9 +337,10 @@ __global__ void __launch_bounds__(SUM_THREADS) k_group_reduce(GroupArgs a, AuxWo
                 total.add(part);
             }
         }
-        total.round(acc);
         dst = a.out_rows + (size_t)n * f.D;
     }
+    Row acc;
+    total.round(acc);
     acc.spill(red + wave * ROW, lane);
     __syncthreads();
     for (int i = threadIdx.x; i < f.D; i += SUM_THREADS) dst[i] = sum_waves<SUM_THREADS>(red, ROW, i);

@@ -276,6 +276,27 @@ def test_sgns_grad_by_pairs_of_words_whatever_outputs_are_asked_for(case):
     m.close()
 
 
+def test_long_sums_of_the_gradient_by_pairs_do_not_drift():
+    """2^19 centers of one word, scores of zero, four negative words with one and the same row u: the center's row is
+    (N/2 - 1/2) u.  Every factor is exact (P = 2^22), so a chunk's share is off by the roundings of its product, of its
+    wave's sum and of its own; 4096 of them are added up, and the waves' sums and the row rounded: 5 roundings of 2^-24, not
+    one per chunk."""
+    V, D, w, N, n = 4, 64, 4, 15, 1 << 19
+    gen = torch.Generator().manual_seed(5)
+    u = 1.0 + torch.rand(D, generator=gen)
+    tables = (torch.zeros((V, D), device="cuda"), u.repeat(V, 1).cuda())
+    m = B.Model(V, D, B.F32, w, N, n, 0, 9, np.full(V, 10, np.uint64), tables=tables)
+    g = m.grad_buffers()
+    m.sgns_grad(torch.zeros(n + 100, dtype=torch.int32, device="cuda"), 50, n, 0, g)
+    m.status()
+    (ids, rows), _ = g.to_host()
+    want = 0.5 * (N - 1) * u.double().numpy()
+    err = np.abs(rows[0].astype(np.float64) / want - 1).max()
+    _say("drift", err)
+    assert list(ids) == [0] and err <= 5 * 2.0 ** -24
+    m.close()
+
+
 def _random_grad_cases(n, seed):
     """Seeded shapes: narrow to wide rows, windows 1..6, 0..12 negatives, batches from one center up, streams
     from flat to steep, vocabularies from two words up, batches at the start, inside and at the end of the
