@@ -175,6 +175,14 @@ struct Prefetched {
     }
 };
 
+// What is expected of the words that a mini-batch meets, going by the unigram counts.
+struct WordStats {
+    double different = 1.0;    // share of a position's negatives that are different words
+    double hottest = 0.0;      // share of the most frequent word among all negatives,
+    double per_pair = 0.0;     // the same word's occurrences among the tasks of a pair
+    double center = 0.0;       // and its share of the centers
+};
+
 // A bucket of the alias table; the two lie side by side, so that a draw reads both with one access.
 struct Draw {
     uint32_t thr;
@@ -203,8 +211,7 @@ struct tensair_model {
     int4 *group_meta = nullptr;
     u32 *wbase[2], *wblk[2];   // tensair_grad_add: place of every 64-row word in the summed gradient
     std::vector<Draw> h_draw;  // the same on the host
-    double different = 1.0;    // share of a position's negatives that are different words, as expected
-    double hottest = 0.0;      // share of the most frequent word among all negatives
+    WordStats words;
     // second stream, forked from and joined to the caller's stream with events: the forward pass beside the sort of a
     // large mini-batch that was not prepared, the preparation of an announced one that is too large to ride
     hipStream_t side = nullptr;
@@ -302,19 +309,24 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
 // probability is below 1 keep floor(p * 2^32) as acceptance threshold and hand the rest
 // of their mass to a donor; work lists are filled in ascending id order and consumed
 // from the back, so the table is a deterministic function of the counts.
-// *different: how many of n draws are different words, as a share of n, roughly; *hottest: the largest probability.
-bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double n, double *different, double *hottest)
+// n: draws per position, N: per pair.
+bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double n, int N, WordStats &words)
 {
     draw.resize((size_t)V);
     std::vector<double> prob((size_t)V);
-    double total = 0.0;
+    double total = 0.0, tokens = 0.0;
+    i64 most = 0;
     for (i64 i = 0; i < V; ++i) {
         prob[(size_t)i] = std::pow((double)counts[i], 0.75);
         total += prob[(size_t)i];
+        tokens += (double)counts[i];
+        if (counts[i] > counts[most]) most = i;
         draw[(size_t)i] = {0xFFFFFFFFu, (int32_t)i};
     }
     if (!(total > 0.0)) return false;
-    *hottest = *std::max_element(prob.begin(), prob.end()) / total;
+    words.hottest = prob[(size_t)most] / total;
+    words.center = (double)counts[most] / tokens;
+    words.per_pair = words.center + N * words.hottest;
     std::vector<int32_t> lo, hi;
     lo.reserve((size_t)V);
     hi.reserve((size_t)V);
@@ -328,7 +340,7 @@ bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double 
         met += x - 0.37 * x * x;
         (q < 1.0 ? lo : hi).push_back((int32_t)i);
     }
-    *different = n > 0.0 ? met / n : 1.0;
+    words.different = n > 0.0 ? met / n : 1.0;   // roughly
     const double two32 = 4294967296.0;
     while (!lo.empty() && !hi.empty()) {
         const int32_t poor = lo.back();
@@ -495,7 +507,7 @@ int tensair_model_init(tensair_model **out, const tensair_config *cfg, void *w_i
     m->w_in = w_in;
     m->w_out = w_out;
     carve(*cfg, sz, (char *)workspace, m);
-    if (!build_alias(unigram_counts, cfg->vocab, m->h_draw, 2.0 * cfg->window * cfg->negatives, &m->different, &m->hottest)) {
+    if (!build_alias(unigram_counts, cfg->vocab, m->h_draw, 2.0 * cfg->window * cfg->negatives, cfg->negatives, m->words)) {
         delete m;
         return fail(TENSAIR_EINVAL, "unigram_counts has no positive entry");
     }
@@ -836,10 +848,26 @@ static void abandon_side_work(tensair_model *m)
     m->set[0].hist_clean = m->set[1].hist_clean = false;
 }
 
+// Whether chaining the longest row that a mini-batch is expected to have takes as long as a phase of a preparation, which
+// then rides with it for nothing.  A workgroup adds up 32 partials at a time (as many per group of lanes, where rows are
+// narrow), 0.8 us each time.  After 16 times a phase is always hidden; after 4 it is better off there than under the update
+// of small tables, which is as short itself, while that of larger ones hides it.  Step, us, phase under the update / riding
+// here: after 16 times and more, D = 132, 6 000 centers, 1 000 words, Zipf exponent 1.0 92.9 / 86.0, 30 000 words, 1.2 109.6 /
+// 107.4, D = 64, 1 000 words, 1.4 76.3 / 71.5; after 4 to 16, 300 words, D = 132 and 2 500 centers 54.9 / 50.2, 8 000 words
+// and 6 000 centers 107.8 / 101.2; 8 000 words, D = 300 63.1 / 64.3, 16 000 67.6 / 71.9; 1 000 words, D = 64 50.2 / 52.2.
+static bool long_chain(const tensair_model *m, i64 P, int n_centers)
+{
+    const int D = m->cfg.dim, side_by_side = D > TN_SUB_MAX_DIM ? 1 : D > 64 ? 2 : D > 32 ? 4 : 8;
+    const int times = D > TN_SUB_MAX_DIM && m->cfg.vocab * D <= (i64)1 << 21 ? 4 : 16;
+    const double out = m->words.per_pair * (double)P, in = m->words.center * n_centers;
+    const i64 O = P * (m->cfg.negatives + 1);
+    return std::max(out / (1 << tn_seg_shift(O, D)), in / (1 << tn_seg_shift(n_centers, D))) >= times * 32 * side_by_side;
+}
+
 // Whether the gradient of a mini-batch goes by pairs of words (group.hip).  Such a mini-batch is prepared by its own call.
 static bool goes_by_pairs(const tensair_model *m, i64 P)
 {
-    return m->sz.group && m->different <= pairs_below(m->cfg.dim) && m->hottest <= TN_GROUP_MAX_SHARE &&
+    return m->sz.group && m->words.different <= pairs_below(m->cfg.dim) && m->words.hottest <= TN_GROUP_MAX_SHARE &&
            P * (m->cfg.negatives + 1) > TN_GROUP_MIN_OCC;
 }
 
@@ -982,7 +1010,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     f.center_part = m->center_part;
     f.center_loss = mean_loss ? m->center_loss : nullptr;   // loss terms only on request
     f.inv_P = 1.0f / (float)P;
-    f.repeats = m->different <= TN_REPEATS_BELOW && 2 * c.window * Np1 <= TN_REPEAT_MAX_TASKS;
+    f.repeats = m->words.different <= TN_REPEATS_BELOW && 2 * c.window * Np1 <= TN_REPEAT_MAX_TASKS;
 
     AuxWork aux_fwd, aux_red;     // what rides at the front of the forward pass / of the reduction
     tn_aux_none(aux_fwd);
@@ -1185,12 +1213,13 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, n_centers, f.inv_P, mean_loss);
         if (next_rider(m, false, x, st)) tn_aux_add_prep(aux_red, x);
         PrepPhase y;
-        // the chaining of long rows is short (4 us where a pass of the sort takes 9): a phase rides with it only where there
+        // where the chaining of long rows is short (4 us where a pass of the sort takes 9), a phase rides with it only if there
         // are more left than the table update and the next forward pass can take (1 024 centers, 50 000 words: step 54.6
         // -> 49.0 us with the second pass under the update instead)
         const int later = 1 + (fuse && tn_apply_carries(c.dim, c.vocab) ? 1 : 0);
         const bool rider = tn_seg_chains(r_out.n, c.dim) + tn_seg_chains(r_in.n, c.dim) > 0 &&
-                           m->pend.phase + later < prep_phases(s, true) && next_rider(m, false, y, st);
+                           (long_chain(m, P, n_centers) || m->pend.phase + later < prep_phases(s, true)) &&
+                           next_rider(m, false, y, st);
         tn_launch_segreduce(&r_out, &r_in, &aux_red, rider ? &y : nullptr, st);
     } else {         // one after the other, so that each can be timed
         if (mean_loss) tn_launch_loss(m->center_loss, n_centers, f.inv_P, mean_loss, st);

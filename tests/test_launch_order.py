@@ -219,3 +219,22 @@ def test_stages_of_the_gradient_by_pairs_are_timed_one_by_one(trace):
 def test_a_word_that_is_most_of_the_negatives_is_not_counted_by_pairs(trace, counts, pairs):
     did = names(trace([["grad", 100, 5000, 0]], counts=counts, vocab=len(counts), dim=64, window=8, negatives=15, max_centers=5000)[0]["did"])
     assert ("k_group_rows" in did) == pairs and any("forward" in k for k in did) != pairs
+
+
+@pytest.mark.parametrize("V,D,n,others,rides", [
+    (300, 132, 2500, 64, True), (300, 132, 2500, 1000, False),        # the update of small tables is as short as the chaining
+    (300, 64, 2500, 64, False),                                       # narrow rows are chained faster
+    (60_000, 132, 2500, 4, False), (60_000, 132, 5000, 4, True)])     # a larger update hides a phase, unless the chain is long
+def test_a_phase_rides_with_the_chaining_of_long_rows_where_that_takes_longer(trace, V, D, n, others, rides):
+    """One word a thousand times, the others `others` times each: 0.18 occurrences per pair (139 tiles of 32 in 25 000 pairs), 0.02
+    (16) and, among a thousand words, 0.5 (387, and 774 in 50 000 pairs)."""
+    counts = [1000] + [others] * (min(V, 1000) - 1)
+    batch = lambda i: [n * i, n, 0]                                            # noqa: E731
+    calls = [["prefetch"] + batch(0)]
+    for i in range(4):
+        calls += [["prefetch"] + batch(i + 1), ["step"] + batch(i) + [0]]
+    model = dict(counts=counts, vocab=V, dim=D, window=5, negatives=5, max_centers=n)
+    chaining = lambda c: [g for k, g, _ in launches(c["did"]) if k == "k_segfixup"]     # noqa: E731
+    got = [g for c in trace(calls, **model) if c["call"][0] == "step" for g in chaining(c)]
+    alone = chaining(trace([["grad", 0, n, 0]], **model)[0])[0]
+    assert len(got) == 4 and [g > alone for g in got[:3]] == [rides] * 3
