@@ -458,18 +458,52 @@ static i64 union_rows(const ApplyArgs &a)
     return cap;
 }
 static bool sparse_union(const ApplyArgs &a, i64 min_v) { return a.V >= min_v && 4 * union_rows(a) < 3 * a.V; }
-// less than a fifth of a row of capacity per vocabulary row: a launch that stays on the chip and sweeps over the vocabulary,
-// with the index words of the next two groups of rows on their way while the rows of one are worked on, so that a wave's
-// start and its look-ups are paid once and not per group; the groups are small (the few waves with the frequent words would
-// work on long after the others).  Against the shapes below, sweep / no sweep, whole calls with 3 peers: 200 000 words,
-// D = 256 19.9 / 22.6 us, 400 000 25.8 / 37.5, 800 000 50.0 / 54.7, 1.2 million 69.0 / 66.4, 2 million 82.5 / 74.6, 4 million
-// 120.6 / 128.9; bfloat16 D = 200, 2 million 65.8 / 67.5, 4 million 91.7 / 115.6 and, more touched, 210.7 / 236.0; rows of
-// 128 elements in bfloat16 200 000 words 16.8 / 18.0, 800 000 26.9 / 45.6, 1.2 million 51.7 / 52.4, 2 million 81.5 / 72.5;
-// of 64 100 000 14.7 / 17.7, 800 000 24.5 / 30.9, 1.6 million 33.0 / 33.0; of 32 100 000 14.9 / 13.5, 200 000 16.4 / 20.7,
-// 800 000 20.5 / 21.9, 1.6 million 29.6 / 27.8.  Groups: 4 / 8 rows 400 000 words, D = 256 25.8 / 30.7, 800 000 in bfloat16,
-// D = 400 60.9 / 50.9; 8 / 16 rows 4 million, bfloat16 99.5 / 91.7
+// Few rows of a large vocabulary touched: a launch that stays on the chip and sweeps over the vocabulary, with the index words
+// of the next two groups of rows on their way while the rows of one are worked on, so that a wave's start and its look-ups are
+// paid once and not per group; the groups are small (the few waves with the frequent words would work on long after the
+// others).  Against the shapes below a wave saves what it does for groups that are empty, and takes those that are not one
+// after the other, with one row on its way at a time: the wider the rows and the more of them, the sooner that is the longer
+// way.  So the line lies at a share of the vocabulary's rows, going by the sources' capacities: at most a row of capacity per
+// `sweep_share` vocabulary rows.  Whole calls, no sweep / sweep, with 0.02, 0.09 and 0.19 rows of capacity per vocabulary row:
+//   D = 132      250 000 words 24.1 / 16.8, 27.5 / 20.5, 32.2 / 27.5; 600 000 28.2 / 23.0, 36.2 / 32.5, 41.8 / 45.9; 900 000 41.4 /
+//                31.0, 53.4 / 50.8, 77.7 / 81.5; 1.3 million 45.7 / 38.2, 68.2 / 65.7, 107 / 104; 2 million 54.1 / 47.8, 100 / 91.6, 158 /
+//                144; 4.5 million 109 / 78.3, 206 / 172, 336 / 295;
+//   D = 300      250 000 25.0 / 18.4, 31.6 / 29.3, 40.2 / 39.2; 700 000 53.9 / 38.5, 73.3 / 69.5, 103 / 107; 1.3 million 61.9 / 50.2, 101 /
+//                110, 172 / 189; 3 million 91.5 / 82.9 (0.05 144 / 140), 210 / 212, 383 / 397; 4.5 million 132 / 115 (0.05 212 / 194), 305 / 303,
+//                565 / 573;
+//   D = 512, bfloat16 (0.02, 0.05, 0.09) 400 000 35.6 / 23.4, 39.3 / 29.4, 44.1 / 38.2; 900 000 49.1 / 35.2, 55.6 / 54.1, 75.9 / 82.4;
+//                2 million 62.7 / 56.8, 99.9 / 94.8, 152 / 154; 3 million 91.5 / 79.5, 148 / 141, 225 / 227;
+//   D = 600      250 000 32.5 / 28.8, 40.9 / 35.7, 51.6 / 47.4 (0.19 76.0 / 82.5); 600 000 65.3 / 41.4, 82.9 / 65.2, 102 / 94.9; 1.3
+//                million 77.6 / 78.5, 111 / 125; 3 million 134 / 127, 234 / 235, 370 / 391.
+// Groups of 4 / 8 rows: 400 000 words, D = 256 25.8 / 30.7, 800 000 in bfloat16, D = 400 60.9 / 50.9; 8 / 16 rows: 2 million, D = 200
+// in bfloat16 41.6 / 51.7, 3 million 55.5 / 57.5, D = 300 140 / 153,
+// D = 512 in bfloat16 91.8 / 79.3; 4.5 million, D = 200 in bfloat16 76.7 / 68.9.  A grid that fits the
+// registers of every row width (4 to 6 waves per SIMD above 256 elements instead of 7) is up to 19 % slower than this one.
 #define SWEEP_MIN_V 131072
 static bool sweep_union(const ApplyArgs &a) { return a.V >= SWEEP_MIN_V && 5 * union_rows(a) < a.V; }
+// vocabulary rows per row of capacity from which on the update sweeps with whole waves per row; 0: not at all.  bfloat16 tables of
+// more than 256 elements take more registers (a wave per SIMD less is on the chip): D = 300 at 600 000 words 70.9 / 60.9 and 80.9 /
+// 73.6 with 0.09 and 0.13 rows of capacity, D = 512 in bfloat16 61.5 / 63.7 and 74.1 / 82.8.
+static int sweep_share(i64 V, int D, bool bf16)
+{
+    const int iters = (D / 4 + WAVE - 1) / WAVE;
+    if (V < SWEEP_MIN_V) return 0;
+    if (iters == 1) return V >= 524288 && V < 1000000 ? 11 : 5;
+    if (V < (iters == 2 && !bf16 ? 655360 : 524288)) return iters == 2 ? 5 : 7;
+    if (V >= 1000000 && V < 3000000) return iters == 2 ? 32 : 0;
+    return V >= 4000000 && iters == 2 && !bf16 ? 11 : 16;
+}
+// Rows of at most 128 elements are short: here it is the groups that are not empty that a wave of a sweep pays for.  Whole calls,
+// no sweep / sweep: 8 lanes per row, D = 32, 25 000 rows of capacity at 250 000 words 21.9 / 18.7, 47 000 22.5 / 20.6, 20 000 at 400 000
+// 21.6 / 19.3, 60 000 22.4 / 23.4, 16 000 at 800 000 21.5 / 20.3, 40 000 22.6 / 25.4, 152 000 26.7 / 36.1; 16 lanes, D = 64, 25 000
+// at 250 000 19.3 / 18.5, 47 000 20.0 / 20.7, 20 000 at 400 000 19.3 / 19.4, 40 000 20.2 / 22.1, 16 000 at 800 000 25.2 / 21.3, 80 000
+// 29.0 / 30.1, in bfloat16 27.1 / 30.8; 32 lanes, D = 128, 76 000 at 400 000 31.7 / 31.3, 80 000 at 800 000 44.0 / 33.4, 152 000
+// 52.8 / 47.1.  From a million words on 1.2 million, D = 128 in bfloat16 51.7 / 52.4, 1.6 million, D = 64 33.0 / 33.0.
+static bool sweep_sub(const ApplyArgs &a, int sub)
+{
+    if (!sweep_union(a) || a.V >= 1000000) return false;
+    return sub == 32 || (sub == 8 && a.V < 300000) || union_rows(a) <= 28000;
+}
 
 // 4 rows per group of lanes and wave, or 32 rows per wave where few rows are touched (8 M words, D = 128, bf16:
 // update 0.67 -> 0.42 ms; 16 M words, D = 64: 0.58 -> 0.40 ms), from 655 360 words on (whole call with 32 rows per wave /
@@ -480,7 +514,7 @@ static bool sweep_union(const ApplyArgs &a) { return a.V >= SWEEP_MIN_V && 5 * u
 template <typename T, int SUB, bool STREAM, typename Rider>
 static void launch_apply_sub(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
-    if (sweep_union(a) && a.V < 1000000) {
+    if (sweep_sub(a, SUB)) {
         if (SUB < 32 || a.V < 393216) launch_apply_sub_r<T, SUB, 2, STREAM, true>(a, rider, st);
         else launch_apply_sub_r<T, SUB, 4, STREAM, true>(a, rider, st);
     } else if (SUB > 8 && sparse_union(a, 655360)) launch_apply_sub_r<T, SUB, 16, STREAM, false>(a, rider, st);
@@ -526,9 +560,10 @@ template <typename T, bool STREAM, bool PACKED, typename Rider>
 static void launch_apply_t(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
     const i64 unit = sizeof(T) == 2 || PACKED ? 73728 : 131072;
-    if (sweep_union(a) && (a.V < 1000000 || a.V >= 3000000)) {
+    const int share = sweep_share(a.V, a.D, sizeof(T) == 2);
+    if (share > 0 && share * union_rows(a) < a.V) {
         if (a.V < 655360) launch_apply_g<T, 4, STREAM, PACKED, true>(a, rider, st);
-        else if (a.V < 1000000) launch_apply_g<T, 8, STREAM, PACKED, true>(a, rider, st);
+        else if (a.V < (a.D > 4 * WAVE && sizeof(T) == 4 ? 4000000 : 3000000)) launch_apply_g<T, 8, STREAM, PACKED, true>(a, rider, st);
         else launch_apply_g<T, 16, STREAM, PACKED, true>(a, rider, st);
     } else if (sparse_union(a, unit * ((a.D / 4 + WAVE - 1) / WAVE + 1))) launch_apply_g<T, APPLY_G_SPARSE, STREAM, PACKED, false>(a, rider, st);
     else if (!STREAM && a.V < APPLY_SMALL_V) launch_apply_g<T, 1, STREAM, PACKED, false>(a, rider, st);

@@ -442,8 +442,8 @@ def test_dasgd_apply_parity_few_rows_of_a_large_vocabulary(dtype, V, D, stride, 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("V,D,stride,K,thin", [
-    # few rows touched: from 786 432 words on more vocabulary rows per wave, below it as many as elsewhere
-    (786_431, 132, 132, 2, 400), (786_432, 132, 160, 2, 400), (800_011, 100, 104, 3, 400), (800_011, 36, 36, 1, 400),
+    # three eighths of a row of capacity per vocabulary row: more vocabulary rows per wave, without a sweep
+    (786_431, 132, 132, 2, 2), (786_432, 132, 160, 2, 2), (800_011, 100, 104, 3, 2), (800_011, 36, 36, 1, 2),
     # small vocabularies: one row per wave or group of lanes, up to 16 384 words (times rows per wave)
     (16_383, 132, 132, 3, 1), (16_384, 132, 132, 3, 1), (32_767, 100, 100, 2, 1), (32_768, 100, 100, 2, 1),
     (131_071, 32, 32, 1, 10), (1, 8, 8, 1, 1)])
@@ -452,19 +452,22 @@ def test_dasgd_apply_parity_at_the_borders_of_its_shapes(dtype, V, D, stride, K,
 
 
 @pytest.mark.parametrize("dtype,V,D,stride,K", [
-    # few rows touched: on both sides of the vocabulary from which more of its rows are taken per wave
+    # three eighths of a row of capacity per vocabulary row (too many for a sweep): on both sides of the vocabulary from which
+    # more of its rows are taken per wave
     ("f32", 262_143, 132, 132, 2), ("f32", 262_144, 132, 132, 2), ("f32", 393_215, 300, 300, 1), ("f32", 393_216, 300, 304, 1),
     ("bf16", 147_455, 132, 136, 2), ("bf16", 147_456, 132, 136, 2), ("bf16", 294_911, 516, 516, 1), ("bf16", 294_912, 516, 516, 1),
-    ("f32", 655_359, 100, 100, 2), ("f32", 655_360, 100, 100, 2), ("bf16", 655_360, 36, 36, 2), ("f32", 655_360, 32, 32, 2)])
+    ("f32", 655_359, 100, 100, 2), ("f32", 655_360, 100, 100, 2), ("bf16", 655_360, 36, 36, 2), ("f32", 655_360, 32, 32, 2),
+    ("f32", 1_000_003, 132, 132, 1), ("bf16", 1_000_000, 128, 128, 2)])
 def test_dasgd_apply_parity_at_the_borders_of_its_sparse_shape(dtype, V, D, stride, K):
-    _apply_parity(dtype, V, D, stride, K, True, thin=400)
+    _apply_parity(dtype, V, D, stride, K, True, thin=2)
 
 
 @pytest.mark.parametrize("dtype,V,D,K", [
-    # less than a fifth of a row of capacity per vocabulary row: from 131 072 words on the update sweeps over the vocabulary,
-    # in small groups of rows (other sizes from 393 216 and 655 360 words on), up to a million words
+    # a hundredth of a row of capacity per vocabulary row: from 131 072 words on the update sweeps over the vocabulary, in small
+    # groups of rows (other sizes from 393 216 and 655 360 words on), rows of at most 128 elements up to a million words
     ("f32", 131_071, 132, 3), ("f32", 131_072, 132, 3), ("bf16", 655_361, 132, 1), ("f32", 131_072, 8, 2),
-    ("bf16", 400_037, 64, 3), ("bf16", 393_215, 128, 3), ("f32", 393_217, 100, 1), ("f32", 999_999, 36, 2), ("f32", 1_000_000, 36, 2)])
+    ("bf16", 400_037, 64, 3), ("bf16", 393_215, 128, 3), ("f32", 393_217, 100, 1), ("f32", 999_999, 36, 2), ("f32", 1_000_000, 36, 2),
+    ("f32", 1_000_000, 132, 2), ("bf16", 131_075, 1024, 1), ("f32", 140_000, 600, 2), ("bf16", 1_000_001, 260, 1)])
 def test_dasgd_apply_parity_where_it_sweeps_over_the_vocabulary(dtype, V, D, K):
     _apply_parity(dtype, V, D, D, K, True, thin=60)
 
@@ -1027,9 +1030,16 @@ def test_grad_pack_parity(V, D, ui, uo):
 
 
 @pytest.mark.parametrize("dtype,V,D,K", [                  # messages take the whole-wave shape at every dimension: its groups
-    ("f32", 131_072, 8, 3), ("bf16", 655_359, 8, 3), ("f32", 655_360, 36, 1), ("bf16", 999_999, 8, 2), ("f32", 3_000_001, 8, 3)])
+    ("f32", 131_072, 8, 3), ("bf16", 655_359, 8, 3), ("f32", 655_360, 36, 1), ("bf16", 999_999, 8, 2), ("f32", 3_000_001, 8, 3),
+    ("bf16", 2_999_999, 8, 1), ("f32", 3_000_000, 8, 2)])
 def test_dasgd_apply_packed_parity_where_it_sweeps_over_the_vocabulary(dtype, V, D, K):
     test_dasgd_apply_packed_parity(dtype, V, D, D, K, True, 60)
+
+
+@pytest.mark.parametrize("dtype,V,D,K", [("f32", 262_143, 8, 1), ("bf16", 147_456, 8, 2), ("f32", 1_000_000, 12, 2), ("bf16", 2_999_999, 8, 1)])
+def test_dasgd_apply_packed_parity_in_its_sparse_shape(dtype, V, D, K):
+    """Too many rows for a sweep (0.375 rows of capacity per vocabulary row)."""
+    test_dasgd_apply_packed_parity(dtype, V, D, D, K, True, 2)
 
 
 @pytest.mark.parametrize("V,ua,ub", [(131_072, (500, 9_000), (77, 4_000)), (524_287, (5, 30_001), (4_000, 70_000)),

@@ -238,3 +238,24 @@ def test_a_phase_rides_with_the_chaining_of_long_rows_where_that_takes_longer(tr
     got = [g for c in trace(calls, **model) if c["call"][0] == "step" for g in chaining(c)]
     alone = chaining(trace([["grad", 0, n, 0]], **model)[0])[0]
     assert len(got) == 4 and [g > alone for g in got[:3]] == [rides] * 3
+
+
+F, H = B.F32, B.BF16
+
+
+@pytest.mark.parametrize("D,dtype,V,rows,sweeps", [            # rows: vocabulary rows per row of capacity, or the capacity itself
+    (132, F, 131_071, 6, False), (132, F, 131_072, 6, True), (256, H, 524_287, 5.1, True), (256, F, 524_287, 4.9, False),
+    (256, F, 524_288, 10.9, False), (256, H, 524_288, 11.1, True), (256, F, 999_999, 10.9, False), (256, F, 1_000_000, 5.1, True),
+    (256, F, 4_000_000, 5.1, True), (260, H, 524_287, 5.1, True), (512, H, 524_288, 15.9, False), (512, H, 524_288, 16.1, True),
+    (260, F, 655_359, 5.1, True), (512, F, 655_360, 15.9, False), (512, F, 999_999, 16.1, True), (512, F, 1_000_000, 31, False),
+    (512, F, 1_000_000, 33, True), (512, H, 2_999_999, 31, False), (512, F, 3_000_000, 16.1, True), (300, F, 3_999_999, 15.9, False),
+    (300, F, 4_000_000, 11.1, True), (300, F, 4_000_000, 10.9, False), (300, H, 4_000_000, 15.9, False), (516, F, 524_287, 6.9, False),
+    (516, F, 524_287, 7.1, True), (1024, H, 999_999, 16.1, True), (1024, F, 1_000_000, 1000, False), (1024, F, 2_999_999, 1000, False),
+    (1024, H, 3_000_000, 16.1, True), (128, F, 131_071, 6, False), (128, F, 131_072, 6, True), (128, H, 999_999, 5.1, True),
+    (128, F, 1_000_000, 100, False), (64, F, 400_000, 28_000, True), (64, H, 400_000, 28_001, False), (36, F, 140_000, 5.1, True),
+    (32, F, 299_999, 5.1, True), (32, F, 300_000, 5.1, False), (32, H, 300_000, 28_000, True)])
+def test_borders_of_the_sweep_of_the_update(trace, D, dtype, V, rows, sweeps):
+    """A sweep's grid is what fits the chip, 256 compute units times 7; the other shapes' covers the vocabulary."""
+    rows = int(V / rows) if rows <= 1000 else rows
+    did = trace([["apply", 60, rows, 0]], **dict(SMALL, vocab=V, dim=D, dtype=dtype, max_centers=64))[0]["did"]
+    assert (launches(did)[-1][1] == 256 * 7) == sweeps
