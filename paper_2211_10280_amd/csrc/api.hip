@@ -865,10 +865,23 @@ static bool long_chain(const tensair_model *m, i64 P, int n_centers)
 }
 
 // Whether the gradient of a mini-batch goes by pairs of words (group.hip).  Such a mini-batch is prepared by its own call.
+// Counting a chunk and adding up a word look at every word and every chunk, whatever they hold: that has to be paid for by
+// occurrences per word, the more of them the cheaper an occurrence is by itself -- narrow rows, positions that repeat words.
+// Step, us, by occurrences / by pairs (expected share of different words 0.5 to 0.6): D = 32, 128 tasks per position, 128
+// occurrences per word 146 / 187, 192 196 / 227, 256 279 / 268; D = 128, 94 166 / 206, 141 220 / 249, 188 293 / 295; D = 256,
+// 94 187 / 210, 141 249 / 255, 188 327 / 303, 256 tasks 94 181 / 189, 141 236 / 222; (0.65 to 0.83) D = 32, 256 tasks, 94
+// 180 / 203, 141 241 / 248, 188 302 / 293; D = 132, 128 tasks, 94 235 / 245, 128 234 / 216, 256 tasks 94 231 / 207; D = 512, 94,
+// 0.6 248 / 248, 256 tasks 246 / 221.
 static bool goes_by_pairs(const tensair_model *m, i64 P)
 {
-    return m->sz.group && m->words.different <= pairs_below(m->cfg.dim) && m->words.hottest <= TN_GROUP_MAX_SHARE &&
-           P * (m->cfg.negatives + 1) > TN_GROUP_MIN_OCC;
+    const tensair_config &c = m->cfg;
+    const WordStats &x = m->words;
+    const i64 O = P * (c.negatives + 1);
+    if (!m->sz.group || x.different > pairs_below(c.dim) || x.hottest > TN_GROUP_MAX_SHARE || O <= TN_GROUP_MIN_OCC) return false;
+    const bool repeat = x.different < 0.65;
+    const int per_word = c.dim > 256 ? 0 : c.dim <= 64 ? (repeat ? 200 : 150) : c.dim <= TN_SUB_MAX_DIM ? (repeat ? 150 : 90)
+                         : repeat ? 136 : 2 * c.window * (c.negatives + 1) < 256 ? 104 : 90;
+    return O >= per_word * c.vocab;
 }
 
 int tensair_prefetch(tensair_model *m, const int32_t *tokens, int64_t n_tokens, int64_t center_begin,
