@@ -203,3 +203,22 @@ def ulp_err_at_t(got, want, ref, chunk=1 << 26):
         mx = max(mx, float(err.max()))
         beyond += int((err > 2).sum())
     return mx, beyond / max(g.numel(), 1)
+
+
+# More than 2^20 occurrences over at most 12 288 words that repeat: the gradient goes by pairs of words (which the launches
+# of each case are checked for).  Words and 64-word groups just full and of one word, every row shape, centers in chunks of 64 positions and
+# of one, both ends of the stream, the fewest tasks per position.
+PAIR_CASES = [
+    # V, D, stride, zipf, w, N, B, begin, dtype
+    (4, 4, 4, 1.0, 8, 15, 4097, 8, "f32"), (40, 32, 32, 1.2, 8, 15, 4200, 0, "f32"), (64, 132, 136, 0.5, 8, 15, 4099, 1901, "bf16"),
+    (65, 300, 320, 0.5, 8, 15, 4097, 300, "f32"), (2_000, 512, 512, 1.4, 8, 15, 4111, 5, "bf16"), (5_000, 260, 260, 1.5, 8, 31, 2500, 0, "bf16"),
+    (10_000, 256, 256, 1.5, 8, 15, 6000, 0, "f32"), (12_288, 64, 64, 1.5, 8, 31, 4900, 100, "f32"), (30, 520, 520, 0.8, 4, 15, 8_300, 17, "f32"),
+    (50, 1024, 1024, 0.8, 8, 15, 4100, 0, "f32"), (50, 772, 772, 0.8, 8, 15, 4100, 0, "bf16")]
+
+
+def pair_stream(case):
+    """Tokens and unigram counts of such a case."""
+    V, D, _, zipf, _, _, n, begin, _ = case
+    p = np.arange(1, V + 1, dtype=np.float64) ** -zipf
+    tok = np.random.default_rng(V + D).choice(V, size=max(begin + n, 6000), p=p / p.sum()).astype(np.int32)
+    return tok, np.bincount(tok, minlength=V).astype(np.uint64)

@@ -15,8 +15,8 @@ import pytest
 import torch
 
 import oracle
-from helpers import (BF16_CHAIN_FRAC, BF16_CHAIN_MAX, BF16_MSG_CHAIN_FRAC, BF16_MSG_CHAIN_MAX, BF16_ULP, FORCED_BEYOND, TOL_DELTA, TOL_LOSS, TOL_ROWS, TOL_TABLE, bf16_to_f32, bf16_ulp_err,
-                     bf16_ulp_err_t, delta_rel_l2_t, rel_l2, rel_l2_t, rows_rel, to_dev, ulp_err_at_t, ulp_stats_t)
+from helpers import (BF16_CHAIN_FRAC, BF16_CHAIN_MAX, BF16_MSG_CHAIN_FRAC, BF16_MSG_CHAIN_MAX, BF16_ULP, FORCED_BEYOND, PAIR_CASES, TOL_DELTA, TOL_LOSS, TOL_ROWS, TOL_TABLE, bf16_to_f32, bf16_ulp_err,
+                     bf16_ulp_err_t, delta_rel_l2_t, pair_stream, rel_l2, rel_l2_t, rows_rel, to_dev, ulp_err_at_t, ulp_stats_t)
 from oracle.driver import OracleWorker
 from paper_2211_10280_amd import binding as B
 import workload as W
@@ -175,12 +175,13 @@ def test_sgns_grad_parity_where_words_repeat(case):
     _grad_parity(case)
 
 
-@pytest.mark.parametrize("w,N", [(8, 15), (3, 84), (3, 85)])      # 256, 510 and 516 tasks per position: the last goes the plain way
+# 256, 510 and 516 tasks per position: the last goes the plain way; 4200 positions: by pairs of words
+@pytest.mark.parametrize("w,N,Bc", [(8, 15, 90), (3, 84, 90), (3, 85, 90), (8, 15, 4200), (3, 84, 2100)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_mean_loss_where_scores_overflow(w, N, dtype):
+def test_mean_loss_where_scores_overflow(w, N, Bc, dtype):
     """A word whose dot products overflow to +inf loses nothing as a context, one with -inf nothing as a negative: the
     loss is that of the other words (whose scores are zero: ln 2 each), whatever forward pass is taken."""
-    V, D, T, Bc = 40, 16, 2_000, 90
+    V, D, T = 40, 16, 2_000 if Bc < 1000 else 5_000
     rng = np.random.default_rng(w + N)
     tok = rng.integers(0, 20, T).astype(np.int32)                  # words 0..19 are met as contexts only ...
     counts = np.zeros(V, np.uint64)
@@ -228,14 +229,11 @@ def test_sgns_grad_parity_at_the_borders_of_its_tiles(case):
     _grad_parity(case)
 
 
-# more than 2^20 occurrences over at most 12 288 words that repeat: the gradient goes by pairs of words.  Words and 64-word groups just full, every row shape, centers in chunks of 64 positions and
-# of one, both ends of the stream, the fewest tasks per position
-PAIR_CASES = [
-    # V, D, stride, zipf, w, N, B, begin, dtype
-    (4, 4, 4, 1.0, 8, 15, 4097, 8, "f32"), (40, 32, 32, 1.2, 8, 15, 4200, 0, "f32"), (64, 132, 136, 0.5, 8, 15, 4099, 1901, "bf16"),
-    (65, 300, 320, 0.5, 8, 15, 4097, 300, "f32"), (2_000, 512, 512, 1.4, 8, 15, 4111, 5, "bf16"), (5_000, 260, 260, 1.5, 8, 31, 2500, 0, "bf16"),
-    (10_000, 256, 256, 1.5, 8, 15, 6000, 0, "f32"), (12_288, 64, 64, 1.5, 8, 31, 2200, 100, "f32"), (30, 520, 520, 0.8, 4, 15, 8_300, 17, "f32"),
-    (50, 1024, 1024, 0.8, 8, 15, 4100, 0, "f32"), (50, 772, 772, 0.8, 8, 15, 4100, 0, "bf16")]
+@pytest.mark.parametrize("case", PAIR_CASES, ids=lambda c: f"V{c[0]}_D{c[1]}_B{c[6]}_{c[8]}")
+def test_sgns_grad_parity_by_pairs_of_words(case):
+    """Against the oracle, with every optional output."""
+    V, D, stride, zipf, w, N, n, begin, dtype = case
+    _grad_parity((V, D, stride, None, zipf, w, N, n, begin, dtype), stream=pair_stream(case))
 
 
 @pytest.mark.parametrize("case", PAIR_CASES, ids=lambda c: f"V{c[0]}_D{c[1]}_B{c[6]}_{c[8]}")
@@ -244,10 +242,7 @@ def test_sgns_grad_by_pairs_of_words_whatever_outputs_are_asked_for(case):
     when the call finds in the workspace what one before it left."""
     V, D, stride, zipf, w, N, n, begin, dtype = case
     _say("pairs", case)
-    rng = np.random.default_rng(V + D)
-    p = np.arange(1, V + 1, dtype=np.float64) ** -zipf
-    tok = rng.choice(V, size=max(begin + n, 6000), p=p / p.sum()).astype(np.int32)
-    counts = np.bincount(tok, minlength=V).astype(np.uint64)
+    tok, counts = pair_stream(case)
     bd = DT[dtype][0]
     tables = tuple(_tables_to_dev(t, dtype) for t in _random_tables(V, D, stride, dtype, seed=3))
     m = B.Model(V, D, bd, w, N, n, 0, 11, counts, row_stride=stride, tables=tables)
@@ -273,6 +268,79 @@ def test_sgns_grad_by_pairs_of_words_whatever_outputs_are_asked_for(case):
     assert [tag for tag, _ in B.tensair_profile_read(m.h)] == [B.PROFILE_TAGS[i] for i in (1, 3, 4, 2, 5, 6)]
     for (gi, gr), (wi, wr) in zip(got.to_host(), want.to_host()):
         assert np.array_equal(gi, wi) and np.array_equal(gr, wr)
+    m.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_gradient_by_pairs_of_words_with_rows_that_are_not_finite(dtype):
+    """Rows of NaN, of infinities and of values whose dot products overflow in either table reach the rows of the words that
+    met them and no others, as in a sum over the pairs that occur taken in 64 bits."""
+    V, D, w, N, n, begin = 60, 12, 8, 15, 4200, 100
+    rng = np.random.default_rng(8)
+    tok = rng.integers(0, 30, begin + n + 50).astype(np.int32)               # words 30 and on are met as negatives only
+    tok[200:1500:400], tok[300:1500:400], tok[2000] = 40, 41, 42              # three words are met a few times
+    counts = np.full(V, 50, np.uint64)
+    counts[:10] = 0                                                           # and ten never as negatives
+    Wi, Wo = rng.standard_normal((V, D)).astype(np.float32) * 0.3, rng.standard_normal((V, D)).astype(np.float32) * 0.3
+    Wi[40], Wi[41, 3], Wi[42] = np.nan, np.inf, 1e30
+    Wo[2], Wo[3, 5], Wo[4] = np.nan, -np.inf, 1e30                            # contexts that are no negatives
+    Wi[3], Wo[40] = 0.0, 0.0                                                  # 0 * inf = NaN
+    tdt = DT[dtype][2]
+    d_in, d_out = torch.from_numpy(Wi).cuda().to(tdt), torch.from_numpy(Wo).cuda().to(tdt)
+    m = B.Model(V, D, DT[dtype][0], w, N, n, 0, 5, counts, tables=(d_in, d_out))
+    t = torch.from_numpy(tok).cuda()
+    P = m.pair_count(len(tok), begin, n)
+    g, neg = m.grad_buffers(), torch.zeros(P * N, dtype=torch.int32, device="cuda")
+    m.sgns_grad(t, begin, n, 0, g, negatives_dbg=neg)
+    m.status()
+    pos, q = oracle.pairs(len(tok), w, begin, n)
+    ctx = tok[pos + np.where(q < w, q - w, q - w + 1)]
+    met = np.zeros((V, V, 2))                                                 # center, word: as a negative, as a context
+    np.add.at(met, (tok[pos], ctx, 1), 1)
+    np.add.at(met, (np.repeat(tok[pos], N), neg.cpu().numpy(), 0), 1)
+    v, u = d_in.double().cpu().numpy(), d_out.double().cpu().numpy()
+    gin, gout = np.zeros((V, D)), np.zeros((V, D))
+    with np.errstate(all="ignore"):
+        for c, j in np.argwhere(met.sum(2) > 0):
+            s = np.float64(np.float32((v[c] * u[j]).sum()))
+            scale = (met[c, j, 0] / (1 + np.exp(-s)) - met[c, j, 1] / (1 + np.exp(s))) / P
+            gin[c] += scale * u[j]
+            gout[j] += scale * v[c]
+    for (ids, rows), want in zip(g.to_host(), (gin, gout)):
+        want = want[ids]
+        bad = ~np.isfinite(want)
+        assert bad.any() and not bad.all()
+        assert np.array_equal(np.isfinite(rows), ~bad), [(i, r, x) for i, r, x in zip(ids, rows, want) if (np.isfinite(r) != np.isfinite(x)).any()][:3]
+        assert np.array_equal(np.isnan(rows), np.isnan(want))
+        large = ~bad & (np.abs(want) > 1e20)                                  # a term of 1e30 hides the others of its sum
+        assert np.allclose(rows[large], want[large], rtol=1e-5)
+        for r in np.flatnonzero(~(bad | large).any(1)):
+            assert rows_rel(rows[r:r + 1], want[r:r + 1]) <= TOL_ROWS
+    m.close()
+
+
+@pytest.mark.parametrize("n", [60, 4200])                   # by occurrences; by pairs of words
+def test_ids_out_of_range_count_as_word_0_and_are_reported(n):
+    V, D, w, N = 300, 64, 8, 15
+    tok = W.zipf_stream(V, 1.1, 6_000, 5)
+    counts = W.unigram_counts(tok, V)
+    bad, clean = tok.copy(), tok.copy()
+    at = np.array([120, 121, 150, 170, 3_000, 3_001, 4_400])
+    bad[at], clean[at] = [-1, V, 1 << 30, -(1 << 31), V + 1, V, (1 << 31) - 1], 0
+    Wi, Wo = _random_tables(V, D, D, "f32", seed=2)
+    m = B.Model(V, D, B.F32, w, N, n, 0, 5, counts, tables=(_tables_to_dev(Wi, "f32"), _tables_to_dev(Wo, "f32")))
+    got = []
+    for stream, reported in ((clean, False), (bad, True)):
+        g, loss = m.grad_buffers(), torch.zeros(1, device="cuda")
+        m.sgns_grad(torch.from_numpy(stream).cuda(), 110, n, 0, g, mean_loss=loss)
+        if reported:
+            with pytest.raises(B.TensairError) as e:
+                m.status()
+            assert e.value.code == B.EDATA
+        else:
+            m.status()
+        got.append(_grad_snapshot(g, loss))
+    assert _same(*got)
     m.close()
 
 
@@ -322,12 +390,13 @@ def test_sgns_grad_parity_random_shapes(case):
     _grad_parity(case)
 
 
-def _grad_parity(case, resample=False):
+def _grad_parity(case, resample=False, stream=None):
     V, D, stride, T, zs, w, N, Bc, begin, dtype = case
     _say("grad case", case, "resampled negatives" if resample else "")
     bd, od, tdt, _ = DT[dtype]
-    tok = W.zipf_stream(V, zs, T, 5)
-    counts = W.unigram_counts(tok, V)
+    tok = W.zipf_stream(V, zs, T, 5) if stream is None else stream[0]
+    counts = W.unigram_counts(tok, V) if stream is None else stream[1]
+    T = len(tok)
     Wi, Wo = _random_tables(V, D, stride, dtype, seed=V + D)
     d_in, d_out = _tables_to_dev(Wi, dtype), _tables_to_dev(Wo, dtype)
     m = B.Model(V, D, bd, w, N, Bc, 0, 0xC0FFEE, counts, worker_id=3, row_stride=stride, tables=(d_in, d_out),
@@ -1477,12 +1546,13 @@ def test_sgns_grad_parity_with_four_passes_of_the_sort():
 
 @pytest.mark.parametrize("sizes", [(5000, 1600, 1600, 1600, 5200, 5000, 60, 1600, 1000, 5000),
                                    (2400, 2400, 2400, 60, 4000, 1600, 2400, 5000, 2400, 2400, 2040, 2041, 2400)])
+@pytest.mark.parametrize("V", [300, 50_000])
 @pytest.mark.parametrize("call", ["step", "grad"])
-def test_mini_batches_too_large_to_ride_among_others_give_the_same_bits(call, sizes):
-    """Mini-batches of 628 and more tiles (prepared by their own calls, forward pass on the second stream) and of 257 to
-    512 (prepared on the second stream beside the call before) among smaller ones (whose phases ride, also beside a
-    large one), announced two deep, against the same calls without announcements."""
-    V, D, T, w, N = 50_000, 64, 60_000, 8, 15
+def test_mini_batches_too_large_to_ride_among_others_give_the_same_bits(call, V, sizes):
+    """Mini-batches of 628 and more tiles (prepared by their own calls, forward pass on the second stream or, over 300 words,
+    by pairs of words) and of 257 to 512 (prepared on the second stream beside the call before) among smaller ones (whose
+    phases ride, also beside a large one), announced two deep, against the same calls without announcements."""
+    D, T, w, N = 64, 60_000, 8, 15
     tok = W.zipf_stream(V, 1.1, T, 5)
     counts = W.unigram_counts(tok, V)
     Wi, Wo = _random_tables(V, D, D, "f32", seed=11)
@@ -1552,12 +1622,13 @@ def test_mini_batches_announced_one_at_a_time_give_the_same_bits(V, D, peers):
         assert _same(a, b), i
 
 
-@pytest.mark.parametrize("n", [60, 1500])                 # chained preparation; counted, forward pass on the second stream
+# chained preparation; counted, forward pass on the second stream; by pairs of words
+@pytest.mark.parametrize("V,T,n", [(5000, 30_000, 60), (5000, 30_000, 1500), (300, 60_000, 4200)])
 @pytest.mark.parametrize("call", ["step", "grad"])
-def test_a_captured_call_replays_between_eager_ones(n, call):
+def test_a_captured_call_replays_between_eager_ones(V, T, n, call):
     """A call recorded into a HIP graph and replayed several times, with eager calls (announced ones too) in between,
     against the same calls made eagerly: the same bits at every replay and in every call."""
-    V, D, T, w, N = 5000, 64, 30_000, 8, 15
+    D, w, N = 64, 8, 15
     tok = W.zipf_stream(V, 1.1, T, 5)
     counts = W.unigram_counts(tok, V)
     Wi, Wo = _random_tables(V, D, D, "f32", seed=12)

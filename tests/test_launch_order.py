@@ -7,6 +7,7 @@ import sys
 
 import pytest
 
+from helpers import PAIR_CASES, pair_stream
 from paper_2211_10280_amd import binding as B
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -238,6 +239,29 @@ def test_a_phase_rides_with_the_chaining_of_long_rows_where_that_takes_longer(tr
     got = [g for c in trace(calls, **model) if c["call"][0] == "step" for g in chaining(c)]
     alone = chaining(trace([["grad", 0, n, 0]], **model)[0])[0]
     assert len(got) == 4 and [g > alone for g in got[:3]] == [rides] * 3
+
+
+@pytest.mark.parametrize("case", PAIR_CASES, ids=lambda c: f"V{c[0]}_D{c[1]}_B{c[6]}_{c[8]}")
+def test_the_cases_of_the_gradient_by_pairs_go_by_pairs(trace, case):
+    V, D, stride, _, w, N, n, begin, dtype = case
+    tok, counts = pair_stream(case)
+    did = names(trace([["grad", begin, n, 0]], tokens=len(tok), counts=counts.tolist(), vocab=V, dim=D, row_stride=stride, window=w,
+                      negatives=N, max_centers=n, dtype=B.F32 if dtype == "f32" else B.BF16)[0]["did"])
+    assert [k for k in did if k.startswith("k_group")] == ["k_group_count", "k_group_rows", "k_group_any", "k_group_reduce"]
+
+
+# words, rows, window, negatives, centers on both sides of a border, the Zipf exponent of the counts: occurrences in all (2^20), tasks per
+# position (128 and 512), words (12 288), occurrences per word by width of the rows, tasks and how much positions repeat words
+@pytest.mark.parametrize("V,D,w,N,below,above,zipf", [
+    (300, 64, 8, 15, 4096, 4097, 1.1), (300, 300, 1, 62, 20_000, None, 1.1), (300, 300, 1, 63, None, 20_000, 1.1),
+    (300, 300, 8, 31, None, 2100, 1.1), (300, 300, 8, 32, 2100, None, 1.1), (12_288, 300, 8, 15, None, 4097, 1.5), (12_289, 300, 8, 15, 9000, None, 1.5),
+    (12_000, 64, 8, 15, 9374, 9375, 1.5), (12_000, 68, 8, 15, 7031, 7032, 1.5), (12_000, 132, 8, 15, 6374, 6375, 1.5),
+    (12_000, 64, 8, 15, 7031, 7032, 1.2), (12_000, 132, 8, 7, 9749, 9750, 1.2), (12_000, 132, 8, 15, 4218, 4219, 1.2),
+    (12_000, 256, 8, 15, 4218, 4219, 1.2), (12_000, 260, 8, 15, 4096, 4097, 1.2)])
+def test_borders_of_the_gradient_by_pairs(trace, V, D, w, N, below, above, zipf):
+    counts = [max(1, round(2e6 * (i + 1) ** -zipf)) for i in range(V)]
+    got = trace([["grad", 100, n, 0] for n in (below, above) if n], counts=counts, vocab=V, dim=D, window=w, negatives=N, max_centers=20_000)
+    assert ["k_group_rows" in names(c["did"]) for c in got] == [False] * (below is not None) + [True] * (above is not None)
 
 
 F, H = B.F32, B.BF16
