@@ -8,7 +8,7 @@
 //   forward   one workgroup per center position: the center row stays in registers, the
 //             context/negative rows are gathered once, g is stored per occurrence and the
 //             center's share of Gin is combined across waves through LDS;
-//   segreduce the occurrences sorted by row id are cut into fixed tiles (32, or 8 for small lists);
+//   segreduce the occurrences sorted by row id are cut into fixed tiles (of 8, 16 or 32 by their number);
 //             a wave sums, in sorted order, the short rows that begin in its tile and its share
 //             of long rows, whose partials a second kernel chains in tile order.  Load balance
 //             is therefore independent of how hot a row is.

@@ -10,10 +10,10 @@
 //                   the W_out gradient, and a share of the center word's W_in gradient;
 //   k_group_reduce  adds up, for every word, the rows of the chunks that have it (one workgroup per word, the chunks in
 //                   order), and for every center word its shares.
-// No occurrence is sorted and nothing is chained.  The last two are bound by row gathers out of L2; against sorting the
-// occurrences beside a forward pass position by position (see prep_dev.h, grad.hip) the step above takes 319 us, 472 before.
-// (Counting and rows in one kernel, a chunk per workgroup, left most of the chip waiting for the chunks of
-// the frequent center words: 383 us.)
+// No occurrence is sorted (unless the offsets of the sorted occurrences are asked for) and nothing is chained.  The last two
+// are bound by row gathers out of L2; against sorting the occurrences beside a forward pass position by position (see
+// prep_dev.h, grad.hip) the step above takes 319 us, 472 before.  (Counting and rows in one kernel, a chunk per workgroup,
+// left most of the chip waiting for the chunks of the frequent center words: 446 us at best.)
 #include "aux_dev.h"
 #include "dev_common.h"
 #include "forward_dev.h"

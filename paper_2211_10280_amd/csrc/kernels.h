@@ -222,7 +222,10 @@ static inline int tn_seg_chains(i64 n, int D)
 // Zipf exponents of 1.1, 1.3 and 1.45; 32 000 words, one workgroup per compute unit, 419 / 574 and 303 / 451)
 #define TN_GROUP_MAX_VOCAB 12288
 #define TN_GROUP_MIN_OCC (1 << 20)
-#define TN_GROUP_MIN_TASKS 128   // per position: a chunk's counters are cleared and listed whatever it holds
+// per position: a chunk's counters are cleared and listed whatever it holds.  Step of 9 420 centers with 128 tasks each, by
+// occurrences / by pairs: 700 words, D = 64 130 / 125 us, D = 256 in bfloat16 182 / 127, 4 000 words 164 / 160 and 199 / 163; not
+// measured below.
+#define TN_GROUP_MIN_TASKS 128
 // positions of a center word that are counted together: their tasks' counts fit 16 bits (step of 16 384 centers, 256 tasks
 // each, with 64 / 128 positions 338 / 325 us)
 static inline int tn_group_positions(int per_center) { return per_center <= 256 ? 128 : 64; }   // per_center <= TN_REPEAT_MAX_TASKS
