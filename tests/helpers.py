@@ -205,9 +205,9 @@ def ulp_err_at_t(got, want, ref, chunk=1 << 26):
     return mx, beyond / max(g.numel(), 1)
 
 
-# More than 2^20 occurrences over at most 12 288 words that repeat: the gradient goes by pairs of words (which the launches
-# of each case are checked for).  Words and 64-word groups just full and of one word, every row shape, centers in chunks of 64 positions and
-# of one, both ends of the stream, the fewest tasks per position.
+# More than 2^20 occurrences over at most 12 288 words that repeat: the gradient goes by pairs of words (the launches of
+# every case are checked).  Words and 64-word groups just full and of one word, every row shape, centers in chunks of 64
+# positions and of one, both ends of the stream, the fewest tasks per position.
 PAIR_CASES = [
     # V, D, stride, zipf, w, N, B, begin, dtype
     (4, 4, 4, 1.0, 8, 15, 4097, 8, "f32"), (40, 32, 32, 1.2, 8, 15, 4200, 0, "f32"), (64, 132, 136, 0.5, 8, 15, 4099, 1901, "bf16"),

@@ -504,8 +504,8 @@ def test_dasgd_apply_parity(dtype, V, D, stride, K, own):
                                           (70_001, 128, 128, 7), (50_000, 100, 104, 15), (20_011, 64, 64, 3),
                                           (30_000, 36, 36, 1)])
 def test_dasgd_apply_parity_few_rows_of_a_large_vocabulary(dtype, V, D, stride, K):
-    """Gradients that touch a few per cent of the vocabulary: the update then runs in its shape for sparse
-    unions (more vocabulary rows per wave)."""
+    """Gradients that touch a few per cent of the vocabulary, most of whose waves find nothing: vocabularies too small for the
+    shapes made for that, and one (300 007 words) that the update sweeps over."""
     _apply_parity(dtype, V, D, stride, K, True, thin=40)
 
 
