@@ -205,10 +205,13 @@ struct tensair_model {
     u64 *mask_alt[2];          // a second set (buffer 1): inside tensair_step the two are used in turn, so that
                                // the one the next step will index can be cleared while this step still reads its own
     bool mask_clean[2] = {false, false};   // buffer b is all zeros (or will be when everything enqueued so far has run)
-    u64 *group_masks = nullptr;        // see GroupArgs
-    u64 *group_any = nullptr;
+    u64 *group_masks = nullptr, *group_any = nullptr, *group_turned = nullptr;    // see GroupArgs
     unsigned short *group_starts = nullptr;
-    int4 *group_meta = nullptr;
+    int4 *group_meta = nullptr, *group_frequent = nullptr;
+    int *group_n = nullptr;
+    double *group_hot_rows = nullptr;
+    float *group_hot_part = nullptr;
+    u32 *group_dense = nullptr;
     u32 *wbase[2], *wblk[2];   // tensair_grad_add: place of every 64-row word in the summed gradient
     std::vector<Draw> h_draw;  // the same on the host
     WordStats words;
@@ -281,7 +284,10 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
     p = take((size_t)(s.tiles_out + s.tiles_in) * 4); if (m) m->long_list = (int *)p;
     p = take((size_t)s.Omax * 4); if (m) m->g = (float *)p;
     p = take((size_t)s.Bmax * D * 4); if (m) m->center_part = (float *)p;
-    p = take((size_t)s.Bmax * 4); if (m) m->center_loss = (float *)p;
+    const int per_center = 2 * c.window * (c.negatives + 1);
+    const i64 frequent = s.group ? tn_group_frequent(c.vocab, per_center, s.Bmax) : 0;
+    const size_t hot_blocks = s.group ? (size_t)s.words * tn_group_slices(c.vocab, frequent) : 0;
+    p = take(((size_t)s.Bmax + hot_blocks) * 4); if (m) m->center_loss = (float *)p;
     p = take((size_t)s.tiles_out * 2 * D * 4); if (m) m->part_out = (float *)p;
     p = take((size_t)s.tiles_in * 2 * D * 4); if (m) m->part_in = (float *)p;
     p = take((size_t)(s.tiles_out / TN_SEG_XBLOCK + 2) * D * 4); if (m) m->cross_out = (float *)p;
@@ -289,11 +295,17 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
     p = take((size_t)(s.tiles_out / TN_SEG_XBLOCK + 2) * 4); if (m) m->xinfo_out = (int *)p;
     p = take((size_t)(s.tiles_in / TN_SEG_XBLOCK + 2) * 4); if (m) m->xinfo_in = (int *)p;
     if (s.group) {
-        const size_t pitch = (size_t)tn_group_pitch(c.vocab, s.Bmax);
-        p = take((size_t)s.words * 8); if (m) m->group_any = (u64 *)p;
-        p = take((size_t)s.words * pitch * 8); if (m) m->group_masks = (u64 *)p;
-        p = take((size_t)s.words * pitch * 2); if (m) m->group_starts = (unsigned short *)p;
-        p = take(pitch * 16); if (m) m->group_meta = (int4 *)p;
+        const size_t words = (size_t)s.words, most = (size_t)frequent;
+        p = take(words * 8); if (m) m->group_any = (u64 *)p;
+        p = take(cap_in * words * 8); if (m) m->group_masks = (u64 *)p;
+        p = take(cap_in * words * 2); if (m) m->group_starts = (unsigned short *)p;
+        p = take((cap_in + 63) / 64 * 64 * words * 8); if (m) m->group_turned = (u64 *)p;
+        p = take(cap_in * 16); if (m) m->group_meta = (int4 *)p;
+        p = take(most * 16); if (m) m->group_frequent = (int4 *)p;
+        p = take(256); if (m) m->group_n = (int *)p;
+        p = take(hot_blocks * 64 * D * 8); if (m) m->group_hot_rows = (double *)p;
+        p = take(most * words * D * 4); if (m) m->group_hot_part = (float *)p;
+        p = take((size_t)tn_group_chunks(c.vocab, per_center, s.Bmax) * 64 * words * 4); if (m) m->group_dense = (u32 *)p;
     }
     for (int t = 0; t < 2; ++t) {
         p = take((size_t)(s.words + 1) * K1 * 4); if (m) m->start[t] = (u32 *)p;
@@ -577,6 +589,7 @@ struct BatchWork {
     BatchDesc b;
     i64 P, O;
     u32 epoch, worker_id;
+    bool centers_only;     // the occurrences are not listed
 };
 
 static BatchWork batch_work(const tensair_config &c, const int32_t *tokens, i64 n_tokens, i64 center_begin,
@@ -595,6 +608,7 @@ static BatchWork batch_work(const tensair_config &c, const int32_t *tokens, i64 
     w.O = P * (c.negatives + 1);
     w.epoch = epoch;
     w.worker_id = c.worker_id;
+    w.centers_only = false;
     return w;
 }
 
@@ -622,6 +636,13 @@ static SortedSide sorted_side(const tensair_model *m, const BatchSet &S, int sid
             S.long_cnt + side};
 }
 
+static NoiseDraw noise_draw(const tensair_model *m, const BatchWork &w)
+{
+    const tensair_config &c = m->cfg;
+    return {c.vocab, m->draw, (u32)(c.seed & 0xFFFFFFFFu), (u32)(c.seed >> 32), w.worker_id + 65536u * w.epoch,
+            (c.flags & TENSAIR_RESAMPLE_NEGATIVES) != 0};
+}
+
 // One phase as it is launched.  Key lists: out-side occurrences at [0, O), in-side centers at [Omax, Omax + n_centers);
 // the unsorted keys in keys[0] are never written again (the forward pass reads them); the passes go 0 -> 1 -> 2 -> 1.
 static void make_prep_phase(tensair_model *m, BatchSet &S, const BatchWork &w, bool chained, int phase,
@@ -636,17 +657,13 @@ static void make_prep_phase(tensair_model *m, BatchSet &S, const BatchWork &w, b
     if (phase == 0) {
         PrepKeys &k = x.keys;
         x.kind = PREP_KEYS;
-        const i64 slots = (i64)w.b.n_centers * 2 * c.window * (c.negatives + 1);
+        k.centers_only = w.centers_only;
+        const i64 slots = k.centers_only ? (i64)w.b.n_centers : (i64)w.b.n_centers * 2 * c.window * (c.negatives + 1);
         const int per_block = tn_prep_keys_slots(slots);
         x.blocks = (int)((slots + per_block - 1) / per_block);
         k.items = per_block / BLOCK;
         k.b = w.b;
-        k.V = c.vocab;
-        k.draw = m->draw;
-        k.k0 = (u32)(c.seed & 0xFFFFFFFFu);
-        k.k1 = (u32)(c.seed >> 32);
-        k.ctr3 = w.worker_id + 65536u * w.epoch;
-        k.resample = (c.flags & TENSAIR_RESAMPLE_NEGATIVES) != 0;
+        k.noise = noise_draw(m, w);
         k.out_keys = S.keys[0];
         k.in_keys = S.keys[0] + s.Omax;
         k.pair_center = S.pair_center;
@@ -1045,8 +1062,12 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         for (int t = 0; t < 2; ++t) fa.mask[t] = pick ? m->mask_alt[t] : m->mask[t];
         m->mask_clean[pick] = false;
         const bool own_early = prepared && !split;   // the own id lists exist when the forward pass starts
-        tn_aux_add_index(aux_fwd, fa, own_early ? 0 : 1, fa.n_src);
-        if (!own_early && !by_pairs) tn_aux_add_index(aux_red, fa, 0, 1);
+        tn_aux_add_index(aux_fwd, fa, own_early || by_pairs ? 0 : 1, fa.n_src);
+        if (by_pairs) {           // the out-side ids come with the sums, which index them
+            aux_fwd.apply.src[1][0].ids = nullptr;
+        } else if (!own_early) {
+            tn_aux_add_index(aux_red, fa, 0, 1);
+        }
         if (!m->mask_clean[1 - pick]) {
             const size_t all = (size_t)s.words * (size_t)(c.max_peers + 1 > 2 ? c.max_peers + 1 : 2);
             tn_aux_add_clear(aux_red, pick ? m->mask[0] : m->mask_alt[0], pick ? m->mask[1] : m->mask_alt[1], all);
@@ -1059,17 +1080,21 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     const RowIndexDst out = {grad_out->out.row_ids, grad_out->out.n_rows, seg_offsets_out, grad_out->out.capacity};
     PrepPhase x;
     if (by_pairs) {
-        // the positions sorted by their center's word, then the gradient itself.  Its sums take the same order whatever
-        // outputs are asked for; the occurrences are sorted for their offsets alone (gradient of 16 384 centers, 10 000
-        // words, 256 tasks each, without / with them 290 / 357 us; by occurrences 477).
+        // the positions sorted by their center's word, then the gradient itself, whose counting draws the negatives by
+        // itself.  Its sums take the same order whatever outputs are asked for; the occurrences are listed for the negatives
+        // and sorted for their offsets alone.  Where every stage is being timed the count of the sort stays in a launch of its
+        // own, as in long sorts.
+        const bool list = seg_offsets_out || negatives_dbg;
+        const bool chain = overlap && !list && prep_tiles(c, 0, n_centers) <= TN_PREP_CHAIN_OWN;
         BatchWork sorted_lists = w;
+        sorted_lists.centers_only = !list;
         if (!seg_offsets_out) sorted_lists.O = 0;
-        for (int i = 0; i < prep_phases(s, false); ++i) {
-            make_prep_phase(m, S, sorted_lists, false, i, in, out, negatives_dbg, x);
+        for (int i = 0; i < prep_phases(s, chain); ++i) {
+            make_prep_phase(m, S, sorted_lists, chain, i, in, out, negatives_dbg, x);
             before_prep_phase(m, S, x.kind, st);
             tn_launch_prep(x, st);
             if (i == 0) mark(m, PF_KEYS, st);
-            if (i + 1 == prep_sort_end(s, false)) mark(m, PF_SORT, st);
+            if (i + 1 == prep_sort_end(s, chain)) mark(m, PF_SORT, st);
         }
         mark(m, PF_SEGMENTS, st);
         if (beside) {
@@ -1083,36 +1108,52 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         GroupArgs ga;
         memset(&ga, 0, sizeof(ga));
         ga.f = f;
+        ga.noise = noise_draw(m, w);
+        ga.status = m->status;
         ga.vals = si.vals;
         ga.seg_of = si.seg_of;
         ga.seg_start = si.seg_start;
         ga.n_in = grad_out->in.n_rows;
+        ga.in_ids = grad_out->in.row_ids;
         ga.words = (int)s.words;
-        ga.pitch = (int)tn_group_pitch(c.vocab, n_centers);
         ga.per_center = 2 * c.window * Np1;
-        ga.positions = tn_group_positions(ga.per_center);
+        ga.rare = (int)tn_group_rare(c.vocab, ga.per_center, n_centers);
+        ga.chunk = (int)tn_group_chunk(ga.per_center, n_centers);
+        ga.most_frequent = (int)tn_group_frequent(c.vocab, ga.per_center, n_centers);
+        ga.slices = tn_group_slices(c.vocab, ga.most_frequent);
+        ga.parts = tn_group_parts(c.vocab, ga.slices, c.dim);
+        ga.dense = m->group_dense;
         ga.list = S.keys[1];      // the out-side list's room: not sorted, or no longer needed
         ga.counts = S.keys[2];
         ga.any = m->group_any;
         ga.masks = m->group_masks;
         ga.starts = m->group_starts;
+        ga.turned = m->group_turned;
         ga.meta = m->group_meta;
+        ga.frequent = m->group_frequent;
+        ga.n_frequent = m->group_n;
+        ga.hot_rows = m->group_hot_rows;
+        ga.hot_part = m->group_hot_part;
         ga.in_rows = grad_out->in.row_grads;
         ga.out_rows = grad_out->out.row_grads;
         ga.out_ids = grad_out->out.row_ids;
         ga.out_n = grad_out->out.n_rows;
+        if (fuse) {
+            ga.index_mask = m->fused_apply->mask[1] + idx_at(s.words, 0, 0);
+            ga.index_start = m->fused_apply->start[1] + idx_at(s.words, 0, 0);
+        }
+        const int losses = n_centers + ga.words * ga.slices;
         tn_launch_group(ga, GROUP_ROWS, aux_fwd, st);
         mark(m, PF_FORWARD, st);
         if (overlap) {
-            if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, n_centers, f.inv_P, mean_loss);
+            if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, losses, f.inv_P, mean_loss);
             tn_launch_group(ga, GROUP_SUMS_IN | GROUP_SUMS_OUT, aux_red, st);
         } else {         // one after the other, so that each can be timed
-            if (mean_loss) tn_launch_loss(m->center_loss, n_centers, f.inv_P, mean_loss, st);
+            if (mean_loss) tn_launch_loss(m->center_loss, losses, f.inv_P, mean_loss, st);
             tn_launch_group(ga, GROUP_SUMS_IN, aux_red, st);
             mark(m, PF_REDUCE_IN, st);
             tn_launch_group(ga, GROUP_SUMS_OUT, aux_red, st);
         }
-        if (fuse) tn_launch_apply_index(*m->fused_apply, 0, 1, st);
         mark(m, PF_REDUCE_OUT, st);
         HIP_TRY(hipGetLastError());
         return TENSAIR_OK;

@@ -23,21 +23,21 @@ __device__ __forceinline__ FwdCenter fwd_center(const FwdArgs &a, int i)
     return x;
 }
 
-// A word that is a context (k & 0xFFFF) and a negative (k >> 16) so many times of one center word, with dot product s: g of a
+// A word that is a context and a negative so many times of one center word, with dot product s: g of a
 // context and of a negative, and what the word's row is scaled by; the loss terms come on top of `loss`.
 template <bool LOSS>
-__device__ __forceinline__ float pair_scale(u32 k, float s, float inv_P, float &loss, float &g1, float &g0)
+__device__ __forceinline__ float pair_scale(u32 contexts, u32 negatives, float s, float inv_P, float &loss, float &g1, float &g0)
 {
     // sigmoid(s) - label without cancellation: label 1: -1/(1+e^s), label 0: 1/(1+e^-s)
     g1 = -(1.0f / (1.0f + expf(s))) * inv_P;
     g0 = 1.0f / (1.0f + expf(-s)) * inv_P;
-    const float n1 = (float)(k & 0xFFFFu), n0 = (float)(k >> 16);
+    const float n1 = (float)contexts, n0 = (float)negatives;
     if (LOSS) {
         // loss terms: softplus(-s) for a context, softplus(s) for a negative; one that does not occur is left
         // out, not taken zero times (it is infinite where the dot product has overflowed)
         const float tail = log1pf(expf(-fabsf(s)));
-        if (k & 0xFFFFu) loss += n1 * (fmaxf(-s, 0.f) + tail);
-        if (k >> 16) loss += n0 * (fmaxf(s, 0.f) + tail);
+        if (contexts) loss += n1 * (fmaxf(-s, 0.f) + tail);
+        if (negatives) loss += n0 * (fmaxf(s, 0.f) + tail);
     }
     return fmaf(n1, g1, n0 * g0);
 }
@@ -145,7 +145,7 @@ struct RepeatList {
     template <bool LOSS>
     __device__ __forceinline__ float scale(int t, float s, float inv_P, float &loss) const
     {
-        return pair_scale<LOSS>(ucnt[t], s, inv_P, loss, gp[t], gn[t]);
+        return pair_scale<LOSS>(ucnt[t] & 0xFFFFu, ucnt[t] >> 16, s, inv_P, loss, gp[t], gn[t]);
     }
     // g of every task, after a barrier
     __device__ __forceinline__ void store_g(const FwdArgs &a, const FwdCenter &x) const

@@ -59,12 +59,17 @@ struct BatchDesc {
 // 23.7 us, 6 000 - / 29.9 / 29.4, gradient of 12 000 - / 41.3 / 40.0; step, 61 000 56.3 / 54.6 / 55.4, 64 000 - / 43.0 / 45.0;
 // 85 000 60.1 / 62.0, 143 000 64.5 / 66.1).
 static inline int tn_prep_keys_slots(i64 slots) { return slots <= 16384 ? 256 : slots <= 65536 ? 512 : PREP_KEYS_SLOTS; }
-struct PrepKeys {
-    BatchDesc b;
+// the negatives' draws: pure functions of the position, the offset and the negative's number
+struct NoiseDraw {
     i64 V;
     const uint2 *draw;     // [V] alias table: threshold, alias
     u32 k0, k1, ctr3;
     int resample;          // a negative equal to the pair's center or context word is drawn once more
+};
+struct PrepKeys {
+    BatchDesc b;
+    NoiseDraw noise;
+    int centers_only;      // the in-side list alone (in a launch of its own)
     u32 *out_keys, *in_keys;
     int *pair_center, *neg_dbg, *status;
     u32 *hist;             // [2 lists][passes][2^bits] digit counts, added to: zero before (NULL: not wanted)
@@ -217,33 +222,86 @@ static inline int tn_seg_chains(i64 n, int D)
 
 // ---- stages 4 and 5 of a very large mini-batch over a small vocabulary whose words repeat (group.hip)
 // up to TN_GROUP_MAX_VOCAB words (a counter each in LDS) and more than TN_GROUP_MIN_OCC occurrences
-// (three workgroups' counters fit a compute unit's LDS up to here; step of 8 192 centers, 256 tasks each, 3 peers, D = 256,
+// (a counter and a bucket of the alias table per word fit a compute unit's LDS up to here; an earlier form, step of 8 192 centers, 256 tasks each, 3 peers, D = 256,
 // by occurrences / by pairs: 1 323 words 263 / 163 us, 2 000 220 / 166, 5 000 332 / 255, 10 000 400 / 296, 331 / 246 and 303 / 234 with
 // Zipf exponents of 1.1, 1.3 and 1.45; 32 000 words, one workgroup per compute unit, 419 / 574 and 303 / 451)
 #define TN_GROUP_MAX_VOCAB 12288
 #define TN_GROUP_MIN_OCC (1 << 20)
-// per position: a chunk's counters are cleared and listed whatever it holds.  Step of 9 420 centers with 128 tasks each, by
+// per position.  Step of 9 420 centers with 128 tasks each, by
 // occurrences / by pairs: 700 words, D = 64 130 / 125 us, D = 256 in bfloat16 182 / 127, 4 000 words 164 / 160 and 199 / 163; not
 // measured below.
 #define TN_GROUP_MIN_TASKS 128
-// positions of a center word that are counted together: their tasks' counts fit 16 bits (step of 16 384 centers, 256 tasks
-// each, with 64 / 128 positions 338 / 325 us)
-static inline int tn_group_positions(int per_center) { return per_center <= 256 ? 128 : 64; }   // per_center <= TN_REPEAT_MAX_TASKS
+#define TN_GROUP_HOT 16        // frequent center words that a workgroup takes at a time
+// A center word of more than so many positions is frequent: it is taken against the whole vocabulary, others against the list of
+// the words they met.  A pair of a list takes three to four times as long as one of all pairs: from where two words in seven are
+// met, nearly, as are of three tasks for every two words.  Step of 16 384 centers, 10 000 words, D = 256, 256 tasks: frequent from
+// 16 / 32 / 64 positions on 199 / 193 / 194 us, from 177 217, from 255 237; 12 000 words, D = 1 024, 512 tasks, 2 355 centers from 5 / 36 / 108
+// 661 / 559 / 616.
+static inline i64 tn_group_rare(i64 V, int per_center, i64 n_centers)        // per_center <= TN_REPEAT_MAX_TASKS
+{
+    const i64 padded = (V + 63) / 64 * 64, least = (padded * 3 / 2 + per_center - 1) / per_center, few = (n_centers + 511) / 512;
+    const i64 most = 65535 / per_center;                                     // a list's counts fit 16 bits
+    const i64 n = least > few ? least : few;
+    return n < 4 ? 4 : n < most ? n : most;
+}
+// Positions of a frequent center word that are counted together: their counts fit 16 bits.
+static inline i64 tn_group_chunk(int per_center, i64 n_centers)
+{
+    const i64 few = (n_centers + 2047) / 2048, most = 65535 / per_center, least = per_center <= 256 ? 64 : 32;
+    return few < least ? least : few < most ? few : most;
+}
+// Frequent center words and their chunks, at most, of any mini-batch of up to n_centers positions.
+static inline i64 tn_group_frequent(i64 V, int per_center, i64 n_centers)
+{
+    const i64 least = n_centers / (tn_group_rare(V, per_center, 1) + 1), many = n_centers * per_center / 65535 + 1;
+    const i64 n = least < 1024 ? least : many < 1024 ? 1024 : many < least ? many : least;
+    return n < V ? n : V;
+}
+static inline i64 tn_group_chunks(i64 V, int per_center, i64 n_centers)
+{
+    const i64 many = n_centers * per_center / 65535 + 1, n = n_centers / 32;
+    return (n < 2048 ? n + 1 : many < 2048 ? 2048 : many) + tn_group_frequent(V, per_center, n_centers);
+}
+// Workgroups per 64 words of the vocabulary that share the frequent center words, and that share the rows' elements: several
+// where the vocabulary alone would leave most of the chip idle (step of 2 355 centers, 512 tasks, 40 words, D = 1 024: 123 us with
+// three workgroups in all, 86 with twelve).
+static inline int tn_group_slices(i64 V, i64 frequent)
+{
+    const i64 some = 1024 / ((V + 63) / 64), all = (frequent + TN_GROUP_HOT - 1) / TN_GROUP_HOT;
+    return (int)(all < 1 ? 1 : some < all ? (some < 1 ? 1 : some) : all);
+}
+static inline int tn_group_parts(i64 V, int slices, int D)
+{
+    const i64 some = 512 / ((V + 63) / 64 * slices), all = (D + 255) / 256;
+    return (int)(some < 1 ? 1 : some < all ? some : all);
+}
 struct GroupArgs {
-    FwdArgs f;               // g: scales of the chunks' words, in the place of their list entries; center_part and center_loss by sorted position
+    FwdArgs f;               // g: scales of the rare center words' words, in the place of their list entries; center_part by sorted
+                             // position; center_loss too, then a workgroup of the frequent ones each
+    NoiseDraw noise;
+    int *status;
     const u32 *vals;         // positions in the order of their center words
-    const int *seg_of, *seg_start, *n_in;
-    int words, pitch;        // 64-word groups of the vocabulary; chunks that there is room for
-    int positions, per_center;   // of a chunk, at most; tasks of a position, at most
-    u32 *list, *counts;      // [positions in all][per_center] the chunks' words, from their first position's place on
+    const int *seg_of, *seg_start, *n_in, *in_ids;
+    int words;               // 64-word groups of the vocabulary
+    int rare, chunk;         // see tn_group_rare, tn_group_chunk
+    int per_center;          // tasks of a position, at most
+    int slices, parts, most_frequent;   // see tn_group_slices
+    u32 *dense;              // [chunks][64 * words] counts of the chunks of frequent center words
+    u32 *list, *counts;      // [positions in all][per_center] the rare center words' words, from their first position's place on
     u64 *any;                // [words] words that occur
-    u64 *masks;              // [words][pitch] words of a chunk
-    unsigned short *starts;  // [words][pitch] words of the chunk before these
-    int4 *meta;              // [pitch] center word, first sorted position, words
+    u64 *masks;              // [center words][words] words of a rare center word
+    unsigned short *starts;  // [center words][words] words of its list before these
+    u64 *turned;             // [center words / 64][64 * words] a word's rare center words
+    int4 *meta;              // [center words] the word, first sorted position, words in the list (none if frequent), 1 + number if frequent
+    int4 *frequent;          // the word, row, chunks, the first of them
+    int *n_frequent;
+    double *hot_rows;        // [slices][64 * words][D] what the frequent center words give a word's row
+    float *hot_part;         // [frequent][words][D] what 64 words give a frequent center word's row
     float *in_rows, *out_rows;
     int *out_ids, *out_n;
+    u64 *index_mask;         // [words] the table update's index of the out-side rows (NULL: not wanted)
+    u32 *index_start;
 };
-static inline i64 tn_group_pitch(i64 V, i64 n_centers) { return ((n_centers < V ? n_centers : V) + n_centers / 64 + 64) & ~(i64)63; }
 struct AuxWork;
 // what: the pairs and their rows, or one of the tables' sums or both; `aux` rides with the rows, with the sums
 enum { GROUP_ROWS = 0, GROUP_SUMS_IN = 1, GROUP_SUMS_OUT = 2 };

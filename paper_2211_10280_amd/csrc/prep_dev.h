@@ -55,6 +55,21 @@ __device__ __forceinline__ int take_ticket(u32 *counter, u32 *word)
     return t;
 }
 
+// ---------------------------------------------------------------- draws
+// negative k of offset index q of the position p: its random block, the bucket that a word of it names, and the word from the
+// bucket's threshold and alias; once more from the block's other two words
+__device__ __forceinline__ philox_out noise_block(const NoiseDraw &a, i64 p, u32 q, u32 k)
+{
+    return philox4x32_10((u32)((u64)p & 0xFFFFFFFFu), (u32)((u64)p >> 32), q * 65536u + k, a.ctr3, a.k0, a.k1);
+}
+__device__ __forceinline__ u32 noise_bucket(const NoiseDraw &a, u32 r) { return (u32)(((u64)r * (u64)a.V) >> 32); }
+__device__ __forceinline__ int noise_word(u32 bucket, u32 r, uint2 e) { return r < e.x ? (int)bucket : (int)e.y; }
+__device__ __forceinline__ int noise_again(const NoiseDraw &a, u32 r2, u32 r3)
+{
+    const u32 bucket = noise_bucket(a, r2);
+    return noise_word(bucket, r3, a.draw[bucket]);
+}
+
 // ---------------------------------------------------------------- keys
 // Slot s of the mini-batch is (center i, offset index q, k): k = 0 is the context, k = 1..N are the negatives.
 // Writes the out-side key list [pair][N+1] (pair-major, the order of the occurrence list), the in-side key of every
@@ -86,7 +101,7 @@ __device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblo
         const u32 i = t / per_center, rem = t - i * per_center, q = rem / Np1, k = rem - q * Np1;
         const i64 p = b.begin + (i64)i;
         int c = b.tok[p];
-        if ((u32)c >= (u32)a.V) {  // invalid token: keep every later access in range, flag it
+        if ((u32)c >= (u32)a.noise.V) {  // invalid token: keep every later access in range, flag it
             c = 0;
             atomicOr(a.status, ST_BAD_ID);
         }
@@ -107,7 +122,7 @@ __device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblo
         }
         const i64 pair = pairs_before(p, b.T, b.w) - b.pair_base + rank;
         int ctx = b.tok[p + o];
-        if ((u32)ctx >= (u32)a.V) {
+        if ((u32)ctx >= (u32)a.noise.V) {
             ctx = 0;
             atomicOr(a.status, ST_BAD_ID);
         }
@@ -116,16 +131,10 @@ __device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblo
             id = ctx;
             a.pair_center[pair] = c;
         } else {
-            const philox_out r = philox4x32_10((u32)((u64)p & 0xFFFFFFFFu), (u32)((u64)p >> 32), q * 65536u + (k - 1u),
-                                               a.ctr3, a.k0, a.k1);
-            u32 bkt = (u32)(((u64)r.r0 * (u64)a.V) >> 32);
-            uint2 e = a.draw[bkt];           // threshold, alias
-            id = (r.r1 < e.x) ? (int)bkt : (int)e.y;
-            if (a.resample && (id == c || id == ctx)) {   // the variant: one more draw from the block's other two words
-                bkt = (u32)(((u64)r.r2 * (u64)a.V) >> 32);
-                e = a.draw[bkt];
-                id = (r.r3 < e.x) ? (int)bkt : (int)e.y;
-            }
+            const philox_out r = noise_block(a.noise, p, q, k - 1u);
+            const u32 bkt = noise_bucket(a.noise, r.r0);
+            id = noise_word(bkt, r.r1, a.noise.draw[bkt]);
+            if (a.noise.resample && (id == c || id == ctx)) id = noise_again(a.noise, r.r2, r.r3);   // the variant
             if (a.neg_dbg) a.neg_dbg[pair * b.N + (k - 1u)] = id;
         }
         a.out_keys[pair * Np1 + k] = (u32)id;
@@ -142,6 +151,34 @@ __device__ __forceinline__ void prep_keys(const PrepKeys &a, int block, int nblo
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * nhist; i += THREADS)
         if (lds[i]) atomicAdd(&a.hist[i], lds[i]);
+}
+
+// The in-side list alone: a workgroup's items * THREADS centers and their digit counts; clears as the keys do.
+template <int THREADS>
+__device__ __forceinline__ void prep_center_keys(const PrepKeys &a, int block, int nblocks, u32 *lds)
+{
+    const BatchDesc &b = a.b;
+    const int nd = 1 << a.bits, nhist = a.passes * nd;
+    if (a.hist)
+        for (int i = threadIdx.x; i < nhist; i += THREADS) lds[i] = 0;
+    for (size_t i = (size_t)block * THREADS + threadIdx.x; i < a.n_clear; i += (size_t)nblocks * THREADS) a.clear[i] = 0;
+    __syncthreads();
+    for (int j = 0; j < a.items; ++j) {
+        const int i = (block * a.items + j) * THREADS + (int)threadIdx.x;
+        if (i >= b.n_centers) break;
+        int c = b.tok[b.begin + i];
+        if ((u32)c >= (u32)a.noise.V) {
+            c = 0;
+            atomicOr(a.status, ST_BAD_ID);
+        }
+        a.in_keys[i] = (u32)c;
+        if (a.hist)
+            for (int p = 0; p < a.passes; ++p) atomicAdd(&lds[p * nd + (((u32)c >> (p * a.bits)) & (u32)(nd - 1))], 1u);
+    }
+    if (!a.hist) return;
+    __syncthreads();
+    for (int i = threadIdx.x; i < nhist; i += THREADS)
+        if (lds[i]) atomicAdd(&a.hist[nhist + i], lds[i]);
 }
 
 // ---------------------------------------------------------------- one pass of the sort

@@ -52,15 +52,20 @@ struct WaveRow {
     {
         LoadedRow<T, NQ, TAIL> r;
         r.load(row, D, lane);
-#pragma unroll
-        for (int it = 0; it < NQ; ++it) q[it] = r.chunk(it);
-        t = TAIL ? r.tail() : 0.f;
+        widen(r);
     }
     __device__ __forceinline__ void zero()
     {
 #pragma unroll
         for (int it = 0; it < NQ; ++it) q[it] = make_float4(0.f, 0.f, 0.f, 0.f);
         t = 0.f;
+    }
+    template <typename T>
+    __device__ __forceinline__ void widen(const LoadedRow<T, NQ, TAIL> &r)
+    {
+#pragma unroll
+        for (int it = 0; it < NQ; ++it) q[it] = r.chunk(it);
+        t = TAIL ? r.tail() : 0.f;
     }
     template <typename R>
     __device__ __forceinline__ float dot(const R &o) const

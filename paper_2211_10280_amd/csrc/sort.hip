@@ -5,7 +5,8 @@
 
 __global__ void __launch_bounds__(BLOCK) k_prep_keys(PrepPhase x)
 {
-    prep_keys<BLOCK>(x.keys, (int)blockIdx.x, (int)gridDim.x, ride_lds);
+    if (x.keys.centers_only) prep_center_keys<BLOCK>(x.keys, (int)blockIdx.x, (int)gridDim.x, ride_lds);
+    else prep_keys<BLOCK>(x.keys, (int)blockIdx.x, (int)gridDim.x, ride_lds);
 }
 
 template <bool CHAINED>

@@ -271,6 +271,21 @@ def test_sgns_grad_by_pairs_of_words_whatever_outputs_are_asked_for(case):
     m.close()
 
 
+@pytest.mark.parametrize("V,D,w,N,n,begin,dtype,resample", [
+    (200, 68, 8, 15, 4400, 0, "f32", False), (128, 256, 8, 15, 4400, 300, "bf16", True), (129, 516, 8, 31, 2300, 40, "f32", True)])
+def test_gradient_by_pairs_of_words_at_the_borders_of_frequent_and_rare_ones(V, D, w, N, n, begin, dtype, resample):
+    """Center words of as many positions as a wave counts by itself, as are still rare, as are counted together, twice
+    that, and one more of each; every other word is met as a context or as a negative.  Against the oracle."""
+    per_center = 2 * w * (N + 1)
+    small, rare, chunk = 1024 // per_center, -(-n // 512), 64 if per_center <= 256 else 32
+    sizes = [k + i for k in (1, small, rare, chunk, 2 * chunk) for i in (0, 1)]
+    rng = np.random.default_rng(V)
+    centers = np.concatenate([np.full(k, 2 * i) for i, k in enumerate(sizes)])
+    centers = rng.permutation(np.concatenate([centers, rng.choice([30, 31, 64, 127], n - len(centers))]))
+    tok = np.concatenate([rng.integers(0, V, begin), centers, rng.integers(0, V, 50)]).astype(np.int32)
+    _grad_parity((V, D, D, None, None, w, N, n, begin, dtype), resample=resample, stream=(tok, np.full(V, 60, np.uint64)))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_gradient_by_pairs_of_words_with_rows_that_are_not_finite(dtype):
     """Rows of NaN, of infinities and of values whose dot products overflow in either table reach the rows of the words that
