@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtensair.so")
-SOURCES = ["api.hip", "sample.hip", "sort.hip", "grad.hip", "grad_sub.hip", "group.hip", "reduce.hip", "reduce_sub.hip", "apply.hip", "apply_ride.hip", "dense.hip", "probe.hip", "noalloc.hip"]
+SOURCES = ["api.hip", "sample.hip", "sort.hip", "grad.hip", "grad_sub.hip", "group.hip", "reduce.hip", "reduce_sub.hip", "apply.hip", "apply_ride.hip", "apply_chain.hip", "dense.hip", "probe.hip", "noalloc.hip"]
 HEADERS = ["dev_common.h", "kernels.h", "aux_dev.h", "prep_dev.h", "apply_kernels.h", "rows_dev.h", "group_dev.h", "forward_dev.h", "reduce_dev.h", os.path.join("..", "..", "include", "tensair.h")]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

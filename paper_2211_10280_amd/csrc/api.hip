@@ -197,7 +197,7 @@ struct tensair_model {
     uint2 *draw;               // alias table: threshold, alias
     int *status;
     BatchSet set[2];
-    int *long_list;
+    int4 *long_list;
     float *g, *center_part, *center_loss, *part_out, *part_in, *cross_out, *cross_in;
     int *xinfo_out, *xinfo_in;
     u32 *start[2];
@@ -212,6 +212,7 @@ struct tensair_model {
     double *group_hot_rows = nullptr;
     float *group_hot_part = nullptr;
     u32 *group_dense = nullptr;
+    u64 *long_mask[2];         // rows of a step's own gradient that the table update chains, per table
     u32 *wbase[2], *wblk[2];   // tensair_grad_add: place of every 64-row word in the summed gradient
     std::vector<Draw> h_draw;  // the same on the host
     WordStats words;
@@ -234,6 +235,7 @@ struct tensair_model {
     // forward pass (clearing) and of the segmented reduction (the id lists), on the caller's stream
     ApplyArgs *fused_apply = nullptr;
     bool fused_index_done = false;
+    ChainWork chain = {};               // tensair_step: the chaining of long rows that its update takes along (no blocks: none)
     bool prepare_under_apply = false;   // tensair_step: the table update is long enough to hide a preparation ...
     bool ride_long_update = false;      // ... many times over
     Prefetched deferred;                // the mini-batch to prepare under that update (enqueued by tensair_step)
@@ -281,7 +283,7 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
         p = take((cap_in + 1) * 4); if (b) b->off_in = (int *)p;
         p = take((cap_out + 1) * 4); if (b) b->off_out = (int *)p;
     }
-    p = take((size_t)(s.tiles_out + s.tiles_in) * 4); if (m) m->long_list = (int *)p;
+    p = take((size_t)(s.tiles_out + s.tiles_in) * 16); if (m) m->long_list = (int4 *)p;
     p = take((size_t)s.Omax * 4); if (m) m->g = (float *)p;
     p = take((size_t)s.Bmax * D * 4); if (m) m->center_part = (float *)p;
     const int per_center = 2 * c.window * (c.negatives + 1);
@@ -311,6 +313,7 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
         p = take((size_t)(s.words + 1) * K1 * 4); if (m) m->start[t] = (u32 *)p;
         p = take((size_t)s.words * K1 * 8); if (m) m->mask[t] = (u64 *)p;
         p = take((size_t)s.words * K1 * 8); if (m) m->mask_alt[t] = (u64 *)p;
+        p = take((size_t)s.words * 8); if (m) m->long_mask[t] = (u64 *)p;
         p = take((size_t)s.words * 4); if (m) m->wbase[t] = (u32 *)p;
         p = take((size_t)(s.words / TN_UNION_WORDS + 1) * 4); if (m) m->wblk[t] = (u32 *)p;
     }
@@ -881,6 +884,26 @@ static bool long_chain(const tensair_model *m, i64 P, int n_centers)
     return std::max(out / (1 << tn_seg_shift(O, D)), in / (1 << tn_seg_shift(n_centers, D))) >= times * 32 * side_by_side;
 }
 
+// Whether the table update of a step chains the long rows itself, a workgroup each at the front of its grid (apply_kernels.h),
+// instead of a launch before it: where the preparation of the mini-batch after it finds a launch for every phase without that
+// one, and the longest row expected is chained as fast as the rest is updated (in rounds as in long_chain: up to 16; up to 4
+// where the update of wide rows of a small vocabulary is as short itself).  Step, us, a launch before it / the update: 1 000 words,
+// D = 32, 64 centers 21.9 / 18.6; 1 316 words, D = 136, 64 centers 25.4 / 18.8; 1 119 words, D = 120, 1 380 centers 49.0 / 40.1; 6 433 words, D = 252,
+// 2 160 centers 54.0 / 45.8; 50 000 words, D = 128, 1 024 centers 46.8 / 43.2; 50 000 words, D = 512, 1 000 centers, 5 peers 152 / 143; more
+// rounds: 300 words, D = 300, 300 centers 36.7 / 40.8, 5 000 words 37.1 / 37.2, D = 200 35.2 / 30.9.  Not with packed peers of narrow rows, whose update
+// of a large vocabulary makes use of the waves that the chaining's registers take: 260 000 words, D = 32, 1 000 centers 89 / 92,
+// D = 200 113 / 110.
+static bool chains_with_update(const tensair_model *m, i64 P, int n_centers, bool packed)
+{
+    const tensair_config &c = m->cfg;
+    const i64 O = P * (c.negatives + 1);
+    const int side_by_side = c.dim > TN_SUB_MAX_DIM ? 1 : c.dim > 64 ? 2 : c.dim > 32 ? 4 : 8;
+    const int times = c.dim > TN_SUB_MAX_DIM && c.vocab * c.dim <= (i64)1 << 19 ? 4 : 16;
+    const double out = m->words.per_pair * (double)P / (1 << tn_seg_shift(O, c.dim)), in = m->words.center * n_centers / (1 << tn_seg_shift(n_centers, c.dim));
+    return O <= TN_CHAIN_UPDATE_MAX_OCC && prep_phases(m->sz, true) <= 4 && tn_apply_carries(c.dim, c.vocab) &&
+           !tn_streams(c.vocab, c.row_stride, c.dtype) && !(packed && c.dim <= TN_SUB_MAX_DIM && c.vocab > 131072) && std::max(out, in) <= times * 32.0 * side_by_side;
+}
+
 // Whether the gradient of a mini-batch goes by pairs of words (group.hip).  Such a mini-batch is prepared by its own call.
 // Counting a chunk and adding up a word look at every word and every chunk, whatever they hold: that has to be paid for by
 // occurrences per word, the more of them the cheaper an occurrence is by itself -- narrow rows, positions that repeat words.
@@ -1025,6 +1048,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
             m->pend = following;
         }
     }
+    const bool chain_later = fuse && !by_pairs && chains_with_update(m, P, n_centers, m->fused_apply->packed);
     mark(m, PF_BEGIN_GRAD, st);
 
     FwdArgs f;
@@ -1074,6 +1098,10 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
             m->mask_clean[1 - pick] = true;
         }
         m->fused_index_done = true;
+        if (chain_later) {        // the update before this call is the last reader of the rows noted there
+            tn_aux_add_clear(aux_fwd, m->long_mask[0], m->long_mask[1], (size_t)s.words);
+            for (int t = 0; t < 2; ++t) fa.skip[t] = m->long_mask[t];
+        }
     }
 
     const RowIndexDst in = {grad_out->in.row_ids, grad_out->in.n_rows, seg_offsets_in, grad_out->in.capacity};
@@ -1263,6 +1291,13 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
     r_out.table = m->w_in;
     r_out.dtype = c.dtype;
     r_out.stride = c.row_stride;
+    if (chain_later) {
+        r_in.row_ids = prepared ? S.ids_in : grad_out->in.row_ids;
+        r_out.row_ids = prepared ? S.ids_out : grad_out->out.row_ids;
+        r_in.long_mask = m->long_mask[0];
+        r_out.long_mask = m->long_mask[1];
+        tn_chain_work(m->chain, r_out, r_in);
+    }
     if (overlap) {   // both sides in one launch
         if (mean_loss) tn_aux_add_loss(aux_red, m->center_loss, n_centers, f.inv_P, mean_loss);
         if (next_rider(m, false, x, st)) tn_aux_add_prep(aux_red, x);
@@ -1271,7 +1306,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
         // are more left than the table update and the next forward pass can take (1 024 centers, 50 000 words: step 54.6
         // -> 49.0 us with the second pass under the update instead)
         const int later = 1 + (fuse && tn_apply_carries(c.dim, c.vocab) ? 1 : 0);
-        const bool rider = tn_seg_chains(r_out.n, c.dim) + tn_seg_chains(r_in.n, c.dim) > 0 &&
+        const bool rider = !chain_later && tn_seg_chains(r_out.n, c.dim) + tn_seg_chains(r_in.n, c.dim) > 0 &&
                            (long_chain(m, P, n_centers) || m->pend.phase + later < prep_phases(s, true)) &&
                            next_rider(m, false, y, st);
         tn_launch_segreduce(&r_out, &r_in, &aux_red, rider ? &y : nullptr, st);
@@ -1365,7 +1400,7 @@ static int apply_impl(tensair_model *m, const tensair_sparse_grad *own, const te
     tn_launch_apply_clear(a, st);
     tn_launch_apply_index(a, 0, a.n_src, st);
     mark(m, PF_APPLY_INDEX, st);
-    tn_launch_apply_update(a, nullptr, st);
+    tn_launch_apply_update(a, nullptr, nullptr, st);
     ++m->apply_serial;
     mark(m, PF_APPLY_UPDATE, st);
     HIP_TRY(hipGetLastError());
@@ -1501,6 +1536,7 @@ static int step_impl(tensair_model *m, const int32_t *tokens, int64_t n_tokens, 
     }
     m->fused_apply = &a;
     m->fused_index_done = false;
+    m->chain.blocks = 0;
     m->deferred.valid = false;
     {   // rough times of the table update (bytes of the gradient blocks at their largest, at 5 TB/s) and of
         // the preparation of a mini-batch (0.2 ns per occurrence plus its launches)
@@ -1529,7 +1565,8 @@ static int step_impl(tensair_model *m, const int32_t *tokens, int64_t n_tokens, 
     if ((rc = enqueue_deferred_prepare(m, ev, st))) return rc;
     PrepPhase x;
     const bool rider = m->prof_level < 2 && tn_apply_carries(a.D, a.V) && next_rider(m, false, x, st);
-    tn_launch_apply_update(a, rider ? &x : nullptr, st);
+    tn_launch_apply_update(a, rider ? &x : nullptr, m->chain.blocks ? &m->chain : nullptr, st);
+    m->chain.blocks = 0;
     ++m->apply_serial;
     mark(m, PF_APPLY_UPDATE, st);
     HIP_TRY(hipGetLastError());

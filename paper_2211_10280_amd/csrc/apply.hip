@@ -128,9 +128,10 @@ void tn_launch_apply_index(const ApplyArgs &a, int k_begin, int k_end, hipStream
     hipLaunchKernelGGL(k_apply_index, dim3(blocks, k_end - k_begin, 2), dim3(BLOCK), 0, st, a, k_begin);
 }
 
-void tn_launch_apply_update(const ApplyArgs &a, const PrepPhase *rider, hipStream_t st)
+void tn_launch_apply_update(const ApplyArgs &a, const PrepPhase *rider, const ChainWork *chain, hipStream_t st)
 {
-    if (rider) tn_launch_apply_update_riding(a, *rider, st);
+    if (chain) tn_launch_apply_update_chaining(a, rider, *chain, st);
+    else if (rider) tn_launch_apply_update_riding(a, *rider, st);
     else launch_apply(a, NoRider(), st);
 }
 

@@ -187,8 +187,10 @@ struct SegReduceArgs {
     float *cross;          // [ceil(ntiles / TN_SEG_XBLOCK)][D] scratch: partials of long rows per block of tiles
                            // (the launcher clears the pointer for problems of at most TN_SEG_CROSS_MIN tiles)
     int *long_cnt;         // [1] number of long rows found (zeroed by the segment scan)
-    int *long_list;        // [ntiles] tiles in which a long row begins, in no particular order
+    int4 *long_list;       // [ntiles] the long rows, in no particular order: the tile it begins in, the row, tiles after that one, word (where noted)
     int *xinfo;            // [ceil(ntiles / TN_SEG_XBLOCK)] scratch: does a long row cross the block's border
+    const int *row_ids;    // [U] the rows' words, where the table update chains the long ones ...
+    u64 *long_mask;        // ... which are noted here too, a bit per word (else NULL)
     int D;
     // source of the contribution of an entry:
     //  mode 0 (out-side): value = occurrence index o; row = g[o] * W_in[pair_center[o/(N+1)]]
@@ -213,6 +215,16 @@ struct SegReducePair {
     int blocks_in;    // workgroups of the in-side problem at the front of the grid
 };
 void tn_launch_segreduce_sub(SegReducePair &p, const AuxWork &aux, const PrepPhase &rider, hipStream_t st);
+// The chaining of long rows left to the table update (tn_launch_apply_update): each is summed and applied by a workgroup at the
+// front of its grid.
+struct ChainWork {
+    SegReducePair p;
+    int blocks;       // workgroups; p.blocks_in of them take the in-side rows
+};
+#ifndef TN_CHAIN_UPDATE_MAX_OCC
+#define TN_CHAIN_UPDATE_MAX_OCC 131072     // occurrences up to which it is (chains_with_update; not measured beyond)
+#endif
+void tn_chain_work(ChainWork &c, const SegReduceArgs &out, const SegReduceArgs &in);
 // workgroups that chain long rows: they exist only where a problem has more than one tile
 static inline int tn_seg_chains(i64 n, int D)
 {
@@ -327,6 +339,7 @@ struct ApplyArgs {
     ApplySrc src[2][TN_MAX_SRC];
     u32 *start[2];           // [words+1][n_src]
     u64 *mask[2];            // [words][n_src]
+    const u64 *skip[2];      // [words] rows that the chaining of long rows updates, a bit each (NULL: none)
     float lr;
     int *status;
     int packed;              // 1: the peers' rows (sources 1..) are bfloat16 messages, the own gradient's fp32
@@ -371,8 +384,10 @@ void tn_launch_apply_index(const ApplyArgs &a, int k_begin, int k_end, hipStream
 // whether a phase can ride with the update: its workgroups come on top of those for the rows (of 16 vocabulary rows
 // each, at least), and one launch has to hold them all
 static inline bool tn_apply_carries(int D, i64 V) { return D <= 512 && (V + 15) / 16 + TN_PREP_CHAIN_MAX <= TN_MAX_BLOCKS; }
-void tn_launch_apply_update(const ApplyArgs &a, const PrepPhase *rider, hipStream_t st);   // rider may be NULL
+void tn_launch_apply_update(const ApplyArgs &a, const PrepPhase *rider, const ChainWork *chain, hipStream_t st);   // both may be NULL
 void tn_launch_apply_update_riding(const ApplyArgs &a, const PrepPhase &rider, hipStream_t st);
+void tn_launch_apply_update_chaining(const ApplyArgs &a, const PrepPhase *rider, const ChainWork &chain, hipStream_t st);   // not where tn_streams
+static inline bool tn_streams(i64 V, int stride, int dtype) { return 2 * V * (i64)stride * (dtype == 0 ? 4 : 2) > ((i64)1 << 30); }
 
 // ---- sum of sparse gradients: out = src_0 + src_1 + ... on the union of their rows
 struct GradSumArgs {

@@ -124,7 +124,7 @@ extern "C" int tensair_dasgd_apply_static(void *w_in, void *w_out, int64_t vocab
     hipStream_t st = (hipStream_t)stream;
     tn_launch_apply_clear(a, st);
     tn_launch_apply_index(a, 0, a.n_src, st);
-    tn_launch_apply_update(a, nullptr, st);
+    tn_launch_apply_update(a, nullptr, nullptr, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return tn_fail(TENSAIR_EHIP, "dasgd_apply_static: %s", hipGetErrorString(e));
     return TENSAIR_OK;

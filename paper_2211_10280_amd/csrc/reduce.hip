@@ -1,6 +1,8 @@
 // The segmented reduction, a row per wave (see reduce_dev.h).
 #include <string.h>
 
+#include <algorithm>
+
 #include "reduce_dev.h"
 #include "rows_dev.h"
 
@@ -136,7 +138,7 @@ __device__ __forceinline__ void segreduce_tile(const SegReduceArgs &a, int block
         }
     }
     flush();
-    if (dest == 2) seg_note_long(a, tile);
+    if (dest == 2) seg_note_long(a, tile, cur);
 }
 
 template <typename T, int NQ, bool TAIL>
@@ -183,6 +185,18 @@ static void launch_segreduce_d(SegReducePair &p, int D, const AuxWork &aux, cons
     case 3: launch_segreduce_t<T, 3, false>(p, aux, rider, st); break;
     default: launch_segreduce_t<T, 4, false>(p, aux, rider, st); break;
     }
+}
+
+void tn_chain_work(ChainWork &c, const SegReduceArgs &out, const SegReduceArgs &in)
+{
+    memset(&c, 0, sizeof(c));
+    c.p.out = out;
+    c.p.in = in;
+    c.p.out.shift = tn_seg_shift(out.n, out.D);
+    c.p.in.shift = tn_seg_shift(in.n, in.D);
+    c.p.out.cross = c.p.in.cross = nullptr;
+    c.p.blocks_in = std::min(tn_seg_chains(in.n, in.D), 64);
+    c.blocks = c.p.blocks_in + std::min(tn_seg_chains(out.n, out.D), 512);
 }
 
 // Either problem may be absent (NULL): the other one then runs alone.

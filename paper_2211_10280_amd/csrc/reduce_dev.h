@@ -101,11 +101,14 @@ struct SegWindow {
     }
 };
 
-// a long row begins in this tile: leave its tile for the kernel that chains the partials
+// a long row begins in this tile: leave it, and where it ends, for the kernel that chains the partials
 // (integer counter; the order of the list does not matter, every chain is independent)
-__device__ __forceinline__ void seg_note_long(const SegReduceArgs &a, int tile)
+__device__ __forceinline__ void seg_note_long(const SegReduceArgs &a, int tile, int row)
 {
-    if (lane_id() == 0) a.long_list[atomicAdd(a.long_cnt, 1)] = tile;
+    if (lane_id() != 0) return;
+    const int end = a.seg_start[row + 1], word = a.long_mask != nullptr ? a.row_ids[row] : 0;
+    a.long_list[atomicAdd(a.long_cnt, 1)] = make_int4(tile, row, ((end - 1) >> a.shift) - tile, word);
+    if (a.long_mask != nullptr) atomicOr((unsigned long long *)&a.long_mask[word >> 6], 1ull << (word & 63));
 }
 
 // ---------------------------------------------------------------- chains of partials
@@ -114,60 +117,78 @@ __device__ __forceinline__ void seg_note_long(const SegReduceArgs &a, int tile)
 #define FIXUP_THREADS 512
 #define FIXUP_WAVES (FIXUP_THREADS / WAVE)
 
-// The sum of `n` rows of D floats, the j-th at src(j), over the waves of a workgroup: this wave's share goes to its row of
-// red; `first` (may be NULL) comes on top.  A row per wave (float4 registers per lane: ITERS) ...
+// The sum of `n` rows of D floats, the j-th at src(j), in FIXUP_WAVES shares, several by each of the workgroup's WAVES waves,
+// side by side where it has fewer: a share goes to its row of red; `first` (may be NULL) comes on top.  A row per wave (float4
+// registers per lane: ITERS) ...
 template <int ITERS>
 struct WideChain {
     static constexpr int row = ITERS * WAVE * 4;
-    template <typename Src>
+    template <int WAVES = FIXUP_WAVES, typename Src>
     static __device__ __forceinline__ void sum(int D, int n, const float *first, Src src, float (*red)[row])
     {
+        constexpr int SHARES = FIXUP_WAVES / WAVES, UNROLL = SHARES * ITERS > 2 && SHARES > 1 ? SEG_UNROLL / 2 : SEG_UNROLL;
         const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id(), C4 = D >> 2;
-        float4 acc[ITERS];
-        zero_row<ITERS>(acc);
-        if (first && wave == 0) load_row<float, ITERS>(acc, first, C4, lane);
-        for (int j0 = wave; j0 < n; j0 += FIXUP_WAVES * SEG_UNROLL) {
-            float4 r[SEG_UNROLL][ITERS];
+        float4 acc[SHARES][ITERS];
 #pragma unroll
-            for (int x = 0; x < SEG_UNROLL; ++x) {
-                const int j = j0 + x * FIXUP_WAVES;
-                const float *p = src(j);
-                if (j < n) load_row<float, ITERS>(r[x], p, C4, lane);
-                else zero_row<ITERS>(r[x]);
-            }
+        for (int h = 0; h < SHARES; ++h) zero_row<ITERS>(acc[h]);
+        if (first && wave == 0) load_row<float, ITERS>(acc[0], first, C4, lane);
+        for (int j0 = wave; j0 < n; j0 += FIXUP_WAVES * UNROLL) {
+            float4 r[UNROLL][SHARES][ITERS];
 #pragma unroll
-            for (int x = 0; x < SEG_UNROLL; ++x) add_row<ITERS>(acc, r[x]);
+            for (int x = 0; x < UNROLL; ++x)
+#pragma unroll
+                for (int h = 0; h < SHARES; ++h) {
+                    const int j = j0 + x * FIXUP_WAVES + h * WAVES;
+                    const float *p = src(j);
+                    if (j < n) load_row<float, ITERS>(r[x][h], p, C4, lane);
+                    else zero_row<ITERS>(r[x][h]);
+                }
+#pragma unroll
+            for (int x = 0; x < UNROLL; ++x)
+#pragma unroll
+                for (int h = 0; h < SHARES; ++h) add_row<ITERS>(acc[h], r[x][h]);
         }
 #pragma unroll
-        for (int it = 0; it < ITERS; ++it) *(float4 *)&red[wave][(lane + WAVE * it) * 4] = acc[it];
+        for (int h = 0; h < SHARES; ++h)
+#pragma unroll
+            for (int it = 0; it < ITERS; ++it) *(float4 *)&red[wave + h * WAVES][(lane + WAVE * it) * 4] = acc[h][it];
     }
 };
 // ... or one per group of SUB lanes (rows of at most 4 * SUB elements)
 template <int SUB>
 struct GroupChain {
     static constexpr int row = SUB * 4;
-    template <typename Src>
+    template <int WAVES = FIXUP_WAVES, typename Src>
     static __device__ __forceinline__ void sum(int D, int n, const float *first, Src src, float (*red)[row])
     {
-        constexpr int STEP = FIXUP_WAVES * (WAVE / SUB);
+        constexpr int RPW = WAVE / SUB, STEP = FIXUP_WAVES * RPW, SHARES = FIXUP_WAVES / WAVES;
         const int wave = uniform((int)(threadIdx.x >> 6)), lane = lane_id();
-        const int slot = lane / SUB, sl = lane % SUB, g = wave * (WAVE / SUB) + slot;
+        const int slot = lane / SUB, sl = lane % SUB, g = wave * RPW + slot;
         const bool in = sl < (D >> 2);
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (first && in && g == 0) acc = ld4(first + 4 * sl);
+        float4 acc[SHARES];
+#pragma unroll
+        for (int h = 0; h < SHARES; ++h) acc[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (first && in && g == 0) acc[0] = ld4(first + 4 * sl);
         for (int j0 = g; j0 - slot < n; j0 += STEP * SEG_UNROLL) {
-            float4 r[SEG_UNROLL];
+            float4 r[SEG_UNROLL][SHARES];
 #pragma unroll
-            for (int x = 0; x < SEG_UNROLL; ++x) {
-                const int j = j0 + x * STEP;
-                r[x] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (in && j < n) r[x] = ld4(src(j) + 4 * sl);
-            }
+            for (int x = 0; x < SEG_UNROLL; ++x)
 #pragma unroll
-            for (int x = 0; x < SEG_UNROLL; ++x) axpy4(acc, 1.0f, r[x]);
+                for (int h = 0; h < SHARES; ++h) {
+                    const int j = j0 + x * STEP + h * WAVES * RPW;
+                    r[x][h] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (in && j < n) r[x][h] = ld4(src(j) + 4 * sl);
+                }
+#pragma unroll
+            for (int x = 0; x < SEG_UNROLL; ++x)
+#pragma unroll
+                for (int h = 0; h < SHARES; ++h) axpy4(acc[h], 1.0f, r[x][h]);
         }
-        acc = sum_groups<SUB>(acc);
-        if (slot == 0) *(float4 *)&red[wave][4 * sl] = acc;
+#pragma unroll
+        for (int h = 0; h < SHARES; ++h) {
+            acc[h] = sum_groups<SUB>(acc[h]);
+            if (slot == 0) *(float4 *)&red[wave + h * WAVES][4 * sl] = acc[h];
+        }
     }
 };
 
@@ -184,31 +205,35 @@ __device__ __forceinline__ void chain_store(float *dst, int D, float (*red)[Chai
     }
 }
 
-// Chains the partials of long rows in tile order: one workgroup per long row (grid-strided
-// over the list the reduction left), its waves sharing the chain part[tile][1], part[tile+1][0], ...
+// Chains the partials of a long row that the reduction listed, in tile order: the waves share the chain
+// part[tile][1], part[tile+1][0], ...
+template <typename Chain, int WAVES>
+__device__ __forceinline__ void segfixup_row(const SegReduceArgs &a, int4 entry, float (*red)[Chain::row])
+{
+    const int tile = uniform(entry.x), len = uniform(entry.z);   // tiles after this one that hold a leading partial
+    // the chain: leading partials of the tiles up to the next border of a tile block, then one
+    // partial per tile block (k_segcross), the last of which ends where the row ends
+    const int b1 = tile / TN_SEG_XBLOCK + 1;
+    const int to_border = a.cross ? b1 * TN_SEG_XBLOCK - 1 - tile : len;   // no block partials: walk it all
+    const int nd = len < to_border ? len : to_border;
+    const int nc = (len > to_border) ? ((tile + len) / TN_SEG_XBLOCK - b1 + 1) : 0;
+    // the j-th partial by selects (with a branch per partial the chain is longer: gradient of 6 000 centers, 100 words, 2 600 partials
+    // of D = 300 in the longest row 147 us, by selects 138)
+    const u32 near_step = 2 * (u32)a.D, far_step = (u32)a.D;
+    const float *near = a.part + (size_t)(tile + 1) * near_step, *far = a.cross + (i64)(b1 - nd) * a.D;
+    Chain::template sum<WAVES>(a.D, nd + nc, a.part + ((size_t)tile * 2 + 1) * a.D,
+                               [=](int j) { return (j < nd ? near : far) + (size_t)(u32)j * (j < nd ? near_step : far_step); }, red);
+}
+// one workgroup per long row
 template <typename Chain>
 __device__ __forceinline__ void segfixup_rows(const SegReduceArgs &a, int first, int stride, float (*red)[Chain::row])
 {
+    int4 entry = a.long_list[first];        // there is one per tile, and no more workgroups: with the count, not after it
     const int count = *a.long_cnt;
     for (int i = first; i < count; i += stride) {
-        const int tile = a.long_list[i];
-        const int t1 = min(a.n, (tile + 1) << a.shift);
-        const int row = a.seg_of[t1 - 1];
-        const int end = a.seg_start[row + 1];
-        const int len = ((end - 1) >> a.shift) - tile;   // tiles after this one that hold a leading partial
-        // the chain: leading partials of the tiles up to the next border of a tile block, then one
-        // partial per tile block (k_segcross), the last of which ends where the row ends
-        const int b1 = tile / TN_SEG_XBLOCK + 1;
-        const int to_border = a.cross ? b1 * TN_SEG_XBLOCK - 1 - tile : len;   // no block partials: walk it all
-        const int nd = len < to_border ? len : to_border;
-        const int nc = (len > to_border) ? ((tile + len) / TN_SEG_XBLOCK - b1 + 1) : 0;
-        // the j-th partial by selects (with a branch per partial the chain is longer: gradient of 6 000 centers, 100 words, 2 600 partials
-        // of D = 300 in the longest row 147 us, by selects 138)
-        const u32 near_step = 2 * (u32)a.D, far_step = (u32)a.D;
-        const float *near = a.part + (size_t)(tile + 1) * near_step, *far = a.cross + (i64)(b1 - nd) * a.D;
-        Chain::sum(a.D, nd + nc, a.part + ((size_t)tile * 2 + 1) * a.D,
-                   [=](int j) { return (j < nd ? near : far) + (size_t)(u32)j * (j < nd ? near_step : far_step); }, red);
-        chain_store<Chain>(a.out_rows + (size_t)row * a.D, a.D, red);
+        if (i > first) entry = a.long_list[i];
+        segfixup_row<Chain, FIXUP_WAVES>(a, entry, red);
+        chain_store<Chain>(a.out_rows + (size_t)uniform(entry.y) * a.D, a.D, red);
         __syncthreads();
     }
 }
@@ -279,7 +304,7 @@ static void launch_segreduce_tiles(SegReducePair &p, const PrepPhase &rider, hip
         hipLaunchKernelGGL((k_segcross<Chain>), dim3(xb_in + xb_out), dim3(FIXUP_THREADS), 0, st, p);
     }
     const int fix_out = tn_seg_chains(p.out.n, p.out.D), fix_in = tn_seg_chains(p.in.n, p.in.D);
-    if (fix_out + fix_in > 0) {
+    if (fix_out + fix_in > 0 && p.out.long_mask == nullptr) {
         p.blocks_in = fix_in;
         const unsigned own = 4u * FIXUP_WAVES * Chain::row, riding = ride_lds_bytes<FIXUP_THREADS>(rider);
         hipLaunchKernelGGL((k_segfixup<Chain>), dim3(rider.blocks + fix_out + fix_in), dim3(FIXUP_THREADS),

@@ -150,7 +150,7 @@ __device__ __forceinline__ void segreduce_tile_sub(const SegReduceArgs &a, int b
         if (next == n) store(win.last_dest, cur, sum);
         else if ((heads >> next) & 1ull) store(began_before(next - 1) ? 1 : 0, cur, sum);
     }
-    if (win.last_dest == 2) seg_note_long(a, tile);
+    if (win.last_dest == 2) seg_note_long(a, tile, rd_lane(win.seg_l, win.tile_len - 1));
 }
 
 template <typename T, int SUB>

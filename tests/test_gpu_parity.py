@@ -1169,6 +1169,55 @@ def test_step_packed_writes_the_own_gradient_as_a_message(K):
     m.close()
 
 
+@pytest.mark.parametrize("V,D,dtype,K,packed,batch,flags", [
+    (300, 4, "f32", 0, False, 400, 0), (900, 32, "bf16", 2, False, 700, 0), (2_000, 36, "f32", 1, True, 500, 0), (5_000, 64, "bf16", 3, True, 300, 0),
+    (20_000, 68, "f32", 31, False, 60, 0), (1_000, 128, "bf16", 0, False, 500, B.STOCHASTIC_ROUNDING), (3_000, 132, "f32", 2, False, 90, 0),
+    (40, 256, "bf16", 1, True, 400, 0), (150_000, 260, "f32", 1, False, 200, 0), (140_000, 64, "f32", 1, False, 200, 0),
+    (262_144, 100, "bf16", 1, True, 150, B.STOCHASTIC_ROUNDING), (64, 300, "f32", 1, True, 1_100, 0), (3_000, 512, "bf16", 2, False, 500, B.STOCHASTIC_ROUNDING)])
+def test_long_rows_chained_by_the_update_give_the_bits_of_separate_calls(V, D, dtype, K, packed, batch, flags):
+    """A small step leaves the rows that many occurrences meet to its update; gradient calculation and application as
+    calls of their own chain them in a launch before it.  Own gradient, message and tables, over announced steps."""
+    w, N = 5, 7
+    tok = W.zipf_stream(V, 1.3, 20_000, 5)
+    counts = W.unigram_counts(tok, V)
+    dtok = torch.from_numpy(tok).cuda()
+    models = []
+    for _ in range(2):
+        tables = tuple(_tables_to_dev(t, dtype) for t in _random_tables(V, D, D, dtype, seed=4))
+        models.append(B.Model(V, D, DT[dtype][0], w, N, batch, K, 6, counts, row_stride=D, tables=tables, flags=flags))
+    a, b = models
+    peers = []
+    for k in range(K):
+        g = a.grad_buffers()
+        a.sgns_grad(dtok, 10_000 + 37 * k, batch, 1, g)
+        if packed:
+            g, full = a.packed_buffers(), g
+            a.grad_pack(full, g)
+        peers.append(g)
+    own_a, own_b = a.grad_buffers(), b.grad_buffers()
+    msg_a, msg_b = (a.packed_buffers(), b.packed_buffers()) if packed else (None, None)
+    a.prefetch(dtok, 0, batch, 0)
+    for t in range(4):
+        a.prefetch(dtok, (t + 1) * batch, batch, 0)
+        b.sgns_grad(dtok, t * batch, batch, 0, own_b)
+        if packed:
+            a.step_packed(dtok, t * batch, batch, 0, peers, 0.5, own_a, msg_a)
+            b.grad_pack(own_b, msg_b)
+            b.dasgd_apply_packed(own_b, peers, 0.5)
+            for (i, x), (j, y) in zip(msg_a.to_host(), msg_b.to_host()):
+                assert np.array_equal(i, j) and np.array_equal(x, y)
+        else:
+            a.step(dtok, t * batch, batch, 0, peers, 0.5, own_a)
+            b.dasgd_apply(own_b, peers, 0.5)
+        a.status()
+        b.status()
+        assert _same(_grad_snapshot(own_a, torch.zeros(1)), _grad_snapshot(own_b, torch.zeros(1))), t
+        for x, y in ((a.w_in, b.w_in), (a.w_out, b.w_out)):
+            assert torch.equal(x.view(torch.int16 if dtype == "bf16" else torch.int32), y.view(torch.int16 if dtype == "bf16" else torch.int32)), t
+    a.close()
+    b.close()
+
+
 def test_grad_pack_errors():
     V, D = 500, 16
     rng = np.random.default_rng(3)

@@ -241,6 +241,21 @@ def test_a_phase_rides_with_the_chaining_of_long_rows_where_that_takes_longer(tr
     assert len(got) == 4 and [g > alone for g in got[:3]] == [rides] * 3
 
 
+# words, rows, table, centers and negatives on both sides of a border: phases of the preparation (2^18 words), streamed tables (2^30
+# bytes), elements of a row (512), occurrences (131 072), partials of the longest row expected (16 times 32, times rows side by side; 4
+# times where the table has at most 2^19 elements of wide rows)
+@pytest.mark.parametrize("V,D,stride,dtype,n,N,most,chains", [
+    (262_144, 64, 64, B.F32, 60, 5, 1, True), (262_145, 64, 64, B.F32, 60, 5, 1, False), (250_000, 512, 536, B.F32, 60, 5, 1, True),
+    (250_000, 512, 540, B.F32, 60, 5, 1, False), (250_000, 512, 540, B.BF16, 60, 5, 1, True), (50_000, 512, 512, B.F32, 60, 5, 1, True),
+    (50_000, 516, 516, B.F32, 60, 5, 1, False), (50_000, 64, 64, B.F32, 1638, 7, 1, True), (50_000, 64, 64, B.F32, 1640, 7, 1, False),
+    (1_000, 300, 300, B.F32, 1600, 7, 50, True), (1_000, 300, 300, B.F32, 1600, 7, 150, False), (1_800, 300, 300, B.F32, 1600, 7, 150, True),
+    (1_800, 300, 300, B.F32, 1600, 7, 1500, False), (1_000, 128, 128, B.F32, 1600, 7, 1500, True)])
+def test_small_steps_chain_long_rows_in_their_update(trace, V, D, stride, dtype, n, N, most, chains):
+    got = trace([["step", 100, n, 0, 1], ["grad", 9_000, n, 0]], counts=[10 * most] + [10] * (min(V, 1000) - 1), vocab=V, dim=D, row_stride=stride,
+                dtype=dtype, window=5, negatives=N, max_centers=n, max_peers=1)
+    assert ["k_segfixup" in names(c["did"]) for c in got] == [not chains, True]
+
+
 @pytest.mark.parametrize("case", PAIR_CASES, ids=lambda c: f"V{c[0]}_D{c[1]}_B{c[6]}_{c[8]}")
 def test_the_cases_of_the_gradient_by_pairs_go_by_pairs(trace, case):
     V, D, stride, _, w, N, n, begin, dtype = case
