@@ -13,11 +13,11 @@
 //   k_group_reduce  adds up, for every word, what the frequent center words give it and the rows of the rare ones that have it
 //                   (one workgroup per word), and for every center word its shares.
 // No occurrence is listed or sorted (unless the negatives or the offsets of the sorted occurrences are asked for) and nothing is
-// chained.  The step above takes 194 us; with chunks of up to 128 positions of any center word, listed all of them, and the
+// chained.  The step above takes 191 us; with chunks of up to 128 positions of any center word, listed all of them, and the
 // draws made by a launch before, 319; with the occurrences sorted beside a forward pass position by position (see
 // prep_dev.h, grad.hip) 472.  Its launches: the centers' sort 26 us (61 with counts in launches of their own and the keys of
-// all occurrences), counts 46 (91, bound by scattered 8-byte stores of the chunks' bits; now by draws, latency and atomics in LDS), rows
-// 49 (77), bits 7, sums 49 (67: row gathers out of L2).
+// all occurrences), counts 44 (91, bound by scattered 8-byte stores of the chunks' bits; now by draws, latency and atomics in LDS), rows
+// 50 (77), bits 7, sums 50 (67: row gathers out of L2).
 #include "aux_dev.h"
 #include "dev_common.h"
 #include "forward_dev.h"
@@ -382,7 +382,8 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_count(GroupArgs a)
 
 // ---------------------------------------------------------------- frequent center words
 // 64 words of the vocabulary against the frequent center words, GROUP_HOT at a time (every `slices` times as many: the
-// workgroups of a slice; of `parts` workgroups, where that would be too few, each has all dot products and a part of the rows): their counts, dot products by matrix instructions, scales, then the words' sums over the center words
+// workgroups of a slice; of `parts` workgroups, where that would be too few, each has all dot products and a part of the
+// rows): their counts, dot products by matrix instructions, scales, then the words' sums over the center words
 // and the center words' sums over the words, all but the sigmoid in double: a pair's scale stands for up to all of its tasks, and
 // its rounding is not averaged over many of them.
 typedef double v4d __attribute__((ext_vector_type(4)));
