@@ -269,9 +269,11 @@ static inline i64 tn_group_frequent(i64 V, int per_center, i64 n_centers)
     const i64 n = least < 1024 ? least : many < 1024 ? 1024 : many < least ? many : least;
     return n < V ? n : V;
 }
+// A chunk is a 2 048th of the positions; where that is fewer than `least`, `least`; and never more than a whole number of positions whose
+// counts fit.  On top of so many comes a chunk that is not full per frequent center word.
 static inline i64 tn_group_chunks(i64 V, int per_center, i64 n_centers)
 {
-    const i64 many = n_centers * per_center / 65535 + 1, n = n_centers / 32;
+    const i64 many = n_centers / (65535 / per_center) + 1, n = n_centers / 32;
     return (n < 2048 ? n + 1 : many < 2048 ? 2048 : many) + tn_group_frequent(V, per_center, n_centers);
 }
 // Workgroups per 64 words of the vocabulary that share the frequent center words, and that share the rows' elements: several

@@ -286,6 +286,39 @@ def test_gradient_by_pairs_of_words_at_the_borders_of_frequent_and_rare_ones(V, 
     _grad_parity((V, D, D, None, None, w, N, n, begin, dtype), resample=resample, stream=(tok, np.full(V, 60, np.uint64)))
 
 
+def test_gradient_by_pairs_of_words_with_chunks_that_hold_no_more_positions():
+    """262 214 centers of 512 tasks, 16 words: a chunk is as many positions as its counts of 16 bits allow (127, not the
+    2 048th of them), which makes more chunks than any smaller mini-batch has.  Against sums in 64 bits over the counted pairs."""
+    V, D, w, N, n, begin = 16, 12, 8, 31, 262_214, 8
+    _say("pairs, capped chunks", n)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    tok = torch.randint(0, V, (n + 16,), generator=gen, device="cuda", dtype=torch.int32)
+    Wi, Wo = (torch.randn((V, D), generator=gen, device="cuda") * 0.3 for _ in range(2))
+    m = B.Model(V, D, B.F32, w, N, n, 0, 5, np.full(V, 50, np.uint64), tables=(Wi, Wo))
+    P = m.pair_count(n + 16, begin, n)
+    assert P == 2 * w * n
+    g, loss = m.grad_buffers(), torch.zeros(1, device="cuda")
+    neg = torch.zeros(P * N, dtype=torch.int32, device="cuda")
+    for asked in ({"negatives_dbg": neg}, {}):
+        g.in_rows.fill_(float("nan"))
+        g.out_rows.fill_(float("nan"))
+        m.sgns_grad(tok, begin, n, 0, g, mean_loss=loss, **asked)
+        m.status()
+        c = tok[begin:begin + n].long()
+        met = torch.stack([torch.bincount(torch.repeat_interleave(c, 2 * w * N) * V + neg.long(), minlength=V * V),
+                           sum(torch.bincount(c * V + tok[begin + o:begin + o + n].long(), minlength=V * V) for o in range(-w, w + 1) if o)])
+        met = met.view(2, V, V).double()
+        v, u = Wi.double(), Wo.double()
+        s = v @ u.T
+        scale = (met[0] * torch.sigmoid(s) - met[1] * torch.sigmoid(-s)) / P
+        lost = float((met[0] * torch.nn.functional.softplus(s) + met[1] * torch.nn.functional.softplus(-s)).sum()) / P
+        for (ids, rows), want in zip(g.to_host(), (scale @ u, scale.T @ v)):
+            assert list(ids) == list(range(V))
+            assert rows_rel(rows, want.cpu().numpy()) <= TOL_ROWS
+        assert abs(float(loss.item()) - lost) <= TOL_LOSS * lost
+    m.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_gradient_by_pairs_of_words_with_rows_that_are_not_finite(dtype):
     """Rows of NaN, of infinities and of values whose dot products overflow in either table reach the rows of the words that
