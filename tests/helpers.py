@@ -222,3 +222,20 @@ def pair_stream(case):
     p = np.arange(1, V + 1, dtype=np.float64) ** -zipf
     tok = np.random.default_rng(V + D).choice(V, size=max(begin + n, 6000), p=p / p.sum()).astype(np.int32)
     return tok, np.bincount(tok, minlength=V).astype(np.uint64)
+
+
+# By pairs of words, 512 tasks each: 12 288 words take five slices of 16 frequent center words at a time, 36 positions are still rare.
+# 100 words are frequent, most of them just so; one has as many positions as a rare one may.
+ROUNDS_CASE = (12_288, 8, 31, 4900, 100)       # V, w, N, B, begin
+ROUNDS_SIZES = [37] * 96 + [64, 65, 69, 97, 36]
+
+
+def rounds_stream():
+    """Tokens and unigram counts of that case."""
+    V, _, _, n, begin = ROUNDS_CASE
+    rng = np.random.default_rng(V)
+    centers = np.concatenate([np.full(k, 120 * i + 3) for i, k in enumerate(ROUNDS_SIZES)])
+    rest = 120 * rng.integers(0, V // 120, n - len(centers)) + 60
+    tok = np.concatenate([rng.integers(0, V, begin), rng.permutation(np.concatenate([centers, rest])), rng.integers(0, V, 50)]).astype(np.int32)
+    p = np.arange(1, V + 1, dtype=np.float64) ** -1.5
+    return tok, np.maximum(1e6 * p, 1).astype(np.uint64)

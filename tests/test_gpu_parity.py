@@ -15,8 +15,8 @@ import pytest
 import torch
 
 import oracle
-from helpers import (BF16_CHAIN_FRAC, BF16_CHAIN_MAX, BF16_MSG_CHAIN_FRAC, BF16_MSG_CHAIN_MAX, BF16_ULP, FORCED_BEYOND, PAIR_CASES, TOL_DELTA, TOL_LOSS, TOL_ROWS, TOL_TABLE, bf16_to_f32, bf16_ulp_err,
-                     bf16_ulp_err_t, delta_rel_l2_t, pair_stream, rel_l2, rel_l2_t, rows_rel, to_dev, ulp_err_at_t, ulp_stats_t)
+from helpers import (BF16_CHAIN_FRAC, BF16_CHAIN_MAX, BF16_MSG_CHAIN_FRAC, BF16_MSG_CHAIN_MAX, BF16_ULP, FORCED_BEYOND, PAIR_CASES, ROUNDS_CASE, TOL_DELTA, TOL_LOSS, TOL_ROWS, TOL_TABLE, bf16_to_f32, bf16_ulp_err,
+                     bf16_ulp_err_t, delta_rel_l2_t, pair_stream, rel_l2, rel_l2_t, rounds_stream, rows_rel, to_dev, ulp_err_at_t, ulp_stats_t)
 from oracle.driver import OracleWorker
 from paper_2211_10280_amd import binding as B
 import workload as W
@@ -319,6 +319,14 @@ def test_gradient_by_pairs_of_words_with_chunks_that_hold_no_more_positions():
     m.close()
 
 
+@pytest.mark.parametrize("D,dtype", [(64, "f32"), (260, "bf16"), (516, "f32")])
+def test_gradient_by_pairs_of_words_with_more_frequent_ones_than_a_round_takes(D, dtype):
+    """The workgroups of 64 words have taken every slice of the frequent center words and go on to a second round: rows, words
+    that were met and the loss are carried over.  Against the oracle."""
+    V, w, N, n, begin = ROUNDS_CASE
+    _grad_parity((V, D, D, None, None, w, N, n, begin, dtype), stream=rounds_stream())
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_gradient_by_pairs_of_words_with_rows_that_are_not_finite(dtype):
     """Rows of NaN, of infinities and of values whose dot products overflow in either table reach the rows of the words that
@@ -394,9 +402,9 @@ def test_ids_out_of_range_count_as_word_0_and_are_reported(n):
 
 def test_long_sums_of_the_gradient_by_pairs_do_not_drift():
     """2^19 centers of one word, scores of zero, four negative words with one and the same row u: the center's row is
-    (N/2 - 1/2) u.  Every factor is exact (P = 2^22), so a chunk's share is off by the roundings of its product, of its
-    wave's sum and of its own; 4096 of them are added up, and the waves' sums and the row rounded: 5 roundings of 2^-24, not
-    one per chunk."""
+    (N/2 - 1/2) u.  The counts of 2 048 chunks, beyond 16 bits, are added up as whole numbers, and four scales meet in
+    one matrix product in double: every factor is exact (P = 2^22), so the row is off by the roundings of the 64 words' share, of
+    its wave's sum and of its own, far below the 5 roundings of 2^-24 allowed."""
     V, D, w, N, n = 4, 64, 4, 15, 1 << 19
     gen = torch.Generator().manual_seed(5)
     u = 1.0 + torch.rand(D, generator=gen)
@@ -410,6 +418,54 @@ def test_long_sums_of_the_gradient_by_pairs_do_not_drift():
     err = np.abs(rows[0].astype(np.float64) / want - 1).max()
     _say("drift", err)
     assert list(ids) == [0] and err <= 5 * 2.0 ** -24
+    m.close()
+
+
+def test_a_word_that_thousands_of_rare_center_words_met_does_not_drift():
+    """12 228 rare center words with one and the same row u, scores of zero, 60 words that are negatives only: the row of
+    one that is drawn k times is k / (2 P) u.  Every scale is exact (P = 2^17), so it is off by the roundings of four terms, of
+    its wave's sum (1 500 terms, in double) and of its own: 6 roundings of 2^-24.  (With the waves' sums in fp32, 50.)"""
+    V, D, w, N, n = 12_288, 260, 4, 15, 16_384
+    gen = torch.Generator().manual_seed(6)
+    u = 1.0 + torch.rand(D, generator=gen)
+    counts = np.zeros(V, np.uint64)
+    counts[:60] = 10
+    tok = (60 + torch.arange(n + 8) % (V - 60)).to(torch.int32).cuda()
+    m = B.Model(V, D, B.F32, w, N, n, 0, 9, counts, tables=(u.repeat(V, 1).cuda(), torch.zeros((V, D), device="cuda")))
+    P = m.pair_count(n + 8, 4, n)
+    assert P == 1 << 17
+    g, neg = m.grad_buffers(), torch.zeros(P * N, dtype=torch.int32, device="cuda")
+    m.sgns_grad(tok, 4, n, 0, g, negatives_dbg=neg)
+    m.status()
+    _, (ids, rows) = g.to_host()
+    drawn = np.bincount(neg.cpu().numpy(), minlength=60)
+    want = (drawn[:, None] / (2.0 * P)) * u.double().numpy()
+    err = np.abs(rows[:60].astype(np.float64) / want - 1).max()
+    _say("drift", err)
+    assert list(ids[:60]) == list(range(60)) and len(drawn) == 60 and err <= 6 * 2.0 ** -24
+    m.close()
+
+
+def test_a_frequent_center_word_that_met_all_of_a_large_vocabulary_does_not_drift():
+    """4 096 centers of one word, scores of zero, 614 negative words with one and the same row u in all 192 groups of 64: the
+    center's row is N/2 u (its own row in W_out, the only context, is zero).  It is off by the roundings of the 64 words'
+    shares (exact scales, P = 2^15, and products in double), of its wave's sum (24 shares, in double) and of its own: 3 of 2^-24."""
+    V, D, w, N, n = 12_288, 260, 4, 63, 4096
+    gen = torch.Generator().manual_seed(7)
+    u = 1.0 + torch.rand(D, generator=gen)
+    counts = np.zeros(V, np.uint64)
+    counts[7::20] = 10
+    Wo = u.repeat(V, 1)
+    Wo[5] = 0.0
+    m = B.Model(V, D, B.F32, w, N, n, 0, 9, counts, tables=(torch.zeros((V, D), device="cuda"), Wo.cuda()))
+    assert m.pair_count(n + 8, 4, n) == 1 << 15
+    g = m.grad_buffers()
+    m.sgns_grad(torch.full((n + 8,), 5, dtype=torch.int32, device="cuda"), 4, n, 0, g)
+    m.status()
+    (ids, rows), (ids_out, _) = g.to_host()
+    err = np.abs(rows[0].astype(np.float64) / (0.5 * N * u.double().numpy()) - 1).max()
+    _say("drift", err)
+    assert list(ids) == [5] and list(ids_out) == sorted([5, *range(7, V, 20)]) and err <= 3 * 2.0 ** -24
     m.close()
 
 

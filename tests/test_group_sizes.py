@@ -7,6 +7,7 @@ import subprocess
 import numpy as np
 import pytest
 
+from helpers import ROUNDS_CASE, rounds_stream
 from paper_2211_10280_amd import build
 
 SHIM = """
@@ -64,3 +65,13 @@ def test_every_mini_batch_fits_what_the_largest_reserves(sizes, tasks):
             room = [sizes.frequent(V, tasks, n), sizes.chunks(V, tasks, n), sizes.slices(V, tasks, n)]
             assert all(a <= b for a, b in zip(worst, room)), (V, tasks, n, "needed", worst, "reserved", room)
             assert worst[1] <= 65535                                                 # a chunk's number, 16 bits in the counting
+
+
+def test_the_stream_of_many_frequent_words_takes_a_second_round(sizes):
+    V, w, N, n, begin = ROUNDS_CASE
+    tasks = 2 * w * (N + 1)
+    positions = np.bincount(rounds_stream()[0][begin:begin + n], minlength=V)
+    rare, slices = sizes.rare(V, tasks, n), sizes.slices(V, tasks, n)
+    frequent = int((positions > rare).sum())
+    assert {rare, rare + 1} <= set(positions.tolist())
+    assert 16 * slices < frequent < 2 * 16 * slices and frequent % 16

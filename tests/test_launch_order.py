@@ -7,7 +7,7 @@ import sys
 
 import pytest
 
-from helpers import PAIR_CASES, pair_stream
+from helpers import PAIR_CASES, ROUNDS_CASE, pair_stream, rounds_stream
 from paper_2211_10280_amd import binding as B
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -265,6 +265,15 @@ def test_the_cases_of_the_gradient_by_pairs_go_by_pairs(trace, case):
     assert [k for k in did if k.startswith("k_group")] == ["k_group_count", "k_group_rows", "k_group_any", "k_group_reduce"]
 
 
+@pytest.mark.parametrize("D,dtype", [(64, B.F32), (260, B.BF16), (516, B.F32)])
+def test_the_case_of_many_frequent_words_goes_by_pairs(trace, D, dtype):
+    V, w, N, n, begin = ROUNDS_CASE
+    tok, counts = rounds_stream()
+    did = names(trace([["grad", begin, n, 0]], tokens=len(tok), counts=counts.tolist(), vocab=V, dim=D, window=w, negatives=N, max_centers=n,
+                      dtype=dtype)[0]["did"])
+    assert "k_group_rows" in did
+
+
 # words, rows, window, negatives, centers on both sides of a border, the Zipf exponent of the counts: occurrences in all (2^20), tasks per
 # position (128 and 512), words (12 288), occurrences per word by width of the rows, tasks and how much positions repeat words
 @pytest.mark.parametrize("V,D,w,N,below,above,zipf", [
@@ -298,17 +307,3 @@ def test_borders_of_the_sweep_of_the_update(trace, D, dtype, V, rows, sweeps):
     rows = int(V / rows) if rows <= 1000 else rows
     did = trace([["apply", 60, rows, 0]], **dict(SMALL, vocab=V, dim=D, dtype=dtype, max_centers=64))[0]["did"]
     assert (launches(did)[-1][1] == 256 * 7) == sweeps
-
-
-# words, rows, window, negatives, centers on both sides of a border, the Zipf exponent of the counts: occurrences in all (2^20), tasks per
-# position (128 and 512), words (12 288), occurrences per word by width of the rows, tasks and how much positions repeat words
-@pytest.mark.parametrize("V,D,w,N,below,above,zipf", [
-    (300, 64, 8, 15, 4096, 4097, 1.1), (300, 300, 1, 62, 20_000, None, 1.1), (300, 300, 1, 63, None, 20_000, 1.1),
-    (300, 300, 8, 31, None, 2100, 1.1), (300, 300, 8, 32, 2100, None, 1.1), (12_288, 300, 8, 15, None, 4097, 1.5), (12_289, 300, 8, 15, 9000, None, 1.5),
-    (12_000, 64, 8, 15, 9374, 9375, 1.5), (12_000, 68, 8, 15, 7031, 7032, 1.5), (12_000, 132, 8, 15, 6374, 6375, 1.5),
-    (12_000, 64, 8, 15, 7031, 7032, 1.2), (12_000, 132, 8, 7, 9749, 9750, 1.2), (12_000, 132, 8, 15, 4218, 4219, 1.2),
-    (12_000, 256, 8, 15, 4218, 4219, 1.2), (12_000, 260, 8, 15, 4096, 4097, 1.2)])
-def test_borders_of_the_gradient_by_pairs(trace, V, D, w, N, below, above, zipf):
-    counts = [max(1, round(2e6 * (i + 1) ** -zipf)) for i in range(V)]
-    got = trace([["grad", 100, n, 0] for n in (below, above) if n], counts=counts, vocab=V, dim=D, window=w, negatives=N, max_centers=20_000)
-    assert ["k_group_rows" in names(c["did"]) for c in got] == [False] * (below is not None) + [True] * (above is not None)
