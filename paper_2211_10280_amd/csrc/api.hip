@@ -900,7 +900,7 @@ static bool chains_with_update(const tensair_model *m, i64 P, int n_centers, boo
     const int side_by_side = c.dim > TN_SUB_MAX_DIM ? 1 : c.dim > 64 ? 2 : c.dim > 32 ? 4 : 8;
     const int times = c.dim > TN_SUB_MAX_DIM && c.vocab * c.dim <= (i64)1 << 19 ? 4 : 16;
     const double out = m->words.per_pair * (double)P / (1 << tn_seg_shift(O, c.dim)), in = m->words.center * n_centers / (1 << tn_seg_shift(n_centers, c.dim));
-    return O <= TN_CHAIN_UPDATE_MAX_OCC && prep_phases(m->sz, true) <= 4 && tn_apply_carries(c.dim, c.vocab) &&
+    return O <= TN_CHAIN_UPDATE_MAX_OCC && c.vocab <= TN_CHAIN_UPDATE_MAX_V && tn_apply_carries(c.dim, c.vocab) &&
            !tn_streams(c.vocab, c.row_stride, c.dtype) && !(packed && c.dim <= TN_SUB_MAX_DIM && c.vocab > 131072) && std::max(out, in) <= times * 32.0 * side_by_side;
 }
 

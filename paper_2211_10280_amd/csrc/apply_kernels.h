@@ -32,8 +32,8 @@ struct PhaseRider {
     __host__ __device__ __forceinline__ int blocks() const { return x.blocks; }
     unsigned lds_bytes() const { return ride_lds_bytes(x); }
 };
-// the same and the chaining of long rows, behind it: with tables that are not streamed (tn_streams), whose updates leave
-// registers to it
+// the same and the chaining of long rows, behind it: with up to TN_CHAIN_UPDATE_MAX_V words and tables that are not streamed
+// (tn_streams), whose updates leave registers to it
 struct ChainRider : PhaseRider {
     static constexpr bool chains = true;
     ChainWork chain;
@@ -647,10 +647,11 @@ static bool sweep_sub(const ApplyArgs &a, int sub)
 template <typename T, int SUB, bool STREAM, typename Rider>
 static void launch_apply_sub(const ApplyArgs &a, const Rider &rider, hipStream_t st)
 {
-    if (sweep_sub(a, SUB)) {
-        if (SUB < 32 || a.V < 393216) launch_apply_sub_r<T, SUB, 2, STREAM, true>(a, rider, st);
-        else launch_apply_sub_r<T, SUB, 4, STREAM, true>(a, rider, st);
-    } else if (SUB > 8 && sparse_union(a, 655360)) launch_apply_sub_r<T, SUB, 16, STREAM, false>(a, rider, st);
+    if constexpr (!Rider::chains) {     // not in a vocabulary of TN_CHAIN_UPDATE_MAX_V words
+        if (SUB == 32 && a.V >= 393216 && sweep_sub(a, SUB)) return launch_apply_sub_r<T, SUB, 4, STREAM, true>(a, rider, st);
+        if (SUB > 8 && sparse_union(a, 655360) && !sweep_sub(a, SUB)) return launch_apply_sub_r<T, SUB, 16, STREAM, false>(a, rider, st);
+    }
+    if (sweep_sub(a, SUB)) launch_apply_sub_r<T, SUB, 2, STREAM, true>(a, rider, st);
     else if (!STREAM && a.V < APPLY_SMALL_V * (WAVE / SUB)) launch_apply_sub_r<T, SUB, 1, STREAM, false>(a, rider, st);
     else launch_apply_sub_r<T, SUB, APPLY_SUB_ROWS, STREAM, false>(a, rider, st);
 }
@@ -695,9 +696,11 @@ static void launch_apply_t(const ApplyArgs &a, const Rider &rider, hipStream_t s
     const i64 unit = sizeof(T) == 2 || PACKED ? 73728 : 131072;
     const int share = sweep_share(a.V, a.D, sizeof(T) == 2);
     if (share > 0 && share * union_rows(a) < a.V) {
-        if (a.V < 655360) launch_apply_g<T, 4, STREAM, PACKED, true>(a, rider, st);
-        else if (a.V < (a.D > 4 * WAVE && sizeof(T) == 4 ? 4000000 : 3000000)) launch_apply_g<T, 8, STREAM, PACKED, true>(a, rider, st);
-        else launch_apply_g<T, 16, STREAM, PACKED, true>(a, rider, st);
+        if constexpr (!Rider::chains) { // not in a vocabulary of TN_CHAIN_UPDATE_MAX_V words
+            if (a.V >= (a.D > 4 * WAVE && sizeof(T) == 4 ? 4000000 : 3000000)) return launch_apply_g<T, 16, STREAM, PACKED, true>(a, rider, st);
+            if (a.V >= 655360) return launch_apply_g<T, 8, STREAM, PACKED, true>(a, rider, st);
+        }
+        launch_apply_g<T, 4, STREAM, PACKED, true>(a, rider, st);
     } else if (sparse_union(a, unit * ((a.D / 4 + WAVE - 1) / WAVE + 1))) launch_apply_g<T, APPLY_G_SPARSE, STREAM, PACKED, false>(a, rider, st);
     else if (!STREAM && a.V < APPLY_SMALL_V) launch_apply_g<T, 1, STREAM, PACKED, false>(a, rider, st);
     else launch_apply_g<T, APPLY_G, STREAM, PACKED, false>(a, rider, st);

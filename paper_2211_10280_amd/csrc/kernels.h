@@ -224,6 +224,7 @@ struct ChainWork {
 #ifndef TN_CHAIN_UPDATE_MAX_OCC
 #define TN_CHAIN_UPDATE_MAX_OCC 131072     // occurrences up to which it is (chains_with_update; not measured beyond)
 #endif
+#define TN_CHAIN_UPDATE_MAX_V (1 << 2 * TN_RADIX_MAX_BITS)     // words up to which it is: their keys are sorted in two passes
 void tn_chain_work(ChainWork &c, const SegReduceArgs &out, const SegReduceArgs &in);
 // workgroups that chain long rows: they exist only where a problem has more than one tile
 static inline int tn_seg_chains(i64 n, int D)
