@@ -285,8 +285,10 @@ __device__ __forceinline__ int apply_block(int bid, int nblocks)
 #define APPLY_MAX_WAVES 7
 #endif
 // With the chaining of long rows in the launch: its registers left 4 to 5 waves per SIMD to large updates (messages, 260 000 words,
-// D = 32, 1 000 centers, 5 peers 89 -> 107 us, D = 88 in bfloat16 without messages 80 -> 87), so those shapes are held to 6; small ones are
-// bound by the chaining itself, which spills then (1 000 words, D = 32: 18.6 -> 20.5).
+// D = 32, 1 000 centers, 5 peers 89 -> 107 us), so those shapes are held to 6; small ones are
+// bound by the chaining itself, which spills then (1 000 words, D = 32: 18.6 -> 20.5).  Steps as a share of those with a launch
+// for the chaining, held to 7 / 6 / 5 / not at all: with messages, D = 132 to 256, 131 072 to 262 144 words, 4 rows per wave 1.02 / 0.97 /
+// 1.00 / 1.07, 16 0.82 / 0.81 / 0.81 / 0.81, sweeps 1.01 / 0.96 / 0.97 / 0.99; D up to 128, one row per wave 0.97 / 0.92 / 0.90 / 0.90.
 // SWEEP: a wave takes one group of rows after the other, `stride` apart (see launch_apply_t); else one.
 template <typename T, int ITERS, int G, bool STREAM, bool PACKED, bool SWEEP, typename Rider>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(Rider::chains && (PACKED || (SWEEP && ITERS == 1)) ? 6 : 1, APPLY_MAX_WAVES)))
@@ -395,8 +397,12 @@ k_apply(ApplyArgs a, int nblocks, Rider rider)
 #ifndef APPLY_SUB_ROWS
 #define APPLY_SUB_ROWS 4   // rows per group of lanes and wave
 #endif
+// With the chaining of long rows in the launch, several rows per group of lanes: held to 5 waves per SIMD nothing spills (to 6, up to 24
+// registers per lane).  Steps of 32 768 to 262 144 words, 0 to 7 peers, as a share of those with a launch for the chaining, held to 7 /
+// 6 / 5 / not at all: 4 rows in fp32 0.94 / 0.96 / 0.91 / 0.91 (the slowest shape 1.04 / 1.08 / 1.01 / 1.01), in bfloat16 0.95 / 0.92 / 0.91 / 0.91
+// (1.07 / 1.02 / 1.01 / 1.07), sweeps 1.10 / 0.93 / 0.90 / 0.91 (1.22 / 1.01 / 0.98 / 1.00).
 template <typename T, int SUB, int ROWS, bool STREAM, bool SWEEP, typename Rider>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(Rider::chains && (SWEEP || ROWS > 1) ? 6 : 1, APPLY_MAX_WAVES)))
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(Rider::chains && (SWEEP || ROWS > 1) ? 5 : 1, APPLY_MAX_WAVES)))
 k_apply_sub(ApplyArgs a, int nblocks, Rider rider)
 {
     if (apply_rides<T, 1, SUB, STREAM, false>(a, rider)) return;
