@@ -886,19 +886,23 @@ static bool long_chain(const tensair_model *m, i64 P, int n_centers)
 
 // Whether the table update of a step chains the long rows itself, a workgroup each at the front of its grid (apply_kernels.h),
 // instead of a launch before it: where the preparation of the mini-batch after it finds a launch for every phase without that
-// one, and the longest row expected is chained as fast as the rest is updated (in rounds as in long_chain: up to 16; up to 4
-// where the update of wide rows of a small vocabulary is as short itself).  Step, us, a launch before it / the update: 1 000 words,
-// D = 32, 64 centers 21.9 / 18.6; 1 316 words, D = 136, 64 centers 25.4 / 18.8; 1 119 words, D = 120, 1 380 centers 49.0 / 40.1; 6 433 words, D = 252,
-// 2 160 centers 54.0 / 45.8; 50 000 words, D = 128, 1 024 centers 46.8 / 43.2; 50 000 words, D = 512, 1 000 centers, 5 peers 152 / 143; more
-// rounds: 300 words, D = 300, 300 centers 36.7 / 40.8, 5 000 words 37.1 / 37.2, D = 200 35.2 / 30.9.  Not with packed peers of narrow rows, whose update
-// of a large vocabulary makes use of the waves that the chaining's registers take: 260 000 words, D = 32, 1 000 centers 89 / 92,
-// D = 200 113 / 110.
+// one, and the longest row expected is chained as fast as the rest is updated (in rounds as in long_chain: up to 16; up to 4 and
+// 8 where the update of wide rows of a small vocabulary is as short itself).  Step, us, a launch before it / the update: 1 000
+// words, D = 32, 64 centers 21.9 / 18.6; 1 316 words, D = 136, 64 centers 25.4 / 18.8; 1 119 words, D = 120, 1 380 centers 49.0
+// / 40.1; 6 433 words, D = 252, 2 160 centers 54.0 / 45.8; 50 000 words, D = 128, 1 024 centers 46.8 / 43.2; 50 000 words, D =
+// 512, 1 000 centers, 5 peers 152 / 143; more rounds: 300 words, D = 300, 300 centers 36.7 / 40.8, 5 000 words 37.1 / 37.2, D =
+// 200 35.2 / 30.9; 9 to 13 rounds, 3 576 words, D = 272, 788 centers, messages 44.4 / 47.5, 3 827 in bfloat16, D = 260, 309
+// centers 40.8 / 43.1, without messages 3 221, D = 400, 491 centers 50.4 / 52.3 (tables of 2^19 to 2^21 elements of wide rows,
+// as a share: 4 to 8 rounds 0.86 in the mean, none above 1.00; more 0.95, up to 1.07).  Not with packed peers of narrow rows,
+// whose update of a large vocabulary makes use of the waves that the chaining's registers take: 260 000 words, D = 32, 1 000
+// centers 89 / 92, D = 200 113 / 110.
 static bool chains_with_update(const tensair_model *m, i64 P, int n_centers, bool packed)
 {
     const tensair_config &c = m->cfg;
     const i64 O = P * (c.negatives + 1);
     const int side_by_side = c.dim > TN_SUB_MAX_DIM ? 1 : c.dim > 64 ? 2 : c.dim > 32 ? 4 : 8;
-    const int times = c.dim > TN_SUB_MAX_DIM && c.vocab * c.dim <= (i64)1 << 19 ? 4 : 16;
+    const i64 elements = c.dim > TN_SUB_MAX_DIM ? c.vocab * c.dim : (i64)1 << 62;
+    const int times = elements <= (i64)1 << 19 ? 4 : elements <= (i64)1 << 21 ? 8 : 16;
     const double out = m->words.per_pair * (double)P / (1 << tn_seg_shift(O, c.dim)), in = m->words.center * n_centers / (1 << tn_seg_shift(n_centers, c.dim));
     return O <= TN_CHAIN_UPDATE_MAX_OCC && c.vocab <= TN_CHAIN_UPDATE_MAX_V && tn_apply_carries(c.dim, c.vocab) &&
            !tn_streams(c.vocab, c.row_stride, c.dtype) && !(packed && c.dim <= TN_SUB_MAX_DIM && c.vocab > 131072) && std::max(out, in) <= times * 32.0 * side_by_side;

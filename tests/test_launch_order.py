@@ -243,12 +243,13 @@ def test_a_phase_rides_with_the_chaining_of_long_rows_where_that_takes_longer(tr
 
 # words, rows, table, centers and negatives on both sides of a border: phases of the preparation (2^18 words), streamed tables (2^30
 # bytes), elements of a row (512), occurrences (131 072), partials of the longest row expected (16 times 32, times rows side by side; 4
-# times where the table has at most 2^19 elements of wide rows)
+# times where the table has at most 2^19 elements of wide rows, 8 times up to 2^21)
 @pytest.mark.parametrize("V,D,stride,dtype,n,N,most,chains", [
     (262_144, 64, 64, B.F32, 60, 5, 1, True), (262_145, 64, 64, B.F32, 60, 5, 1, False), (250_000, 512, 536, B.F32, 60, 5, 1, True),
     (250_000, 512, 540, B.F32, 60, 5, 1, False), (250_000, 512, 540, B.BF16, 60, 5, 1, True), (50_000, 512, 512, B.F32, 60, 5, 1, True),
     (50_000, 516, 516, B.F32, 60, 5, 1, False), (50_000, 64, 64, B.F32, 1638, 7, 1, True), (50_000, 64, 64, B.F32, 1640, 7, 1, False),
     (1_000, 300, 300, B.F32, 1600, 7, 50, True), (1_000, 300, 300, B.F32, 1600, 7, 150, False), (1_800, 300, 300, B.F32, 1600, 7, 150, True),
+    (1_800, 300, 300, B.F32, 1600, 7, 250, False), (6_990, 300, 300, B.F32, 1600, 7, 250, False), (6_992, 300, 300, B.F32, 1600, 7, 250, True),
     (1_800, 300, 300, B.F32, 1600, 7, 1500, False), (1_000, 128, 128, B.F32, 1600, 7, 1500, True)])
 def test_small_steps_chain_long_rows_in_their_update(trace, V, D, stride, dtype, n, N, most, chains):
     got = trace([["step", 100, n, 0, 1], ["grad", 9_000, n, 0]], counts=[10 * most] + [10] * (min(V, 1000) - 1), vocab=V, dim=D, row_stride=stride,
