@@ -895,8 +895,9 @@ static bool long_chain(const tensair_model *m, i64 P, int n_centers)
 // centers 40.8 / 43.1, without messages 3 221, D = 400, 491 centers 50.4 / 52.3 (tables of 2^19 to 2^21 elements of wide rows,
 // as a share: 4 to 8 rounds 0.86 in the mean, none above 1.00; more 0.95, up to 1.07).  Not with packed peers of narrow rows,
 // whose update of a large vocabulary makes use of the waves that the chaining's registers take: 260 000 words, D = 32, 1 000
-// centers 89 / 92, D = 200 113 / 110.
-static bool chains_with_update(const tensair_model *m, i64 P, int n_centers, bool packed)
+// centers 89 / 92, D = 200 113 / 110; nor, with bfloat16 tables, of rows of up to 256 elements where few are touched (the update's
+// sweeps): 240 802 words, D = 224, 73 centers, 5 peers 40.8 / 42.6, 21 such shapes 0.99 in the mean, 19 of up to 196 608 words 0.97.
+static bool chains_with_update(const tensair_model *m, i64 P, int n_centers, const ApplyArgs &a)
 {
     const tensair_config &c = m->cfg;
     const i64 O = P * (c.negatives + 1);
@@ -904,8 +905,10 @@ static bool chains_with_update(const tensair_model *m, i64 P, int n_centers, boo
     const i64 elements = c.dim > TN_SUB_MAX_DIM ? c.vocab * c.dim : (i64)1 << 62;
     const int times = elements <= (i64)1 << 19 ? 4 : elements <= (i64)1 << 21 ? 8 : 16;
     const double out = m->words.per_pair * (double)P / (1 << tn_seg_shift(O, c.dim)), in = m->words.center * n_centers / (1 << tn_seg_shift(n_centers, c.dim));
+    const bool slow = a.packed && (c.dim <= TN_SUB_MAX_DIM ? c.vocab > 131072
+                                   : c.dim <= 256 && c.dtype == TENSAIR_BF16 && c.vocab > 196608 && 5 * tn_union_rows(a) < c.vocab);
     return O <= TN_CHAIN_UPDATE_MAX_OCC && c.vocab <= TN_CHAIN_UPDATE_MAX_V && tn_apply_carries(c.dim, c.vocab) &&
-           !tn_streams(c.vocab, c.row_stride, c.dtype) && !(packed && c.dim <= TN_SUB_MAX_DIM && c.vocab > 131072) && std::max(out, in) <= times * 32.0 * side_by_side;
+           !tn_streams(c.vocab, c.row_stride, c.dtype) && !slow && std::max(out, in) <= times * 32.0 * side_by_side;
 }
 
 // Whether the gradient of a mini-batch goes by pairs of words (group.hip).  Such a mini-batch is prepared by its own call.
@@ -1052,7 +1055,7 @@ static int sgns_grad_impl(tensair_model *m, const int32_t *tokens, int64_t n_tok
             m->pend = following;
         }
     }
-    const bool chain_later = fuse && !by_pairs && chains_with_update(m, P, n_centers, m->fused_apply->packed);
+    const bool chain_later = fuse && !by_pairs && chains_with_update(m, P, n_centers, *m->fused_apply);
     mark(m, PF_BEGIN_GRAD, st);
 
     FwdArgs f;

@@ -589,14 +589,7 @@ static void launch_apply_sub_r(const ApplyArgs &a, const Rider &rider, hipStream
 }
 
 // few of the vocabulary's rows touched, going by the sources' capacities (see launch_apply_t)
-static i64 union_rows(const ApplyArgs &a)
-{
-    i64 cap = 0;
-    for (int k = 0; k < a.n_src; ++k)
-        if (a.src[1][k].ids != nullptr) cap += a.src[1][k].capacity;
-    return cap;
-}
-static bool sparse_union(const ApplyArgs &a, i64 min_v) { return a.V >= min_v && 4 * union_rows(a) < 3 * a.V; }
+static bool sparse_union(const ApplyArgs &a, i64 min_v) { return a.V >= min_v && 4 * tn_union_rows(a) < 3 * a.V; }
 // Few rows of a large vocabulary touched: a launch that stays on the chip and sweeps over the vocabulary, with the index words
 // of the next two groups of rows on their way while the rows of one are worked on, so that a wave's start and its look-ups are
 // paid once and not per group; the groups are small (the few waves with the frequent words would work on long after the
@@ -619,7 +612,7 @@ static bool sparse_union(const ApplyArgs &a, i64 min_v) { return a.V >= min_v &&
 // D = 512 in bfloat16 91.8 / 79.3; 4.5 million, D = 200 in bfloat16 76.7 / 68.9.  A grid that fits the
 // registers of every row width (4 to 6 waves per SIMD above 256 elements instead of 7) is up to 19 % slower than this one.
 #define SWEEP_MIN_V 131072
-static bool sweep_union(const ApplyArgs &a) { return a.V >= SWEEP_MIN_V && 5 * union_rows(a) < a.V; }
+static bool sweep_union(const ApplyArgs &a) { return a.V >= SWEEP_MIN_V && 5 * tn_union_rows(a) < a.V; }
 // vocabulary rows per row of capacity from which on the update sweeps with whole waves per row; 0: not at all.  bfloat16 tables of
 // more than 256 elements take more registers (a wave per SIMD less is on the chip): D = 300 at 600 000 words 70.9 / 60.9 and 80.9 /
 // 73.6 with 0.09 and 0.13 rows of capacity, D = 512 in bfloat16 61.5 / 63.7 and 74.1 / 82.8.
@@ -641,7 +634,7 @@ static int sweep_share(i64 V, int D, bool bf16)
 static bool sweep_sub(const ApplyArgs &a, int sub)
 {
     if (!sweep_union(a) || a.V >= 1000000) return false;
-    return sub == 32 || (sub == 8 && a.V < 300000) || union_rows(a) <= 28000;
+    return sub == 32 || (sub == 8 && a.V < 300000) || tn_union_rows(a) <= 28000;
 }
 
 // 4 rows per group of lanes and wave, or 32 rows per wave where few rows are touched (8 M words, D = 128, bf16:
@@ -701,7 +694,7 @@ static void launch_apply_t(const ApplyArgs &a, const Rider &rider, hipStream_t s
 {
     const i64 unit = sizeof(T) == 2 || PACKED ? 73728 : 131072;
     const int share = sweep_share(a.V, a.D, sizeof(T) == 2);
-    if (share > 0 && share * union_rows(a) < a.V) {
+    if (share > 0 && share * tn_union_rows(a) < a.V) {
         if constexpr (!Rider::chains) { // not in a vocabulary of TN_CHAIN_UPDATE_MAX_V words
             if (a.V >= (a.D > 4 * WAVE && sizeof(T) == 4 ? 4000000 : 3000000)) return launch_apply_g<T, 16, STREAM, PACKED, true>(a, rider, st);
             if (a.V >= 655360) return launch_apply_g<T, 8, STREAM, PACKED, true>(a, rider, st);

@@ -384,6 +384,14 @@ void tn_aux_add_index(AuxWork &x, const ApplyArgs &a, int k_begin, int k_end);
 
 void tn_launch_apply_clear(const ApplyArgs &a, hipStream_t st);
 void tn_launch_apply_index(const ApplyArgs &a, int k_begin, int k_end, hipStream_t st);
+// rows of W_out that an update's sources may have, by their capacities
+static inline i64 tn_union_rows(const ApplyArgs &a)
+{
+    i64 cap = 0;
+    for (int k = 0; k < a.n_src; ++k)
+        if (a.src[1][k].ids != nullptr) cap += a.src[1][k].capacity;
+    return cap;
+}
 // whether a phase can ride with the update: its workgroups come on top of those for the rows (of 16 vocabulary rows
 // each, at least), and one launch has to hold them all
 static inline bool tn_apply_carries(int D, i64 V) { return D <= 512 && (V + 15) / 16 + TN_PREP_CHAIN_MAX <= TN_MAX_BLOCKS; }

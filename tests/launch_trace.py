@@ -5,7 +5,7 @@ enqueued, as JSON.  A process of its own, without torch, whose own HIP runtime w
 
 calls.json: {"model": {...fields of tensair_config...}, "tokens": T, "counts": unigram counts (64 words once if absent),
 "calls": [[name, ...], ...]} with the calls
-    ["grad", begin, n, epoch, output...] (optional outputs: "negatives", "offsets_in", "offsets_out")   ["step", begin, n, epoch, peers]   ["prefetch", begin, n, epoch]   ["rebind", worker]
+    ["grad", begin, n, epoch, output...] (optional outputs: "negatives", "offsets_in", "offsets_out")   ["step", begin, n, epoch, peers]   ["step_packed", begin, n, epoch, peers, rows_out of each]   ["prefetch", begin, n, epoch]   ["rebind", worker]
     ["apply", rows_in, rows_out, peers]   ["capture", 0 | 1]   ["profile", level]
 Every pointer is made up: nothing reads or writes them."""
 import ctypes as C
@@ -81,6 +81,9 @@ def main():
             elif name == "grad":
                 dbg = [vp(pointer()) if o in a[3:] else None for o in ("negatives", "offsets_in", "offsets_out")]
                 rc = lib.tensair_sgns_grad(*batch, C.byref(own), None, *dbg, stream)
+            elif name == "step_packed":
+                peers = (Grad * max(a[3], 1))(*[grad(own.in_.capacity, a[4]) for _ in range(a[3])])
+                rc = lib.tensair_step_packed(*batch, peers, i32(a[3]), C.c_float(0.1), C.byref(own), None, None, stream)
             else:
                 peers = (Grad * max(a[3], 1))(*[grad(own.in_.capacity, own.out.capacity) for _ in range(a[3])])
                 rc = lib.tensair_step(*batch, peers, i32(a[3]), C.c_float(0.1), C.byref(own), None, stream)

@@ -257,6 +257,17 @@ def test_small_steps_chain_long_rows_in_their_update(trace, V, D, stride, dtype,
     assert ["k_segfixup" in names(c["did"]) for c in got] == [not chains, True]
 
 
+# with messages, on both sides: words (131 072 with narrow rows, 196 608 with bfloat16 tables and rows of up to 256 elements, of which
+# few are touched), elements of a row, rows of capacity (a fifth of the words; the own gradient has 3 600)
+@pytest.mark.parametrize("V,D,dtype,rows,chains", [
+    (131_072, 128, B.F32, 100, True), (131_073, 128, B.F32, 100, False), (131_073, 132, B.F32, 100, True), (262_144, 132, B.F32, 100, True),
+    (196_608, 132, B.BF16, 100, True), (196_609, 132, B.BF16, 100, False), (196_609, 256, B.BF16, 100, False), (196_609, 260, B.BF16, 100, True),
+    (200_000, 200, B.BF16, 36_399, False), (200_000, 200, B.BF16, 36_400, True)])
+def test_small_steps_with_messages_chain_long_rows_in_their_update(trace, V, D, dtype, rows, chains):
+    got = trace([["step_packed", 100, 60, 0, 1, rows]], vocab=V, dim=D, dtype=dtype, window=5, negatives=5, max_centers=60, max_peers=1)
+    assert got[0]["rc"] == 0 and ("k_segfixup" in names(got[0]["did"])) == (not chains)
+
+
 @pytest.mark.parametrize("case", PAIR_CASES, ids=lambda c: f"V{c[0]}_D{c[1]}_B{c[6]}_{c[8]}")
 def test_the_cases_of_the_gradient_by_pairs_go_by_pairs(trace, case):
     V, D, stride, _, w, N, n, begin, dtype = case
