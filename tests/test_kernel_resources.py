@@ -53,3 +53,10 @@ def test_narrow_updates_that_chain_long_rows_keep_their_registers(kernels):
     chaining = {n: k for n, k in kernels.items() if "k_apply_sub" in n and "ChainRider" in n}
     assert len(chaining) == 18                     # two types, three widths, three grids
     assert {n: k[".vgpr_spill_count"] for n, k in chaining.items() if k[".vgpr_spill_count"]} == {}
+
+
+def test_keys_that_run_beside_a_forward_pass_are_small(kernels):
+    """The keys of a large announced mini-batch find room among the waves of the forward pass before it: with 89 scalar registers
+    instead of 62 (the list of centers alone in the same kernel) they took until its end, and calls up to 12 % longer."""
+    keys = [k for n, k in kernels.items() if "k_prep_keys" in n]
+    assert keys and all(k[".sgpr_count"] <= 72 and k[".vgpr_count"] <= 32 for k in keys)
