@@ -209,8 +209,7 @@ struct tensair_model {
     unsigned short *group_starts = nullptr;
     int4 *group_meta = nullptr, *group_frequent = nullptr;
     int *group_n = nullptr;
-    double *group_hot_rows = nullptr;
-    float *group_hot_part = nullptr;
+    double *group_hot_rows = nullptr, *group_hot_part = nullptr;
     u32 *group_dense = nullptr;
     u64 *long_mask[2];         // rows of a step's own gradient that the table update chains, per table
     u32 *wbase[2], *wblk[2];   // tensair_grad_add: place of every 64-row word in the summed gradient
@@ -306,7 +305,7 @@ size_t carve(const tensair_config &c, const Sizes &s, char *base, tensair_model 
         p = take(most * 16); if (m) m->group_frequent = (int4 *)p;
         p = take(256); if (m) m->group_n = (int *)p;
         p = take(hot_blocks * 64 * D * 8); if (m) m->group_hot_rows = (double *)p;
-        p = take(most * words * D * 4); if (m) m->group_hot_part = (float *)p;
+        p = take(most * words * D * 8); if (m) m->group_hot_part = (double *)p;
         p = take((size_t)tn_group_chunks(c.vocab, per_center, s.Bmax) * 64 * words * 4); if (m) m->group_dense = (u32 *)p;
     }
     for (int t = 0; t < 2; ++t) {

@@ -53,10 +53,12 @@ __device__ __forceinline__ float sum_waves(const float *red, int row, int e)
     return (float)s;
 }
 
-// A wave's row of long sums.  Hundreds of chunks are added up for a frequent word, and in one chain of fp32 additions that
-// loses accuracy (rows of W_out against 64 bits 2.6e-7; sums of four or eight rows added up in fp32 1.3e-7; in double 0.6e-7 to
-// 0.9e-7; the reduction of sorted occurrences, whose sums meet in a tree, 0.7e-7 to 1.0e-7.  The shares of a center word are as
-// many as it has chunks: 500 000 centers of 2 words 1.5e-7 in fp32, 0.9e-7 in double).
+// A wave's row of long sums, in double: a word's over the rows of the rare center words that have it, group by group of four or
+// two (12 228 equal ones, added up in fp32, were off by 50 roundings, now by less than 6), and what the slices of the frequent
+// center words give it; a center word's over its shares, of which a rare one has one per `per_center` words of its list and a frequent
+// one one per 64 words of the vocabulary.  Those are kept in double themselves: few of them are most of a row, and rounding them
+// first is not averaged out (16 384 centers, 10 000 words, Zipf exponent 1.5, D = 256: rows of W_in against 64 bits 6.7e-8, now 6.2e-8, over 120
+// inputs; rows of W_out 6.2e-8; both by occurrences 8.6e-8).
 template <int NQ, bool TAIL>
 struct LongRow {
     double q[NQ][4], t;
@@ -77,21 +79,30 @@ struct LongRow {
         }
         if (TAIL) t += x.t;
     }
-    __device__ __forceinline__ void add64(const double *row, int D, int lane)
+    __device__ __forceinline__ void load64(const double *row, int D, int lane)
     {
         const int C4 = TAIL ? NQ * WAVE : (D >> 2);
+        zero();
 #pragma unroll
         for (int it = 0; it < NQ; ++it) {
             const int c = lane + WAVE * it;
             if (c < C4) {
                 const double2 lo = *(const double2 *)(row + 4 * c), hi = *(const double2 *)(row + 4 * c + 2);
-                q[it][0] += lo.x;
-                q[it][1] += lo.y;
-                q[it][2] += hi.x;
-                q[it][3] += hi.y;
+                q[it][0] = lo.x;
+                q[it][1] = lo.y;
+                q[it][2] = hi.x;
+                q[it][3] = hi.y;
             }
         }
-        if (TAIL && 4 * WAVE * NQ + lane < D) t += row[4 * WAVE * NQ + lane];
+        if (TAIL && 4 * WAVE * NQ + lane < D) t = row[4 * WAVE * NQ + lane];
+    }
+    __device__ __forceinline__ void add(const LongRow &x)
+    {
+#pragma unroll
+        for (int it = 0; it < NQ; ++it)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) q[it][j] += x.q[it][j];
+        if (TAIL) t += x.t;
     }
     template <typename T>
     __device__ __forceinline__ void axpy(double a, const LoadedRow<T, NQ, TAIL> &x)
@@ -105,20 +116,6 @@ struct LongRow {
             q[it][3] = fma(a, (double)v.w, q[it][3]);
         }
         if (TAIL) t = fma(a, (double)x.tail(), t);
-    }
-    // to memory, in double
-    __device__ __forceinline__ void store64(double *row, int D, int lane) const
-    {
-        const int C4 = TAIL ? NQ * WAVE : (D >> 2);
-#pragma unroll
-        for (int it = 0; it < NQ; ++it) {
-            const int c = lane + WAVE * it;
-            if (c < C4) {
-                *(double2 *)(row + 4 * c) = make_double2(q[it][0], q[it][1]);
-                *(double2 *)(row + 4 * c + 2) = make_double2(q[it][2], q[it][3]);
-            }
-        }
-        if (TAIL && 4 * WAVE * NQ + lane < D) row[4 * WAVE * NQ + lane] = t;
     }
     __device__ __forceinline__ void round(WaveRow<NQ, TAIL> &x) const
     {
@@ -517,7 +514,7 @@ __device__ __forceinline__ void hot_words(const FwdArgs &f, const HotLds &l, boo
 
 // of the center words, over the 64 words from w0 on; row h at dst + h * pitch
 template <typename T>
-__device__ __forceinline__ void hot_centers(const FwdArgs &f, const HotLds &l, bool odd, int nh, int w0, int d0, float *dst, size_t pitch, int lane)
+__device__ __forceinline__ void hot_centers(const FwdArgs &f, const HotLds &l, bool odd, int nh, int w0, int d0, double *dst, size_t pitch, int lane)
 {
     constexpr int STEPS = 4;
     const int part = lane >> 4, mine = lane & 15, d = d0 + 4 * mine, last = (int)f.V - 1;
@@ -551,7 +548,10 @@ __device__ __forceinline__ void hot_centers(const FwdArgs &f, const HotLds &l, b
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int h = 4 * r + part;
-        if (h < nh) st4(dst + (size_t)h * pitch + d, make_float4((float)sum[0][r], (float)sum[1][r], (float)sum[2][r], (float)sum[3][r]));
+        if (h >= nh) continue;
+        double2 *at = (double2 *)(dst + (size_t)h * pitch + d);
+        at[0] = make_double2(sum[0][r], sum[1][r]);
+        at[1] = make_double2(sum[2][r], sum[3][r]);
     }
 }
 
@@ -766,16 +766,17 @@ __global__ void __launch_bounds__(SUM_THREADS) __attribute__((amdgpu_waves_per_e
     if (b < blocks_hot) {                   // a frequent center word: the shares of all 64 words
         if (b >= *a.n_frequent) return;
         const int r = uniform(a.frequent[b].y);
-        const float *rows = a.hot_part + (size_t)b * a.words * f.D;
-        for (int q0 = wave; q0 < a.words; q0 += 4 * SUM_WAVES) {
-            LoadedRow<float, NQ, TAIL> x[4];
+        constexpr int AT_ONCE = NQ == 1 ? 4 : 2;
+        const double *rows = a.hot_part + (size_t)b * a.words * f.D;
+        for (int q0 = wave; q0 < a.words; q0 += AT_ONCE * SUM_WAVES) {
+            LongRow<NQ, TAIL> x[AT_ONCE];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (q0 + j * SUM_WAVES < a.words) x[j].load(rows + (size_t)(q0 + j * SUM_WAVES) * f.D, f.D, lane);
+            for (int j = 0; j < AT_ONCE; ++j) {
+                if (q0 + j * SUM_WAVES < a.words) x[j].load64(rows + (size_t)(q0 + j * SUM_WAVES) * f.D, f.D, lane);
                 else x[j].zero();
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) total.axpy(1.0, x[j]);
+            for (int j = 0; j < AT_ONCE; ++j) total.add(x[j]);
         }
         Row acc;
         total.round(acc);
@@ -830,7 +831,11 @@ __global__ void __launch_bounds__(SUM_THREADS) __attribute__((amdgpu_waves_per_e
     if (!here) return;
     if (threadIdx.x == 0) a.out_ids[n] = b;
     const int hot = uniform(*a.n_frequent), slices = min(a.slices, (hot + GROUP_HOT - 1) / GROUP_HOT);
-    for (int s = wave; s < slices; s += SUM_WAVES) total.add64(a.hot_rows + ((size_t)s * (64 * a.words) + b) * f.D, f.D, lane);
+    for (int s = wave; s < slices; s += SUM_WAVES) {
+        LongRow<NQ, TAIL> x;
+        x.load64(a.hot_rows + ((size_t)s * (64 * a.words) + b) * f.D, f.D, lane);
+        total.add(x);
+    }
     // a wave takes every SUM_WAVES-th center word
     for (int g0 = 0; g0 < (U + WAVE - 1) / WAVE; g0 += WAVE) {
         u64 has = 0;

@@ -311,7 +311,7 @@ struct GroupArgs {
     int4 *frequent;          // the word, row, chunks, the first of them
     int *n_frequent;
     double *hot_rows;        // [slices][64 * words][D] what the frequent center words give a word's row
-    float *hot_part;         // [frequent][words][D] what 64 words give a frequent center word's row
+    double *hot_part;        // [frequent][words][D] what 64 words give a frequent center word's row
     float *in_rows, *out_rows;
     int *out_ids, *out_n;
     u64 *index_mask;         // [words] the table update's index of the out-side rows (NULL: not wanted)

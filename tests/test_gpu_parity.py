@@ -469,6 +469,31 @@ def test_a_frequent_center_word_that_met_all_of_a_large_vocabulary_does_not_drif
     m.close()
 
 
+@pytest.mark.parametrize("D", [64, 260, 1024])
+def test_the_shares_of_a_frequent_center_word_are_not_rounded_before_they_are_added_up(D):
+    """4 096 centers of one word, scores of zero, negatives in two groups of 64 words with a row of their own each, both
+    added up by one wave: the center's row is (c u + c' u') / (2 P), c and c' the draws of either, every scale exact (P = 2^15), rounded
+    once.  (Shares rounded to fp32 before: one element in three is off by a unit.)"""
+    V, w, N, n = 1024, 4, 63, 4096
+    gen = torch.Generator().manual_seed(8)
+    u = 1.0 + torch.rand((2, D), generator=gen)
+    counts = np.zeros(V, np.uint64)
+    counts[10:20] = counts[522:532] = 10
+    Wo = torch.zeros((V, D))
+    Wo[10:20], Wo[522:532] = u[0], u[1]
+    m = B.Model(V, D, B.F32, w, N, n, 0, 9, counts, tables=(torch.zeros((V, D), device="cuda"), Wo.cuda()))
+    P = m.pair_count(n + 8, 4, n)
+    assert P == 1 << 15
+    g, neg = m.grad_buffers(), torch.zeros(P * N, dtype=torch.int32, device="cuda")
+    m.sgns_grad(torch.full((n + 8,), 5, dtype=torch.int32, device="cuda"), 4, n, 0, g, negatives_dbg=neg)
+    m.status()
+    (ids, rows), _ = g.to_host()
+    second = int((neg >= 512).sum())
+    want = ((P * N - second) * u[0].double().numpy() + second * u[1].double().numpy()) / (2.0 * P)
+    assert list(ids) == [5] and np.array_equal(rows[0], want.astype(np.float32))
+    m.close()
+
+
 def _random_grad_cases(n, seed):
     """Seeded shapes: narrow to wide rows, windows 1..6, 0..12 negatives, batches from one center up, streams
     from flat to steep, vocabularies from two words up, batches at the start, inside and at the end of the
