@@ -138,7 +138,9 @@ typedef struct {
  * update measurably likes (the padding columns are never read or written).  Returns -1 for a bad argument. */
 int32_t tensair_aligned_row_stride(int32_t dim, int32_t dtype);
 
-/* Bytes of DEVICE workspace tensair_model_init needs for `cfg` (0 if cfg is invalid). */
+/* Bytes of DEVICE workspace tensair_model_init needs for `cfg` (0 if cfg is invalid).  All of it is for the largest
+ * mini-batch (max_centers), whatever its words: with at most 12 288 words, 128 to 512 tasks per position (2 * window *
+ * (negatives + 1)) and more than 2^20 occurrences a third of it may be room for frequent center words. */
 size_t tensair_workspace_bytes(const tensair_config *cfg);
 
 /* Rows a tensair_sparse_grad must hold for a batch of `n_centers`:

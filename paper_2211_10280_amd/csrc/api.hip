@@ -375,13 +375,15 @@ bool build_alias(const uint64_t *counts, i64 V, std::vector<Draw> &draw, double 
 // measured at expected shares of 0.45 to 0.9, it gains below 0.9 (0.87: step 306 against 310 us) and loses nothing above
 // but the table's cost (0.6 % at 0.9).
 #define TN_REPEATS_BELOW 0.85
-// The same for going by pairs of words (group.hip): rows of more than 128 elements gain wherever words repeat (expected
-// share 0.84: step 332 -> 255 us), narrow ones, whose gathers weigh less, a little (D = 64: 0.84 231 -> 247, 0.82 298 -> 284,
-// 0.67 251 -> 237, 0.44 179 -> 164).
+// The same for going by pairs of words (group.hip): rows of more than 128 elements gain wherever words repeat, narrow ones,
+// whose gathers weigh less, less so.  Step over 12 000 words, 1.3 million occurrences of 256 tasks per position, by occurrences / by
+// pairs, expected share 0.78, 0.82, 0.87, 0.92: D = 64 180 / 171, 191 / 186, 202 / 204, 220 / 235; D = 128 207 / 174, 219 / 189, 233 / 207,
+// 252 / 240; D = 132 223 / 177, 237 / 191, 255 / 211, 273 / 245; 128 tasks, D = 64 192 / 163, 205 / 178, 214 / 199, 229 / 230.
 static double pairs_below(int D) { return D <= TN_SUB_MAX_DIM ? 0.8 : TN_REPEATS_BELOW; }
-// ... and only where no word is most of the negatives: the occurrences of a word are counted one after the other (step, 256
-// tasks each, D = 32, by occurrences / by pairs: one word, 4 200 centers 103 / 185 us, 65 536 centers 817 / 1 961; a share of
-// 0.63 96 / 110 and 722 / 979; of 0.42 92 / 94 and 672 / 597).
+// ... and only where no word is most of the negatives: an earlier form counted a word's occurrences by additions one after the other
+// and was slower there (4 200 centers of 256 tasks, one word 103 by occurrences / 185 us by pairs then, a share of 0.63 96 / 110).  This
+// one is not (step, D = 32, by occurrences / by pairs: one word, 4 200 centers 103 / 62, 65 536 centers 809 / 154; a share of 0.63
+// 96 / 59 and 717 / 147; of 0.42 92 / 59 and 673 / 151): the line could go.
 #define TN_GROUP_MAX_SHARE 0.5
 // Stage tags of tensair_profile_read.  A tag's duration runs from the previous mark to its own.
 enum { PF_BEGIN_GRAD = 0, PF_KEYS, PF_FORWARD, PF_SORT, PF_SEGMENTS, PF_REDUCE_IN, PF_REDUCE_OUT,
@@ -913,11 +915,13 @@ static bool chains_with_update(const tensair_model *m, i64 P, int n_centers, con
 // Whether the gradient of a mini-batch goes by pairs of words (group.hip).  Such a mini-batch is prepared by its own call.
 // Counting a chunk and adding up a word look at every word and every chunk, whatever they hold: that has to be paid for by
 // occurrences per word, the more of them the cheaper an occurrence is by itself -- narrow rows, positions that repeat words.
-// Step, us, by occurrences / by pairs (expected share of different words 0.5 to 0.6): D = 32, 128 tasks per position, 128
-// occurrences per word 146 / 187, 192 196 / 227, 256 279 / 268; D = 128, 94 166 / 206, 141 220 / 249, 188 293 / 295; D = 256,
-// 94 187 / 210, 141 249 / 255, 188 327 / 303, 256 tasks 94 181 / 189, 141 236 / 222; (0.65 to 0.83) D = 32, 256 tasks, 94
-// 180 / 203, 141 241 / 248, 188 302 / 293; D = 132, 128 tasks, 94 235 / 245, 128 234 / 216, 256 tasks 94 231 / 207; D = 512, 94,
-// 0.6 248 / 248, 256 tasks 246 / 221.
+// The lines lie where an earlier form broke even, which took nearly twice as long: this one does from about 90 occurrences per word on, so
+// nothing that goes by pairs is slower for it.  Step over 12 000 words, us, by occurrences / by pairs: expected share of different words
+// 0.55, 128 tasks per position, D = 32, 94 occurrences per word 138 / 117, 160 185 / 129, 200 212 / 135; D = 128, 94 151 / 120,
+// 160 212 / 132; D = 256, 94 164 / 127, 128 202 / 130, 160 237 / 138; 256 tasks, D = 32, 87 123 / 123, 94 132 / 118, 200 196 / 141; D = 256,
+// 94 159 / 127, 160 225 / 144; share 0.72, 128 tasks, D = 32, 87 148 / 146, 94 159 / 140, 160 213 / 165; D = 132, 94 196 / 144, 128
+// 239 / 159; 256 tasks, D = 32, 87 144 / 150, 94 150 / 149, 160 196 / 171; D = 132, 94 190 / 154; D = 320, 0.55, 87 occurrences 160 / 144, D = 512
+// 220 / 165.
 static bool goes_by_pairs(const tensair_model *m, i64 P)
 {
     const tensair_config &c = m->cfg;

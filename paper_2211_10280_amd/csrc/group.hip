@@ -16,8 +16,9 @@
 // chained.  The step above takes 191 us; with chunks of up to 128 positions of any center word, listed all of them, and the
 // draws made by a launch before, 319; with the occurrences sorted beside a forward pass position by position (see
 // prep_dev.h, grad.hip) 472.  Its launches: the centers' sort 26 us (61 with counts in launches of their own and the keys of
-// all occurrences), counts 44 (91, bound by scattered 8-byte stores of the chunks' bits; now by draws, latency and atomics in LDS), rows
-// 50 (77), bits 7, sums 50 (67: row gathers out of L2).
+// all occurrences), counts 44 (91, bound by scattered 8-byte stores of the chunks' bits; now a chain of round trips: 44 too without the
+// additions in LDS, 34 without the draws), rows 50 (77; the frequent words' workgroups alone 36, of which a wave's matrix instructions are 5,
+// the rare ones' 37), bits 7, sums 50 (67: row gathers out of L2).
 #include "aux_dev.h"
 #include "dev_common.h"
 #include "forward_dev.h"
@@ -399,7 +400,9 @@ struct HotLds {
 // s[h][w]: dot product of row words[h] of w_in and row first + w of w_out, for 16 of each, by one wave.  A matrix instruction takes
 // 4 elements of 16 rows of each table, a lane one of each row; a lane loads 4 neighbouring ones for four instructions.  In double
 // (a score's rounding is in all of its tasks); rows of more than 512 elements, of which the forward pass adds up 12 and more in a
-// chain too, 16 at a time in fp32: a quarter of the time (40 words, D = 1 024, 2 355 centers of 512 tasks: step 85 / 74 us).
+// chain too, 16 at a time in fp32: a quarter of the time (40 words, D = 1 024, 2 355 centers of 512 tasks: step 85 / 74 us) for an
+// error of the rows against 64 bits that is up to 3 % larger (250 inputs, 10 000 words, D = 1 024 6.7 -> 6.8e-8, 40 words, D = 768 6.2 -> 6.4) and
+// below that of pairs whose scores are sums in fp32 throughout (120 inputs, D = 516 6.2 / 6.5, D = 1 024 6.4 / 6.9, 40 words, D = 768 6.6 / 7.0).
 template <typename T>
 __device__ __forceinline__ void hot_dots(const FwdArgs &f, int word_l, int first, float (*s)[WAVE], int col, int lane, u32 &odd)
 {

@@ -222,7 +222,9 @@ struct ChainWork {
     int blocks;       // workgroups; p.blocks_in of them take the in-side rows
 };
 #ifndef TN_CHAIN_UPDATE_MAX_OCC
-#define TN_CHAIN_UPDATE_MAX_OCC 131072     // occurrences up to which it is (chains_with_update; not measured beyond)
+// Occurrences up to which it is (chains_with_update).  Beyond, up to 520 000, 60 steps with the chaining in the update take 0.96 of the time
+// with a launch of its own in the mean, from 0.83 to 1.02: the line could lie higher.
+#define TN_CHAIN_UPDATE_MAX_OCC 131072
 #endif
 #define TN_CHAIN_UPDATE_MAX_V (1 << 2 * TN_RADIX_MAX_BITS)     // words up to which it is: their keys are sorted in two passes
 void tn_chain_work(ChainWork &c, const SegReduceArgs &out, const SegReduceArgs &in);
@@ -234,15 +236,17 @@ static inline int tn_seg_chains(i64 n, int D)
 }
 
 // ---- stages 4 and 5 of a very large mini-batch over a small vocabulary whose words repeat (group.hip)
-// up to TN_GROUP_MAX_VOCAB words (a counter each in LDS) and more than TN_GROUP_MIN_OCC occurrences
-// (a counter and a bucket of the alias table per word fit a compute unit's LDS up to here; an earlier form, step of 8 192 centers, 256 tasks each, 3 peers, D = 256,
-// by occurrences / by pairs: 1 323 words 263 / 163 us, 2 000 220 / 166, 5 000 332 / 255, 10 000 400 / 296, 331 / 246 and 303 / 234 with
-// Zipf exponents of 1.1, 1.3 and 1.45; 32 000 words, one workgroup per compute unit, 419 / 574 and 303 / 451)
+// Up to so many words a counter and a bucket of the alias table per word fit a compute unit's LDS.  Step of 8 192 centers, 256 tasks
+// each, 3 peers, D = 256, Zipf exponent 1.3, by occurrences / by pairs: 1 323 words 231 / 116 us, 2 000 239 / 120, 5 000 258 / 141, 10 000
+// 273 / 170 (exponent 1.1 338 / 235, 1.45 235 / 140), 12 288 277 / 179.
 #define TN_GROUP_MAX_VOCAB 12288
+// Occurrences from which on it goes by pairs: an announced mini-batch of no more is sorted beside the call before it and goes by
+// occurrences, and one that nobody announced has to give the same bits (step of 1 000 words, a million occurrences of 128 tasks
+// each, by occurrences announced 98 us at D = 64, 138 at D = 256, not announced 121 and 151, by pairs 87 and 94).
 #define TN_GROUP_MIN_OCC (1 << 20)
-// per position.  Step of 9 420 centers with 128 tasks each, by
-// occurrences / by pairs: 700 words, D = 64 130 / 125 us, D = 256 in bfloat16 182 / 127, 4 000 words 164 / 160 and 199 / 163; not
-// measured below.
+// Tasks per position, at least: where an earlier form, which took nearly twice as long, gained nothing.  Step of 1.2 million
+// occurrences by occurrences / by pairs: 128 tasks, 700 words, D = 64 128 / 87 us, D = 256 in bfloat16 168 / 92, 4 000 words 154 / 111 and
+// 195 / 115; 64 tasks, 700 words, D = 64 143 / 96, D = 256 189 / 104, 4 000 words 173 / 125 and 219 / 134: the line could lie lower.
 #define TN_GROUP_MIN_TASKS 128
 #define TN_GROUP_HOT 16        // frequent center words that a workgroup takes at a time
 // A center word of more than so many positions is frequent: it is taken against the whole vocabulary, others against the list of
